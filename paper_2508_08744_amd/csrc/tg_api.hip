@@ -3,6 +3,7 @@
 #include "../../include/tagore_knn.h"
 #include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_exact.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -593,33 +594,33 @@ extern "C" int tg_exact_knn(const float* X, int64_t n, int32_t d, int32_t k, int
     }
     const int ld = round_up4(d);
     const bool pad = (ld != d) || ((reinterpret_cast<uintptr_t>(X) & 15) != 0);
-    const int slices = tg_exact_slices(n, nq);
-    Carver c{nullptr, 0};
-    c.take<float>(pad ? (size_t)n * ld : 0);
-    c.take<float>(n);
-    c.take<float>(n);
-    c.take<u64>((size_t)nq * slices * k);
-    const size_t bytes = (c.used + 255) & ~(size_t)255;
-    void* ws = nullptr;
-    if (hipMalloc(&ws, bytes) != hipSuccess) {
+    // The scratch lives in stream order, like the workspace of tg_knn_build.  Where the fp16 copy of X cannot be had,
+    // the fp32 rows are screened as they are.
+    bool f16 = tg_exact_use_f16(n, ld, nq);
+    int64_t batch = 0;
+    size_t fixed = 0, bytes = 0;
+    const size_t padded = pad ? ((size_t)n * ld * sizeof(float) + 255) & ~(size_t)255 : 0;
+    char* ws = nullptr;
+    for (;; f16 = false) {
+        fixed = tg_exact_fixed_bytes(n, ld, metric, f16);
+        batch = nq < 16384 ? nq : 16384;
+        // An allocation of 64 MiB or more costs 0.35 ms to give back (65 us below that): where the lists are what makes it so large,
+        // the queries go in several batches (about 60 us each).
+        if (padded + fixed < (32u << 20) && nq <= 16384)
+            for (int64_t parts = 1; padded + fixed + tg_exact_query_bytes(batch, ld, f16) >= (64u << 20); ++parts)
+                batch = ((nq + parts - 1) / parts + 127) & ~127ll;
+        if (batch > nq) batch = nq;
+        bytes = padded + fixed + tg_exact_query_bytes(batch, ld, f16);
+        if (hipMallocAsync(reinterpret_cast<void**>(&ws), bytes, s) == hipSuccess) break;
         (void)hipGetLastError();
-        return fail(TG_ERR_OUT_OF_MEMORY, "scratch of %zu bytes could not be allocated", bytes);
+        if (!f16) return fail(TG_ERR_OUT_OF_MEMORY, "scratch of %zu bytes could not be allocated", bytes);
     }
-    Carver w{reinterpret_cast<char*>(ws), 0};
-    float* xp = w.take<float>(pad ? (size_t)n * ld : 0);
-    TgGraph g = {};
-    g.n = n; g.d = d; g.ld = ld; g.k = k; g.metric = metric;
-    g.X = pad ? xp : X;
-    g.nrm = w.take<float>(n);
-    g.rnorm = w.take<float>(n);
-    u64* partial = w.take<u64>((size_t)nq * slices * k);
+    float* xp = reinterpret_cast<float*>(ws);
     if (pad) tg_launch_pad_rows(X, n, d, xp, ld, s);
-    if (metric == 2) tg_launch_norms(g, nullptr, nullptr, s);
-    tg_launch_exact_knn(g.X, ld, g.nrm, g.rnorm, n, d, k, metric, query_rows, nq, out_ids, out_dist, partial, slices, s);
-    int rc = launch_status("exact k-NN");
-    hipError_t e = hipStreamSynchronize(s);
-    (void)hipFree(ws);
-    if (rc == TG_OK && e != hipSuccess) return fail(TG_ERR_HIP, "exact k-NN failed: %s", hipGetErrorString(e));
+    tg_launch_exact_screened(pad ? xp : X, ld, n, d, k, metric, query_rows, nq, f16, ws + padded, ws + padded + fixed, batch, out_ids, out_dist, s);
+    const int rc = launch_status("exact k-NN");
+    const hipError_t e = hipFreeAsync(ws, s);
+    if (rc == TG_OK && e != hipSuccess) return fail(TG_ERR_HIP, "releasing the scratch failed: %s", hipGetErrorString(e));
     return rc;
 }
 
@@ -664,7 +665,7 @@ extern "C" int tg_exact_knn_static(const float* X, int64_t n, int32_t d, int32_t
     if ((d & 3) || (reinterpret_cast<uintptr_t>(X) & 15))
         return fail(TG_ERR_UNSUPPORTED, "the allocation-free exact k-NN needs d %% 4 == 0 and a 16-byte aligned X (a padded copy would have to be allocated)");
     if (nq == 0) return TG_OK;
-    // layout: inverse norms (cosine only), then the partial lists; fewer slices when they would not fit
+    // layout of the direct measurement: inverse norms (cosine only), then the partial lists; fewer slices when they would not fit
     Carver c{nullptr, 0};
     if (metric == 2) { c.take<float>(n); c.take<float>(n); }
     const size_t fixed = (c.used + 255) & ~(size_t)255;
@@ -678,6 +679,17 @@ extern "C" int tg_exact_knn_static(const float* X, int64_t n, int32_t d, int32_t
     int rc = static_scratch(&base);
     if (rc != TG_OK) return rc;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    // the screened search, where its lists fit: as many queries at a time as there is room for
+    const size_t sfixed = tg_exact_fixed_bytes(n, d, metric, false);
+    for (int64_t parts = 1; sfixed < TG_STATIC_SCRATCH_BYTES; ++parts) {
+        const int64_t batch = ((nq + parts - 1) / parts + 63) & ~63ll;
+        if (sfixed + tg_exact_query_bytes(batch < nq ? batch : nq, d, false) <= TG_STATIC_SCRATCH_BYTES) {
+            tg_launch_exact_screened(X, d, n, d, k, metric, query_rows, nq, false, base, reinterpret_cast<char*>(base) + sfixed, batch < nq ? batch : nq,
+                                     out_ids, out_dist, s);
+            return launch_status("exact k-NN (static scratch)");
+        }
+        if (batch <= 64) break;
+    }
     Carver w{reinterpret_cast<char*>(base), 0};
     TgGraph g = {};
     g.n = n; g.d = d; g.ld = d; g.k = k; g.metric = metric;
@@ -688,7 +700,7 @@ extern "C" int tg_exact_knn_static(const float* X, int64_t n, int32_t d, int32_t
         tg_launch_norms(g, nullptr, nullptr, s);           // writes every word it later reads
     }
     u64* partial = w.take<u64>((size_t)nq * slices * k);   // every word read by the merge is written by the scan
-    tg_launch_exact_knn(g.X, g.ld, g.nrm, g.rnorm, n, d, k, metric, query_rows, nq, out_ids, out_dist, partial, slices, s);
+    tg_launch_exact_knn(g.X, g.ld, g.rnorm, n, k, metric, query_rows, nq, 0, nullptr, nullptr, out_ids, out_dist, partial, slices, s);
     return launch_status("exact k-NN (static scratch)");
 }
 

@@ -106,10 +106,6 @@ void tg_launch_finalize(const TgGraph& g, int recompute, const uint32_t* range, 
 void tg_launch_export(const TgGraph& g, int32_t* ids, float* dist, uint8_t* fresh, hipStream_t s);
 void tg_launch_import(const TgGraph& g, const int32_t* ids, const float* dist, const uint8_t* fresh, hipStream_t s);
 void tg_launch_pad_rows(const float* X, int64_t n, int d, float* Xp, int ld, hipStream_t s);
-int tg_exact_slices(int64_t n, int64_t nq);
-void tg_launch_exact_knn(const float* X, int ld, const float* nrm, const float* rnorm, int64_t n, int d, int k,
-                         int metric, const int64_t* rows, int64_t nq, int32_t* out_ids, float* out_dist,
-                         unsigned long long* partial /* nq x slices x k */, int nslices, hipStream_t s);
 size_t tg_scan_tmp_elems(int64_t n);
 void tg_launch_prune_rank(const int32_t* ids, int64_t n, int k, int d_out, int32_t* out_ids, int32_t* counts /* or null */,
                           hipStream_t s);
