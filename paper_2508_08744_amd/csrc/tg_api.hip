@@ -160,7 +160,7 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->sm.bsz = c.take<u32>(n);
     h->sm.wl = c.take<u64>((size_t)3 * (n + TG_MAX_PARTS));
     h->sm.wl_cnt = c.take<u32>(TG_WL_LISTS);
-    h->sm.scan_tmp = c.take<u64>(tg_scan_tmp_elems(h->sm.nbuckets));
+    h->sm.wave_ok = tg_join_wave_ok(ld) ? 1 : 0;
     h->sm.parts = p.parts;
     h->sm.parts_shift = p.parts == 8 ? 3 : p.parts == 4 ? 2 : p.parts == 2 ? 1 : 0;
     h->sm.adj_words = h->sm.BC > 64 ? 4 : 2;
@@ -310,7 +310,6 @@ static int phase1_round(tg_knn_handle* h, int64_t* updates)
     const int r = h->round;
     int sp = begin_span(h, SPAN_SAMPLE, r);
     tg_launch_reverse(h->g, h->sm, tg_hash_seed(h->p.seed, TG_TAG_REV(r)), h->stream);
-    tg_launch_bin(h->g, h->sm, h->p.parts, h->stream);
     end_span(h, sp);
     for (int part = 0; part < h->p.parts; ++part) {
         // the anchors v = part mod parts: their blocks are joined, then every list takes in what it was handed

@@ -179,3 +179,6 @@ __device__ inline u32 tg_wave_sort32(u32 key)
 }
 
 __device__ inline u64 tg_lanemask_lt() { return (1ull << tg_lane()) - 1ull; }
+
+// work record of the join: anchor | |NEW| << 32 | (|NEW|+|OLD|) << 40
+__device__ inline u64 tg_pack_rec(u32 v, int nN, int nT) { return (u64)v | ((u64)nN << 32) | ((u64)nT << 40); }

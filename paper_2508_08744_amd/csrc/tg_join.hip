@@ -549,8 +549,6 @@ struct WaveItem {
     const u32* bids;
     int nN, nT, MT, NT;       // MT = NT = 0: nothing to do for this item
 };
-// work record: anchor | |NEW| << 32 | (|NEW|+|OLD|) << 40
-__device__ inline u64 pack_rec(u32 v, int nN, int nT) { return (u64)v | ((u64)nN << 32) | ((u64)nT << 40); }
 
 struct WaveShared {
     u32 salt[2][64];
@@ -587,7 +585,7 @@ __global__ __launch_bounds__(256) void join_wave_kernel(TgGraph g, TgSample sm, 
         const int64_t wc = w < count ? w : count - 1;
         u64 rec;
         if (MODE == 0) rec = wl[wc];
-        else rec = pack_rec((u32)wc, xsizes[wc * 2], xsizes[wc * 2] + xsizes[wc * 2 + 1]);
+        else rec = tg_pack_rec((u32)wc, xsizes[wc * 2], xsizes[wc * 2] + xsizes[wc * 2 + 1]);
         return w < count ? rec : 0ull;
     };
     auto decode = [&](u64 rec) {
@@ -865,38 +863,6 @@ __global__ __launch_bounds__(256) void join_wave_kernel(TgGraph g, TgSample sm, 
     if (MODE == 0 && prev_nT > 0) flush_cells(buf ^ 1, prev_v, prev_nT);
 }
 
-// ---------------------------------------------------------------------------------------
-// Work lists: anchors with something to join, by part of the round (v mod parts) and by block size.
-// List 0: at most 3 row groups, list 1: exactly 4, list 2: more.  Without the wave kernel (longer rows
-// or lists) list 1 takes every block of at most 4 row groups and list 0 stays empty.  The list of
-// (part, size class) is wl + (part * 3 + class) * cap with cap = ceil(n / parts) records.
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void bin_kernel(TgSample sm, int64_t n, int wave_ok, int parts, int64_t cap)
-{
-    __shared__ u32 lcnt[TG_WL_LISTS], lbase[TG_WL_LISTS];
-    const int tid = threadIdx.x;
-    if (tid < TG_WL_LISTS) lcnt[tid] = 0u;
-    __syncthreads();
-    const int64_t v = (int64_t)blockIdx.x * 256 + tid;
-    int list = -1, nN = 0, nT = 0;
-    if (v < n) {
-        const u32 z = sm.bsz[v];
-        nN = (int)(z & 0xFFu);
-        nT = (int)(z >> 8);
-        if (nN > 0 && nT >= 2) {
-            const int NT = (nT + 15) >> 4;
-            const int bin = NT > 4 ? 2 : (NT == 4 || !wave_ok) ? 1 : 0;
-            list = (int)(v % parts) * 3 + bin;
-        }
-    }
-    // place inside the workgroup's share of the list, then one global atomic per workgroup and list
-    const u32 mypos = list >= 0 ? atomicAdd(lcnt + list, 1u) : 0u;
-    __syncthreads();
-    if (tid < TG_WL_LISTS) lbase[tid] = lcnt[tid] ? atomicAdd(sm.wl_cnt + tid, lcnt[tid]) : 0u;
-    __syncthreads();
-    if (list >= 0 && (int64_t)lbase[list] + mypos < cap) sm.wl[(int64_t)list * cap + lbase[list] + mypos] = pack_rec((u32)v, nN, nT);
-}
-
 static size_t join_lds_bytes(int DK, int rows)
 {
     return JOIN_HDR_BYTES + JOIN_ADJ_BYTES + JOIN_CELL_BYTES + (size_t)rows * (DK + 4) * sizeof(float);
@@ -1010,15 +976,7 @@ static void launch_wave_dump(const TgGraph& g, const int32_t* blk, const int32_t
     else launch_wave_dump_k<GMAX, METRIC, 8>(g, blk, sizes, nb, out, gmin, s);
 }
 
-// The register-resident kernel applies to rows of at most 128 floats.
-static bool wave_path(const TgGraph& g) { return g.ld <= 128; }
-
-void tg_launch_bin(const TgGraph& g, const TgSample& sm, int parts, hipStream_t s)
-{
-    tg_launch_fill_u32(sm.wl_cnt, TG_WL_LISTS, 0u, s);
-    hipLaunchKernelGGL(bin_kernel, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, sm, g.n, wave_path(g) ? 1 : 0, parts,
-                       wl_cap(g.n, parts));
-}
+static bool wave_path(const TgGraph& g) { return tg_join_wave_ok(g.ld); }
 
 void tg_launch_join(const TgGraph& g, const TgSample& sm, const TgCand& c, int part, int parts, uint64_t hs_slot,
                     unsigned long long* stat_bins, hipStream_t s)

@@ -61,7 +61,7 @@ struct TgSample {
     uint32_t* bsz;            // n: |NEW| | (|NEW|+|OLD|) << 8
     unsigned long long* wl;   // 3 x (n + TG_MAX_PARTS): this round's join work lists (anchor | sizes), by part of the round and block size
     uint32_t* wl_cnt;         // TG_WL_LISTS: their lengths
-    unsigned long long* scan_tmp; // block sums of the prefix sum over the buckets
+    int32_t wave_ok;          // the register-resident join applies (short rows): which work list a block goes to
     int32_t parts, parts_shift;   // a round's anchors are joined in `parts` = 1 << parts_shift parts: v goes to part v % parts, slot v / parts
     uint32_t* adj;                // ceil(n / parts) x BC x adj_words: of the part in hand, per anchor slot and member, bit x = the
     int32_t adj_words;            // node at block position x is in that member's list already (2 words for blocks of at most 64, else 4)
@@ -82,8 +82,8 @@ void tg_launch_fill_u64(unsigned long long* p, size_t count, unsigned long long 
 void tg_launch_fill_u32(uint32_t* p, size_t count, uint32_t v, hipStream_t s);
 void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hipStream_t s);
 int tg_rev_bucket_shift(int64_t n);
-// work lists of the coming round from the stored blocks: anchor v goes to part v mod parts
-void tg_launch_bin(const TgGraph& g, const TgSample& sm, int parts, hipStream_t s);
+// rows the register-resident join takes
+static inline bool tg_join_wave_ok(int ld) { return ld <= 128; }
 // which members of a block sit in which member's list, for the anchors of one part: sm.adj (to run before tg_launch_join of that part);
 // the same, copied to n x 128 x 4 words for inspection
 void tg_launch_adj(const TgGraph& g, const TgSample& sm, int part, hipStream_t s);
@@ -106,7 +106,6 @@ void tg_launch_finalize(const TgGraph& g, int recompute, const uint32_t* range, 
 void tg_launch_export(const TgGraph& g, int32_t* ids, float* dist, uint8_t* fresh, hipStream_t s);
 void tg_launch_import(const TgGraph& g, const int32_t* ids, const float* dist, const uint8_t* fresh, hipStream_t s);
 void tg_launch_pad_rows(const float* X, int64_t n, int d, float* Xp, int ld, hipStream_t s);
-size_t tg_scan_tmp_elems(int64_t n);
 void tg_launch_prune_rank(const int32_t* ids, int64_t n, int k, int d_out, int32_t* out_ids, int32_t* counts /* or null */,
                           hipStream_t s);
 // rule 0: distance rule, thr = alpha^2; 1: angle rule, thr = 4 cos^2(gamma); 2: dispersion rule, thr unused

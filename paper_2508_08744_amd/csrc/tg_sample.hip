@@ -72,69 +72,45 @@ __global__ __launch_bounds__(REV_BUCKET_THREADS) void rev_bucket_kernel(TgGraph 
     });
 }
 
-// ---- exclusive prefix sum of cnt[0..n) into off[0..n], three passes (cnt stays) -------------------------
-#define SCAN_BLOCK 1024   // elements per workgroup (256 threads x 4)
-
-__global__ __launch_bounds__(256) void scan_partial_kernel(const u32* deg, int64_t n, u64* block_sums)
+// ---- exclusive prefix sum of the buckets' counts (cnt stays), off[n] = their sum; one workgroup, which also empties the round's work lists.
+// (Three launches over the same words, as it was, took 13 us whatever n; this takes 5 for up to 8192 buckets.)
+#define SCAN_THREADS 1024
+#define SCAN_EACH 8
+__global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(const u32* __restrict__ cnt, int64_t n, u64* __restrict__ off, u32* __restrict__ wl_cnt)
 {
-    __shared__ u64 red[4];
-    int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK + threadIdx.x * 4;
-    u64 s = 0;
-    for (int i = 0; i < 4; ++i) if (base + i < n) s += deg[base + i];
-    for (int o = 32; o > 0; o >>= 1) s += tg_shfl_xor64(s, o);
-    if (tg_lane() == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) block_sums[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-}
-// one workgroup scans the block sums in place (exclusive), and writes the grand total to off[n]
-__global__ __launch_bounds__(256) void scan_sums_kernel(u64* block_sums, int64_t nblocks, u64* off_total)
-{
-    __shared__ u64 carry_s;
-    __shared__ u64 wsum[4];
-    if (threadIdx.x == 0) carry_s = 0;
-    __syncthreads();
-    for (int64_t base = 0; base < nblocks; base += 256) {
-        int64_t i = base + threadIdx.x;
-        u64 x = i < nblocks ? block_sums[i] : 0;
-        u64 incl = x;
+    __shared__ u64 wsum[SCAN_THREADS / 64];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tg_lane();
+    if (tid < TG_WL_LISTS) wl_cnt[tid] = 0u;
+    u64 carry = 0;
+    for (int64_t base = 0; base < n; base += SCAN_THREADS * SCAN_EACH) {
+        const int64_t i0 = base + (int64_t)tid * SCAN_EACH;
+        u32 x[SCAN_EACH];
+        u64 sum = 0;
+#pragma unroll
+        for (int i = 0; i < SCAN_EACH; ++i) { x[i] = i0 + i < n ? cnt[i0 + i] : 0u; sum += x[i]; }
+        u64 incl = sum;
         for (int o = 1; o < 64; o <<= 1) {
-            u64 y = tg_shfl64(incl, max(tg_lane() - o, 0));
-            if (tg_lane() >= o) incl += y;
+            const u64 y = tg_shfl64(incl, max(lane - o, 0));
+            if (lane >= o) incl += y;
         }
-        if (tg_lane() == 63) wsum[threadIdx.x >> 6] = incl;
+        if (lane == 63) wsum[wave] = incl;
         __syncthreads();
-        u64 pre = carry_s;
-        for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) pre += wsum[w];
-        if (i < nblocks) block_sums[i] = pre + incl - x;
-        __syncthreads();
-        if (threadIdx.x == 255) carry_s = pre + incl;
+        u64 before = carry, all = 0;
+        for (int w = 0; w < SCAN_THREADS / 64; ++w) {
+            if (w < wave) before += wsum[w];
+            all += wsum[w];
+        }
+        u64 run = before + incl - sum;
+#pragma unroll
+        for (int i = 0; i < SCAN_EACH; ++i) {
+            if (i0 + i < n) off[i0 + i] = run;
+            run += x[i];
+        }
+        carry += all;
         __syncthreads();
     }
-    if (threadIdx.x == 0) *off_total = carry_s;
+    if (tid == 0) off[n] = carry;
 }
-__global__ __launch_bounds__(256) void scan_final_kernel(const u32* deg, int64_t n, const u64* block_sums, u64* off)
-{
-    __shared__ u64 wsum[4];
-    int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK + threadIdx.x * 4;
-    u32 x[4];
-    u64 s = 0;
-    for (int i = 0; i < 4; ++i) { x[i] = base + i < n ? deg[base + i] : 0u; s += x[i]; }
-    u64 incl = s;
-    for (int o = 1; o < 64; o <<= 1) {
-        u64 y = tg_shfl64(incl, max(tg_lane() - o, 0));
-        if (tg_lane() >= o) incl += y;
-    }
-    if (tg_lane() == 63) wsum[threadIdx.x >> 6] = incl;
-    __syncthreads();
-    u64 pre = block_sums[blockIdx.x];
-    for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) pre += wsum[w];
-    u64 run = pre + incl - s;
-    for (int i = 0; i < 4; ++i) {
-        if (base + i < n) off[base + i] = run;
-        run += x[i];
-    }
-}
-size_t tg_scan_tmp_elems(int64_t n) { return (size_t)((n + SCAN_BLOCK - 1) / SCAN_BLOCK) + 1; }
 
 // ---- per node: keep the R smallest (priority, source) of each class, then assemble the block --
 // Block of anchor v:  NEW = new_fwd ++ (new_rev not yet there),
@@ -230,6 +206,7 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
     __shared__ u32 tpos[TG_REV_MAX_W];
     __shared__ u64 part[4][2][64];
     __shared__ u32 asm_keys[4][ASM_WORDS], asm_tags[4][ASM_WORDS];
+    __shared__ u32 lcnt[TG_WL_LISTS], lbase[TG_WL_LISTS];
     const int lane = tg_lane(), wave = threadIdx.x >> 6;
     const int64_t b = bfirst + blockIdx.x;
     if (b >= sm.nbuckets) return;
@@ -248,8 +225,8 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
     }
     __syncthreads();
     if (wave == 0) {
-        // exclusive prefix sum over the W targets: a lane takes W / 64 neighbouring ones
-        const int per = W >> 6;
+        // exclusive prefix sum over the W targets: a lane takes W / 64 neighbouring ones (fewer targets than lanes: the first W lanes one each)
+        const int per = W < 64 ? (lane < W ? 1 : 0) : W >> 6;
         u32 sum = 0;
         for (int i = 0; i < per; ++i) sum += tpos[lane * per + i];
         u32 incl = sum;
@@ -340,6 +317,35 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
         assemble_block(g, sm, u, w_list, (u32)best_new, min(tot_new, sm.R), (u32)best_old, min(tot_old, sm.R), asm_keys[wave], asm_tags[wave]);
         abeg = nbeg; aend = nend; e_first = e_next; w_list = w_next;
     }
+    // Work lists of the join: the bucket's anchors with something to join, by part of the round (v mod parts) and by block size.
+    // List 0: at most 3 row groups, list 1: exactly 4, list 2: more.  Without the register-resident join (longer rows)
+    // list 1 takes every block of at most 4 row groups and list 0 stays empty.  The list of (part, size class) is
+    // wl + (part * 3 + class) * cap with cap = ceil(n / parts) records.  One global atomic per workgroup and list.
+    if (threadIdx.x < TG_WL_LISTS) lcnt[threadIdx.x] = 0u;
+    __syncthreads();                    // (and every block of the bucket is stored)
+    const int64_t cap = (g.n + sm.parts - 1) / sm.parts;
+    for (int t0 = 0; t0 < W; t0 += 256) {
+        const int t = t0 + (int)threadIdx.x;
+        const int64_t v = (b << sm.bshift) + t;
+        int list = -1, nN = 0, nT = 0;
+        if (t < W && v < g.n) {
+            const u32 z = sm.bsz[v];
+            nN = (int)(z & 0xFFu);
+            nT = (int)(z >> 8);
+            if (nN > 0 && nT >= 2) {
+                const int NT = (nT + 15) >> 4;
+                const int bin = NT > 4 ? 2 : (NT == 4 || !sm.wave_ok) ? 1 : 0;
+                list = ((int)v & (sm.parts - 1)) * 3 + bin;
+            }
+        }
+        const u32 mypos = list >= 0 ? atomicAdd(lcnt + list, 1u) : 0u;
+        __syncthreads();
+        if (threadIdx.x < TG_WL_LISTS) lbase[threadIdx.x] = lcnt[threadIdx.x] ? atomicAdd(sm.wl_cnt + threadIdx.x, lcnt[threadIdx.x]) : 0u;
+        __syncthreads();
+        if (list >= 0 && (int64_t)lbase[list] + mypos < cap) sm.wl[(int64_t)list * cap + lbase[list] + mypos] = tg_pack_rec((u32)v, nN, nT);
+        if (threadIdx.x < TG_WL_LISTS) lcnt[threadIdx.x] = 0u;
+        __syncthreads();
+    }
 }
 
 // blocks as stored -> the boundary's fixed n x 128 layout (padding -1) and (|NEW|, |OLD|)
@@ -370,8 +376,10 @@ void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hi
     int kp = 1;
     while (kp < g.k) kp <<= 1;
     const int per_step = (REV_BUCKET_THREADS / 64) * (64 / kp);   // lists a workgroup reads at a time
-    // about 2^14 edges per workgroup (measured: many short walks beat long runs per bucket)
+    // about 2^14 edges per workgroup (measured at 1M x 32: many short walks beat long runs per bucket), fewer where that would leave CUs without
+    // one (10 000 x 16: 18 + 9 us for the two walks with 10 workgroups)
     int64_t chunk = (1 << 14) / g.k;
+    if (chunk > (g.n + 255) / 256) chunk = (g.n + 255) / 256;
     chunk = (chunk + per_step - 1) / per_step * per_step;
     const unsigned grid = (unsigned)((g.n + chunk - 1) / chunk);
     for (int pass = 0; pass < 2; ++pass) {
@@ -384,22 +392,20 @@ void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hi
                 hipLaunchKernelGGL(rev_bucket_kernel<true>, dim3(grid), dim3(REV_BUCKET_THREADS), 0, s, g, sm.S, kp, sm.bshift, b0, nb, chunk, sm.bcnt,
                                    (const u64*)sm.boff, sm.ebuf);
         }
-        if (pass == 0) {
-            const int64_t nsb = (sm.nbuckets + SCAN_BLOCK - 1) / SCAN_BLOCK;
-            hipLaunchKernelGGL(scan_partial_kernel, dim3((unsigned)nsb), dim3(256), 0, s, sm.bcnt, sm.nbuckets, sm.scan_tmp);
-            hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, s, sm.scan_tmp, nsb, sm.boff + sm.nbuckets);
-            hipLaunchKernelGGL(scan_final_kernel, dim3((unsigned)nsb), dim3(256), 0, s, (const u32*)sm.bcnt, sm.nbuckets, sm.scan_tmp, sm.boff);
-        }
+        if (pass == 0)
+            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, (const u32*)sm.bcnt, sm.nbuckets, sm.boff, sm.wl_cnt);
     }
     for (int64_t bf = 0; bf < sm.nbuckets; bf += (1 << 20))
         hipLaunchKernelGGL(rev_select_kernel, dim3((unsigned)(sm.nbuckets - bf < (1 << 20) ? sm.nbuckets - bf : (1 << 20))), dim3(256), 0, s, g, sm,
                            hs_rev, bf);
 }
-// buckets of 2^shift targets: 128 (measured: the smaller the faster, down to there), more where the bucket step would otherwise
-// need more than four launches, each of which reads every list
+// Buckets of 2^shift targets: the smallest (16 at least) of which one launch of the bucket step takes all, because a workgroup of
+// the selection serves a bucket and n / 2^shift of them have to fill the chip; at 1M nodes that is 128.  More where the bucket step would
+// otherwise need more than four launches, each of which reads every list.
 int tg_rev_bucket_shift(int64_t n)
 {
-    int sh = 7;
+    int sh = 4;
+    while (sh < 7 && ((n + (1ll << sh) - 1) >> sh) > TG_REV_BUCKETS) ++sh;
     while (sh < TG_REV_MAX_SHIFT && ((n + (1ll << sh) - 1) >> sh) > 4 * TG_REV_BUCKETS) ++sh;
     return sh;
 }
