@@ -95,12 +95,13 @@ struct tg_knn_handle {
     TgSample sm;
     TgCand cd;
     hipStream_t stream;
+    u64* d_counters;     // the two arrays below
     u64* d_updates;      // TG_MAX_ROUNDS x TG_STAT_BINS partial counters (spread to avoid one hot address)
     u64* d_stat_bins;    // TG_MAX_ROUNDS x 2 x TG_STAT_BINS
     float* x_padded;     // own copy of X when the caller's rows are not 16-byte friendly
     uint8_t* xq;         // 8-bit screening copy of X, written when phase 2 begins
     float* xqm;          // its grid (three words, see TgGraph)
-    u32* d_screen_on;    // device flag: screening still pays (decided after each screened round)
+    u32* d_screen_on;    // device flags, one per phase-2 round: screening still pays (decided after each screened round for the next)
     u32* d_undefined;    // device counter: rows of X without a defined distance (written with the norms)
     uint16_t* xh;        // fp16 copy of X for the local join (join_f16 = 1, 2)
     u32* d_f16_ok;       // join_f16 = 2: device flag, 1 while every value of X is an fp16 number
@@ -138,8 +139,8 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->xqm = c.take<float>(64);          // also where the norms leave the range of the values
     h->g.Xq = h->xq;
     h->g.Xqm = h->xqm;
-    h->d_screen_on = c.take<u32>(64);
-    h->d_undefined = h->d_screen_on + 32;        // a word of its own line in the same 256 bytes
+    h->d_screen_on = c.take<u32>(TG_MAX_ROUNDS + 1);
+    h->d_undefined = c.take<u32>(64);
     // the register-resident join reads 64, 96 or 128 columns per row (4, 6 or 8 steps of 16); longer rows are whole steps of 32
     h->g.ldh = ld <= 64 ? 64 : ld <= 96 ? 96 : ld <= 128 ? 128 : (d + 31) & ~31;
     h->xh = p.join_f16 ? c.take<uint16_t>((size_t)n * h->g.ldh) : nullptr;
@@ -174,8 +175,9 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     }
     h->cd.C = p.C;
     h->cd.slots = c.take<u64>((size_t)n * p.C);
-    h->d_updates = c.take<u64>((size_t)TG_MAX_ROUNDS * TG_STAT_BINS);
-    h->d_stat_bins = c.take<u64>((size_t)TG_MAX_ROUNDS * 2 * TG_STAT_BINS);
+    h->d_counters = c.take<u64>((size_t)3 * TG_MAX_ROUNDS * TG_STAT_BINS);
+    h->d_updates = h->d_counters;
+    h->d_stat_bins = h->d_counters + (size_t)TG_MAX_ROUNDS * TG_STAT_BINS;
     *need = (c.used + 255) & ~(size_t)255;
 }
 
@@ -236,10 +238,17 @@ extern "C" int tg_knn_create(tg_knn_handle** out, const float* X, int64_t n, int
     h->norms_done = false;
     h->lists_ready = false;
     if (h->x_padded) tg_launch_pad_rows(X, n, d, h->x_padded, h->g.ld, h->stream);
-    tg_launch_fill_u32(h->sm.bcnt, (size_t)h->sm.nbuckets, 0u, h->stream);
-    tg_launch_fill_u64(h->cd.slots, (size_t)n * p->C, TG_EMPTY_KEY, h->stream);
-    tg_launch_fill_u64(h->d_updates, (size_t)TG_MAX_ROUNDS * TG_STAT_BINS, 0ull, h->stream);
-    tg_launch_fill_u64(h->d_stat_bins, (size_t)TG_MAX_ROUNDS * 2 * TG_STAT_BINS, 0ull, h->stream);
+    TgSetup z = {};
+    z.slots = h->cd.slots;
+    z.nslots = (size_t)n * p->C;
+    z.counters = h->d_counters;
+    z.ncounters = (size_t)3 * TG_MAX_ROUNDS * TG_STAT_BINS;
+    z.bcnt = h->sm.bcnt;
+    z.nbuckets = (size_t)h->sm.nbuckets;
+    z.range = reinterpret_cast<uint32_t*>(h->xqm);
+    z.undefined = h->d_undefined;
+    z.f16_ok = h->d_f16_ok;
+    tg_launch_setup(z, h->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         delete h;
@@ -269,7 +278,6 @@ static void ensure_norms(tg_knn_handle* h)
     if (h->norms_done) return;
     int sp = begin_span(h, SPAN_NORMS, 0);
     tg_launch_norms(h->g, reinterpret_cast<uint32_t*>(h->xqm), h->d_undefined, h->stream);
-    if (h->d_f16_ok) tg_launch_fill_u32(h->d_f16_ok, 1, 1u, h->stream);
     // rounding every row whatever its values (join_f16 = 1): a row with a value beyond +-65504 has no fp16 copy to rank on, and is counted
     if (h->xh) tg_launch_narrow(h->g, h->xh, h->d_f16_ok, h->d_f16_ok ? nullptr : h->d_undefined, h->stream);
     end_span(h, sp);
@@ -336,8 +344,7 @@ extern "C" int tg_knn_begin_phase2(tg_knn_handle* h)
 {
     if (!h) return fail(TG_ERR_INVALID_ARG, "handle is NULL");
     if (!h->lists_ready) return fail(TG_ERR_INVALID_ARG, "no lists yet: call tg_knn_init or tg_knn_import first");
-    tg_launch_mark_all_fresh(h->g, h->stream);
-    if (h->xq) tg_launch_fill_u32(h->d_screen_on, 1, 1u, h->stream);
+    tg_launch_mark_all_fresh(h->g, h->xq ? h->d_screen_on + h->rounds2 : nullptr, h->stream);
     if (!h->phase2 && h->xq) {
         ensure_norms(h);
         int sp = begin_span(h, SPAN_NORMS, 0);
@@ -356,7 +363,7 @@ extern "C" int tg_knn_phase2_round(tg_knn_handle* h, int64_t* updates)
     if (h->round >= TG_MAX_ROUNDS) return fail(TG_ERR_INVALID_ARG, "more than %d rounds", TG_MAX_ROUNDS);
     const int r = h->round;
     int sp = begin_span(h, SPAN_JOIN, r);
-    tg_launch_phase2(h->g, h->p.m, h->d_updates + (size_t)r * TG_STAT_BINS, h->d_stat_bins + (size_t)r * 2 * TG_STAT_BINS, h->d_screen_on,
+    tg_launch_phase2(h->g, h->p.m, h->d_updates + (size_t)r * TG_STAT_BINS, h->d_stat_bins + (size_t)r * 2 * TG_STAT_BINS, h->d_screen_on + h->rounds2,
                      h->stream);
     end_span(h, sp);
     u32* t = h->g.gid; h->g.gid = h->g.gid_next; h->g.gid_next = t;   // the written lists are current now

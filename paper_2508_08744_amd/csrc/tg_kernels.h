@@ -72,7 +72,20 @@ struct TgCand {
     unsigned long long* slots;   // n x C keys, TG_EMPTY_KEY when free
 };
 
-// range: two words for the smallest and largest value of X, or NULL; undefined: one word that counts the rows without a defined distance, or NULL
+// what tg_launch_setup writes: the words of a workspace that a build expects to start from
+struct TgSetup {
+    unsigned long long* slots;      // nslots (even) x TG_EMPTY_KEY
+    size_t nslots;
+    unsigned long long* counters;   // ncounters x 0
+    size_t ncounters;
+    uint32_t* bcnt;                 // nbuckets x 0
+    size_t nbuckets;
+    uint32_t* range;                // see tg_launch_norms and tg_launch_quantize
+    uint32_t* undefined;
+    uint32_t* f16_ok;               // 1, or null
+};
+void tg_launch_setup(const TgSetup& z, hipStream_t s);
+// range: two words for the smallest and largest value of X (which start at ordered +infinity and -infinity) and the flag at TG_RANGE_NONINT, or NULL; undefined: a word to which the rows without a defined distance are added, or NULL
 void tg_launch_norms(const TgGraph& g, uint32_t* range, uint32_t* undefined, hipStream_t s);
 void tg_launch_init(const TgGraph& g, uint64_t hs_init, hipStream_t s);
 void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, hipStream_t s);
@@ -98,9 +111,10 @@ void tg_launch_join_distances(const TgGraph& g, const int32_t* blk, const int32_
 // flip: the entries sampled as new for this round become old (first update of a round)
 void tg_launch_update(const TgGraph& g, const TgSample& sm, const TgCand& c, unsigned long long* updates,
                       bool flip, hipStream_t s);
-void tg_launch_mark_all_fresh(const TgGraph& g, hipStream_t s);
+// screen_on: set to 1, or null
+void tg_launch_mark_all_fresh(const TgGraph& g, uint32_t* screen_on, hipStream_t s);
 void tg_launch_phase2(const TgGraph& g, int m, unsigned long long* updates, unsigned long long* stat_bins,
-                      uint32_t* screen_on /* device flag, used when g.Xq is set */, hipStream_t s);
+                      uint32_t* screen_on /* used when g.Xq is set: the round's flag; the next word becomes the next round's */, hipStream_t s);
 // range: the words tg_launch_norms filled, or null: where they show whole numbers whose fp32 sums are all exact, nothing is recomputed
 void tg_launch_finalize(const TgGraph& g, int recompute, const uint32_t* range, int32_t* out_ids, float* out_dist, hipStream_t s);
 void tg_launch_export(const TgGraph& g, int32_t* ids, float* dist, uint8_t* fresh, hipStream_t s);

@@ -42,6 +42,29 @@ void tg_launch_fill_u32(u32* p, size_t count, u32 v, hipStream_t s)
     if (count) hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(count, 256)), dim3(256), 0, s, p, count, v);
 }
 
+// What a build expects in its workspace before the first step, in one launch (11 launches of 2-6 us each otherwise: 48 us of a
+// build of 10 000 nodes): empty candidate slots, zero counters, the starting values of the range of X and of the flags.
+__global__ __launch_bounds__(256) void setup_kernel(TgSetup z)
+{
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    uint4* slots = reinterpret_cast<uint4*>(z.slots);
+    for (size_t i = i0; i < z.nslots / 2; i += stride) slots[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    for (size_t i = i0; i < z.ncounters; i += stride) z.counters[i] = 0ull;
+    for (size_t i = i0; i < z.nbuckets; i += stride) z.bcnt[i] = 0u;
+    if (i0 == 0) {
+        z.range[0] = 0xFF800000u;            // ordered +infinity: the smallest value so far
+        z.range[1] = 0x007FFFFFu;            // ordered -infinity
+        z.range[2] = 0u;                     // largest distance of a row from its grid point
+        z.range[TG_RANGE_NONINT] = 0u;
+        *z.undefined = 0u;
+        if (z.f16_ok) *z.f16_ok = 1u;
+    }
+}
+void tg_launch_setup(const TgSetup& z, hipStream_t s)
+{
+    hipLaunchKernelGGL(setup_kernel, dim3(grid_for(z.nslots / 2, 256)), dim3(256), 0, s, z);
+}
+
 // rows of d floats -> rows of ld floats, zero padded
 __global__ void pad_rows_kernel(const float* __restrict__ X, int64_t n, int d, float* __restrict__ Xp, int ld)
 {
@@ -109,21 +132,20 @@ __global__ __launch_bounds__(256) void norms_kernel(const float* __restrict__ X,
     if (threadIdx.x == 0) {
         u32 a = s_lo[0], b = s_hi[0];
         for (int i = 1; i < 16; ++i) { a = min(a, s_lo[i]); b = max(b, s_hi[i]); }
-        atomicMin(range + 0, a);
-        atomicMax(range + 1, b);
+        // atomics on one address take turns (about 25 ns each): only workgroups that move an end of the range use one
+        if (a < __atomic_load_n(range + 0, __ATOMIC_RELAXED)) atomicMin(range + 0, a);
+        if (b > __atomic_load_n(range + 1, __ATOMIC_RELAXED)) atomicMax(range + 1, b);
     }
     if (__ballot(nonint) != 0ull && tg_lane() == 0 && range[TG_RANGE_NONINT] == 0u) range[TG_RANGE_NONINT] = 1u;
 }
 void tg_launch_norms(const TgGraph& g, uint32_t* range, uint32_t* undefined, hipStream_t s)
 {
-    if (undefined) tg_launch_fill_u32(undefined, 1, 0u, s);
-    if (range) {
-        tg_launch_fill_u32(range + 0, 1, 0xFF800000u, s);      // ordered +infinity: the smallest value so far
-        tg_launch_fill_u32(range + 1, 1, 0x007FFFFFu, s);      // ordered -infinity
-        tg_launch_fill_u32(range + TG_RANGE_NONINT, 1, 0u, s);
-    }
+    // with the range asked for, few workgroups at small n: they all end at once and would queue at its two words (10 000 x 32: 28 us
+    // with 625 workgroups, 37 511 x 52: 106 us with 2048)
     const int64_t wgs = (g.n + 15) / 16;
-    hipLaunchKernelGGL(norms_kernel, dim3((unsigned)(wgs < 2048 ? wgs : 2048)), dim3(256), 0, s, g.X, g.n, g.d, g.ld, g.nrm,
+    int64_t most = 2048;
+    if (range && g.n * g.ld < (int64_t)1 << 25) most = 256;
+    hipLaunchKernelGGL(norms_kernel, dim3((unsigned)(wgs < most ? wgs : most)), dim3(256), 0, s, g.X, g.n, g.d, g.ld, g.nrm,
                        g.metric == 2 ? g.rnorm : (float*)nullptr, range, undefined);
 }
 
@@ -190,14 +212,14 @@ __global__ __launch_bounds__(256) void quantize_kernel(TgGraph g, uint8_t* __res
     if (threadIdx.x == 0) {
         float e = s_err[0];
         for (int i = 1; i < 16; ++i) e = fmaxf(e, s_err[i]);
-        atomicMax(grid + 2, __float_as_uint(e));          // not negative: the bit patterns order the values
+        // not negative: the bit patterns order the values
+        if (__float_as_uint(e) > __atomic_load_n(grid + 2, __ATOMIC_RELAXED)) atomicMax(grid + 2, __float_as_uint(e));
     }
 }
 void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, hipStream_t s)
 {
-    // the first two words of the grid (smallest and largest value of X) were found together with the norms
+    // the first two words of the grid (smallest and largest value of X) were found together with the norms, the third starts at zero
     u32* grid = reinterpret_cast<u32*>(Xqm);
-    tg_launch_fill_u32(grid + 2, 1, 0u, s);
     const int64_t range_wgs = (g.n + 15) / 16;
     hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)(range_wgs < 2048 ? range_wgs : 2048)), dim3(256), 0, s, g, Xq, grid);
 }
@@ -732,17 +754,18 @@ void tg_launch_update(const TgGraph& g, const TgSample& sm, const TgCand& c, u64
     });
 }
 
-// phase switch: every entry unvisited
-__global__ void mark_fresh_kernel(u32* gid, size_t count)
+// phase switch: every entry unvisited; screening is tried in the coming round
+__global__ void mark_fresh_kernel(u32* gid, size_t count, u32* screen_on)
 {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0 && screen_on) *screen_on = 1u;
     size_t stride = (size_t)gridDim.x * blockDim.x;
     for (; i < count; i += stride) gid[i] |= 0x80000000u;
 }
-void tg_launch_mark_all_fresh(const TgGraph& g, hipStream_t s)
+void tg_launch_mark_all_fresh(const TgGraph& g, uint32_t* screen_on, hipStream_t s)
 {
     size_t count = (size_t)g.n * g.k;
-    hipLaunchKernelGGL(mark_fresh_kernel, dim3(grid_for(count, 256)), dim3(256), 0, s, g.gid, count);
+    hipLaunchKernelGGL(mark_fresh_kernel, dim3(grid_for(count, 256)), dim3(256), 0, s, g.gid, count, screen_on);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -905,20 +928,20 @@ void phase2_screen_kernel(TgGraph g, int m, int set_words, u64* updates, u64* st
 {
     phase2_body<true>(g, m, set_words, updates, stat_bins, screen_on);
 }
-__global__ __launch_bounds__(64 * LISTS_WAVES) void phase2_plain_kernel(TgGraph g, int m, int set_words, u64* updates, u64* stat_bins,
-                                                                        const u32* screen_on)
-{
-    phase2_body<false>(g, m, set_words, updates, stat_bins, screen_on);
-}
 // Screening pays when the 8-bit codes are nearly lossless (byte-valued features); on real-valued
 // data in high dimension most candidates pass the bound and its reads are wasted.  After a
 // screened round: if more than half of the candidates went on to the fp32 evaluation, the
-// following rounds measure every candidate directly.
-__global__ __launch_bounds__(256) void screen_decide_kernel(const u64* __restrict__ stat_bins, u32* screen_on)
+// following rounds measure every candidate directly.  The first workgroup of the plain variant, launched behind
+// the screened one, decides and leaves the answer in the next round's word (its own word is still being read by its neighbours).
+__device__ __forceinline__ void screen_decide(const u64* __restrict__ stat_bins, u32* screen_on)
 {
-    __shared__ u64 red[2][4];
+    __shared__ u64 red[2][LISTS_WAVES];
     u64 pairs = 0, measured = 0;
-    for (int i = threadIdx.x; i < TG_STAT_BINS; i += 256) {
+    if (screen_on[0] == 0u) {
+        if (threadIdx.x == 0) screen_on[1] = 0u;
+        return;
+    }
+    for (int i = threadIdx.x; i < TG_STAT_BINS; i += 64 * LISTS_WAVES) {
         pairs += stat_bins[i];
         measured += stat_bins[TG_STAT_BINS + i];
     }
@@ -929,10 +952,16 @@ __global__ __launch_bounds__(256) void screen_decide_kernel(const u64* __restric
     if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = pairs; red[1][threadIdx.x >> 6] = measured; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        pairs = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-        measured = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-        if (*screen_on != 0u && 2 * measured > pairs) *screen_on = 0u;
+        pairs = measured = 0;
+        for (int i = 0; i < LISTS_WAVES; ++i) { pairs += red[0][i]; measured += red[1][i]; }
+        screen_on[1] = 2 * measured > pairs ? 0u : 1u;
     }
+}
+__global__ __launch_bounds__(64 * LISTS_WAVES) void phase2_plain_kernel(TgGraph g, int m, int set_words, u64* updates, u64* stat_bins,
+                                                                        u32* screen_on)
+{
+    if (screen_on && blockIdx.x == 0) screen_decide(stat_bins, screen_on);
+    phase2_body<false>(g, m, set_words, updates, stat_bins, screen_on);
 }
 #define PHASE2_GRID 16384
 void tg_launch_phase2(const TgGraph& g, int m, u64* updates, u64* stat_bins, u32* screen_on, hipStream_t s)
@@ -948,11 +977,10 @@ void tg_launch_phase2(const TgGraph& g, int m, u64* updates, u64* stat_bins, u32
         hipLaunchKernelGGL(phase2_screen_kernel, dim3((unsigned)blocks), dim3(64 * LISTS_WAVES), shm, s, g, m, set_words, updates, stat_bins,
                            (const u32*)screen_on);
         hipLaunchKernelGGL(phase2_plain_kernel, dim3((unsigned)blocks), dim3(64 * LISTS_WAVES), shm, s, g, m, set_words, updates, stat_bins,
-                           (const u32*)screen_on);
-        hipLaunchKernelGGL(screen_decide_kernel, dim3(1), dim3(256), 0, s, (const u64*)stat_bins, screen_on);
+                           screen_on);
     } else {
         hipLaunchKernelGGL(phase2_plain_kernel, dim3((unsigned)blocks), dim3(64 * LISTS_WAVES), shm, s, g, m, set_words, updates, stat_bins,
-                           (const u32*)nullptr);
+                           (u32*)nullptr);
     }
 }
 
