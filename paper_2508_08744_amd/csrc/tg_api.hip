@@ -351,6 +351,7 @@ extern "C" int tg_knn_begin_phase2(tg_knn_handle* h)
         ensure_norms(h);
         int sp = begin_span(h, SPAN_NORMS, 0);
         tg_launch_quantize(h->g, h->xq, h->xqm, h->stream);
+        tg_launch_phase2_probe(h->g, h->p.m, h->d_undefined + 32, h->d_screen_on + h->rounds2, h->stream);
         end_span(h, sp);
     }
     h->phase2 = true;

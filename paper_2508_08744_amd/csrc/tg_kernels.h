@@ -81,7 +81,7 @@ struct TgSetup {
     uint32_t* bcnt;                 // nbuckets x 0
     size_t nbuckets;
     uint32_t* range;                // see tg_launch_norms and tg_launch_quantize
-    uint32_t* undefined;
+    uint32_t* undefined;            // this word and three of the next line
     uint32_t* f16_ok;               // 1, or null
 };
 void tg_launch_setup(const TgSetup& z, hipStream_t s);
@@ -113,6 +113,8 @@ void tg_launch_update(const TgGraph& g, const TgSample& sm, const TgCand& c, uns
                       bool flip, hipStream_t s);
 // screen_on: set to 1, or null
 void tg_launch_mark_all_fresh(const TgGraph& g, uint32_t* screen_on, hipStream_t s);
+// decides whether the first round screens; words: three zeros
+void tg_launch_phase2_probe(const TgGraph& g, int m, uint32_t* words, uint32_t* screen_on, hipStream_t s);
 void tg_launch_phase2(const TgGraph& g, int m, unsigned long long* updates, unsigned long long* stat_bins,
                       uint32_t* screen_on /* used when g.Xq is set: the round's flag; the next word becomes the next round's */, hipStream_t s);
 // range: the words tg_launch_norms filled, or null: where they show whole numbers whose fp32 sums are all exact, nothing is recomputed

@@ -57,6 +57,7 @@ __global__ __launch_bounds__(256) void setup_kernel(TgSetup z)
         z.range[2] = 0u;                     // largest distance of a row from its grid point
         z.range[TG_RANGE_NONINT] = 0u;
         *z.undefined = 0u;
+        for (int i = 0; i < 3; ++i) z.undefined[32 + i] = 0u;      // (of the phase-2 probe)
         if (z.f16_ok) *z.f16_ok = 1u;
     }
 }
@@ -778,8 +779,9 @@ void tg_launch_mark_all_fresh(const TgGraph& g, uint32_t* screen_on, hipStream_t
 // and repeats are settled through an id set in LDS; the few candidates that survive the
 // screening are put into the list one by one (many: sorted and merged).
 // ---------------------------------------------------------------------------------------
-template <bool SCREEN>
-__device__ __forceinline__ void phase2_node(const TgGraph& g, int64_t v, int m, int set_words, u64* updates, u64* stat_bins)
+// PROBE: nothing is measured or written; counts[0] and counts[1] grow by the candidates of v and by those that pass the screen.
+template <bool SCREEN, bool PROBE>
+__device__ __forceinline__ void phase2_node(const TgGraph& g, int64_t v, int m, int set_words, u64* updates, u64* stat_bins, u32* counts)
 {
     extern __shared__ float smem[];
     const int wave = threadIdx.x >> 6, lane = tg_lane();
@@ -869,6 +871,7 @@ __device__ __forceinline__ void phase2_node(const TgGraph& g, int64_t v, int m, 
         if (alive == 0) continue;
         const int nalive = __popcll(alive);
         measured += nalive;
+        if (PROBE) continue;
         if (!staged) {
             stage_row(g, v, xs);
             staged = true;
@@ -894,6 +897,11 @@ __device__ __forceinline__ void phase2_node(const TgGraph& g, int64_t v, int m, 
             if (lane >= k) L = TG_EMPTY_KEY;
         }
     }
+    if (PROBE) {
+        counts[0] += (u32)evaluated;
+        counts[1] += (u32)measured;
+        return;
+    }
     const int ins = __popcll(__ballot(lane < k && (L & 2ull)));
     if (lane < k) {
         g.gid_next[v * k + lane] = tg_key_id(L) | (((u32)L & 1u) << 31);
@@ -917,7 +925,7 @@ __device__ __forceinline__ void phase2_body(const TgGraph& g, int m, int set_wor
     if (screen_on && (*screen_on != 0u) != SCREEN) return;
     const int wave = threadIdx.x >> 6;
     for (int64_t v = (int64_t)blockIdx.x * LISTS_WAVES + wave; v < g.n; v += (int64_t)gridDim.x * LISTS_WAVES) {
-        phase2_node<SCREEN>(g, v, m, set_words, updates, stat_bins);
+        phase2_node<SCREEN, false>(g, v, m, set_words, updates, stat_bins, nullptr);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
@@ -963,14 +971,64 @@ __global__ __launch_bounds__(64 * LISTS_WAVES) void phase2_plain_kernel(TgGraph 
     if (screen_on && blockIdx.x == 0) screen_decide(stat_bins, screen_on);
     phase2_body<false>(g, m, set_words, updates, stat_bins, screen_on);
 }
-#define PHASE2_GRID 16384
-void tg_launch_phase2(const TgGraph& g, int m, u64* updates, u64* stat_bins, u32* screen_on, hipStream_t s)
+// The same decision for the first round of the phase, from the candidates of up to 2048 nodes spread over the lists: a first round
+// that screens in vain measures nearly everything, four rows at a time (10M x 96, cosine: 68 ms, 40 without screening, which is
+// 4.8 TB/s of rows; more rows at a time in the screened variant cost it registers: 300 000 x 128 bytes: 0.45 -> 0.67 ms a round).
+// words: three zeros, and zeros again at the end; the last workgroup to finish decides.
+#define PROBE_WGS 256
+#define PROBE_EACH 2         // nodes per wave
+__global__ __launch_bounds__(64 * LISTS_WAVES) void phase2_probe_kernel(TgGraph g, int m, int set_words, u32* words, u32* screen_on)
+{
+    __shared__ u32 sum[2];
+    const int wave = threadIdx.x >> 6;
+    if (threadIdx.x < 2) sum[threadIdx.x] = 0u;
+    __syncthreads();
+    u32 counts[2] = {0u, 0u};
+    const int64_t many = (int64_t)PROBE_WGS * LISTS_WAVES * PROBE_EACH;
+    const int64_t apart = g.n / many > 0 ? g.n / many : 1;
+    for (int i = 0; i < PROBE_EACH; ++i) {
+        const int64_t v = (((int64_t)blockIdx.x * LISTS_WAVES + wave) * PROBE_EACH + i) * apart;
+        if (v < g.n) phase2_node<true, true>(g, v, m, set_words, nullptr, nullptr, counts);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (tg_lane() == 0) {
+        atomicAdd(&sum[0], counts[0]);
+        atomicAdd(&sum[1], counts[1]);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    atomicAdd(words + 0, sum[0]);
+    atomicAdd(words + 1, sum[1]);
+    __threadfence();
+    if (atomicAdd(words + 2, 1u) != gridDim.x - 1) return;
+    const u32 pairs = atomicExch(words + 0, 0u), measured = atomicExch(words + 1, 0u);
+    atomicExch(words + 2, 0u);
+    *screen_on = 2u * measured > pairs ? 0u : 1u;
+}
+static size_t phase2_lds(const TgGraph& g, int set_words)
+{
+    return (size_t)LISTS_WAVES * g.ld * sizeof(float) + LISTS_WAVES * (128 + (size_t)set_words) * sizeof(u32) +
+           (size_t)LISTS_WAVES * (g.Xq ? g.ldq + 32 : 0);
+}
+static int phase2_set_words(const TgGraph& g, int m)
 {
     // the id set holds the k listed ids and at most m k candidates; half as many words again, as a power of two
     int set_words = 64;
     while (set_words * 2 < 3 * (g.k + m * g.k)) set_words *= 2;
-    const size_t shm = (size_t)LISTS_WAVES * g.ld * sizeof(float) + LISTS_WAVES * (128 + (size_t)set_words) * sizeof(u32) +
-                       (size_t)LISTS_WAVES * (g.Xq ? g.ldq + 32 : 0);
+    return set_words;
+}
+void tg_launch_phase2_probe(const TgGraph& g, int m, u32* words, u32* screen_on, hipStream_t s)
+{
+    if (g.n < 1 << 15) return;         // (the launch costs about as much as a round of so few nodes can lose)
+    const int set_words = phase2_set_words(g, m);
+    hipLaunchKernelGGL(phase2_probe_kernel, dim3(PROBE_WGS), dim3(64 * LISTS_WAVES), phase2_lds(g, set_words), s, g, m, set_words, words, screen_on);
+}
+#define PHASE2_GRID 16384
+void tg_launch_phase2(const TgGraph& g, int m, u64* updates, u64* stat_bins, u32* screen_on, hipStream_t s)
+{
+    const int set_words = phase2_set_words(g, m);
+    const size_t shm = phase2_lds(g, set_words);
     int64_t blocks = (g.n + LISTS_WAVES - 1) / LISTS_WAVES;
     if (blocks > PHASE2_GRID) blocks = PHASE2_GRID;
     if (g.Xq) {
