@@ -696,7 +696,7 @@ __global__ __launch_bounds__(64 * LISTS_WAVES) void update_kernel(TgGraph g, int
             const bool known = lds_set_insert(seen, set_mask, set_shift, cid, cand);
             if (!cand || known) ck = TG_EMPTY_KEY;
             if (__ballot(ck != TG_EMPTY_KEY) == 0) continue;
-            ck = tg_wave_sort(ck);
+            ck = tg_wave_sort_first(ck, nq - q0);
             L = tg_wave_merge_low(L, ck);
             if (lane >= k) L = TG_EMPTY_KEY;
             if (q0 == 0 && nq > 128) {
