@@ -78,7 +78,10 @@ typedef enum { TG_METRIC_L2 = 0, TG_METRIC_IP = 1, TG_METRIC_COSINE = 2 } tg_met
  *            only those that may still enter the list; the bound is rigorous, so the graph is
  *            the same as with 0, which measures every candidate (section 4.1 as written).
  *            When more than half of a round's candidates pass the bound (real-valued data in
- *            high dimension) the following rounds measure every candidate directly
+ *            high dimension; the first round is judged on a sample of the nodes) the rounds measure every candidate directly.
+ *            Where X holds whole numbers within 255 of each other, small enough that every fp32 sum is exact (see finalize), at
+ *            most 128 of them a row and TG_METRIC_L2, the copy is X itself, and the local join of phase 1 takes its
+ *            (exact) products from it as well: the graph is the same bit for bit
  *   join_f16 1: the local join of phase 1 forms its inner products on the fp16 matrix
  *            instructions from a copy of the vectors rounded to fp16 (round to nearest even;
  *            n x (64, 96, 128, or d rounded up to 32) x 2 bytes of workspace), accumulating in fp32; norms,

@@ -1,8 +1,8 @@
 // The C boundary (include/tagore_knn.h): argument checks, workspace layout, and the round
 // loop of Algorithm 1.  Host code only; every device step is a launcher from tg_kernels.h.
 #include "../../include/tagore_knn.h"
-#include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_device.h"
 #include "tg_exact.h"
 
 #include <cmath>
@@ -139,6 +139,7 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->xqm = c.take<float>(64);          // also where the norms leave the range of the values
     h->g.Xq = h->xq;
     h->g.Xqm = h->xqm;
+    h->g.bytes = h->xq && tg_join_bytes_possible(n, ld, p.metric) ? reinterpret_cast<const uint32_t*>(h->xqm) : nullptr;
     h->d_screen_on = c.take<u32>(TG_MAX_ROUNDS + 1);
     h->d_undefined = c.take<u32>(64);
     // the register-resident join reads 64, 96 or 128 columns per row (4, 6 or 8 steps of 16); longer rows are whole steps of 32
@@ -282,6 +283,7 @@ static void ensure_norms(tg_knn_handle* h)
     tg_launch_norms(h->g, reinterpret_cast<uint32_t*>(h->xqm), h->d_undefined, h->stream);
     // rounding every row whatever its values (join_f16 = 1): a row with a value beyond +-65504 has no fp16 copy to rank on, and is counted
     if (h->xh) tg_launch_narrow(h->g, h->xh, h->d_f16_ok, h->d_f16_ok ? nullptr : h->d_undefined, h->stream);
+    if (h->g.bytes) tg_launch_quantize(h->g, h->xq, h->xqm, true, h->stream);      // bytes: the join reads the codes
     end_span(h, sp);
     h->norms_done = true;
 }
@@ -350,7 +352,7 @@ extern "C" int tg_knn_begin_phase2(tg_knn_handle* h)
     if (!h->phase2 && h->xq) {
         ensure_norms(h);
         int sp = begin_span(h, SPAN_NORMS, 0);
-        tg_launch_quantize(h->g, h->xq, h->xqm, h->stream);
+        tg_launch_quantize(h->g, h->xq, h->xqm, false, h->stream);      // (bytes: done together with the norms)
         tg_launch_phase2_probe(h->g, h->p.m, h->d_undefined + 32, h->d_screen_on + h->rounds2, h->stream);
         end_span(h, sp);
     }

@@ -9,6 +9,7 @@ typedef unsigned long long u64;
 typedef unsigned int u32;
 
 #define TG_WAVE 64
+#define TG_RANGE_NONINT 8        // word of the range buffer: set when a value of X is not a whole number
 #define TG_EMPTY_KEY 0xFFFFFFFFFFFFFFFFull
 #define TG_GOLDEN 0x9E3779B97F4A7C15ull
 #define TG_ID_MASK 0x7FFFFFFFu     // list word: id in bits 0..30, "fresh" mark in bit 31
@@ -194,6 +195,19 @@ __device__ inline u32 tg_wave_sort32(u32 key)
 }
 
 __device__ inline u64 tg_lanemask_lt() { return (1ull << tg_lane()) - 1ull; }
+
+// Whether X holds bytes in the wider sense: whole numbers within 255 of each other, small enough that every fp32 sum of the norms,
+// the inner products and their combination is exact (2 d max|x|^2 <= 2^24).  range: what the kernel of the norms found.
+__device__ inline bool tg_whole_exact(const u32* __restrict__ range, int d)
+{
+    if (range[TG_RANGE_NONINT] != 0u) return false;
+    const float m = fmaxf(fabsf(tg_unord(range[0])), fabsf(tg_unord(range[1])));
+    return 2.0f * (float)d * m * m <= 16777216.0f;
+}
+__device__ inline bool tg_whole_bytes(const u32* __restrict__ range, int d)
+{
+    return tg_whole_exact(range, d) && tg_unord(range[1]) - tg_unord(range[0]) <= 255.0f;
+}
 
 // work record of the join: anchor | |NEW| << 32 | (|NEW|+|OLD|) << 40
 __device__ inline u64 tg_pack_rec(u32 v, int nN, int nT) { return (u64)v | ((u64)nN << 32) | ((u64)nT << 40); }

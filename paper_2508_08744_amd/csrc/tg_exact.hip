@@ -15,8 +15,8 @@
 //   3. The list is cut by its own k-th smallest w + m, what is left is measured directly and sorted.
 // A query whose list overflows (masses of equal distances, or rounding coarser than the distances) is measured
 // against every row directly instead (exact_scan_kernel).
-#include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_device.h"
 #include "tg_exact.h"
 
 #include <cmath>

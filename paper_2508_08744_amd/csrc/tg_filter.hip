@@ -24,8 +24,8 @@
 // 16 s + 4 q .. + 3 of the current chunk of columns of candidate 16 t + r: one load instruction
 // reads 64 contiguous bytes of each of 16 rows.  dis(p, c) is summed in difference form from
 // the same registers.
-#include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_device.h"
 
 // Collect: the neighbours; those and theirs for rows of at most 32 ids; the same for rows of up to 64 ids
 // (a larger id set and queue per wave, which leaves room for three waves per workgroup)

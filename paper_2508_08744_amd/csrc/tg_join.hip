@@ -17,8 +17,8 @@
 //      candidate slots, word by word by atomic minimum.
 // Only pairs (a,b) with a NEW and position a < b are used, so every new-new and new-old
 // pair counts once and old-old pairs never.
-#include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_device.h"
 
 #define JOIN_THREADS 256
 #define JOIN_CELLS 8                                   // cells per member: one per group of eight positions (mod 8)
@@ -574,6 +574,7 @@ __global__ __launch_bounds__(256) void join_wave_kernel(TgGraph g, TgSample sm, 
     const int r16 = lane & 15, q4 = lane >> 4;
     const float INF = __builtin_inff();
     if (g.f16_ok && (*g.f16_ok != 0u) != NARROW) return;      // the other variant's turn
+    if (MODE == 0 && g.bytes && tg_whole_bytes(g.bytes, g.d)) return;      // join_bytes_kernel's
     const int64_t count = wl ? (int64_t)*wl_cnt : direct_count;
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     const u32 idmax = (u32)(g.n - 1);
@@ -863,6 +864,193 @@ __global__ __launch_bounds__(256) void join_wave_kernel(TgGraph g, TgSample sm, 
     if (MODE == 0 && prev_nT > 0) flush_cells(buf ^ 1, prev_v, prev_nT);
 }
 
+// ---------------------------------------------------------------------------------------
+// The join on the 8-bit codes, for X that holds bytes (tg_whole_bytes: found by the kernel of the norms, so both this and
+// the variants above are launched and the flag decides).  c = code - 128 differs from x by one constant, so
+// |x - y|^2 = |c_x|^2 + |c_y|^2 - 2 <c_x, c_y> holds in whole numbers, and it is the very number the fp32 join
+// arrives at, whose sums are all exact then.  A row is 128 bytes instead of 512, a 16 x 16 tile of 128 columns two
+// matrix instructions of 16 cycles instead of 32 of 32, a block of 64 members 32 registers instead of 128.
+// One wave per anchor, blocks of at most 64 members (lists 1 and 0 of the part); register layout, cells and hand-over
+// as in join_wave_kernel.  |c|^2 of every member comes off the diagonal of its group's own tile.
+// 1M x 128, k = 32: the joins of the four rounds take 4.7 + 2.5 + 2.6 + 3.6 ms (8.9 + 5.9 + 6.0 + 6.9 in fp32, 5.8 + 3.3 + 3.5 + 4.9 on the
+// fp16 copy); in the first round what bounds it is the minima in LDS, eight lanes at a time on one cell.
+// ---------------------------------------------------------------------------------------
+typedef int intx4 __attribute__((ext_vector_type(4)));
+#define BYTES_FAR (1 << 28)          // the norm of a row that must not count: its distances are beyond BYTES_MOST
+#define BYTES_MOST 1e8f              // thresholds are cut to this (the distances are at most 2^24)
+struct BytesShared {
+    u64 cell[64 * JOIN_CELLS];       // all empty between blocks
+    int nrm[64], thr[64], id[64];
+    u32 salt[64];
+    u32 adj[64][2];
+};
+template <int KS>
+__global__ __launch_bounds__(256) void join_bytes_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins, int part, int64_t cap)
+{
+    __shared__ __align__(16) BytesShared shs[4];
+    if (!tg_whole_bytes(g.bytes, g.d)) return;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = tg_lane();
+    BytesShared& sh = shs[wave];
+    const int r16 = lane & 15, q4 = lane >> 4;
+    const int64_t nwaves = (int64_t)gridDim.x * 4;
+    const u32 idmax = (u32)(g.n - 1);
+    const int64_t count1 = sm.wl_cnt[part * 3 + 1], count = count1 + sm.wl_cnt[part * 3];
+    const u64* wl1 = sm.wl + (int64_t)(part * 3 + 1) * cap;
+    const u64* wl0 = sm.wl + (int64_t)(part * 3) * cap;
+    auto lds_fence = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto load_rec = [&](int64_t w) -> u64 {
+        const int64_t wc = w < count ? w : count - 1;
+        const u64 rec = wc < count1 ? wl1[wc] : wl0[wc - count1];
+        return w < count ? rec : 0ull;
+    };
+    struct Item { u32 v; int nN, nT; const u32* bids; };
+    auto decode = [&](u64 rec) {
+        Item it;
+        const int nN = (int)((rec >> 32) & 0xFFu), nT = (int)((rec >> 40) & 0xFFu);
+        const bool ok = (u32)rec <= idmax && nN > 0 && nN <= nT && nT >= 2 && nT <= 64 && nT <= sm.BC;
+        it.v = ok ? (u32)rec : 0u;
+        it.nN = ok ? nN : 0;
+        it.nT = ok ? nT : 0;
+        it.bids = sm.blk + (int64_t)it.v * sm.BC;
+        return it;
+    };
+    // ids of this lane's row in every group (rows past the block repeat row 0)
+    auto fetch_ids = [&](const Item& it, u32 (&idr)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int row = 16 * t + r16;
+            idr[t] = min(it.bids[row < it.nT ? row : 0], idmax);
+        }
+    };
+    intx4 X[4][KS];
+    auto fetch_rows = [&](const u32 (&idr)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const int col = 64 * s + 16 * q4;
+                X[t][s] = *reinterpret_cast<const intx4*>(g.Xq + (int64_t)idr[t] * g.ldq + (col < g.ldq ? col : 0));
+            }
+    };
+    for (int c = lane; c < 64 * JOIN_CELLS; c += 64) sh.cell[c] = TG_EMPTY_KEY;
+    int64_t w = (int64_t)blockIdx.x * 4 + wave;
+    if (w >= count) return;
+    Item cur = decode(load_rec(w)), nxt = decode(load_rec(w + nwaves));
+    u32 idn[4];
+    fetch_ids(cur, idn);
+    fetch_rows(idn);
+    int mid = (int)min(cur.bids[lane < cur.nT ? lane : 0], idmax);
+    u64 m_kth = g.kth[mid];
+    u64 m_adj = *reinterpret_cast<const u64*>(sm.adj + (((int64_t)cur.v >> sm.parts_shift) * sm.BC + (lane < cur.nT ? lane : 0)) * (int64_t)sm.adj_words);
+    fetch_ids(nxt, idn);
+    int midn = (int)min(nxt.bids[lane < nxt.nT ? lane : 0], idmax);
+    for (; w < count; w += nwaves) {
+        const u64 rec2 = load_rec(w + 2 * nwaves);
+        const int nN = cur.nN, nT = cur.nT, MT = (nN + 15) >> 4, NT = (nT + 15) >> 4;
+        // the block's member data: one member per lane
+        sh.id[lane] = mid;
+        // one more than the distance of the list's last entry (a whole number, unless the caller imported another list)
+        sh.thr[lane] = (int)fmaxf(0.0f, floorf(fminf(tg_unord((u32)(m_kth >> 32)), BYTES_MOST)) + 1.0f);
+        sh.salt[lane] = (u32)tg_mix64(hs_slot + (u64)(u32)mid);
+        sh.adj[lane][0] = (u32)m_adj;
+        sh.adj[lane][1] = (u32)(m_adj >> 32);
+        // codes -> signed, and the squared norms off the diagonals
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (t >= NT) break;
+            intx4 acc = (intx4){0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const bool real = 64 * s + 16 * q4 < g.ldq;
+                X[t][s] = real ? X[t][s] ^ (int)0x80808080 : (intx4){0, 0, 0, 0};
+                acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(X[t][s], X[t][s], acc, 0, 0, 0);
+            }
+            const int lo = (r16 & 1) ? acc[1] : acc[0], hi = (r16 & 1) ? acc[3] : acc[2];
+            if (q4 == (r16 >> 2)) sh.nrm[16 * t + r16] = 16 * t + r16 < nT ? ((r16 & 2) ? hi : lo) : BYTES_FAR;
+        }
+        if (stat_bins && lane == 0 && nT > 0) {
+            const u64 pairs = (u64)nN * (u64)(nN - 1) / 2 + (u64)nN * (u64)(nT - nN);
+            atomicAdd(stat_bins + (cur.v & (TG_STAT_BINS - 1)), pairs);
+            atomicAdd(stat_bins + TG_STAT_BINS + (cur.v & (TG_STAT_BINS - 1)), (u64)nT);
+        }
+        lds_fence();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i >= MT) break;
+            const int a0 = 16 * i + 4 * q4;
+            intx4 na = *reinterpret_cast<const intx4*>(&sh.nrm[a0]), ta = *reinterpret_cast<const intx4*>(&sh.thr[a0]);
+            const intx4 ida = *reinterpret_cast<const intx4*>(&sh.id[a0]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (a0 + e >= nN) na[e] = BYTES_FAR;               // OLD members meet the NEW ones as columns only
+            u32 adj_a[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = i; j < 4; ++j) {
+                if (j >= NT) break;
+                if (j == i || j == 2) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) adj_a[e] = sh.adj[a0 + e][j >> 1];
+                }
+                intx4 acc = (intx4){0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(X[i][s], X[j][s], acc, 0, 0, 0);
+                const int b = 16 * j + r16;
+                const int nb = sh.nrm[b];
+                const u32 tb = (u32)sh.thr[b], adj_b = sh.adj[b][i >> 1];
+                int dist[4];
+                u32 drow[4], dcol[4];
+                bool prow[4], pcol[4], any = false;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    dist[e] = (na[e] + nb) - 2 * acc[e];
+                    if (i == j && r16 <= 4 * q4 + e) dist[e] = BYTES_FAR;      // only the diagonal tile has pairs on or below the diagonal
+                    // b is a candidate of a unless a's list holds it, and a of b likewise: such a pair gets every bit set
+                    drow[e] = (u32)dist[e] | (u32)__builtin_amdgcn_sbfe((int)adj_a[e], 16 * (j & 1) + r16, 1);
+                    dcol[e] = (u32)dist[e] | (u32)__builtin_amdgcn_sbfe((int)adj_b, 16 * (i & 1) + 4 * q4 + e, 1);
+                    prow[e] = drow[e] < (u32)ta[e];
+                    pcol[e] = dcol[e] < tb;
+                    any |= prow[e] | pcol[e];
+                }
+                if (__ballot(any) == 0ull) continue;
+                const u32 idb = ((u32)sh.id[b] << 2) | 3u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const u64 hi = (u64)(__float_as_uint((float)dist[e]) | 0x80000000u) << 32;
+                    if (prow[e]) atomicMin(&sh.cell[(a0 + e) * JOIN_CELLS + 2 * j + (r16 >> 3)], hi | idb);
+                    if (pcol[e]) atomicMin(&sh.cell[b * JOIN_CELLS + 2 * i + (q4 >> 1)], hi | (u64)(((u32)ida[e] << 2) | 3u));
+                }
+            }
+        }
+        // the next block's rows and member data start travelling, then this block's candidates leave
+        const Item nxt2 = decode(rec2);
+        fetch_rows(idn);
+        const u64 k_next = g.kth[midn];
+        const u64 adj_next =
+            *reinterpret_cast<const u64*>(sm.adj + (((int64_t)nxt.v >> sm.parts_shift) * sm.BC + (lane < nxt.nT ? lane : 0)) * (int64_t)sm.adj_words);
+        fetch_ids(nxt2, idn);
+        const int midn2 = (int)min(nxt2.bids[lane < nxt2.nT ? lane : 0], idmax);
+        lds_fence();
+        for (int p0 = 0; p0 < nT; p0 += 8) {
+            const int p = p0 + (lane >> 3), q = lane & 7;
+            const u64 key = sh.cell[p * JOIN_CELLS + q];
+            if (key != TG_EMPTY_KEY) {
+                sh.cell[p * JOIN_CELLS + q] = TG_EMPTY_KEY;
+                emit_candidate(cd, (u32)sh.id[p], idmax, sh.salt[p], key, cur.v, q);
+            }
+        }
+        lds_fence();
+        cur = nxt;
+        nxt = nxt2;
+        mid = midn;
+        midn = midn2;
+        m_kth = k_next;
+        m_adj = adj_next;
+    }
+}
+
 static size_t join_lds_bytes(int DK, int rows)
 {
     return JOIN_HDR_BYTES + JOIN_ADJ_BYTES + JOIN_CELL_BYTES + (size_t)rows * (DK + 4) * sizeof(float);
@@ -875,6 +1063,7 @@ static void allow_large_lds(K kernel, size_t bytes)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+#define JOIN_BYTES_GRID 1536
 #define JOIN_GRID 2048     // persistent launches: workgroups walk the work list with this stride
 
 static int64_t wl_cap(int64_t n, int parts) { return (n + parts - 1) / parts; }
@@ -982,6 +1171,12 @@ void tg_launch_join(const TgGraph& g, const TgSample& sm, const TgCand& c, int p
                     unsigned long long* stat_bins, hipStream_t s)
 {
     const bool wv = wave_path(g);
+    if (g.bytes) {
+        const int64_t cap = wl_cap(g.n, parts);
+        const dim3 grid(JOIN_BYTES_GRID), block(256);
+        if (g.ldq <= 64) hipLaunchKernelGGL(join_bytes_kernel<1>, grid, block, 0, s, g, sm, c, hs_slot, stat_bins, part, cap);
+        else hipLaunchKernelGGL(join_bytes_kernel<2>, grid, block, 0, s, g, sm, c, hs_slot, stat_bins, part, cap);
+    }
     if (wv) {
         launch_wave_t<3>(g, sm, c, hs_slot, stat_bins, part * 3 + 0, parts, s);
         launch_wave_t<4>(g, sm, c, hs_slot, stat_bins, part * 3 + 1, parts, s);

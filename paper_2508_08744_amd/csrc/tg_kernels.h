@@ -14,7 +14,6 @@
 // of lanes) of its own are therefore launched once per chunk of TG_LAUNCH_NODES nodes and told
 // where their chunk begins; the chunk size is a multiple of every such group size.
 #define TG_LAUNCH_NODES (1ll << 24)
-#define TG_RANGE_NONINT 8        // word of the range buffer: set when a value of X is not a whole number
 #define TG_REV_BUCKETS 8192      // buckets of reverse edges one launch counts in LDS
 #define TG_REV_MAX_SHIFT 11      // a bucket holds at most 2048 targets
 #define TG_REV_MAX_W (1 << TG_REV_MAX_SHIFT)
@@ -44,6 +43,8 @@ struct TgGraph {
     int32_t ldq;        // d rounded up to 16: a row of codes never straddles more lines than it must
     const uint16_t* Xh; // n x ldh: the rows rounded to fp16 for the local join, or null (join in fp32)
     int32_t ldh;        // 64, 96 or 128 (the smallest that holds d), d rounded up to 32 beyond: columns d..ldh-1 are zero
+    const uint32_t* bytes;  // the range of X, or null: set when the join on the 8-bit codes is launched too.  If X turns out to hold bytes
+                            // (tg_whole_bytes) the blocks of at most 64 members are its work and the other variants leave them alone
     const uint32_t* f16_ok; // device flag, or null: 1 while every value of X has turned out to be an fp16 number.  When set,
                             // both variants of the join are launched and the one the flag does not name ends at once
 };
@@ -88,13 +89,17 @@ void tg_launch_setup(const TgSetup& z, hipStream_t s);
 // range: two words for the smallest and largest value of X (which start at ordered +infinity and -infinity) and the flag at TG_RANGE_NONINT, or NULL; undefined: a word to which the rows without a defined distance are added, or NULL
 void tg_launch_norms(const TgGraph& g, uint32_t* range, uint32_t* undefined, hipStream_t s);
 void tg_launch_init(const TgGraph& g, uint64_t hs_init, hipStream_t s);
-void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, hipStream_t s);
+// when: the codes are wanted now if X holds bytes (true) or if it does not (false), or in any case (null range in g.bytes)
+void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, bool when_bytes, hipStream_t s);
 void tg_launch_narrow(const TgGraph& g, uint16_t* Xh, uint32_t* exact_flag /* cleared when a value is no fp16 number, or null */,
                       uint32_t* overflow_rows /* counts the rows with a finite value beyond fp16's range, or null */, hipStream_t s);
 void tg_launch_fill_u64(unsigned long long* p, size_t count, unsigned long long v, hipStream_t s);
 void tg_launch_fill_u32(uint32_t* p, size_t count, uint32_t v, hipStream_t s);
 void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hipStream_t s);
 int tg_rev_bucket_shift(int64_t n);
+// whether the join on the 8-bit codes is worth its launches: they cost about 4 us a part where X turns out to hold no bytes (a round
+// of 65 536 nodes takes 0.4 ms)
+static inline bool tg_join_bytes_possible(int64_t n, int ld, int metric) { return n >= 65536 && ld <= 128 && metric == 0; }
 // rows the register-resident join takes
 static inline bool tg_join_wave_ok(int ld) { return ld <= 128; }
 // which members of a block sit in which member's list, for the anchors of one part: sm.adj (to run before tg_launch_join of that part);

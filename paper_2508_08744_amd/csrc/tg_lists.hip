@@ -6,8 +6,8 @@
 // rewrites a given list in a given kernel; other nodes reach a list only through its
 // candidate slots (atomic minimum) or through the previous round's snapshot.
 #include <hip/hip_fp16.h>
-#include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_device.h"
 
 #define LISTS_WAVES 4   // wavefronts (= nodes) per workgroup
 
@@ -164,11 +164,13 @@ __device__ inline void quantize_grid(const u32* grid, float& lo, float& s)
 {
     lo = tg_unord(grid[0]);
     const float hi = tg_unord(grid[1]);
-    s = hi > lo ? (hi - lo) / 255.0f : 1.0f;
+    // whole numbers within 255 of each other are their own grid: the codes are exact
+    s = grid[TG_RANGE_NONINT] == 0u && hi - lo <= 255.0f ? 1.0f : hi > lo ? (hi - lo) / 255.0f : 1.0f;
 }
-__global__ __launch_bounds__(256) void quantize_kernel(TgGraph g, uint8_t* __restrict__ Xq, u32* __restrict__ grid)
+__global__ __launch_bounds__(256) void quantize_kernel(TgGraph g, uint8_t* __restrict__ Xq, u32* __restrict__ grid, bool when_bytes)
 {
     __shared__ float s_err[16];
+    if (g.bytes && tg_whole_bytes(g.bytes, g.d) != when_bytes) return;
     const int sub = threadIdx.x & 15;
     float lo, s;
     quantize_grid(grid, lo, s);
@@ -217,12 +219,12 @@ __global__ __launch_bounds__(256) void quantize_kernel(TgGraph g, uint8_t* __res
         if (__float_as_uint(e) > __atomic_load_n(grid + 2, __ATOMIC_RELAXED)) atomicMax(grid + 2, __float_as_uint(e));
     }
 }
-void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, hipStream_t s)
+void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, bool when_bytes, hipStream_t s)
 {
     // the first two words of the grid (smallest and largest value of X) were found together with the norms, the third starts at zero
     u32* grid = reinterpret_cast<u32*>(Xqm);
     const int64_t range_wgs = (g.n + 15) / 16;
-    hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)(range_wgs < 2048 ? range_wgs : 2048)), dim3(256), 0, s, g, Xq, grid);
+    hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)(range_wgs < 2048 ? range_wgs : 2048)), dim3(256), 0, s, g, Xq, grid, when_bytes);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1062,12 +1064,9 @@ __global__ __launch_bounds__(64 * LISTS_WAVES) void finalize_kernel(TgGraph g, i
         id = (int)(g.gid[v * k + lane] & TG_ID_MASK);
         dist = g.gdist[v * k + lane];
     }
-    if (recompute && range && g.metric != 2 && range[TG_RANGE_NONINT] == 0u) {
-        // Whole numbers small enough that every fp32 sum of the norms, the inner products and their combination is exact
-        // (2 d max|x|^2 <= 2^24): the distances in the lists are the directly computed ones already, bit for bit.
-        const float m = fmaxf(fabsf(tg_unord(range[0])), fabsf(tg_unord(range[1])));
-        if (2.0f * (float)g.d * m * m <= 16777216.0f) recompute = 0;
-    }
+    // Where every fp32 sum of the norms, the inner products and their combination is exact, the distances in the lists are the
+    // directly computed ones already, bit for bit.
+    if (recompute && range && g.metric != 2 && tg_whole_exact(range, g.d)) recompute = 0;
     if (recompute) {
         stage_row(g, v, xs);
         const float rn_v = g.metric == 2 ? g.rnorm[v] : 1.0f;

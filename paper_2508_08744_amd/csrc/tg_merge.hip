@@ -8,8 +8,8 @@
 // in LDS that keeps for every id the first entry that brought it (global entries come first);
 // the survivors of both rows are sorted as (distance, id) keys with the wave's bitonic network,
 // merged, and the first k are written back.  Rows shorter than k end in id -1, distance +inf.
-#include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_device.h"
 
 #define MERGE_MAP_WORDS 256          // at most 128 ids per node
 #define MERGE_FREE 0xFFFFFFFFu

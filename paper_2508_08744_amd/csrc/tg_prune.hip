@@ -10,8 +10,8 @@
 // per lane and only the entries in front of F's own position in A's row, and each lane looks
 // its D up in the map.  A ballot per row gives the count.  Rows of different useful length are
 // balanced as in the paper, by pairing positions q and k - 1 - q inside one group of lanes.
-#include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_device.h"
 
 #define PRUNE_ENTRIES 256       // 128 buckets of two (id, position) entries for the at most 64 ids of a row
 #define PRUNE_FREE 0xFFFFFFFFu

@@ -8,8 +8,8 @@
 // and, a wave per target, keeps per class the R arrivals with the smallest
 // (hash(round, source, u), source): a uniform subset that does not depend on arrival order.
 // The same wave then assembles the anchor's block and stores it for the join.
-#include "tg_device.h"
 #include "tg_kernels.h"
+#include "tg_device.h"
 
 // ---- walk of a workgroup over the sampled edges of the lists [vbeg, vend): each group of KP lanes
 // (KP = power of two >= k) owns one list at a time
