@@ -28,14 +28,16 @@
 #include "tg_device.h"
 
 // Collect: the neighbours; those and theirs for rows of at most 32 ids; the same for rows of up to 64 ids
-// (a larger id set and queue per wave, which leaves room for three waves per workgroup)
+// (a larger id set and queue per wave)
 #define FILTER_ONE_HOP 1
 #define FILTER_TWO_HOPS 2
 #define FILTER_TWO_HOPS_WIDE 3
-// id set (a power of two, at most half full) and queue of the 2-hop collection: at most k + k * k ids
-__host__ __device__ constexpr int filter_set_words(int collect) { return collect == FILTER_TWO_HOPS_WIDE ? 8192 : 2048; }
+// 2-hop collection of at most k + k * k ids: places of the id set (a power of two, at most half of them taken) and words of the queue
+__host__ __device__ constexpr int filter_set_places(int collect) { return collect == FILTER_TWO_HOPS_WIDE ? 8192 : 2048; }
 __host__ __device__ constexpr int filter_queue_words(int collect) { return collect == FILTER_TWO_HOPS_WIDE ? 4224 : 1088; }
-__host__ __device__ constexpr int filter_waves(int collect) { return collect == FILTER_TWO_HOPS_WIDE ? 3 : 4; }
+#define FILTER_WAVES 4
+#define FILTER_LOADS 8          // rows of second-hop ids on their way at a time
+#define FILTER_NOWHERE 0xFFFFu  // a free place of the id set
 #define FILTER_GRID 16384
 #define FILTER_FREE 0xFFFFFFFFu
 
@@ -108,28 +110,52 @@ __device__ inline void filter_reduce_quarters(float (&dp)[NG])
 template <int NG>
 __device__ inline float filter_own(const float (&dp)[NG], int q4)
 {
-    // lane 16 q + r speaks for row 16 q + r (bit selects: an indexed read would go through scratch)
-    if (NG == 1) return dp[0];
-    if (NG == 2) return (q4 & 1) ? dp[1] : dp[0];
-    const float lo = (q4 & 1) ? dp[1] : dp[0];
-    const float hi = (q4 & 1) ? dp[NG - 1] : dp[2];
-    return (q4 & 2) ? hi : lo;
+    // lane 16 q + r speaks for row 16 q + r (values are picked from copies: an indexed read would go through scratch); rows
+    // past 16 NG are none
+    const float d0 = dp[0], d1 = dp[NG > 1 ? 1 : 0], d2 = dp[NG > 2 ? 2 : 0], d3 = dp[NG > 3 ? 3 : 0];
+    const float lo = (q4 & 1) ? d1 : d0;
+    const float hi = (q4 & 1) ? d3 : d2;
+    return (NG > 2 && (q4 & 2)) ? hi : lo;
 }
 
-template <int WORDS>
-__device__ inline bool filter_set_insert(u32* tab, u32 id, bool active)
+__device__ inline void filter_wave_sync()
 {
-    bool present = false, pending = active;
-    u32 h = (id * 0x9E3779B1u) >> (WORDS == 8192 ? 19 : 21);          // the top log2(WORDS) bits
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Appends the ids of the lanes that are `active` to the queue, each id once and only if it is not there already; returns the
+// queue's new length.  A place of the set holds where in the queue its id is (two bytes instead of the id's four: the set is
+// most of what a wave needs of LDS), or, while the ids of one call meet, 0x8000 | lane, the id being in batch[lane].  Lanes that
+// find the same place free all write it and read back who got it, so the accesses are volatile.  The set is at most half
+// full, so every search ends.
+template <int PLACES>
+__device__ inline int filter_collect(unsigned short* set, int* queue, int* batch, int Q, int id, bool active)
+{
+    volatile unsigned short* T = set;
+    const int lane = tg_lane();
+    const unsigned short mine = (unsigned short)(0x8000 | lane);
+    bool pending = active, fresh = false;
+    u32 h = ((u32)id * 0x9E3779B1u) >> (PLACES == 8192 ? 19 : 21);          // the top log2(PLACES) bits
+    batch[lane] = id;
+    filter_wave_sync();
     while (__ballot(pending)) {
+        if (pending && T[h] == FILTER_NOWHERE) T[h] = mine;
+        filter_wave_sync();
         if (pending) {
-            const u32 old = atomicCAS(tab + h, FILTER_FREE, id);
-            if (old == FILTER_FREE) pending = false;
-            else if (old == id) { present = true; pending = false; }
-            else h = (h + 1) & (WORDS - 1);
+            const u32 e = T[h];
+            const int there = (e & 0x8000u) ? batch[e & 63u] : queue[e];
+            if (e == mine) { fresh = true; pending = false; }
+            else if (there == id) pending = false;
+            else h = (h + 1) & (PLACES - 1);
         }
+        filter_wave_sync();
     }
-    return present;
+    const u64 mask = __ballot(fresh);
+    const int at = Q + __popcll(mask & tg_lanemask_lt());
+    if (fresh) { queue[at] = id; T[h] = (unsigned short)at; }
+    filter_wave_sync();
+    return Q + __popcll(mask);
 }
 
 // Angle at p between p -> r and p -> c from the squared lengths a = |p r|^2, b = |p c|^2, c = |r c|^2:
@@ -182,51 +208,47 @@ __device__ inline u32 filter_wave_max(u32 x)
     return max(max(r0, r1), max(r2, r3));
 }
 
-__device__ inline void filter_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 #define FILTER_RULE_DIST 0
 #define FILTER_RULE_ANGLE 1
 #define FILTER_RULE_DISPERSION 2
-// words of dynamic LDS per wave: the id set and queue of the 2-hop collection, and, later in the same
-// words, the matrix of angles of the dispersion rule (rows of 16 NG + 1 words)
-__host__ __device__ constexpr int filter_dyn_words(int ng, int collect, int rule)
+// Words of LDS per wave.  While ids are collected: the id -> first lane table of one hop (256 words behind the candidates' ids), or
+// the set, queue and batch of two hops.  Afterwards, in the same words: the candidates' ids (64), their distances to p and
+// norms and then their keys (128), and the sets of occluding candidates (128) or the matrix of angles (rows of 16 NG + 1 words).
+// With this a workgroup of the dispersion rule for k in 33..48 takes 40 704 bytes and one of the 2-hop collection 35 072, four a
+// CU (as separate arrays, with ids in the set: 78 and 62 KB, two a CU).
+__host__ __device__ constexpr int filter_lds_words(int ng, int collect, int rule)
 {
-    const int ids = collect == FILTER_ONE_HOP ? 0 : filter_set_words(collect) + filter_queue_words(collect);
-    const int angles = rule == FILTER_RULE_DISPERSION ? 16 * ng * (16 * ng + 1) : 0;
-    return ids > angles ? ids : angles;
+    const int ids = collect == FILTER_ONE_HOP ? 64 + 256 : filter_set_places(collect) / 2 + filter_queue_words(collect) + 64;
+    const int rows = 64 + 128 + (rule == FILTER_RULE_DISPERSION ? 16 * ng * (16 * ng + 1) : 128);
+    return ((ids > rows ? ids : rows) + 3) & ~3;
 }
 
+// Four waves per SIMD for the neighbours alone: the dispersion rule is bound by what a wave does in sequence (products, angles,
+// the greedy), 200 000 x 200, k = 40, d_out = 20: 2.65 ms with 64 rows and two waves, 1.85 ms with 48 rows and four.  Three for two
+// hops, which wait for rows (4 d bytes per distinct id, 5.5 TB/s): with four the compiler spills, 250 000 x 128, k = 32: 8.62
+// against 8.45 ms (9.17 with two waves and the rows of ids read one at a time).
 template <int NG, int KS, bool FULL, bool VEC, int COLLECT, int RULE>
-__global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
+__global__ __launch_bounds__(256, COLLECT == FILTER_ONE_HOP ? 4 : 3) void filter_dist_kernel(FilterArgs A)
 {
     constexpr bool TWO_HOPS = COLLECT != FILTER_ONE_HOP;
-    constexpr int WAVES = filter_waves(COLLECT);
-    constexpr int SET_WORDS = filter_set_words(COLLECT);
+    constexpr int PLACES = filter_set_places(COLLECT);
     constexpr bool ANGLE = RULE == FILTER_RULE_ANGLE;
-    constexpr int DYN = filter_dyn_words(NG, COLLECT, RULE);
+    constexpr int LDS_WORDS = filter_lds_words(NG, COLLECT, RULE);
     constexpr int AS = 16 * NG + 1;      // row stride of the matrix of angles
-    extern __shared__ u32 dyn[];         // per wave: see filter_dyn_words
-    __shared__ int s_cid[4][64];
-    __shared__ __align__(16) float s_dpc[4][64];
-    __shared__ __align__(16) float s_nrm[4][64];
-    __shared__ u32 s_occ[4][128];
-    __shared__ __align__(16) u64 s_key[4][64];       // the candidates' (distance, id) keys, read by every lane
-    __shared__ u32 s_twin[4][256];                   // 1-hop: id -> first lane that lists it (128 ids, 128 lanes)
+    extern __shared__ __align__(16) u32 lds[];
     const int wave = threadIdx.x >> 6, lane = tg_lane();
     const int r16 = lane & 15, q4 = lane >> 4;
-    int* cid = s_cid[wave];
-    float* dpc = s_dpc[wave];
-    float* nrm = s_nrm[wave];
-    u32* occ = s_occ[wave];
-    u64* skey = s_key[wave];
+    u32* own_lds = lds + wave * LDS_WORDS;
+    int* cid = reinterpret_cast<int*>(own_lds);
+    float* dpc = reinterpret_cast<float*>(own_lds + 64);
+    float* nrm = reinterpret_cast<float*>(own_lds + 128);
+    u64* skey = reinterpret_cast<u64*>(own_lds + 64);           // the candidates' (distance, id) keys, read by every lane
+    u32* occ = own_lds + 192;
+    float* ang = reinterpret_cast<float*>(own_lds + 192);
     const int k = A.k;
     const int nchunks = (A.d + 16 * KS - 1) / (16 * KS);
 
-    for (int64_t p = (int64_t)blockIdx.x * WAVES + wave; p < A.n; p += (int64_t)gridDim.x * WAVES) {
+    for (int64_t p = (int64_t)blockIdx.x * FILTER_WAVES + wave; p < A.n; p += (int64_t)gridDim.x * FILTER_WAVES) {
         const float* xp = A.X + p * A.d;
         int m = 0;
         // ---- Collect ----
@@ -236,7 +258,7 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
             // candidate l is entry l of the row; an entry that is no candidate (padding, p itself, an
             // id that an earlier entry lists already) keeps its place as a dead one and reads p's own row
             m = k;
-            u32* tw = s_twin[wave];
+            u32* tw = own_lds + 64;
             for (int i = lane; i < 256; i += 64) tw[i] = FILTER_FREE;
             filter_wave_sync();
             {
@@ -255,32 +277,30 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
             cid[lane] = u_ok ? u : (int)p;
             filter_wave_sync();
         } else {
-            u32* set = dyn + wave * DYN;
-            int* queue = reinterpret_cast<int*>(set + SET_WORDS);
-            for (int i = lane; i < SET_WORDS; i += 64) set[i] = FILTER_FREE;
+            unsigned short* set = reinterpret_cast<unsigned short*>(own_lds);
+            int* queue = reinterpret_cast<int*>(own_lds + PLACES / 2);
+            int* batch = queue + filter_queue_words(COLLECT);
+            for (int i = lane; i < PLACES / 8; i += 64) reinterpret_cast<uint4*>(set)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
             filter_wave_sync();
-            int Q = 0;
-            {
-                const bool fresh = u_ok && !filter_set_insert<SET_WORDS>(set, (u32)u, u_ok);
-                const u64 mask = __ballot(fresh);
-                if (fresh) queue[__popcll(mask & tg_lanemask_lt())] = u;
-                Q = __popcll(mask);
-            }
+            int Q = filter_collect<PLACES>(set, queue, batch, 0, u, u_ok);
             const int per = 64 / A.kp;
             const int my_row = lane / A.kp, r = lane - my_row * A.kp;
-            for (int j0 = 0; j0 < k; j0 += per) {
-                const int j = j0 + my_row;
-                const bool on = my_row < per && j < k && r < k;
-                const int32_t uj = __shfl(u, on ? j : 0);
-                const bool uj_ok = __shfl((int)u_ok, on ? j : 0) != 0;
-                const int32_t w = (on && uj_ok) ? A.ids[(int64_t)uj * k + r] : -1;
-                const bool w_ok = w >= 0 && w < A.n && w != p;
-                const bool fresh = w_ok && !filter_set_insert<SET_WORDS>(set, (u32)w, w_ok);
-                const u64 mask = __ballot(fresh);
-                if (fresh) queue[Q + __popcll(mask & tg_lanemask_lt())] = w;
-                Q += __popcll(mask);
+            for (int j0 = 0; j0 < k; j0 += FILTER_LOADS * per) {
+                int32_t w[FILTER_LOADS];
+#pragma unroll
+                for (int t = 0; t < FILTER_LOADS; ++t) {
+                    const int j = j0 + t * per + my_row;
+                    const bool on = my_row < per && j < k && r < k;
+                    const int32_t uj = __shfl(u, on ? j : 0);
+                    const bool uj_ok = __shfl((int)u_ok, on ? j : 0) != 0;
+                    w[t] = (on && uj_ok) ? A.ids[(int64_t)uj * k + r] : -1;
+                }
+#pragma unroll
+                for (int t = 0; t < FILTER_LOADS; ++t) {
+                    if (j0 + t * per >= k) break;                 // uniform
+                    Q = filter_collect<PLACES>(set, queue, batch, Q, w[t], w[t] >= 0 && w[t] < A.n && w[t] != p);
+                }
             }
-            filter_wave_sync();
             // distance to p of everything collected, 64 at a time; the 64 closest stay, in order
             u64 best = TG_EMPTY_KEY;
             for (int b0 = 0; b0 < Q; b0 += 64) {
@@ -297,6 +317,7 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
                 best = b0 == 0 ? key : tg_wave_merge_low(best, key);
             }
             m = min(min(Q, 64), A.cand_size);
+            filter_wave_sync();                // the queue's words hold the candidates' rows from here on
             if (lane < m) cid[lane] = (int)tg_key_id(best);
             filter_wave_sync();
         }
@@ -347,8 +368,10 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
             if (q4 == (r16 >> 2)) nrm[16 * t + r16] = (r16 & 2) ? hi : lo;
             if (q4 == 0) dpc[16 * t + r16] = dp[t];
         }
-        occ[lane] = 0u;
-        occ[lane + 64] = 0u;
+        if (RULE != FILTER_RULE_DISPERSION) {
+            occ[lane] = 0u;
+            occ[lane + 64] = 0u;
+        }
         filter_wave_sync();
         // occ[C] = the candidates R that would occlude C: not dis(p, C) < alpha^2 dis(R, C), or an angle
         // at p of at most gamma (that relation is symmetric in R and C).  The lane holds its column's
@@ -371,7 +394,6 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
                 const float rc3 = (nR.w + nC) - 2.0f * g.w;
                 if (RULE == FILTER_RULE_DISPERSION) {
                     // the angle of every pair, stored both ways round (row R, column C and the reverse)
-                    float* ang = reinterpret_cast<float*>(dyn + wave * DYN);
                     const int R = 16 * i + 4 * q4, C = 16 * j + r16;
                     const float th0 = filter_angle_at(dR.x, dC, rc0), th1 = filter_angle_at(dR.y, dC, rc1);
                     const float th2 = filter_angle_at(dR.z, dC, rc2), th3 = filter_angle_at(dR.w, dC, rc3);
@@ -416,6 +438,7 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
         const int my_id = lane < m ? cid[lane] : 0;
         const bool dead = TWO_HOPS ? lane >= m : !u_ok;
         const u64 key = dead ? TG_EMPTY_KEY : tg_key(own, (u32)my_id, 0u);
+        filter_wave_sync();                    // (over the distances and norms)
         skey[lane] = key;
         filter_wave_sync();
         // one bit per other candidate, shifted in from below: after J steps candidate j sits at bit J - 1 - j
@@ -434,7 +457,6 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
         const u64 live = ~__ballot(dead);
         const u64 before = (((u64)lt_hi << 32) | lt_lo) & live;
         filter_wave_sync();
-        const u64 occ_by = (((u64)occ[2 * lane + 1] << 32) | occ[2 * lane]) & before;
         // ---- the serial rule as a fixed point ----
         // c is inserted iff no inserted candidate in front of it occludes it.  Starting from "all
         // inserted", every pass settles at least the next candidate in order, so the set stops
@@ -442,7 +464,6 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
         const bool in_cut = !dead && __popcll(before) < A.cand_size;       // the cut to cand_size counts candidates only
         if (RULE == FILTER_RULE_DISPERSION) {
             // ---- greedy insertion: one candidate per pass ----
-            const float* ang = reinterpret_cast<const float*>(dyn + wave * DYN);
             const int want = min(A.d_out, __popcll(__ballot(in_cut)));
             const u32 rnk = (u32)__popcll(before);                  // place among the candidates, nearest first
             float score = 0.0f;                                     // sum of the angles to the inserted nodes
@@ -458,8 +479,11 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
                 const u32 sb = open ? __float_as_uint(score) + 1u : 0u;
                 const u32 top = filter_wave_max(sb);
                 const bool first = open && sb == top;
-                const u32 near = 64u - filter_wave_max(first ? 64u - rnk : 0u);
-                pick = __ballot(first && rnk == near);
+                pick = __ballot(first);
+                if (__popcll(pick) > 1) {                           // (uniform) equal sums
+                    const u32 near = 64u - filter_wave_max(first ? 64u - rnk : 0u);
+                    pick = __ballot(first && rnk == near);
+                }
             }
             if (my_pos >= 0) A.out_ids[p * A.d_out + my_pos] = my_id;
             if (lane >= want && lane < A.d_out) A.out_ids[p * A.d_out + lane] = -1;
@@ -467,6 +491,7 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
             filter_wave_sync();
             continue;
         }
+        const u64 occ_by = (((u64)occ[2 * lane + 1] << 32) | occ[2 * lane]) & before;
         u64 K = __ballot(in_cut);
         for (int pass = 0; pass < 65; ++pass) {
             const u64 Kn = __ballot(in_cut && (occ_by & K) == 0ull);
@@ -485,27 +510,26 @@ __global__ __launch_bounds__(256) void filter_dist_kernel(FilterArgs A)
 }
 
 template <class K>
-static void filter_launch(K kernel, const FilterArgs& A, int waves, size_t shm, hipStream_t s)
+static void filter_launch(K kernel, const FilterArgs& A, size_t shm, hipStream_t s)
 {
     // more than 64 KB of dynamic LDS has to be asked for
     if (shm > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-    int64_t wgs = (A.n + waves - 1) / waves;        // a wave per node; workgroups beyond the grid walk on
+    int64_t wgs = (A.n + FILTER_WAVES - 1) / FILTER_WAVES;        // a wave per node; workgroups beyond the grid walk on
     if (wgs > FILTER_GRID) wgs = FILTER_GRID;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(64 * waves), shm, s, A);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(64 * FILTER_WAVES), shm, s, A);
 }
 
 template <int NG, int COLLECT, int RULE>
 static void launch_filter(const FilterArgs& A, bool vec, hipStream_t s)
 {
-    constexpr int grid = filter_waves(COLLECT);     // waves per workgroup; filter_launch sizes the grid from it
-    const size_t shm = (size_t)filter_waves(COLLECT) * filter_dyn_words(NG, COLLECT, RULE) * sizeof(u32);
+    const size_t shm = (size_t)FILTER_WAVES * filter_lds_words(NG, COLLECT, RULE) * sizeof(u32);
     // two row groups take their columns in chunks of 64, four in chunks of 32: few registers, so that
     // four (three) waves per SIMD cover each other's loads
     constexpr int KS = NG > 2 ? 2 : 4;
     const bool full = vec && (A.d % (16 * KS) == 0);         // no column guards needed
-    if (full) filter_launch(filter_dist_kernel<NG, KS, true, true, COLLECT, RULE>, A, grid, shm, s);
-    else if (vec) filter_launch(filter_dist_kernel<NG, KS, false, true, COLLECT, RULE>, A, grid, shm, s);
-    else filter_launch(filter_dist_kernel<NG, KS, false, false, COLLECT, RULE>, A, grid, shm, s);
+    if (full) filter_launch(filter_dist_kernel<NG, KS, true, true, COLLECT, RULE>, A, shm, s);
+    else if (vec) filter_launch(filter_dist_kernel<NG, KS, false, true, COLLECT, RULE>, A, shm, s);
+    else filter_launch(filter_dist_kernel<NG, KS, false, false, COLLECT, RULE>, A, shm, s);
 }
 
 template <int RULE>
@@ -515,6 +539,7 @@ static void launch_filter_rule(const FilterArgs& A, bool vec, int most, hipStrea
     if (A.hops == 2 && A.k > 32) launch_filter<4, FILTER_TWO_HOPS_WIDE, RULE>(A, vec, s);
     else if (A.hops == 2) launch_filter<4, FILTER_TWO_HOPS, RULE>(A, vec, s);
     else if (most <= 32) launch_filter<2, FILTER_ONE_HOP, RULE>(A, vec, s);
+    else if (most <= 48) launch_filter<3, FILTER_ONE_HOP, RULE>(A, vec, s);
     else launch_filter<4, FILTER_ONE_HOP, RULE>(A, vec, s);
 }
 
