@@ -53,6 +53,22 @@ def test_padding_self_repeats_and_ids_without_a_node():
     _merge_both(n, k, shards)
 
 
+@pytest.mark.parametrize("k,kl,nl", [(32, 32, 151), (31, 17, 8), (32, 33, 77), (33, 32, 77), (1, 32, 33), (32, 1, 1)])
+def test_rows_at_the_edges_of_two_nodes_to_a_wave(k, kl, nl):
+    # up to 32 entries in both rows two nodes share a wave: odd numbers of nodes,
+    # unsorted rows with repeats beside sorted ones
+    rng = np.random.default_rng(100 * k + kl)
+    n, shards = 200, []
+    for _ in range(3):
+        l2g = rng.permutation(n)[:nl].astype(np.int32)
+        l_ids = rng.integers(0, nl, size=(nl, kl)).astype(np.int32)
+        l_dist = rng.integers(0, 40, size=(nl, kl)).astype(np.float32)
+        l_dist[::3].sort(axis=1)
+        l_ids[rng.integers(0, nl, 40), rng.integers(0, kl, 40)] = -1
+        shards.append((l_ids, l_dist, l2g))
+    _merge_both(n, k, shards)
+
+
 def test_a_local_node_without_a_global_row_is_skipped():
     n, k = 50, 4
     g_ids, g_dist = knn.lists_clear(n, k)
