@@ -30,6 +30,7 @@ typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
 #define EX_FULL 0
 #define EX_SAMPLE 1
 #define EX_FIRST 2
+#define EX_ALWAYS 3e38f  // -w of a row without a defined norm on the fp16 side (whose products are finite): above every threshold
 #define EX_QUEUE 128     // pairs a wave of the scan collects before they go to the lists
 #define EX_RT 128        // rows per tile of the scan
 #define EX_CHUNK 128     // bytes of a row per step of the scan (64 fp16 or 32 fp32 columns)
@@ -420,8 +421,9 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
         qself[j] = a.qrow[q];
         qa[j] = m.x; qe[j] = m.y; kq[j] = a.c1 * m.z;
         ntau[j] = -__builtin_inff();
-        if (q >= a.nq || qself[j] < 0) ntau[j] = __builtin_inff();      // no query: nothing passes
+        if (F16 && !(m.z < __builtin_inff())) qa[j] = qe[j] = kq[j] = 0.0f;    // a query without a defined norm: everything passes
         else if (!ALL) ntau[j] = -a.tau[q];
+        if (q >= a.nq || qself[j] < 0) ntau[j] = __builtin_inff();      // no query: nothing passes
     }
 
     floatx4 preB[4], preA[AP];
@@ -465,9 +467,12 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
         if (ch == 0 && tid < EX_RT) {
             const int par = (t - t0) & 1;
             const bool real = t * EX_RT + tid < nvisit;
-            s_c0[par][tid] = !real ? -__builtin_inff() : a.metric == 0 ? -0.5f * pre_rn : 0.0f;
+            const bool undefined = !(pre_rn < __builtin_inff()) || !(pre_c1 < __builtin_inff());
+            s_c0[par][tid] = !real ? -__builtin_inff() : F16 && undefined ? EX_ALWAYS : a.metric == 0 ? -0.5f * pre_rn : 0.0f;
             if (!F16) s_c1[par][tid] = pre_c1;
             float R = (!F16 && a.metric == 2) ? 1.0f : sqrtf(pre_rn), E = pre_er;
+            // a row without a defined norm is bounded by nothing (fp32: nor are its neighbours in the tile then; a maximum alone would pass over a NaN)
+            if (!F16 && undefined) R = __builtin_inff();
 #pragma unroll
             for (int o = 1; o < 16; o <<= 1) {
                 R = fmaxf(R, __shfl_xor(R, o));
@@ -576,7 +581,7 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
             for (int j = 0; j < 4; ++j) {
                 const floatx4 v = value(i, j);
                 const float best = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
-                hits |= (ALL || __ballot(best >= threshold(i, j)) != 0ull) ? 1u << (4 * i + j) : 0u;
+                hits |= (ALL || __ballot(F16 ? best >= threshold(i, j) : !(best < threshold(i, j))) != 0ull) ? 1u << (4 * i + j) : 0u;
             }
         // ... and those tiles one by one (one copy of the code for all of them: unrolled it drowned the loop above)
         while (hits) {
@@ -585,11 +590,12 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
             floatx4 v = (floatx4){0.f, 0.f, 0.f, 0.f};
             float thr = 0.0f;
             int self = -1;
+            bool live = false;                                              // a query whose list still has places
 #pragma unroll
             for (int i = 0; i < WI; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (at == 4 * i + j) { v = value(i, j); thr = threshold(i, j); self = qself[j]; if (ALL && ntau[j] > 0.0f) self = -2; }
+                    if (at == 4 * i + j) { v = value(i, j); thr = threshold(i, j); self = qself[j]; live = ntau[j] < __builtin_inff(); if (ALL && ntau[j] > 0.0f) self = -2; }
             const int ql = wq * 64 + 16 * (at & 3) + r16;
 #pragma unroll 1
             for (int e = 0; e < 4; ++e) {
@@ -601,7 +607,7 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
                     const u32 row = ex_row<SAMPLE>(a, (u32)jv);
                     a.buf[((int64_t)qb * QT + ql) * EX_CAP + jv] = row == (u32)self ? TG_EMPTY_KEY : key_hi | row;
                 } else {
-                    bool pass = ve >= thr && jv < nvisit;
+                    bool pass = (F16 ? ve >= thr : !(ve < thr) && live) && jv < nvisit;     // fp32: an undefined bound rules nothing out
                     if (__ballot(pass) == 0ull) continue;
                     const u32 row = ex_row<SAMPLE>(a, (u32)jv);
                     pass = pass && row != (u32)self;
@@ -654,7 +660,9 @@ __device__ inline u64 ex_upper_key(const ExScanArgs& a, u64 e, float4 qm, float 
     const u32 row = (u32)e;
     const float R = unit ? 1.0f : sqrtf(a.rn[row]) * 1.0001f, E = a.er ? a.er[row] : 0.0f;
     const float m = ex_margin(qm.x, qm.y, kq, R, E, a.c1);
-    return ((u64)tg_ord(tg_unord((u32)(e >> 32)) + m) << 32) | row;
+    const float up = tg_unord((u32)(e >> 32)) + m;
+    if (up != up) return TG_EMPTY_KEY;                                  // an undefined distance bounds no other
+    return ((u64)tg_ord(up) << 32) | row;
 }
 // tau of every query from the entries of a sample: one workgroup per query
 __global__ __launch_bounds__(256) void ex_select_kernel(ExScanArgs a, int k, int fixed_count, int unit)

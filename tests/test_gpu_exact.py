@@ -71,3 +71,29 @@ def test_exact_number_ranges(kind, metric):
     rows = np.concatenate([[17, 2999, 3000, 7999], rng.choice(n, size=150, replace=False)]).astype(np.int64)
     _check(X, 12, metric, rows)
     _check(X, 12, metric, rows[:40].copy(), static=True)
+
+
+# rows without a defined distance (NaN, infinite) have no place in the order, but lists stay full and the defined rows in them are the
+# nearest ones, wherever the others lie (in the first sample, too); every sum over whole numbers is exact
+@pytest.mark.parametrize("n,nq,undefined", [(2049, 40, 3), (2049, 150, 3), (9001, 150, 5), (9001, 40, 8995), (150, 20, 4)])
+@pytest.mark.parametrize("static", [False, True])
+def test_exact_with_undefined_rows(n, nq, undefined, static):
+    rng = np.random.default_rng(n + nq)
+    k, d = 10, 64
+    X = np.rint(rng.normal(0, 40, size=(n, d))).astype(np.float32)
+    order = rng.permutation(n)
+    good = np.sort(order[undefined:])
+    X[order[:undefined], rng.integers(0, d, undefined)] = np.nan
+    X[order[0]] = np.inf
+    rows = good[rng.integers(0, len(good), nq)].astype(np.int64)
+    Xg = torch.from_numpy(X).cuda()
+    ids, dist = (knn.exact_knn_static if static else knn.exact_knn)(Xg, k, "l2", torch.from_numpy(rows).cuda())
+    ids, dist = ids.cpu().numpy(), dist.cpu().numpy()
+    m = min(k, len(good) - 1)
+    oi, od = oracle.brute_force_knn(np.ascontiguousarray(X[good]), m, 0, np.searchsorted(good, rows).astype(np.int64))
+    for q in range(nq):
+        assert len(set(ids[q].tolist())) == k and (ids[q] >= 0).all()
+        real = np.isin(ids[q], good)
+        c = int(real.sum())
+        assert (ids[q][real] == good[oi[q, :c]]).all() and (dist[q][real] == od[q, :c]).all()
+        assert c >= min(m, k - undefined)
