@@ -20,13 +20,13 @@
 #define PRUNE_PASSES 8
 
 // What a lane does in pass t of a round of eight passes that starts at pair p0 depends only on the
-// lane, t, p0 and k: which neighbour F of A it reads (the lane of A's row that holds F), which
-// entry of F's row, and F's own position (0 when the lane has nothing to read: no position is
-// below 0, so such a lane never reports a hit).
+// lane, t, p0 and k: which neighbour F of A it reads (the lane of A's row that holds F, which is F's
+// own position) and which entry of F's row.  A lane with nothing to read has position 0: no position is
+// below 0, so it never reports a hit.  Positions are kept times four throughout, in the map too: the byte
+// address ds_bpermute wants.
 struct PruneLaneTable {
-    int src[PRUNE_PASSES];      // byte address for ds_bpermute: 4 x (lane that holds F)
-    int rr[PRUNE_PASSES];       // entry of F's row
-    u32 jpos[PRUNE_PASSES];     // F's position in A's row, 0 if idle
+    u32 pos4[PRUNE_PASSES];     // 4 x F's position in A's row, 0 if idle
+    u32 rr4[PRUNE_PASSES];      // 4 x entry of F's row
 };
 
 __device__ inline void prune_fill_table(PruneLaneTable& T, int p0, int k, int kp, int per, int npairs, int my_row, int r)
@@ -39,22 +39,26 @@ __device__ inline void prune_fill_table(PruneLaneTable& T, int p0, int k, int kp
         const int j = lo ? jlo : jhi;
         const int rr = lo ? r : r - jlo;
         const bool on = my_row < per && q < npairs && (lo || (jhi != jlo && rr < jhi));
-        T.src[t] = on ? 4 * j : 0;
-        T.rr[t] = on ? rr : 0;
-        T.jpos[t] = on ? (u32)j : 0u;
+        T.pos4[t] = on ? (u32)(4 * j) : 0u;
+        T.rr4[t] = on ? (u32)(4 * rr) : 0u;
     }
 }
 
+// ONE (all pairs in one round of eight passes: k <= 32, the lane table never changes): the neighbours' entries are asked for before
+// the map is built, the next node's row before this one is looked up.  What bounds the kernel is instructions and the latency of the
+// entries: 1M lists of 32: 982 -> 931 us, of 16: 458 -> 436 us; without ONE 300 000 of 64: 1860 -> 1720 us (fewer table registers).  Asking
+// for the entries a whole node ahead took 1023 us (five waves per SIMD instead of six).
+// NEAR: the lists are less than 4 GiB, so an entry's byte offset has 32 bits (half the address registers).
+template <bool ONE, bool NEAR>
 __global__ __launch_bounds__(256) void prune_rank_kernel(const int32_t* __restrict__ ids, int64_t n, int k, int kp, int d_out,
                                                          int32_t* __restrict__ out_ids, int32_t* __restrict__ counts)
 {
-    __shared__ __align__(16) u32 maps[4][2 * PRUNE_ENTRIES];      // entry e: word 2e = id, word 2e + 1 = position
+    __shared__ __align__(16) u32 maps[4][2 * PRUNE_ENTRIES];      // entry e: word 2e = id, word 2e + 1 = position x 4
     const int wave = threadIdx.x >> 6, lane = tg_lane();
     u32* map = maps[wave];
     const int per = 64 / kp;                         // rows of neighbours per pass
     const int my_row = lane / kp, r = lane - my_row * kp;
     const int npairs = (k + 1) >> 1;
-    const bool one_round = npairs <= PRUNE_PASSES * per;          // k <= 32: the table never changes
     PruneLaneTable T;
     prune_fill_table(T, 0, k, kp, per, npairs, my_row, r);
     // the count of position P = lane comes out of the pass that serves pair q = min(P, k - 1 - P):
@@ -62,8 +66,29 @@ __global__ __launch_bounds__(256) void prune_rank_kernel(const int32_t* __restri
     const int myq = min(lane, k - 1 - lane);
     const int lp = 31 - __clz(per);                  // per is a power of two
     const u32 n32 = (u32)n;                          // n < 2^30
-    for (int64_t A = (int64_t)blockIdx.x * 4 + wave; A < n; A += (int64_t)gridDim.x * 4) {
-        const int32_t a = lane < k ? ids[A * k + lane] : -1;
+    const int64_t A0 = (int64_t)blockIdx.x * 4 + wave, step = (int64_t)gridDim.x * 4;
+    if (A0 >= n) return;                             // (no workgroup barrier below)
+    auto row_of = [&](int64_t A) __attribute__((always_inline)) -> int32_t {          // past the end: the last node's, never used
+        const int32_t got = ids[min(A, n - 1) * k + (lane < k ? lane : 0)];
+        return lane < k ? got : -1;
+    };
+    auto gather = [&](int32_t a, int32_t (&D)[PRUNE_PASSES]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < PRUNE_PASSES; ++t) {
+            const int32_t F = __builtin_amdgcn_ds_bpermute((int)T.pos4[t], a);
+            // row 0 where F is no node (one unsigned compare also rejects negative ids): what is found there is counted for F alone,
+            // and F's count is left out at the end
+            const u32 row = (u32)F < n32 ? (u32)F : 0u;
+            if (NEAR) D[t] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(ids) + (row * (4u * (u32)k) + T.rr4[t]));
+            else D[t] = ids[(u64)row * (u32)k + (T.rr4[t] >> 2)];
+        }
+    };
+    int32_t a = ONE ? row_of(A0) : -1, a_after = -1;
+    int32_t D[PRUNE_PASSES];
+    for (int64_t A = A0; A < n; A += step) {
+        if (ONE) a_after = row_of(A + step);
+        if (ONE) gather(a, D);
+        else a = row_of(A);
         const bool a_ok = (u32)a < n32;
         for (int i = lane; i < PRUNE_ENTRIES; i += 64) *reinterpret_cast<uint2*>(map + 2 * i) = make_uint2(PRUNE_FREE, PRUNE_NOPOS);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -76,7 +101,7 @@ __global__ __launch_bounds__(256) void prune_rank_kernel(const int32_t* __restri
             while (__ballot(pending)) {
                 if (pending) {
                     const u32 old = atomicCAS(map + 2 * e, PRUNE_FREE, (u32)a);
-                    if (old == PRUNE_FREE || old == (u32)a) { atomicMin(map + 2 * e + 1, (u32)lane); pending = false; }
+                    if (old == PRUNE_FREE || old == (u32)a) { atomicMin(map + 2 * e + 1, (u32)lane << 2); pending = false; }
                     else e = (e + 1) & (PRUNE_ENTRIES - 1);
                 }
             }
@@ -89,14 +114,9 @@ __global__ __launch_bounds__(256) void prune_rank_kernel(const int32_t* __restri
         // flight before the first look-up.
         u32 c = 0u;
         for (int p0 = 0; p0 < npairs; p0 += PRUNE_PASSES * per) {
-            if (!one_round) prune_fill_table(T, p0, k, kp, per, npairs, my_row, r);
-            int32_t D[PRUNE_PASSES];
-#pragma unroll
-            for (int t = 0; t < PRUNE_PASSES; ++t) {
-                const int32_t F = __builtin_amdgcn_ds_bpermute(T.src[t], a);
-                const bool scan = (T.jpos[t] != 0u) & ((u32)F < n32);        // one unsigned compare also rejects negative ids
-                const int32_t got = ids[(u64)(u32)(scan ? F : 0) * (u32)k + (u32)T.rr[t]];      // row 0 when there is nothing to read
-                D[t] = scan ? got : -1;
+            if (!ONE) {
+                prune_fill_table(T, p0, k, kp, per, npairs, my_row, r);
+                gather(a, D);
             }
             u64 mine = 0ull;                      // the ballot of the pass that serves this lane's position
 #pragma unroll
@@ -109,13 +129,13 @@ __global__ __launch_bounds__(256) void prune_rank_kernel(const int32_t* __restri
                 const uint4 b = *reinterpret_cast<const uint4*>(map + 2 * e);
                 // (no short cuts: every lane evaluates everything, nothing branches)
                 const bool e0 = b.x == d, e1 = b.z == d;
-                bool hit = (e0 & (b.y < T.jpos[t])) | (e1 & (b.w < T.jpos[t]));
+                bool hit = (e0 & (b.y < T.pos4[t])) | (e1 & (b.w < T.pos4[t]));
                 bool pending = !e0 & !e1 & (b.x != PRUNE_FREE) & (b.z != PRUNE_FREE);
                 e = (e + 2) & (PRUNE_ENTRIES - 1);
                 while (__ballot(pending)) {
                     if (pending) {
                         const uint2 w = *reinterpret_cast<const uint2*>(map + 2 * e);
-                        if (w.x == d) { hit = w.y < T.jpos[t]; pending = false; }
+                        if (w.x == d) { hit = w.y < T.pos4[t]; pending = false; }
                         else if (w.x == PRUNE_FREE) pending = false;
                         else e = (e + 1) & (PRUNE_ENTRIES - 1);
                     }
@@ -127,7 +147,7 @@ __global__ __launch_bounds__(256) void prune_rank_kernel(const int32_t* __restri
             if (lane < k && rel >= 0 && rel < PRUNE_PASSES * per) {
                 const int row = rel & (per - 1);
                 const int shift = row * kp + (lane == myq ? 0 : myq);       // the near partner's hits come first
-                c = (u32)__popcll((mine >> shift) & ((1ull << lane) - 1ull));
+                c = a_ok ? (u32)__popcll((mine >> shift) & ((1ull << lane) - 1ull)) : 0u;
             }
         }
         if (counts && lane < k) counts[A * k + lane] = (int32_t)c;
@@ -138,6 +158,7 @@ __global__ __launch_bounds__(256) void prune_rank_kernel(const int32_t* __restri
         if (lane < d_out) out_ids[A * d_out + lane] = keep;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        if (ONE) a = a_after;
     }
 }
 
@@ -147,5 +168,9 @@ void tg_launch_prune_rank(const int32_t* ids, int64_t n, int k, int d_out, int32
     while (kp < k) kp <<= 1;
     int64_t wgs = (n + 3) / 4;
     if (wgs > PRUNE_GRID) wgs = PRUNE_GRID;
-    hipLaunchKernelGGL(prune_rank_kernel, dim3((unsigned)wgs), dim3(256), 0, s, ids, n, k, kp, d_out, out_ids, counts);
+    const bool one_round = (k + 1) / 2 <= PRUNE_PASSES * (64 / kp);
+    const bool near = (uint64_t)n * (uint64_t)k * 4u < (1ull << 32);
+    auto kernel = one_round ? (near ? prune_rank_kernel<true, true> : prune_rank_kernel<true, false>)
+                            : (near ? prune_rank_kernel<false, true> : prune_rank_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(256), 0, s, ids, n, k, kp, d_out, out_ids, counts);
 }

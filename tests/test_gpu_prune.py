@@ -59,3 +59,18 @@ def test_padding_duplicates_and_bad_arguments():
     for bad in (0, k + 1):
         with pytest.raises(knn.TagoreError):
             knn.prune_rank(t, bad)
+
+
+# lists just below 4 GiB and of 4 GiB and more, where an entry's offset takes 64 bits: a small graph in the last rows
+@pytest.mark.parametrize("k", [32, 64])
+@pytest.mark.parametrize("more", [-1, 0, 3001])
+def test_lists_around_four_gibibytes(k, more):
+    n, m = 2 ** 30 // k + more, 1500
+    rng = np.random.default_rng(k)
+    small = np.stack([rng.permutation(m)[:k] for _ in range(m)]).astype(np.int32)
+    ids = torch.zeros((n, k), dtype=torch.int32, device="cuda")
+    ids[n - m:] = torch.from_numpy(small + (n - m)).cuda()
+    want_out, want_cnt = oracle.prune_rank(small, k // 2)
+    out, cnt = knn.prune_rank(ids, k // 2, want_counts=True)
+    assert (cnt[n - m:].cpu().numpy() == want_cnt).all()
+    assert (out[n - m:].cpu().numpy() == want_out + (n - m)).all()
