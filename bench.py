@@ -169,7 +169,7 @@ def main():
         "recall_at_k": recall,
         "recall_ok": bool(recall >= 0.95),
         "join_mfma_pct": 100.0 * achieved / MFMA_FP32_PEAK_TFLOPS,
-        "roofline": {"bound": "mfma", "kernel": "phase-1 local join of one round (join_wave_kernel<3>, <4> and join_kernel of every part; adj_kernel, which runs before them, is timed apart)",
+        "roofline": {"bound": "mfma", "kernel": "phase-1 local join of one round (join_wave_kernel<3>, <4>, or on byte-valued X join_bytes_kernel on i8 matrix instructions, and join_kernel of every part; adj_kernel, which runs before them, is timed apart)",
                      "achieved": achieved,
                      "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / MFMA_FP32_PEAK_TFLOPS,
                      "avg_launch_ms": avg_launch_ms, "launches": launches, "gather_GBps": gather_gbs,
