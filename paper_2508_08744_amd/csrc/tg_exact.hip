@@ -559,7 +559,9 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
             }
             buf ^= 1;
         }
-        // -w of every pair of the tile against -tau - m: which of the wave's 16 x 16 tiles hold a pair that passes ...
+        // -w of every pair of the tile against -tau - m: which of the wave's 16 x 16 tiles hold a pair that passes ...  A bound that is
+        // no number (0 x infinity: a query that rounding took nothing from, 16 rows one of which is infinite once scaled) rules
+        // nothing out, so the tests are "not below", never "at least".
         u32 hits = 0u;
         auto threshold = [&](int i, int j) {
             const float R = s_R[par][wr * WI + i], E = s_E[par][wr * WI + i];
@@ -581,7 +583,7 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
             for (int j = 0; j < 4; ++j) {
                 const floatx4 v = value(i, j);
                 const float best = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
-                hits |= (ALL || __ballot(F16 ? best >= threshold(i, j) : !(best < threshold(i, j))) != 0ull) ? 1u << (4 * i + j) : 0u;
+                hits |= (ALL || __ballot(!(best < threshold(i, j))) != 0ull) ? 1u << (4 * i + j) : 0u;
             }
         // ... and those tiles one by one (one copy of the code for all of them: unrolled it drowned the loop above)
         while (hits) {
@@ -607,7 +609,7 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
                     const u32 row = ex_row<SAMPLE>(a, (u32)jv);
                     a.buf[((int64_t)qb * QT + ql) * EX_CAP + jv] = row == (u32)self ? TG_EMPTY_KEY : key_hi | row;
                 } else {
-                    bool pass = (F16 ? ve >= thr : !(ve < thr) && live) && jv < nvisit;     // fp32: an undefined bound rules nothing out
+                    bool pass = !(ve < thr) && live && jv < nvisit;
                     if (__ballot(pass) == 0ull) continue;
                     const u32 row = ex_row<SAMPLE>(a, (u32)jv);
                     pass = pass && row != (u32)self;

@@ -1,4 +1,6 @@
 """The screened exact k-NN at the edges of its samples, tiles and number ranges, against the brute-force oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -13,7 +15,11 @@ def _check(X, k, metric, rows, static=False):
     Xg = torch.from_numpy(X).cuda()
     rg = torch.from_numpy(rows).cuda()
     ids, dist = (knn.exact_knn_static if static else knn.exact_knn)(Xg, k, metric, rg)
-    ids, dist = ids.cpu().numpy(), dist.cpu().numpy().astype(np.float64)
+    _compare(X, k, metric, rows, ids.cpu().numpy(), dist.cpu().numpy())
+
+
+def _compare(X, k, metric, rows, ids, dist):
+    dist = dist.astype(np.float64)
     mcode = knn.METRICS[metric]
     oi, od = oracle.brute_force_knn(X, k, mcode, rows)
     # An fp32 sum of d terms is off by at most (d + 4) half ulps of the sum of their magnitudes: the L2 distance itself,
@@ -29,6 +35,13 @@ def _check(X, k, metric, rows, static=False):
         a = oracle.distance(X, mcode, int(rows[q]), int(ids[q, j]))
         assert abs(a - od[q, j]) <= 2 * eps * size[q, j]
     assert (ids != rows[:, None]).all() and all(len(set(r)) == k for r in ids.tolist())
+
+
+def _takes_f16(n, d, nq):
+    """Whether tg_exact_knn screens such a search on rows rounded to fp16 (an internal function of the library)."""
+    f = knn.lib()._Z16tg_exact_use_f16lil
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int64, ctypes.c_int, ctypes.c_int64]
+    return f(n, (d + 3) // 4 * 4, nq)
 
 
 # rows around the size of the first sample and the next ones, queries around the tiles and the line between the two scans,
@@ -48,13 +61,7 @@ def test_exact_edges(n, d, k, nq, metric, whole):
         _check(X, k, metric, rows, static=True)
 
 
-# values far from fp16's range, rows far from the origin, one row far from the others, masses of equal distances (more rows than a
-# query's list has places: such queries are measured row by row)
-@pytest.mark.parametrize("kind", ["tiny", "huge", "offset", "outlier", "twins"])
-@pytest.mark.parametrize("metric", ["l2", "ip", "cosine"])
-def test_exact_number_ranges(kind, metric):
-    rng = np.random.default_rng(5)
-    n, d = 9001, 48
+def _ranged(rng, kind, n, d):
     X = rng.normal(0, 1, size=(n, d)).astype(np.float32)
     if kind == "tiny":
         X *= np.float32(1e-9)
@@ -68,6 +75,17 @@ def test_exact_number_ranges(kind, metric):
         X = np.rint(X * 4).astype(np.float32)
         X[(X == 0).all(1)] = 1.0
         X[3000:8000] = X[2999]
+    return X
+
+
+# values far from fp16's range, rows far from the origin, one row far from the others, masses of equal distances (more rows than a
+# query's list has places: such queries are measured row by row)
+@pytest.mark.parametrize("kind", ["tiny", "huge", "offset", "outlier", "twins"])
+@pytest.mark.parametrize("metric", ["l2", "ip", "cosine"])
+def test_exact_number_ranges(kind, metric):
+    rng = np.random.default_rng(5)
+    n, d = 9001, 48
+    X = _ranged(rng, kind, n, d)
     rows = np.concatenate([[17, 2999, 3000, 7999], rng.choice(n, size=150, replace=False)]).astype(np.int64)
     _check(X, 12, metric, rows)
     _check(X, 12, metric, rows[:40].copy(), static=True)
@@ -97,3 +115,40 @@ def test_exact_with_undefined_rows(n, nq, undefined, static):
         c = int(real.sum())
         assert (ids[q][real] == good[oi[q, :c]]).all() and (dist[q][real] == od[q, :c]).all()
         assert c >= min(m, k - undefined)
+
+
+# Rows whose squared norm is finite as it stands and infinite once scaled for fp16 (components of 2^57 where the others are at most 1), and
+# rows without a norm: what shares a group of 16 rows of the scan with them still has its place in the lists.  The queries are exact in
+# fp16, so their own residual is zero.  Every sum over the whole numbers (and over the powers of two) is exact.
+@pytest.mark.parametrize("metric,kind", [("ip", "far"), ("l2", "far"), ("l2", "nan"), ("l2", "inf")])
+def test_exact_f16_neighbours_of_rows_without_a_bound(metric, kind):
+    n, d, k, nq = 40000, 128, 10, 500
+    assert _takes_f16(n, d, nq)
+    rng = np.random.default_rng(11)
+    X = rng.integers(-1 if metric == "ip" else 0, 2, size=(n, d)).astype(np.float32)
+    rows = rng.choice(np.arange(1000, n - 1000), size=nq, replace=False).astype(np.int64)
+    check = np.arange(0, nq, 12)
+    taken = set(rows.tolist()) | set(range(0, n, n // 512))          # queries, and the rows that the scale is taken from
+    groups = 0
+    for i, q in enumerate(check):
+        g = 16 * int(rows[q] // 16 + 40)
+        if taken & set(range(g, g + 16)) or (kind == "nan" and groups == 4):
+            continue
+        taken |= set(range(g, g + 16))
+        groups += 1
+        # three rows as near to the query as any, and one odd row, or nothing but odd rows behind them
+        X[g:g + 3] = X[rows[q]]
+        for r in range(g + 5, g + 16 if i % 2 and kind != "nan" else g + 6):
+            X[r] = 2.0 ** 57 * (1 - 2 * rng.integers(0, 2, size=d)) if kind == "far" else np.nan if kind == "nan" else np.inf
+    assert groups > 10 or kind == "nan"
+    ids, dist = knn.exact_knn(torch.from_numpy(X).cuda(), k, metric, torch.from_numpy(rows).cuda())
+    ids, dist = ids[torch.from_numpy(check).cuda()].cpu().numpy(), dist[torch.from_numpy(check).cuda()].cpu().numpy()
+    good = np.nonzero(np.isfinite(X).all(1))[0]
+    oi, od = oracle.brute_force_knn(np.ascontiguousarray(X[good]), k, knn.METRICS[metric], np.searchsorted(good, rows[check]).astype(np.int64))
+    if kind != "nan":                                                # (an infinite distance comes last)
+        assert (ids == good[oi]).all() and (dist == od).all()
+        return
+    for j in range(len(check)):                                      # a row without a distance may be listed anywhere: 4 of 10 places at most
+        real = np.isin(ids[j], good)
+        c = int(real.sum())
+        assert c >= k - 4 and (ids[j][real] == good[oi[j, :c]]).all() and (dist[j][real] == od[j, :c]).all()
