@@ -44,7 +44,18 @@ def _takes_f16(n, d, nq):
     return f(n, (d + 3) // 4 * 4, nq)
 
 
-# rows around the size of the first sample and the next ones, queries around the tiles and the line between the two scans,
+def _check_f16(X, k, metric, rows, some):
+    """All queries on fp16 rows against the fp32 rows, the first `some` of them against the oracle."""
+    assert X.shape[1] % 4 == 0 and _takes_f16(*X.shape, len(rows))
+    Xg, rg = torch.from_numpy(X).cuda(), torch.from_numpy(rows).cuda()
+    got, want = knn.exact_knn(Xg, k, metric, rg), knn.exact_knn_static(Xg, k, metric, rg)
+    # both measure what they list directly, in the same order of sums
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    _compare(X, k, metric, rows[:some], got[0][:some].cpu().numpy(), got[1][:some].cpu().numpy())
+
+
+# (all of these are few enough pairs to be screened on the fp32 rows; the fp16 rows have tests of their own below)
+# rows around the size of the first sample and the next ones, queries around the tiles,
 # rows of one 16-byte piece, of whole steps, of one value more
 @pytest.mark.parametrize("n,d,k,nq,metric", [
     (65, 1, 64, 65, "l2"), (2047, 64, 33, 64, "l2"), (2048, 65, 1, 65, "ip"), (2049, 128, 64, 128, "cosine"), (4097, 32, 2, 63, "l2"),
@@ -152,3 +163,27 @@ def test_exact_f16_neighbours_of_rows_without_a_bound(metric, kind):
         real = np.isin(ids[j], good)
         c = int(real.sum())
         assert c >= k - 4 and (ids[j][real] == good[oi[j, :c]]).all() and (dist[j][real] == od[j, :c]).all()
+
+
+# The search on fp16 rows: every query against the search on fp32 rows (static, which never narrows), some against the oracle.  Rows of less than
+# a step, of whole steps, of one value more, queries too long to stay in LDS, and queries that end within a tile.
+@pytest.mark.parametrize("n,d,k,nq,metric", [
+    (140000, 16, 64, 1000, "l2"), (80000, 32, 1, 1000, "ip"), (60001, 36, 33, 999, "cosine"), (40000, 96, 10, 640, "l2"),
+    (33001, 128, 32, 513, "ip"), (33001, 132, 32, 513, "l2"), (20000, 300, 16, 400, "cosine"), (9001, 500, 5, 500, "ip"), (12000, 1200, 10, 150, "l2")])
+@pytest.mark.parametrize("whole", [True, False])
+def test_exact_f16_edges(n, d, k, nq, metric, whole):
+    rng = np.random.default_rng(n + d)
+    X = np.rint(rng.normal(0, 9, size=(n, d))).astype(np.float32) if whole else rng.normal(0, 1, size=(n, d)).astype(np.float32)
+    if metric == "cosine":
+        X[(X == 0).all(1)] = 1.0
+    _check_f16(X, k, metric, rng.choice(n, size=nq, replace=False).astype(np.int64), 24)
+
+
+@pytest.mark.parametrize("kind", ["tiny", "huge", "offset", "outlier", "twins"])
+@pytest.mark.parametrize("metric", ["l2", "ip", "cosine"])
+def test_exact_f16_number_ranges(kind, metric):
+    rng = np.random.default_rng(7)
+    n, d = 45001, 48
+    X = _ranged(rng, kind, n, d)
+    rows = np.concatenate([[17, 2999, 3000, 7999], rng.choice(n, size=996, replace=False)]).astype(np.int64)
+    _check_f16(X, 12, metric, rows, 40)
