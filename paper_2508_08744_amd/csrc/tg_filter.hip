@@ -211,39 +211,62 @@ __device__ inline u32 filter_wave_max(u32 x)
 #define FILTER_RULE_DIST 0
 #define FILTER_RULE_ANGLE 1
 #define FILTER_RULE_DISPERSION 2
-// Words of LDS per wave.  While ids are collected: the id -> first lane table of one hop (256 words behind the candidates' ids), or
-// the set, queue and batch of two hops.  Afterwards, in the same words: the candidates' ids (64), their distances to p and
+// The neighbours under a threshold rule: 2.75 KB of LDS a wave are enough for arrays of their own, registers (three or four waves per
+// SIMD) are what limits the waves, and a wait before the keys replace the distances is saved: 100 000 x 300, k = 32: 680 -> 671 us,
+// 60 000 x 37, k = 64: 348 -> 344 us.
+__host__ __device__ constexpr bool filter_apart(int collect, int rule) { return collect == FILTER_ONE_HOP && rule != FILTER_RULE_DISPERSION; }
+
+// Words of dynamic LDS per wave.  While ids are collected: the id -> first lane table of one hop (256 words behind the candidates' ids),
+// or the set, queue and batch of two hops.  Afterwards, in the same words: the candidates' ids (64), their distances to p and
 // norms and then their keys (128), and the sets of occluding candidates (128) or the matrix of angles (rows of 16 NG + 1 words).
 // With this a workgroup of the dispersion rule for k in 33..48 takes 40 704 bytes and one of the 2-hop collection 35 072, four a
 // CU (as separate arrays, with ids in the set: 78 and 62 KB, two a CU).
 __host__ __device__ constexpr int filter_lds_words(int ng, int collect, int rule)
 {
+    if (filter_apart(collect, rule)) return 0;
     const int ids = collect == FILTER_ONE_HOP ? 64 + 256 : filter_set_places(collect) / 2 + filter_queue_words(collect) + 64;
     const int rows = 64 + 128 + (rule == FILTER_RULE_DISPERSION ? 16 * ng * (16 * ng + 1) : 128);
     return ((ids > rows ? ids : rows) + 3) & ~3;
 }
 
-// Four waves per SIMD for the neighbours alone: the dispersion rule is bound by what a wave does in sequence (products, angles,
-// the greedy), 200 000 x 200, k = 40, d_out = 20: 2.65 ms with 64 rows and two waves, 1.85 ms with 48 rows and four.  Three for two
-// hops, which wait for rows (4 d bytes per distinct id, 5.5 TB/s): with four the compiler spills, 250 000 x 128, k = 32: 8.62
-// against 8.45 ms (9.17 with two waves and the rows of ids read one at a time).
+// Waves per SIMD that the compiler must leave room for.  Four for the neighbours under the dispersion rule, which is bound by what a
+// wave does in sequence (products, angles, the greedy): 200 000 x 200, k = 40, d_out = 20: 2.65 ms with 64 rows and two waves, 1.85 ms
+// with 48 rows and four; and for 33..48 neighbours under the others, which have the registers (111) anyway.  No demand on the other
+// threshold instances, which wait for rows: asked for four, that of up to 32 neighbours gets fewer loads on their way (100 000 x 128,
+// k = 32: 310 us against 274) and that of 49..64 spills (60 000 x 37, k = 64: 353 against 344 us).  Three for two hops, which wait for
+// rows too (4 d bytes per distinct id, 5.5 TB/s): with four the compiler spills, 250 000 x 128, k = 32: 8.62 against 8.45 ms (9.17 with
+// two waves and the rows of ids read one at a time).
+__host__ __device__ constexpr int filter_least_waves(int ng, int collect, int rule)
+{
+    if (collect != FILTER_ONE_HOP) return 3;
+    return rule == FILTER_RULE_DISPERSION || ng == 3 ? 4 : 1;
+}
+
 template <int NG, int KS, bool FULL, bool VEC, int COLLECT, int RULE>
-__global__ __launch_bounds__(256, COLLECT == FILTER_ONE_HOP ? 4 : 3) void filter_dist_kernel(FilterArgs A)
+__global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE)) void filter_dist_kernel(FilterArgs A)
 {
     constexpr bool TWO_HOPS = COLLECT != FILTER_ONE_HOP;
     constexpr int PLACES = filter_set_places(COLLECT);
     constexpr bool ANGLE = RULE == FILTER_RULE_ANGLE;
+    constexpr bool APART = filter_apart(COLLECT, RULE);
     constexpr int LDS_WORDS = filter_lds_words(NG, COLLECT, RULE);
     constexpr int AS = 16 * NG + 1;      // row stride of the matrix of angles
+    constexpr int AW = APART ? FILTER_WAVES : 1;
     extern __shared__ __align__(16) u32 lds[];
+    __shared__ int s_cid[AW][64];                       // (these six: unused and not allocated unless APART)
+    __shared__ __align__(16) float s_dpc[AW][64];
+    __shared__ __align__(16) float s_nrm[AW][64];
+    __shared__ u32 s_occ[AW][128];
+    __shared__ __align__(16) u64 s_key[AW][64];
+    __shared__ u32 s_twin[AW][256];
     const int wave = threadIdx.x >> 6, lane = tg_lane();
     const int r16 = lane & 15, q4 = lane >> 4;
     u32* own_lds = lds + wave * LDS_WORDS;
-    int* cid = reinterpret_cast<int*>(own_lds);
-    float* dpc = reinterpret_cast<float*>(own_lds + 64);
-    float* nrm = reinterpret_cast<float*>(own_lds + 128);
-    u64* skey = reinterpret_cast<u64*>(own_lds + 64);           // the candidates' (distance, id) keys, read by every lane
-    u32* occ = own_lds + 192;
+    int* cid = APART ? s_cid[wave] : reinterpret_cast<int*>(own_lds);
+    float* dpc = APART ? s_dpc[wave] : reinterpret_cast<float*>(own_lds + 64);
+    float* nrm = APART ? s_nrm[wave] : reinterpret_cast<float*>(own_lds + 128);
+    u64* skey = APART ? s_key[wave] : reinterpret_cast<u64*>(own_lds + 64);           // the candidates' (distance, id) keys, read by every lane
+    u32* occ = APART ? s_occ[wave] : own_lds + 192;
     float* ang = reinterpret_cast<float*>(own_lds + 192);
     const int k = A.k;
     const int nchunks = (A.d + 16 * KS - 1) / (16 * KS);
@@ -258,7 +281,7 @@ __global__ __launch_bounds__(256, COLLECT == FILTER_ONE_HOP ? 4 : 3) void filter
             // candidate l is entry l of the row; an entry that is no candidate (padding, p itself, an
             // id that an earlier entry lists already) keeps its place as a dead one and reads p's own row
             m = k;
-            u32* tw = own_lds + 64;
+            u32* tw = APART ? s_twin[wave] : own_lds + 64;
             for (int i = lane; i < 256; i += 64) tw[i] = FILTER_FREE;
             filter_wave_sync();
             {
@@ -438,7 +461,7 @@ __global__ __launch_bounds__(256, COLLECT == FILTER_ONE_HOP ? 4 : 3) void filter
         const int my_id = lane < m ? cid[lane] : 0;
         const bool dead = TWO_HOPS ? lane >= m : !u_ok;
         const u64 key = dead ? TG_EMPTY_KEY : tg_key(own, (u32)my_id, 0u);
-        filter_wave_sync();                    // (over the distances and norms)
+        if (!APART) filter_wave_sync();        // (over the distances and norms)
         skey[lane] = key;
         filter_wave_sync();
         // one bit per other candidate, shifted in from below: after J steps candidate j sits at bit J - 1 - j
