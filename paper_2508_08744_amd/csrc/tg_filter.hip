@@ -158,6 +158,26 @@ __device__ inline int filter_collect(unsigned short* set, int* queue, int* batch
     return Q + __popcll(mask);
 }
 
+// The same on a set that holds the ids themselves (four bytes a place, free: FILTER_FREE): one atomic per step of a search, where the
+// above takes a read, a write, a read back and the waits between them.
+template <int PLACES>
+__device__ inline int filter_collect_ids(u32* set, int* queue, int Q, int id, bool active)
+{
+    bool pending = active, fresh = false;
+    u32 h = ((u32)id * 0x9E3779B1u) >> (PLACES == 8192 ? 19 : 21);          // the top log2(PLACES) bits
+    while (__ballot(pending)) {
+        if (pending) {
+            const u32 old = atomicCAS(set + h, FILTER_FREE, (u32)id);
+            if (old == FILTER_FREE) { fresh = true; pending = false; }
+            else if (old == (u32)id) pending = false;
+            else h = (h + 1) & (PLACES - 1);
+        }
+    }
+    const u64 mask = __ballot(fresh);
+    if (fresh) queue[Q + __popcll(mask & tg_lanemask_lt())] = id;
+    return Q + __popcll(mask);
+}
+
 // Angle at p between p -> r and p -> c from the squared lengths a = |p r|^2, b = |p c|^2, c = |r c|^2:
 // acos((a + b - c) / (2 sqrt(a b))), the arc cosine from the eight-term polynomial of Abramowitz and
 // Stegun 4.4.46 (acos x = sqrt(1 - x) (a0 + .. + a7 x^7) on [0, 1], pi - acos(-x) below 0).  Every
@@ -216,6 +236,12 @@ __device__ inline u32 filter_wave_max(u32 x)
 // 60 000 x 37, k = 64: 348 -> 344 us.
 __host__ __device__ constexpr bool filter_apart(int collect, int rule) { return collect == FILTER_ONE_HOP && rule != FILTER_RULE_DISPERSION; }
 
+// Rows of at most 32 ids within two hops under the dispersion rule: the matrix of angles (16.6 KB a wave, two workgroups a CU) is larger
+// than a set of ids, so nothing is saved by two-byte places, and two waves per SIMD do not cover their waits: 30 000 x 64, k = 32:
+// 883 -> 779 us, 30 000 x 128: 1242 -> 1138 us.  Where the set sets the number of workgroups two bytes are better (k = 48: 3.29 ms with
+// ids, 2.44 with two bytes).
+__host__ __device__ constexpr bool filter_set_of_ids(int collect, int rule) { return collect == FILTER_TWO_HOPS && rule == FILTER_RULE_DISPERSION; }
+
 // Words of dynamic LDS per wave.  While ids are collected: the id -> first lane table of one hop (256 words behind the candidates' ids),
 // or the set, queue and batch of two hops.  Afterwards, in the same words: the candidates' ids (64), their distances to p and
 // norms and then their keys (128), and the sets of occluding candidates (128) or the matrix of angles (rows of 16 NG + 1 words).
@@ -224,7 +250,8 @@ __host__ __device__ constexpr bool filter_apart(int collect, int rule) { return 
 __host__ __device__ constexpr int filter_lds_words(int ng, int collect, int rule)
 {
     if (filter_apart(collect, rule)) return 0;
-    const int ids = collect == FILTER_ONE_HOP ? 64 + 256 : filter_set_places(collect) / 2 + filter_queue_words(collect) + 64;
+    const int set = filter_set_of_ids(collect, rule) ? filter_set_places(collect) : filter_set_places(collect) / 2 + 64;
+    const int ids = collect == FILTER_ONE_HOP ? 64 + 256 : set + filter_queue_words(collect);
     const int rows = 64 + 128 + (rule == FILTER_RULE_DISPERSION ? 16 * ng * (16 * ng + 1) : 128);
     return ((ids > rows ? ids : rows) + 3) & ~3;
 }
@@ -249,6 +276,7 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE)) void fi
     constexpr int PLACES = filter_set_places(COLLECT);
     constexpr bool ANGLE = RULE == FILTER_RULE_ANGLE;
     constexpr bool APART = filter_apart(COLLECT, RULE);
+    constexpr bool ID_SET = filter_set_of_ids(COLLECT, RULE);
     constexpr int LDS_WORDS = filter_lds_words(NG, COLLECT, RULE);
     constexpr int AS = 16 * NG + 1;      // row stride of the matrix of angles
     constexpr int AW = APART ? FILTER_WAVES : 1;
@@ -300,12 +328,15 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE)) void fi
             cid[lane] = u_ok ? u : (int)p;
             filter_wave_sync();
         } else {
-            unsigned short* set = reinterpret_cast<unsigned short*>(own_lds);
-            int* queue = reinterpret_cast<int*>(own_lds + PLACES / 2);
-            int* batch = queue + filter_queue_words(COLLECT);
-            for (int i = lane; i < PLACES / 8; i += 64) reinterpret_cast<uint4*>(set)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+            constexpr int SET_WORDS = ID_SET ? PLACES : PLACES / 2;          // (a free place is all ones in either set)
+            int* queue = reinterpret_cast<int*>(own_lds + SET_WORDS);
+            auto collect = [&](int Q, int id, bool active) __attribute__((always_inline)) {
+                if (ID_SET) return filter_collect_ids<PLACES>(own_lds, queue, Q, id, active);
+                return filter_collect<PLACES>(reinterpret_cast<unsigned short*>(own_lds), queue, queue + filter_queue_words(COLLECT), Q, id, active);
+            };
+            for (int i = lane; i < SET_WORDS / 4; i += 64) reinterpret_cast<uint4*>(own_lds)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
             filter_wave_sync();
-            int Q = filter_collect<PLACES>(set, queue, batch, 0, u, u_ok);
+            int Q = collect(0, u, u_ok);
             const int per = 64 / A.kp;
             const int my_row = lane / A.kp, r = lane - my_row * A.kp;
             for (int j0 = 0; j0 < k; j0 += FILTER_LOADS * per) {
@@ -321,9 +352,10 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE)) void fi
 #pragma unroll
                 for (int t = 0; t < FILTER_LOADS; ++t) {
                     if (j0 + t * per >= k) break;                 // uniform
-                    Q = filter_collect<PLACES>(set, queue, batch, Q, w[t], w[t] >= 0 && w[t] < A.n && w[t] != p);
+                    Q = collect(Q, w[t], w[t] >= 0 && w[t] < A.n && w[t] != p);
                 }
             }
+            filter_wave_sync();
             // distance to p of everything collected, 64 at a time; the 64 closest stay, in order
             u64 best = TG_EMPTY_KEY;
             for (int b0 = 0; b0 < Q; b0 += 64) {
