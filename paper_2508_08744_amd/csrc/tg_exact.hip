@@ -471,8 +471,11 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
             s_c0[par][tid] = !real ? -__builtin_inff() : F16 && undefined ? EX_ALWAYS : a.metric == 0 ? -0.5f * pre_rn : 0.0f;
             if (!F16) s_c1[par][tid] = pre_c1;
             float R = (!F16 && a.metric == 2) ? 1.0f : sqrtf(pre_rn), E = pre_er;
-            // a row without a defined norm is bounded by nothing (fp32: nor are its neighbours in the tile then; a maximum alone would pass over a NaN)
-            if (!F16 && undefined) R = __builtin_inff();
+            // A row without a defined norm is bounded by nothing.  fp32: nor are its neighbours in the tile then (a maximum alone would pass
+            // over a NaN).  fp16: EX_ALWAYS takes it past any threshold, and its neighbours keep theirs (with an infinite norm among the
+            // maxima a threshold would be 0 x infinity for queries that rounding took nothing from: no number, and no pair passes that).
+            if (undefined) R = F16 ? 0.0f : __builtin_inff();
+            if (F16 && undefined) E = 0.0f;
 #pragma unroll
             for (int o = 1; o < 16; o <<= 1) {
                 R = fmaxf(R, __shfl_xor(R, o));
@@ -559,9 +562,7 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
             }
             buf ^= 1;
         }
-        // -w of every pair of the tile against -tau - m: which of the wave's 16 x 16 tiles hold a pair that passes ...  A bound that is
-        // no number (0 x infinity: a query that rounding took nothing from, 16 rows one of which is infinite once scaled) rules
-        // nothing out, so the tests are "not below", never "at least".
+        // -w of every pair of the tile against -tau - m: which of the wave's 16 x 16 tiles hold a pair that passes ...
         u32 hits = 0u;
         auto threshold = [&](int i, int j) {
             const float R = s_R[par][wr * WI + i], E = s_E[par][wr * WI + i];
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
             for (int j = 0; j < 4; ++j) {
                 const floatx4 v = value(i, j);
                 const float best = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
-                hits |= (ALL || __ballot(!(best < threshold(i, j))) != 0ull) ? 1u << (4 * i + j) : 0u;
+                hits |= (ALL || __ballot(F16 ? best >= threshold(i, j) : !(best < threshold(i, j))) != 0ull) ? 1u << (4 * i + j) : 0u;
             }
         // ... and those tiles one by one (one copy of the code for all of them: unrolled it drowned the loop above)
         while (hits) {
@@ -609,7 +610,7 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
                     const u32 row = ex_row<SAMPLE>(a, (u32)jv);
                     a.buf[((int64_t)qb * QT + ql) * EX_CAP + jv] = row == (u32)self ? TG_EMPTY_KEY : key_hi | row;
                 } else {
-                    bool pass = !(ve < thr) && live && jv < nvisit;
+                    bool pass = (F16 ? ve >= thr : !(ve < thr) && live) && jv < nvisit;     // fp32: an undefined bound rules nothing out
                     if (__ballot(pass) == 0ull) continue;
                     const u32 row = ex_row<SAMPLE>(a, (u32)jv);
                     pass = pass && row != (u32)self;
