@@ -32,7 +32,7 @@ struct ExScanArgs {
     uint32_t* fb_n;
 };
 
-// list / list_n: only these queries (device), or null
+// list / list_n: only these queries (device), or null; with a list the slices are chosen on the device, and partial holds nq x EX_CAP keys
 void tg_launch_exact_knn(const float* X, int ld, const float* rnorm, int64_t n, int k, int metric, const int64_t* rows, int64_t nq,
                          int64_t q_first, const uint32_t* list, const uint32_t* list_n, int32_t* out_ids, float* out_dist,
                          unsigned long long* partial /* nq x slices x k */, int nslices, hipStream_t s);

@@ -187,3 +187,23 @@ def test_exact_f16_number_ranges(kind, metric):
     X = _ranged(rng, kind, n, d)
     rows = np.concatenate([[17, 2999, 3000, 7999], rng.choice(n, size=996, replace=False)]).astype(np.int64)
     _check_f16(X, 12, metric, rows, 40)
+
+
+# Queries whose list overflows (3000 rows equal to them) are measured row by row by waves that are shared out among however many there
+# are: none, one, a group of four and one more, all of them; on both kinds of rows, with slices of 256 rows and as many as fit.
+@pytest.mark.parametrize("n,d,k,nq,f16", [(45001, 48, 64, 1000, True), (20000, 48, 33, 300, False), (6001, 32, 64, 61, False), (70000, 16, 1, 5, False)])
+@pytest.mark.parametrize("listed", ["none", "one", "five", "all"])
+def test_exact_overflowing_queries(n, d, k, nq, f16, listed):
+    rng = np.random.default_rng(n + nq)
+    X = rng.integers(0, 40, size=(n, d)).astype(np.float32)
+    X[1000:4000] = X[1000] + 100.0                                   # (no other query's neighbours)
+    m = {"none": 0, "one": 1, "five": 5, "all": nq}[listed]
+    rows = rng.choice(np.arange(4000, n), size=nq, replace=False)
+    rows[nq - m:] = 1000 + rng.permutation(3000)[:m]
+    rows = rng.permutation(rows).astype(np.int64)
+    assert _takes_f16(n, d, nq) == f16
+    pick = np.concatenate([np.nonzero(rows < 4000)[0][:30], np.nonzero(rows >= 4000)[0][:30]])
+    oi, od = oracle.brute_force_knn(X, k, 0, rows[pick])
+    for f in (knn.exact_knn, knn.exact_knn_static):
+        ids, dist = f(torch.from_numpy(X).cuda(), k, "l2", torch.from_numpy(rows).cuda())
+        assert (ids.cpu().numpy()[pick] == oi).all() and (dist.cpu().numpy()[pick] == od).all()      # (every sum is exact)
