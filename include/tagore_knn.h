@@ -215,7 +215,11 @@ int tg_knn_join_distances(tg_knn_handle* h, const int32_t* blk, const int32_t* s
  * Exact k-NN of selected rows by exhaustive search on the GPU (ground truth for the
  * recall of section 7.1).  query_rows: device int64[nq] row indices into X (NULL = rows
  * 0..nq-1); out_ids device nq x k, out_dist device nq x k (may be NULL).  Order (dist, id).
- * A row index outside [0, n) is refused (checked on the host).
+ * A row index outside [0, n) is refused (checked on the host: with query_rows the call waits for the stream once,
+ * before it enqueues the search).  The search itself and the release of its scratch (hipMallocAsync / hipFreeAsync:
+ * an fp16 copy of X where more than 128 queries make that worth while, and 16 KB per query) are only enqueued: outputs are
+ * valid, and X and query_rows free to change, once `stream` has got past the call; errors of the kernels surface
+ * at the caller's next wait.  Refused with TG_ERR_UNSUPPORTED on a stream that is being captured.
  */
 int tg_exact_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t metric,
                  const int64_t* query_rows, int64_t nq, int32_t* out_ids, float* out_dist,
@@ -223,10 +227,11 @@ int tg_exact_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t metric
 
 /*
  * tg_exact_knn for callers that cannot allocate device memory: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same result as tg_exact_knn, but the scratch (the
- * per-slice partial lists, and for TG_METRIC_COSINE the norms of all n rows) lives in a static device
+ * serving loops, harnesses that forbid hipMalloc.  Same result as tg_exact_knn, but the scratch lives in a static device
  * array of tg_exact_knn_static_scratch_bytes() = 16 MiB that every GPU the library runs on holds until
- * the process ends.  The call allocates and frees nothing, never synchronises, and copies nothing to the
+ * the process ends: the norms of all n rows and 16 KB and a copy of the row per query, for as many queries at a time as
+ * fit; where not even 64 do, per-slice partial lists (and for TG_METRIC_COSINE the norms), which takes longer.
+ * The call allocates and frees nothing, never synchronises, and copies nothing to the
  * host; all work is enqueued on `stream`.
  *   - Needs d % 4 == 0 and a 16-byte aligned X (TG_ERR_UNSUPPORTED otherwise: the padded copy
  *     tg_exact_knn makes would have to be allocated).

@@ -596,6 +596,9 @@ extern "C" int tg_exact_knn(const float* X, int64_t n, int32_t d, int32_t k, int
     if (nq < 0) return fail(TG_ERR_INVALID_ARG, "nq < 0");
     if (nq == 0) return TG_OK;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
+        return fail(TG_ERR_UNSUPPORTED, "tg_exact_knn takes scratch memory and cannot be captured: use tg_exact_knn_static");
     if (query_rows) {   // the row indices come from the caller: check them before a kernel uses them
         std::vector<int64_t> hr((size_t)nq);
         HIP_TRY(hipMemcpyAsync(hr.data(), query_rows, hr.size() * sizeof(int64_t), hipMemcpyDeviceToHost, s));

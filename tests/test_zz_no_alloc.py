@@ -63,3 +63,24 @@ def test_static_scratch_refuses_what_does_not_fit_and_what_would_need_a_copy():
     torch.cuda.synchronize()
     assert torch.equal(got[0][[0, 3]], want[0]) and torch.equal(got[1][[0, 3]], want[1])
     assert int((got[0][[1, 2]] != -1).sum()) == 0 and bool(torch.isinf(got[1][[1, 2]]).all())
+
+
+def test_under_capture_the_static_search_replays_and_the_allocating_one_is_refused():
+    dev = "cuda:0"
+    X = torch.from_numpy(inputs.make("C2", n=9_000, d=64, comps=9)).to(dev)
+    rows = torch.arange(0, 9_000, 45, dtype=torch.int64, device=dev)
+    out = (torch.empty((rows.numel(), 20), dtype=torch.int32, device=dev), torch.empty((rows.numel(), 20), dtype=torch.float32, device=dev))
+    knn.exact_knn_static(X, 20, "l2", rows, out=out)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        with pytest.raises(knn.TagoreError, match="cannot be captured"):
+            knn.exact_knn(X, 20, "l2")
+        knn.exact_knn_static(X, 20, "l2", rows, out=out)
+    for i in range(4):
+        X.copy_(torch.from_numpy(inputs.make("C2", n=9_000, d=64, comps=9 + i)))
+        want = knn.exact_knn(X, 20, "l2", rows)
+        out[0].fill_(-5)
+        g.replay()
+        torch.cuda.synchronize()
+        assert _same(out, want), i
