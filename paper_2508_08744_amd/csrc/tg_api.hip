@@ -610,30 +610,20 @@ extern "C" int tg_exact_knn(const float* X, int64_t n, int32_t d, int32_t k, int
     }
     const int ld = round_up4(d);
     const bool pad = (ld != d) || ((reinterpret_cast<uintptr_t>(X) & 15) != 0);
-    // The scratch lives in stream order, like the workspace of tg_knn_build.  Where the fp16 copy of X cannot be had,
-    // the fp32 rows are screened as they are.
-    bool f16 = tg_exact_use_f16(n, ld, nq);
-    int64_t batch = 0;
-    size_t fixed = 0, bytes = 0;
+    // The scratch lives in stream order, like the workspace of tg_knn_build; where it cannot be had, less of it is asked for.
+    TgExactPlan plan = {};
     const size_t padded = pad ? ((size_t)n * ld * sizeof(float) + 255) & ~(size_t)255 : 0;
     char* ws = nullptr;
-    for (;; f16 = false) {
-        fixed = tg_exact_fixed_bytes(n, ld, metric, f16);
-        batch = nq < 16384 ? nq : 16384;
-        // An allocation of 64 MiB or more costs 0.35 ms to give back (65 us below that): where the lists are what makes it so large,
-        // the queries go in several batches (about 60 us each).
-        if (padded + fixed < (32u << 20) && nq <= 16384)
-            for (int64_t parts = 1; padded + fixed + tg_exact_query_bytes(batch, ld, f16) >= (64u << 20); ++parts)
-                batch = ((nq + parts - 1) / parts + 127) & ~127ll;
-        if (batch > nq) batch = nq;
-        bytes = padded + fixed + tg_exact_query_bytes(batch, ld, f16);
-        if (hipMallocAsync(reinterpret_cast<void**>(&ws), bytes, s) == hipSuccess) break;
+    for (int attempt = 0; ; ++attempt) {
+        if (!tg_exact_plan(n, ld, metric, nq, padded, attempt, &plan))
+            return fail(TG_ERR_OUT_OF_MEMORY, "scratch of %zu bytes could not be allocated", plan.bytes);
+        if (hipMallocAsync(reinterpret_cast<void**>(&ws), plan.bytes, s) == hipSuccess) break;
         (void)hipGetLastError();
-        if (!f16) return fail(TG_ERR_OUT_OF_MEMORY, "scratch of %zu bytes could not be allocated", bytes);
     }
     float* xp = reinterpret_cast<float*>(ws);
     if (pad) tg_launch_pad_rows(X, n, d, xp, ld, s);
-    tg_launch_exact_screened(pad ? xp : X, ld, n, d, k, metric, query_rows, nq, f16, ws + padded, ws + padded + fixed, batch, out_ids, out_dist, s);
+    tg_launch_exact_screened(pad ? xp : X, ld, n, d, k, metric, query_rows, nq, plan.f16 != 0, ws + padded, ws + padded + plan.fixed, plan.batch, out_ids,
+                             out_dist, s);
     const int rc = launch_status("exact k-NN");
     const hipError_t e = hipFreeAsync(ws, s);
     if (rc == TG_OK && e != hipSuccess) return fail(TG_ERR_HIP, "releasing the scratch failed: %s", hipGetErrorString(e));

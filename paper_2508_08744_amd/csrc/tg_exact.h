@@ -40,5 +40,13 @@ int tg_exact_slices(int64_t n, int64_t nq);
 bool tg_exact_use_f16(int64_t n, int ld, int64_t nq);
 size_t tg_exact_fixed_bytes(int64_t n, int ld, int metric, bool f16);
 size_t tg_exact_query_bytes(int64_t nq, int ld, bool f16);
+// what tg_exact_knn allocates: `padded` bytes for its own copy of X, tg_exact_fixed_bytes, tg_exact_query_bytes of `batch` queries
+struct TgExactPlan {
+    int32_t f16;
+    int64_t batch;
+    size_t fixed, bytes;
+};
+// attempt 0 is the fastest, the later ones take less memory; false (and the plan as it was) when there is no such attempt
+bool tg_exact_plan(int64_t n, int ld, int metric, int64_t nq, size_t padded, int attempt, TgExactPlan* plan);
 void tg_launch_exact_screened(const float* X, int ld, int64_t n, int d, int k, int metric, const int64_t* rows, int64_t nq, bool f16,
                               void* fixed, void* per_batch, int64_t batch, int32_t* out_ids, float* out_dist, hipStream_t s);

@@ -860,6 +860,27 @@ size_t tg_exact_query_bytes(int64_t nq, int ld, bool f16)
     return ex_up((size_t)nq * EX_CAP * 8) + ex_up((size_t)pad * ex_qbytes(ld, f16)) + ex_up((size_t)pad * 16) + ex_up((size_t)pad * 4 * EX_CSTRIDE) + 3 * ex_up((size_t)pad * 4 + 4);
 }
 
+bool tg_exact_plan(int64_t n, int ld, int metric, int64_t nq, size_t padded, int attempt, TgExactPlan* plan)
+{
+    // fp16 rows where they are faster, the fp32 rows as they are, then fewer queries at a time: 16384, 4096, 1024, 256, 64
+    const bool half = tg_exact_use_f16(n, ld, nq);
+    const int step = half && attempt > 0 ? attempt - 1 : attempt;
+    if (step > 4) return false;
+    plan->f16 = half && attempt == 0;
+    plan->fixed = tg_exact_fixed_bytes(n, ld, metric, plan->f16 != 0);
+    const int64_t most = 16384 >> (2 * step);
+    int64_t batch = nq < most ? nq : most;
+    // An allocation of 64 MiB or more costs 0.35 ms to give back (65 us below that): where the lists are what makes it so large,
+    // the queries go in several batches (about 60 us each).
+    if (padded + plan->fixed < (32u << 20) && nq <= 16384)
+        for (int64_t parts = 1; padded + plan->fixed + tg_exact_query_bytes(batch, ld, plan->f16 != 0) >= (64u << 20); ++parts)
+            batch = ((nq + parts - 1) / parts + 127) & ~127ll;
+    if (batch > most) batch = most;
+    plan->batch = batch > nq ? nq : batch;
+    plan->bytes = padded + plan->fixed + tg_exact_query_bytes(plan->batch, ld, plan->f16 != 0);
+    return true;
+}
+
 template <bool F16, int QT, bool RES, int MODE>
 static void ex_launch_scan_t(const ExScanArgs& a, hipStream_t s)
 {

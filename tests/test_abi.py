@@ -157,3 +157,28 @@ def test_binding_structures_match_the_header(tmp_path):
     assert [int(out[0]), int(out[1])] == [ctypes.sizeof(knn.Params), ctypes.sizeof(knn.Stats)]
     want = [getattr(knn.Params, f).offset for f in fields_p] + [getattr(knn.Stats, f).offset for f in fields_s]
     assert [int(x) for x in out[2:]] == want
+
+
+class _ExactPlan(ctypes.Structure):
+    _fields_ = [("f16", ctypes.c_int32), ("batch", ctypes.c_int64), ("fixed", ctypes.c_size_t), ("bytes", ctypes.c_size_t)]
+
+
+@pytest.mark.parametrize("n,ld,metric,nq,padded", [
+    (1_000_000, 128, 0, 10_000, 0), (1_000_000, 128, 2, 10_000, 0), (50_000, 96, 2, 64, 0), (5_000, 16, 0, 1, 320_256), (65, 4, 1, 65, 0),
+    (20_000, 8, 0, 100_000, 0), (3_000_000, 960, 0, 129, 0), (2_049, 4096, 1, 16_385, 33_570_816)])
+def test_exact_scratch_gets_smaller_with_every_attempt(n, ld, metric, nq, padded):
+    """tg_exact_knn on a card that is nearly full: it ends at the norms and the lists of 64 queries (an internal function of the library)."""
+    from paper_2508_08744_amd import knn
+    f = knn.lib()._Z13tg_exact_planliilmiP11TgExactPlan
+    f.restype = ctypes.c_bool
+    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_int, ctypes.POINTER(_ExactPlan)]
+    plan, seen = _ExactPlan(), []
+    while f(n, ld, metric, nq, padded, len(seen), ctypes.byref(plan)):
+        assert 1 <= plan.batch <= nq and plan.bytes > padded + plan.fixed
+        assert not plan.f16 or not seen                             # (the fp16 copy is the first attempt's)
+        seen.append((plan.f16, plan.batch, plan.bytes))
+    # (rows of X in fp32 may be packed into more than the copy in fp16 took: from then on it is less and less)
+    assert all(b[2] <= a[2] for a, b in zip(seen[seen[0][0]:], seen[seen[0][0] + 1:])) and len(seen) <= 6
+    assert seen[-1][1] == min(nq, 64) and not seen[-1][0]
+    # the squared norms, the inverse ones, and per query (of two tiles) a list of 2048 places, its packed row and a few words
+    assert seen[-1][2] <= padded + 8 * n + 64 * 2048 * 8 + 128 * (4 * (ld + 32) + 96) + 4096
