@@ -93,7 +93,6 @@ void tg_launch_init(const TgGraph& g, uint64_t hs_init, hipStream_t s);
 void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, bool when_bytes, hipStream_t s);
 void tg_launch_narrow(const TgGraph& g, uint16_t* Xh, uint32_t* exact_flag /* cleared when a value is no fp16 number, or null */,
                       uint32_t* overflow_rows /* counts the rows with a finite value beyond fp16's range, or null */, hipStream_t s);
-void tg_launch_fill_u64(unsigned long long* p, size_t count, unsigned long long v, hipStream_t s);
 void tg_launch_fill_u32(uint32_t* p, size_t count, uint32_t v, hipStream_t s);
 void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hipStream_t s);
 int tg_rev_bucket_shift(int64_t n);

@@ -14,12 +14,6 @@
 // ---------------------------------------------------------------------------------------
 // small utilities
 // ---------------------------------------------------------------------------------------
-__global__ void fill_u64_kernel(u64* p, size_t count, u64 v)
-{
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < count; i += stride) p[i] = v;
-}
 __global__ void fill_u32_kernel(u32* p, size_t count, u32 v)
 {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -32,10 +26,6 @@ static int grid_for(size_t count, int block)
     if (g > 65536) g = 65536;
     if (g < 1) g = 1;
     return (int)g;
-}
-void tg_launch_fill_u64(u64* p, size_t count, u64 v, hipStream_t s)
-{
-    if (count) hipLaunchKernelGGL(fill_u64_kernel, dim3(grid_for(count, 256)), dim3(256), 0, s, p, count, v);
 }
 void tg_launch_fill_u32(u32* p, size_t count, u32 v, hipStream_t s)
 {
