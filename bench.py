@@ -21,6 +21,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 MFMA_FP32_PEAK_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
+MFMA_I8_PEAK_TOPS = 5000.0         # and 8-bit
 HBM_PEAK_GBS = 8000.0
 
 
@@ -64,6 +65,33 @@ def cpu_baseline(config: str, prm, sample_n: int):
                       % (config, sample_n, inputs.CONFIGS[config]["n"], dt),
             "identical": bool((ids == mi).all() and (dist.astype(np.float64) == md).all()),
             "recall_gpu": r_gpu, "recall_plain": r_plain, "recall_gap_vs_plain": r_gpu - r_plain}
+
+
+def joins_codes(X, metric, prm):
+    """Whether the library joins this X on its 8-bit codes: what tg_knn_params.screen says in the header, and n >= 65 536."""
+    n, d = X.shape
+    if not prm.screen or metric != "l2" or d > 128 or n < 65536 or not bool((X == X.round()).all()):
+        return False
+    lo, hi = float(X.min()), float(X.max())
+    return hi - lo <= 255.0 and 2.0 * d * max(abs(lo), abs(hi)) ** 2 <= 2.0 ** 24
+
+
+def join_figures(stats, d, codes):
+    """The phase-1 join of the builds that left these stats: multiplying kernels of one round, on average."""
+    r1 = stats[0]["rounds_phase1"]
+    launches = r1 * len(stats)
+    ms = sum(sum(s["ms_join"][:r1]) for s in stats) / max(launches, 1)
+    # algorithmic operations: 2 d per needed pair (new-new and new-old pairs of every block)
+    ops = 2.0 * d * sum(sum(s["join_pairs"][:r1]) for s in stats) / max(launches, 1)
+    row = float((d + 15) // 16 * 16) if codes else 4.0 * d
+    gather = row * sum(sum(s["join_vectors"][:r1]) for s in stats) / max(launches, 1)
+    peak = MFMA_I8_PEAK_TOPS if codes else MFMA_FP32_PEAK_TFLOPS
+    rate = ops / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
+    gbs = gather / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
+    out = {"bound": "mfma", "achieved": rate, "peak": peak, "unit": "TFLOP/s", "frac": rate / peak}
+    if codes:           # far from the rate of the i8 instructions: what the kernel moves is nearer its bound
+        out = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS}
+    return dict(out, avg_launch_ms=ms, launches=launches, matrix_tops=rate, matrix_peak_tops=peak, gather_GBps=gbs, hbm_gather_frac=gbs / HBM_PEAK_GBS)
 
 
 def main():
@@ -128,17 +156,12 @@ def main():
     truth, _ = knn.exact_knn(Xg, k, metric, rows_g)
     recall = oracle.recall(ids[rows_g].cpu().numpy(), truth.cpu().numpy())
 
-    # dominant kernel: the phase-1 local join (the kernels that multiply).  Algorithmic flops = 2 d per needed pair
-    # (new-new and new-old pairs of every block); duration from the HIP events the library
-    # records on the launch stream around each join launch.
+    # dominant kernel: the phase-1 local join (the kernels that multiply); duration from the HIP events the library
+    # records on the launch stream around each join launch.  Byte-valued rows are joined on their 8-bit codes (a code row per
+    # vector, i8 matrix instructions; the few blocks of more than 64 members in fp32), others in fp32.
     r1 = stats[0]["rounds_phase1"]
-    join_ms = [sum(s["ms_join"][:r1]) for s in stats]
-    join_flops = [2.0 * d * sum(s["join_pairs"][:r1]) for s in stats]
-    launches = r1 * len(stats)
-    avg_launch_ms = sum(join_ms) / max(launches, 1)
-    achieved = (sum(join_flops) / max(launches, 1)) / (avg_launch_ms * 1e-3) / 1e12 if avg_launch_ms > 0 else 0.0
-    gather_gbs = (4.0 * d * sum(sum(s["join_vectors"][:r1]) for s in stats) / max(launches, 1)) / (avg_launch_ms * 1e-3) / 1e9 \
-        if avg_launch_ms > 0 else 0.0
+    codes = joins_codes(Xg, metric, prm)
+    join = join_figures(stats, d, codes)
     last = stats[-1]
     # HBM bytes per join launch from the rocprofv3 FETCH_SIZE / WRITE_SIZE runs kept under profiles/ (calibrated
     # against a plain copy); only quoted for the workload those runs were made on
@@ -168,12 +191,12 @@ def main():
                    "parts": prm.parts, "m": prm.m, "seed": int(prm.seed)},
         "recall_at_k": recall,
         "recall_ok": bool(recall >= 0.95),
-        "join_mfma_pct": 100.0 * achieved / MFMA_FP32_PEAK_TFLOPS,
-        "roofline": {"bound": "mfma", "kernel": "phase-1 local join of one round (join_wave_kernel<3>, <4>, or on byte-valued X join_bytes_kernel on i8 matrix instructions, and join_kernel of every part; adj_kernel, which runs before them, is timed apart)",
-                     "achieved": achieved,
-                     "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / MFMA_FP32_PEAK_TFLOPS,
-                     "avg_launch_ms": avg_launch_ms, "launches": launches, "gather_GBps": gather_gbs,
-                     "hbm_gather_frac": gather_gbs / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_source},
+        "join_mfma_pct": 100.0 * join["matrix_tops"] / join["matrix_peak_tops"],
+        "roofline": dict({"kernel": "phase-1 local join of one round, every part: " +
+                                    ("join_bytes_kernel (i8 matrix instructions on the 8-bit codes), join_kernel for blocks of more than 64 members"
+                                     if codes else "join_wave_kernel<3>, <4> and join_kernel (fp32 matrix instructions)") +
+                                    "; adj_kernel, which runs before them, is timed apart",
+                          "traffic": traffic, "traffic_source": traffic_source}, **join),
         "breakdown_ms": {"norms": last["ms_norms"], "init": last["ms_init"], "finalize": last["ms_finalize"],
                          "sample": sum(last["ms_sample"]), "adjacency": sum(last["ms_adjacency"]), "join": sum(last["ms_join"][:r1]),
                          "update": sum(last["ms_update"]), "phase2": sum(last["ms_join"][r1:])},
@@ -196,27 +219,31 @@ def main():
             out["cpu_baseline"] = cpu_baseline(args.config, prm, min(args.cpu_sample, n))
         print(json.dumps(out))
         return
-    # the same build with the local join on the fp16 matrix instructions where that is exact (join_f16 = 2: the library
-    # checks on the device that every value is an fp16 number, as byte-valued features are; off by default and not part
-    # of `value`): the graph must come out bit for bit the same
+    # the same points moved by a quarter: no bytes any more, so the local join multiplies fp32 rows (join_f16 = 0) or their fp16
+    # copies (join_f16 = 1; a quarter more than a byte is an fp16 number).  Not part of `value`; the distances of the points, and so the truth,
+    # are the same but for rounding
     if args.config == "C2" and n == cfg["n"]:
-        prm16 = bench_params(k)
-        prm16.metric = prm.metric
-        prm16.it1, prm16.it2, prm16.join_f16 = prm.it1, prm.it2, 2
-        ws16 = torch.empty(knn.workspace_bytes(n, d, prm16), dtype=torch.uint8, device=dev)
-        knn.knn_build_ex(Xg, prm16, ws16, want_stats=False)
-        torch.cuda.synchronize()
-        t0 = time.perf_counter()
-        for _ in range(3):
-            ids16, dist16, st16 = knn.knn_build_ex(Xg, prm16, ws16, want_stats=True)
-        torch.cuda.synchronize()
-        ms16 = 1e3 * (time.perf_counter() - t0) / 3
-        r16 = st16["rounds_phase1"]
-        out["join_f16"] = {"ms_per_step": ms16, "points_per_s": n / (ms16 * 1e-3), "ms_join": sum(st16["ms_join"][:r16]),
-                           "join_launch_ms": sum(st16["ms_join"][:r16]) / max(r16, 1),
-                           "recall_at_k": oracle.recall(ids16[rows_g].cpu().numpy(), truth.cpu().numpy()),
-                           "identical_to_fp32_join": bool((ids16 == ids).all() and (dist16 == dist).all())}
-        del ws16, ids16, dist16
+        Xr = Xg + 0.25
+        for name, f16 in (("join_fp32", 0), ("join_f16", 1)):
+            prm_r = bench_params(k)
+            prm_r.metric = prm.metric
+            prm_r.it1, prm_r.it2, prm_r.join_f16 = prm.it1, prm.it2, f16
+            ws_r = torch.empty(knn.workspace_bytes(n, d, prm_r), dtype=torch.uint8, device=dev)
+            knn.knn_build_ex(Xr, prm_r, ws_r, want_stats=False)
+            torch.cuda.synchronize()
+            st_r = []
+            t0 = time.perf_counter()
+            for _ in range(3):
+                ids_r, _, st = knn.knn_build_ex(Xr, prm_r, ws_r, want_stats=True)
+                st_r.append(st)
+            torch.cuda.synchronize()
+            ms_r = 1e3 * (time.perf_counter() - t0) / 3
+            out[name] = {"ms_per_step": ms_r, "points_per_s": n / (ms_r * 1e-3), "ms_join": sum(st_r[-1]["ms_join"][:r1]),
+                         "recall_at_k": oracle.recall(ids_r[rows_g].cpu().numpy(), truth.cpu().numpy())}
+            if not f16:
+                out[name]["roofline"] = join_figures(st_r, d, False)
+            del ws_r, ids_r
+        del Xr
     # the next step after the hot path: rank-based pruning of the graph just built (outside `value`).
     # Algorithmic bytes per node: its row, the entries in front of every neighbour's own position, the output.
     d_out = k // 2
