@@ -2,7 +2,7 @@
 // rows with the smallest (distance, id), distances computed directly from the vectors in fp32.
 //
 // Measuring every pair that way is bound by the vector units (245 ms for 10 000 queries against 1M x 128, k = 32:
-// 10.5 TFLOP/s; this search takes 9.2 ms).  Here the matrix cores bound every pair from both sides first, and only pairs that may be
+// 10.5 TFLOP/s; this search takes 9.3 ms).  Here the matrix cores bound every pair from both sides first, and only pairs that may be
 // among the k nearest are measured directly:
 //   w(q, r) = |r|^2 / 2 - <q, r>  (squared L2; -<q, r> for the inner product, the same on unit vectors for the
 //   cosine) orders the rows for query q.  A tile of w is formed on the matrix cores, either from the rows
@@ -413,7 +413,7 @@ __device__ inline u32 ex_row(const ExScanArgs& a, u32 j)
 // is a register, and -|r|^2 / 2 is where the accumulator starts, so a tile costs three maxima, one compare and a
 // ballot unless something passes.  MODE: all rows (EX_FULL), a sample (EX_SAMPLE), or the first sample, of which everything
 // is kept (EX_FIRST: place = number of the visit).
-// 1M x 128 against 10 000 queries, fp16: 7.0 ms (365 TFLOP/s), waiting for rows: a step is 32 matrix instructions per wave and
+// 1M x 128 against 10 000 queries, fp16: 7.15 ms (358 TFLOP/s), waiting for rows: a step is 32 matrix instructions per wave and
 // the rows of the next one have only that long to arrive.  fp32: 1.0 ms for 256 queries (64 TFLOP/s).
 // ---------------------------------------------------------------------------------------
 template <bool F16, int QT, bool RES, int MODE>
