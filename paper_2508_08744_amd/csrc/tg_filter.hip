@@ -36,7 +36,10 @@
 __host__ __device__ constexpr int filter_set_places(int collect) { return collect == FILTER_TWO_HOPS_WIDE ? 8192 : 2048; }
 __host__ __device__ constexpr int filter_queue_words(int collect) { return collect == FILTER_TWO_HOPS_WIDE ? 4224 : 1088; }
 #define FILTER_WAVES 4
-#define FILTER_LOADS 8          // rows of second-hop ids on their way at a time
+// Rows of second-hop ids on their way at a time.  Rows of X that are no multiple of 16 bytes come value by value, four times the loads, and
+// eight rows of ids before them only hold registers (18 595 x 279, k = 12: 1280 us with eight, 1264 with two; 18 595 x 280 in
+// 16-byte pieces: 460 us with eight, 474 with two).
+__host__ __device__ constexpr int filter_loads(bool vec) { return vec ? 8 : 2; }
 #define FILTER_NOWHERE 0xFFFFu  // a free place of the id set
 #define FILTER_GRID 16384
 #define FILTER_FREE 0xFFFFFFFFu
@@ -262,18 +265,19 @@ __host__ __device__ constexpr int filter_lds_words(int ng, int collect, int rule
 // threshold instances, which wait for rows: asked for four, that of up to 32 neighbours gets fewer loads on their way (100 000 x 128,
 // k = 32: 310 us against 274) and that of 49..64 spills (60 000 x 37, k = 64: 353 against 344 us).  Three for two hops, which wait for
 // rows too (4 d bytes per distinct id, 5.5 TB/s): with four the compiler spills, 250 000 x 128, k = 32: 8.62 against 8.45 ms (9.17 with
-// two waves and the rows of ids read one at a time).
-__host__ __device__ constexpr int filter_least_waves(int ng, int collect, int rule)
+// two waves and the rows of ids read one at a time), and none where rows come value by value (18 595 x 279, k = 12: 1298 -> 1280 us).
+__host__ __device__ constexpr int filter_least_waves(int ng, int collect, int rule, bool vec)
 {
-    if (collect != FILTER_ONE_HOP) return 3;
+    if (collect != FILTER_ONE_HOP) return vec ? 3 : 1;
     return rule == FILTER_RULE_DISPERSION || ng == 3 ? 4 : 1;
 }
 
 template <int NG, int KS, bool FULL, bool VEC, int COLLECT, int RULE>
-__global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE)) void filter_dist_kernel(FilterArgs A)
+__global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) void filter_dist_kernel(FilterArgs A)
 {
     constexpr bool TWO_HOPS = COLLECT != FILTER_ONE_HOP;
     constexpr int PLACES = filter_set_places(COLLECT);
+    constexpr int LOADS = filter_loads(VEC);
     constexpr bool ANGLE = RULE == FILTER_RULE_ANGLE;
     constexpr bool APART = filter_apart(COLLECT, RULE);
     constexpr bool ID_SET = filter_set_of_ids(COLLECT, RULE);
@@ -339,10 +343,10 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE)) void fi
             int Q = collect(0, u, u_ok);
             const int per = 64 / A.kp;
             const int my_row = lane / A.kp, r = lane - my_row * A.kp;
-            for (int j0 = 0; j0 < k; j0 += FILTER_LOADS * per) {
-                int32_t w[FILTER_LOADS];
+            for (int j0 = 0; j0 < k; j0 += LOADS * per) {
+                int32_t w[LOADS];
 #pragma unroll
-                for (int t = 0; t < FILTER_LOADS; ++t) {
+                for (int t = 0; t < LOADS; ++t) {
                     const int j = j0 + t * per + my_row;
                     const bool on = my_row < per && j < k && r < k;
                     const int32_t uj = __shfl(u, on ? j : 0);
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE)) void fi
                     w[t] = (on && uj_ok) ? A.ids[(int64_t)uj * k + r] : -1;
                 }
 #pragma unroll
-                for (int t = 0; t < FILTER_LOADS; ++t) {
+                for (int t = 0; t < LOADS; ++t) {
                     if (j0 + t * per >= k) break;                 // uniform
                     Q = collect(Q, w[t], w[t] >= 0 && w[t] < A.n && w[t] != p);
                 }

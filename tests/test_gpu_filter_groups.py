@@ -45,3 +45,13 @@ def test_two_hops_of_random_rows(rule, k, n):
     X = np.floor(inputs.make("C2", n=n, d=24, comps=5) / 4.0).astype(np.float32)
     ids = rng.integers(0, n, size=(n, k)).astype(np.int32)
     _both(rule, X, ids, min(k, 32), 2)
+
+
+# the same where rows of X are no multiple of 16 bytes, which reads fewer rows of ids at a time: numbers of rows around what one step takes
+@pytest.mark.parametrize("rule", ["dist", "angle", "dispersion"])
+@pytest.mark.parametrize("k,n,d", [(32, 2003, 25), (33, 3001, 39), (9, 700, 30), (4, 60, 3)])
+def test_two_hops_of_rows_read_value_by_value(rule, k, n, d):
+    rng = np.random.default_rng(k + d)
+    X = np.floor(inputs.make("C2", n=n, d=d, comps=5) / 4.0).astype(np.float32)
+    ids = rng.integers(-1, n, size=(n, k)).astype(np.int32)
+    _both(rule, X, ids, min(k, 32), 2)
