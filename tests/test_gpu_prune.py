@@ -74,3 +74,15 @@ def test_lists_around_four_gibibytes(k, more):
     out, cnt = knn.prune_rank(ids, k // 2, want_counts=True)
     assert (cnt[n - m:].cpu().numpy() == want_cnt).all()
     assert (out[n - m:].cpu().numpy() == want_out + (n - m)).all()
+
+
+# a wave serves one node up to 32 768 of them, several beyond: rows that share ids with their neighbours' rows, with repeats, padding, own ids
+# and ids without a row
+@pytest.mark.parametrize("n,k", [(32_768, 32), (32_769, 32), (66_001, 31), (32_767, 16), (40_000, 16), (33_000, 3), (32_770, 1), (70_000, 24)])
+def test_one_node_and_several_nodes_to_a_wave(n, k):
+    rng = np.random.default_rng(n + k)
+    near = (np.arange(n)[:, None] + rng.integers(-2 * k, 2 * k + 1, size=(n, k))) % n        # (a window of 4 k + 1 nodes)
+    ids = near.astype(np.int32)
+    ids[rng.random((n, k)) < 0.03] = -1
+    ids[rng.random((n, k)) < 0.03] = n + 7
+    _check(ids, max(1, k // 2))
