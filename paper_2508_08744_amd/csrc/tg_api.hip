@@ -103,8 +103,7 @@ struct tg_knn_handle {
     float* xqm;          // its grid (three words, see TgGraph)
     u32* d_screen_on;    // device flags, one per phase-2 round: screening still pays (decided after each screened round for the next)
     u32* d_undefined;    // device counter: rows of X without a defined distance (written with the norms)
-    uint16_t* xh;        // fp16 copy of X for the local join (join_f16 = 1, 2)
-    u32* d_f16_ok;       // join_f16 = 2: device flag, 1 while every value of X is an fp16 number
+    uint16_t* xh;        // split copy of X for the local join (short rows; join_f16 = 1: of any rows, high parts only), or null
     int round;           // rounds run so far (both phases)
     int rounds1, rounds2;
     bool phase2;
@@ -142,12 +141,12 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->g.bytes = h->xq && tg_join_bytes_possible(n, ld, p.metric) ? reinterpret_cast<const uint32_t*>(h->xqm) : nullptr;
     h->d_screen_on = c.take<u32>(TG_MAX_ROUNDS + 1);
     h->d_undefined = c.take<u32>(64);
-    // the register-resident join reads 64, 96 or 128 columns per row (4, 6 or 8 steps of 16); longer rows are whole steps of 32
-    h->g.ldh = ld <= 64 ? 64 : ld <= 96 ? 96 : ld <= 128 ? 128 : (d + 31) & ~31;
-    h->xh = p.join_f16 ? c.take<uint16_t>((size_t)n * h->g.ldh) : nullptr;
-    h->d_f16_ok = p.join_f16 == 2 ? c.take<u32>(64) : nullptr;
-    h->g.f16_ok = h->d_f16_ok;
+    h->g.narrow = p.join_f16 == 1 ? 1 : 0;
+    h->g.ldh = (d + 31) & ~31;
+    h->g.ldhr = h->g.narrow ? h->g.ldh : 2 * h->g.ldh;
+    h->xh = h->g.narrow || tg_join_wave_ok(n, ld) ? c.take<uint16_t>((size_t)n * h->g.ldhr) : nullptr;
     h->g.Xh = h->xh;
+    h->g.low = h->xh ? reinterpret_cast<const uint32_t*>(h->xqm) + TG_RANGE_LOW : nullptr;
     h->sm.S = p.S; h->sm.R = p.R;
     h->sm.bshift = tg_rev_bucket_shift(n);
     h->sm.nbuckets = (n + (1ll << h->sm.bshift) - 1) >> h->sm.bshift;
@@ -162,7 +161,7 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->sm.bsz = c.take<u32>(n);
     h->sm.wl = c.take<u64>((size_t)3 * (n + TG_MAX_PARTS));
     h->sm.wl_cnt = c.take<u32>(TG_WL_LISTS);
-    h->sm.wave_ok = tg_join_wave_ok(ld) ? 1 : 0;
+    h->sm.wave_ok = tg_join_wave_ok(n, ld) ? 1 : 0;
     h->sm.parts = p.parts;
     h->sm.parts_shift = p.parts == 8 ? 3 : p.parts == 4 ? 2 : p.parts == 2 ? 1 : 0;
     h->sm.adj_words = h->sm.BC > 64 ? 4 : 2;
@@ -250,7 +249,6 @@ extern "C" int tg_knn_create(tg_knn_handle** out, const float* X, int64_t n, int
     z.nbuckets = (size_t)h->sm.nbuckets;
     z.range = reinterpret_cast<uint32_t*>(h->xqm);
     z.undefined = h->d_undefined;
-    z.f16_ok = h->d_f16_ok;
     tg_launch_setup(z, h->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -280,9 +278,11 @@ static void ensure_norms(tg_knn_handle* h)
 {
     if (h->norms_done) return;
     int sp = begin_span(h, SPAN_NORMS, 0);
-    tg_launch_norms(h->g, reinterpret_cast<uint32_t*>(h->xqm), h->d_undefined, h->stream);
-    // rounding every row whatever its values (join_f16 = 1): a row with a value beyond +-65504 has no fp16 copy to rank on, and is counted
-    if (h->xh) tg_launch_narrow(h->g, h->xh, h->d_f16_ok, h->d_f16_ok ? nullptr : h->d_undefined, h->stream);
+    uint32_t* range = reinterpret_cast<uint32_t*>(h->xqm);
+    const bool on_the_way = h->xh && !h->g.narrow && !h->g.bytes;      // the split copy: written by the kernel of the norms
+    tg_launch_norms(h->g, range, h->d_undefined, on_the_way ? h->xh : nullptr, h->stream);
+    // (join_f16 = 1: a row with a value beyond +-65504 is counted)
+    if (h->xh && !on_the_way) tg_launch_split(h->g, h->xh, range, h->g.narrow ? h->d_undefined : nullptr, h->stream);
     if (h->g.bytes) tg_launch_quantize(h->g, h->xq, h->xqm, true, h->stream);      // bytes: the join reads the codes
     end_span(h, sp);
     h->norms_done = true;
@@ -703,7 +703,7 @@ extern "C" int tg_exact_knn_static(const float* X, int64_t n, int32_t d, int32_t
     if (metric == 2) {
         g.nrm = w.take<float>(n);
         g.rnorm = w.take<float>(n);
-        tg_launch_norms(g, nullptr, nullptr, s);           // writes every word it later reads
+        tg_launch_norms(g, nullptr, nullptr, nullptr, s);  // writes every word it later reads
     }
     u64* partial = w.take<u64>((size_t)nq * slices * k);   // every word read by the merge is written by the scan
     tg_launch_exact_knn(g.X, g.ld, g.rnorm, n, k, metric, query_rows, nq, 0, nullptr, nullptr, out_ids, out_dist, partial, slices, s);
