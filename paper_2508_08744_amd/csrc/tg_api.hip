@@ -106,8 +106,11 @@ struct tg_knn_handle {
     uint16_t* xh;        // split copy of X for the local join (short rows; join_f16 = 1: of any rows, high parts only), or null
     int round;           // rounds run so far (both phases)
     int rounds1, rounds2;
+    u32* gid_phase2;     // the second array of lists, which phase 2 alone has
     bool phase2;
     bool norms_done;
+    bool xq_shared;      // the codes lie where the split copy was ...
+    bool split_lost;     // ... and have been written over it
     bool lists_ready;    // tg_knn_init or tg_knn_import has written the lists
     bool timed;          // record events around the steps (for the stats)
     std::vector<hipEvent_t> ev;
@@ -130,29 +133,30 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->g.nrm = c.take<float>(n);
     h->g.rnorm = c.take<float>(n);
     h->g.gid = c.take<u32>((size_t)n * p.k);
-    h->g.gid_next = c.take<u32>((size_t)n * p.k);
     h->g.gdist = c.take<float>((size_t)n * p.k);
     h->g.kth = c.take<u64>(n);
     h->g.ldq = (d + 15) & ~15;
-    h->xq = p.screen ? c.take<uint8_t>((size_t)n * h->g.ldq) : nullptr;
-    h->xqm = c.take<float>(64);          // also where the norms leave the range of the values
-    h->g.Xq = h->xq;
-    h->g.Xqm = h->xqm;
-    h->g.bytes = h->xq && tg_join_bytes_possible(n, ld, p.metric) ? reinterpret_cast<const uint32_t*>(h->xqm) : nullptr;
-    h->d_screen_on = c.take<u32>(TG_MAX_ROUNDS + 1);
-    h->d_undefined = c.take<u32>(64);
     h->g.narrow = p.join_f16 == 1 ? 1 : 0;
     h->g.ldh = (d + 31) & ~31;
     h->g.ldhr = h->g.narrow ? h->g.ldh : 2 * h->g.ldh;
     h->xh = h->g.narrow || tg_join_wave_ok(n, ld) ? c.take<uint16_t>((size_t)n * h->g.ldhr) : nullptr;
     h->g.Xh = h->xh;
+    // The codes and the split copy (4 bytes per value, so it is the larger one) share a place.  Where X holds bytes and phase 1 reads codes,
+    // the split copy is not written; elsewhere phase 1 reads the split copy, and the codes are written at the phase switch.
+    h->xq_shared = p.screen && h->xh && !h->g.narrow;
+    h->xq = !p.screen ? nullptr : h->xq_shared ? reinterpret_cast<uint8_t*>(h->xh) : c.take<uint8_t>((size_t)n * h->g.ldq);
+    h->xqm = c.take<float>(64);          // also where the norms leave the range of the values
+    h->g.Xq = h->xq;
+    h->g.Xqm = h->xqm;
     h->g.low = h->xh ? reinterpret_cast<const uint32_t*>(h->xqm) + TG_RANGE_LOW : nullptr;
+    h->g.bytes = h->xq && tg_join_bytes_possible(n, ld, p.metric) ? reinterpret_cast<const uint32_t*>(h->xqm) : nullptr;
+    h->d_screen_on = c.take<u32>(TG_MAX_ROUNDS + 1);
+    h->d_undefined = c.take<u32>(64);
     h->sm.S = p.S; h->sm.R = p.R;
     h->sm.bshift = tg_rev_bucket_shift(n);
     h->sm.nbuckets = (n + (1ll << h->sm.bshift) - 1) >> h->sm.bshift;
     h->sm.bcnt = c.take<u32>((size_t)h->sm.nbuckets);
     h->sm.boff = c.take<u64>((size_t)h->sm.nbuckets + 1);
-    h->sm.csr = c.take<u32>((size_t)n * p.k);
     {
         const int fwd = p.k < 2 * p.S ? p.k : 2 * p.S;
         h->sm.BC = (fwd + 2 * p.R + 15) & ~15;
@@ -164,14 +168,18 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->sm.wave_ok = tg_join_wave_ok(n, ld) ? 1 : 0;
     h->sm.parts = p.parts;
     h->sm.parts_shift = p.parts == 8 ? 3 : p.parts == 4 ? 2 : p.parts == 2 ? 1 : 0;
-    h->sm.adj_words = h->sm.BC > 64 ? 4 : 2;
+    h->sm.adj_words = h->sm.BC > 96 ? 4 : h->sm.BC > 64 ? 3 : 2;
     {
-        // the adjacency words of a part and the edges by bucket are never alive together: one place for both
+        // One place for what is never alive together: the sampled edges by bucket and by target, the adjacency words of a part, and the
+        // lists that the rounds of phase 2 write in turn with gid.
         const size_t adj_bytes = (size_t)((n + p.parts - 1) / p.parts) * h->sm.BC * h->sm.adj_words * sizeof(u32);
-        const size_t ebuf_bytes = (size_t)n * p.k * sizeof(u64);
-        u64* both = c.take<u64>((adj_bytes > ebuf_bytes ? adj_bytes : ebuf_bytes) / sizeof(u64) + 1);
+        const size_t edges = (size_t)n * p.k, edge_bytes = edges * (sizeof(u64) + sizeof(u32));
+        u64* both = c.take<u64>((adj_bytes > edge_bytes ? adj_bytes : edge_bytes) / sizeof(u64) + 1);
         h->sm.adj = reinterpret_cast<u32*>(both);
         h->sm.ebuf = both;
+        h->sm.csr = reinterpret_cast<u32*>(both + edges);
+        h->gid_phase2 = reinterpret_cast<u32*>(both);
+        h->g.gid_next = h->gid_phase2;
     }
     h->cd.C = p.C;
     h->cd.slots = c.take<u64>((size_t)n * p.C);
@@ -237,6 +245,7 @@ extern "C" int tg_knn_create(tg_knn_handle** out, const float* X, int64_t n, int
     h->round = h->rounds1 = h->rounds2 = 0;
     h->phase2 = false;
     h->norms_done = false;
+    h->split_lost = false;
     h->lists_ready = false;
     h->timed = true;
     if (h->x_padded) tg_launch_pad_rows(X, n, d, h->x_padded, h->g.ld, h->stream);
@@ -274,6 +283,14 @@ static int launch_status(const char* what)
     return TG_OK;
 }
 
+// Before anything of phase 1 runs: the lists are where phase 1 does not write.
+static void lists_home(tg_knn_handle* h, bool keep)
+{
+    if (h->g.gid != h->gid_phase2) return;
+    if (keep) (void)hipMemcpyAsync(h->g.gid_next, h->g.gid, (size_t)h->g.n * h->g.k * sizeof(u32), hipMemcpyDeviceToDevice, h->stream);
+    u32* t = h->g.gid; h->g.gid = h->g.gid_next; h->g.gid_next = t;
+}
+
 static void ensure_norms(tg_knn_handle* h)
 {
     if (h->norms_done) return;
@@ -292,6 +309,7 @@ extern "C" int tg_knn_init(tg_knn_handle* h)
 {
     if (!h) return fail(TG_ERR_INVALID_ARG, "handle is NULL");
     ensure_norms(h);
+    lists_home(h, false);
     int sp = begin_span(h, SPAN_INIT, 0);
     tg_launch_init(h->g, tg_hash_seed(h->p.seed, TG_TAG_INIT), h->stream);
     end_span(h, sp);
@@ -320,6 +338,10 @@ static int phase1_round(tg_knn_handle* h, int64_t* updates)
     if (h->phase2) return fail(TG_ERR_INVALID_ARG, "phase 1 round after the switch to phase 2");
     if (h->round >= TG_MAX_ROUNDS) return fail(TG_ERR_INVALID_ARG, "more than %d rounds", TG_MAX_ROUNDS);
     const int r = h->round;
+    if (h->split_lost) {         // lists built anew on a handle that had come to phase 2
+        tg_launch_split(h->g, h->xh, reinterpret_cast<uint32_t*>(h->xqm), nullptr, h->stream);
+        h->split_lost = false;
+    }
     int sp = begin_span(h, SPAN_SAMPLE, r);
     tg_launch_reverse(h->g, h->sm, tg_hash_seed(h->p.seed, TG_TAG_REV(r)), h->stream);
     end_span(h, sp);
@@ -353,6 +375,7 @@ extern "C" int tg_knn_begin_phase2(tg_knn_handle* h)
         ensure_norms(h);
         int sp = begin_span(h, SPAN_NORMS, 0);
         tg_launch_quantize(h->g, h->xq, h->xqm, false, h->stream);      // (bytes: done together with the norms)
+        h->split_lost = h->xq_shared;
         tg_launch_phase2_probe(h->g, h->p.m, h->d_undefined + 32, h->d_screen_on + h->rounds2, h->stream);
         end_span(h, sp);
     }
@@ -462,6 +485,7 @@ extern "C" int tg_knn_import(tg_knn_handle* h, const int32_t* ids, const float* 
                 return fail(TG_ERR_INVALID_ARG, "row %lld: id %d out of range", (long long)(i / h->g.k), hi[i]);
     }
     ensure_norms(h);
+    lists_home(h, false);
     tg_launch_import(h->g, ids, dist, fresh, h->stream);
     h->lists_ready = true;
     return launch_status("import");
@@ -471,6 +495,7 @@ extern "C" int tg_knn_sample_blocks(tg_knn_handle* h, int32_t* blk, int32_t* siz
 {
     if (!h || !blk || !sizes) return fail(TG_ERR_INVALID_ARG, "NULL argument");
     if (!h->lists_ready) return fail(TG_ERR_INVALID_ARG, "no lists yet: call tg_knn_init or tg_knn_import first");
+    lists_home(h, true);
     tg_launch_reverse(h->g, h->sm, tg_hash_seed(h->p.seed, TG_TAG_REV(h->round)), h->stream);
     tg_launch_dump_blocks(h->g, h->sm, blk, sizes, h->stream);
     return launch_status("sample");
@@ -480,6 +505,7 @@ extern "C" int tg_knn_block_adjacency(tg_knn_handle* h, uint32_t* adj)
 {
     if (!h || !adj) return fail(TG_ERR_INVALID_ARG, "NULL argument");
     if (!h->lists_ready) return fail(TG_ERR_INVALID_ARG, "no lists yet: call tg_knn_init or tg_knn_import first");
+    lists_home(h, true);
     for (int part = 0; part < h->p.parts; ++part) tg_launch_dump_adj(h->g, h->sm, part, adj, h->stream);
     return launch_status("block adjacency");
 }
@@ -504,7 +530,9 @@ extern "C" int tg_knn_join_distances(tg_knn_handle* h, const int32_t* blk, const
         }
     }
     ensure_norms(h);
-    tg_launch_join_distances(h->g, blk, sizes, nb, out, h->stream);
+    TgGraph g = h->g;
+    if (h->split_lost) g.Xh = nullptr;           // (the workgroup kernel reads X)
+    tg_launch_join_distances(g, blk, sizes, nb, out, h->stream);
     return launch_status("join distances");
 }
 

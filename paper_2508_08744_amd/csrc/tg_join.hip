@@ -68,7 +68,7 @@ __device__ inline float join_row_aux(float aux, float us, int metric) { return m
 
 // ---------------------------------------------------------------------------------------
 // Which members of a block sit in which member's list already: sm.adj, per anchor of the part
-// (slot v / parts) and member p, adj_words words whose bit x says "the node at position x of
+// (slot v / parts) and member p, tg_adj_words words whose bit x says "the node at position x of
 // the block is in p's list".  One wave per anchor.  The block's ids (distinct) go into an
 // open-addressed table in LDS, T8[hash(id) + probes] = block position, a byte each.  The members'
 // lists are then read as one run of 16-byte pieces, 64 pieces per load, so consecutive lanes
@@ -100,7 +100,6 @@ __global__ __launch_bounds__(64 * ADJ_WAVES) void adj_kernel(TgGraph g, TgSample
     constexpr int W = VEC ? 4 : 1;                 // ids per piece; VEC: rows of the lists are 16-byte aligned (k % 4 == 0)
     const int per = k / W;                         // pieces per list
     const int per_sh = (per & (per - 1)) == 0 ? __ffs(per) - 1 : -1;
-    const int aw = sm.adj_words, aw_sh = __ffs(aw) - 1;
     auto lds_fence = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -188,8 +187,12 @@ __global__ __launch_bounds__(64 * ADJ_WAVES) void adj_kernel(TgGraph g, TgSample
             }
         }
         lds_fence();
-        u32* out = sm.adj + a * sm.BC * (int64_t)aw;
-        for (int c = lane; c < nT * aw; c += 64) out[c] = sh.adjw[(c >> aw_sh) * 4 + (c & (aw - 1))];
+        const int aw = tg_adj_words(sm.adj_words, nT);
+        u32* out = sm.adj + a * sm.BC * (int64_t)sm.adj_words;
+        for (int c = lane; c < nT * aw; c += 64) {
+            const int p = aw == 2 ? c >> 1 : aw == 3 ? (c * 43691) >> 17 : c >> 2;      // c / 3 of c < 384
+            out[c] = sh.adjw[p * 4 + (c - p * aw)];
+        }
     }
 }
 void tg_launch_adj(const TgGraph& g, const TgSample& sm, int part, hipStream_t s)
@@ -215,7 +218,8 @@ __global__ void dump_adj_kernel(TgSample sm, int64_t n, int part, uint32_t* out)
         const u32 z = sm.bsz[v];
         const int nN = (int)(z & 0xFFu), nT = (int)(z >> 8);
         const bool joined = nN > 0 && nT >= 2 && nT <= sm.BC;
-        out[((size_t)v * TG_BLOCK_COLS + p) * 4 + wd] = (joined && p < nT && wd < sm.adj_words) ? sm.adj[(a * sm.BC + p) * (int64_t)sm.adj_words + wd] : 0u;
+        const int aw = tg_adj_words(sm.adj_words, nT);
+        out[((size_t)v * TG_BLOCK_COLS + p) * 4 + wd] = (joined && p < nT && wd < aw) ? sm.adj[a * sm.BC * (int64_t)sm.adj_words + p * aw + wd] : 0u;
     }
 }
 void tg_launch_dump_adj(const TgGraph& g, const TgSample& sm, int part, uint32_t* out, hipStream_t s)
@@ -398,9 +402,10 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
     }
     if (MODE == 0 && tid < nT) {
         // which members sit in which member's list (adj_kernel): four words per member here
-        const u32* aw = sm.adj + ((v / sm.parts) * sm.BC + tid) * (int64_t)sm.adj_words;
+        const int words = tg_adj_words(sm.adj_words, nT);
+        const u32* aw = sm.adj + (v >> sm.parts_shift) * sm.BC * (int64_t)sm.adj_words + tid * words;
 #pragma unroll
-        for (int wd = 0; wd < 4; ++wd) s_adj[tid * 4 + wd] = wd < sm.adj_words ? aw[wd] : 0u;
+        for (int wd = 0; wd < 4; ++wd) s_adj[tid * 4 + wd] = wd < words ? aw[wd] : 0u;
     }
     const u32 id_next = tid < ROWS && tid < nxt.nT ? min(nxt.bids[tid], idmax) : 0u;
 
@@ -682,7 +687,7 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
             kth = g.kth[id];
             aux = __uint_as_float((u32)kth);
             // which positions of the block this member's list holds already (adj_kernel); any lane reads a valid word
-            adj = *reinterpret_cast<const u64*>(sm.adj + ((it.v >> sm.parts_shift) * sm.BC + (lane < it.nT ? lane : 0)) * (int64_t)sm.adj_words);
+            adj = *reinterpret_cast<const u64*>(sm.adj + (it.v >> sm.parts_shift) * sm.BC * (int64_t)sm.adj_words + (lane < it.nT ? 2 * lane : 0));
         } else {
             adj = 0ull;
             kth = 0ull;
@@ -999,7 +1004,7 @@ __global__ __launch_bounds__(256) void join_bytes_kernel(TgGraph g, TgSample sm,
     fetch_rows(idn);
     int mid = (int)min(cur.bids[lane < cur.nT ? lane : 0], idmax);
     u64 m_kth = g.kth[mid];
-    u64 m_adj = *reinterpret_cast<const u64*>(sm.adj + (((int64_t)cur.v >> sm.parts_shift) * sm.BC + (lane < cur.nT ? lane : 0)) * (int64_t)sm.adj_words);
+    u64 m_adj = *reinterpret_cast<const u64*>(sm.adj + ((int64_t)cur.v >> sm.parts_shift) * sm.BC * (int64_t)sm.adj_words + (lane < cur.nT ? 2 * lane : 0));
     fetch_ids(nxt, idn);
     int midn = (int)min(nxt.bids[lane < nxt.nT ? lane : 0], idmax);
     for (; w < count; w += nwaves) {
@@ -1084,7 +1089,7 @@ __global__ __launch_bounds__(256) void join_bytes_kernel(TgGraph g, TgSample sm,
         fetch_rows(idn);
         const u64 k_next = g.kth[midn];
         const u64 adj_next =
-            *reinterpret_cast<const u64*>(sm.adj + (((int64_t)nxt.v >> sm.parts_shift) * sm.BC + (lane < nxt.nT ? lane : 0)) * (int64_t)sm.adj_words);
+            *reinterpret_cast<const u64*>(sm.adj + ((int64_t)nxt.v >> sm.parts_shift) * sm.BC * (int64_t)sm.adj_words + (lane < nxt.nT ? 2 * lane : 0));
         fetch_ids(nxt2, idn);
         const int midn2 = (int)min(nxt2.bids[lane < nxt2.nT ? lane : 0], idmax);
         lds_fence();
@@ -1227,7 +1232,7 @@ void tg_launch_join_distances(const TgGraph& g, const int32_t* blk, const int32_
     (void)once;
     int skip_le = 0;
     // same routing by block size as the production join (the split copy is left out where X turns out to hold bytes)
-    if (tg_join_wave_ok(g.n, g.ld) && (g.narrow || !g.bytes)) {
+    if (g.Xh && tg_join_wave_ok(g.n, g.ld) && (g.narrow || !g.bytes)) {
         if (g.metric == 0) { launch_wave_dump<3, 0>(g, blk, sizes, nb, out, 0, s); launch_wave_dump<4, 0>(g, blk, sizes, nb, out, 4, s); }
         else if (g.metric == 1) { launch_wave_dump<3, 1>(g, blk, sizes, nb, out, 0, s); launch_wave_dump<4, 1>(g, blk, sizes, nb, out, 4, s); }
         else { launch_wave_dump<3, 2>(g, blk, sizes, nb, out, 0, s); launch_wave_dump<4, 2>(g, blk, sizes, nb, out, 4, s); }

@@ -33,7 +33,7 @@ struct TgGraph {
     float* nrm;       // n: squared norms
     float* rnorm;     // n: 1/|x| (cosine only, else unused)
     uint32_t* gid;    // n x k list words of the current round: id | fresh << 31
-    uint32_t* gid_next; // n x k, written by a phase-2 round
+    uint32_t* gid_next; // n x k, written by a phase-2 round; before the first one, the place of what phase 1 alone needs (see carve)
     float* gdist;     // n x k
     unsigned long long* kth;   // n: what the join needs of a node besides its vector: ordered distance of its list's last entry
                                // (high word), bits of its squared norm, or inverse norm for cosine (low word)
@@ -66,9 +66,12 @@ struct TgSample {
     uint32_t* wl_cnt;         // TG_WL_LISTS: their lengths
     int32_t wave_ok;          // the register-resident join applies (short rows): which work list a block goes to
     int32_t parts, parts_shift;   // a round's anchors are joined in `parts` = 1 << parts_shift parts: v goes to part v % parts, slot v / parts
-    uint32_t* adj;                // ceil(n / parts) x BC x adj_words: of the part in hand, per anchor slot and member, bit x = the
-    int32_t adj_words;            // node at block position x is in that member's list already (2 words for blocks of at most 64, else 4)
+    uint32_t* adj;                // ceil(n / parts) x BC x adj_words: of the part in hand, per anchor slot and member, bit x = the node at
+    int32_t adj_words;            // block position x is in that member's list already; tg_adj_words(adj_words, members) words per member
 };
+
+// words per member that a block of nT members stores (adj_words: what the largest block takes)
+__host__ __device__ static inline int tg_adj_words(int adj_words, int nT) { return nT <= 64 ? 2 : adj_words; }
 
 struct TgCand {
     int32_t C;

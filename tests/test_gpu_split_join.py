@@ -55,3 +55,32 @@ def test_whole_numbers_under_exact_sums_are_exact(d, most):
     X[:40] = most - rng.integers(0, 2, (40, d))
     for got, gram, nsum, _ in _tile(X, "l2", [(40, 24), (64, 64), (16, 16), (1, 127)], seed=1):
         assert (got == (nsum - 2 * gram).astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("n,d,bytes_", [(1500, 24, False), (66_000, 16, False), (66_000, 16, True)])
+def test_a_handle_starts_again_after_phase_2(n, d, bytes_):
+    """Phase 2 writes its lists and its codes where phase 1 keeps edges, adjacency words and split rows: a second build on the same handle
+    equals the first, and looking at blocks, adjacency and distances between rounds of phase 2 changes nothing."""
+    rng = np.random.default_rng(n)
+    X = rng.uniform(0, 255, (30, d))[rng.integers(0, 30, n)] + rng.normal(0, 9, (n, d))
+    X = np.clip(np.rint(X), 0, 255).astype(np.float32) / (1 if bytes_ else 2)          # (sums of halves are as exact)
+    b = knn.Builder(torch.from_numpy(X).cuda(), knn.default_params(12, 6, seed=5, it1=3, it2=3))
+    blk = torch.from_numpy(rng.integers(0, n, (3, 128), dtype=np.int32))
+    sizes = torch.tensor([[20, 30], [64, 64], [3, 9]], dtype=torch.int32)
+    graphs, tiles = [], []
+    for look in (False, True):
+        b.init()
+        tiles.append(b.join_distances(blk, sizes))
+        for _ in range(3):
+            b.phase1_round()
+        b.begin_phase2()
+        for _ in range(3):
+            b.phase2_round()
+            if look:
+                b.sample_blocks()
+                b.block_adjacency()
+                tiles.append(b.join_distances(blk, sizes))
+        graphs.append(b.finalize())
+    b.close()
+    assert all(torch.equal(x, y) for x, y in zip(*graphs))
+    assert all(torch.equal(torch.nan_to_num(t), torch.nan_to_num(tiles[0])) for t in tiles)
