@@ -107,6 +107,7 @@ struct tg_knn_handle {
     int round;           // rounds run so far (both phases)
     int rounds1, rounds2;
     u32* gid_phase2;     // the second array of lists, which phase 2 alone has
+    u32* order;          // see tg_launch_order
     bool phase2;
     bool norms_done;
     bool xq_shared;      // the codes lie where the split copy was ...
@@ -174,11 +175,16 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
         // lists that the rounds of phase 2 write in turn with gid.
         const size_t adj_bytes = (size_t)((n + p.parts - 1) / p.parts) * h->sm.BC * h->sm.adj_words * sizeof(u32);
         const size_t edges = (size_t)n * p.k, edge_bytes = edges * (sizeof(u64) + sizeof(u32));
-        u64* both = c.take<u64>((adj_bytes > edge_bytes ? adj_bytes : edge_bytes) / sizeof(u64) + 1);
+        const size_t order_bytes = tg_order_pays(n, ld) ? tg_order_space(n) : 0;
+        size_t most = adj_bytes > edge_bytes ? adj_bytes : edge_bytes;
+        if (order_bytes > most) most = order_bytes;
+        u64* both = c.take<u64>(most / sizeof(u64) + 1);
         h->sm.adj = reinterpret_cast<u32*>(both);
         h->sm.ebuf = both;
         h->sm.csr = reinterpret_cast<u32*>(both + edges);
         h->gid_phase2 = reinterpret_cast<u32*>(both);
+        h->order = tg_order_pays(n, ld) ? c.take<u32>(n) : nullptr;
+        h->g.order = nullptr;
         h->g.gid_next = h->gid_phase2;
     }
     h->cd.C = p.C;
@@ -316,6 +322,7 @@ extern "C" int tg_knn_init(tg_knn_handle* h)
     h->round = h->rounds1 = h->rounds2 = 0;
     h->phase2 = false;
     h->lists_ready = true;
+    h->g.order = nullptr;
     return launch_status("init");
 }
 
@@ -331,6 +338,15 @@ static int read_updates(tg_knn_handle* h, int round, int64_t* updates)
     return TG_OK;
 }
 
+// The order in which the steps from here on take the nodes; made once (10M x 96: made again before phase 2, it costs what it gives)
+// where it pays.  It uses the place of phase 1's edges and phase 2's lists, which are between two uses when this is called.
+static void make_order(tg_knn_handle* h)
+{
+    if (!h->order || h->g.order) return;
+    tg_launch_order(h->g, h->order, h->sm.wl_cnt, h->sm.ebuf, h->stream);
+    h->g.order = h->order;
+}
+
 static int phase1_round(tg_knn_handle* h, int64_t* updates)
 {
     if (!h) return fail(TG_ERR_INVALID_ARG, "handle is NULL");
@@ -343,6 +359,7 @@ static int phase1_round(tg_knn_handle* h, int64_t* updates)
         h->split_lost = false;
     }
     int sp = begin_span(h, SPAN_SAMPLE, r);
+    if (r >= 3) make_order(h);           // (the lists of the first rounds are too random to say who is near whom)
     tg_launch_reverse(h->g, h->sm, tg_hash_seed(h->p.seed, TG_TAG_REV(r)), h->stream);
     end_span(h, sp);
     for (int part = 0; part < h->p.parts; ++part) {
@@ -370,6 +387,7 @@ extern "C" int tg_knn_begin_phase2(tg_knn_handle* h)
 {
     if (!h) return fail(TG_ERR_INVALID_ARG, "handle is NULL");
     if (!h->lists_ready) return fail(TG_ERR_INVALID_ARG, "no lists yet: call tg_knn_init or tg_knn_import first");
+    if (!h->phase2) make_order(h);
     tg_launch_mark_all_fresh(h->g, h->xq ? h->d_screen_on + h->rounds2 : nullptr, h->stream);
     if (!h->phase2 && h->xq) {
         ensure_norms(h);

@@ -228,6 +228,19 @@ void tg_launch_dump_adj(const TgGraph& g, const TgSample& sm, int part, uint32_t
     hipLaunchKernelGGL(dump_adj_kernel, dim3(1024), dim3(256), 0, s, sm, g.n, part, out);
 }
 
+// The part of a work list that a workgroup walks.  A list written in the nodes' order (g.order) is cut into eight shares, one for
+// each XCD, which takes every eighth workgroup: what an XCD's waves have in hand at one time are then neighbours.
+struct ListShare {
+    int64_t first, count;        // records
+    int64_t index, workgroups;   // this workgroup, among those that walk the share
+};
+__device__ inline ListShare list_share(int64_t count, bool ordered)
+{
+    if (!ordered || (gridDim.x & 7u)) return {0, count, (int64_t)blockIdx.x, (int64_t)gridDim.x};
+    const int64_t share = (count + 7) >> 3, first = (int64_t)(blockIdx.x & 7u) * share;
+    return {first, min(share, count - first), (int64_t)(blockIdx.x >> 3), (int64_t)(gridDim.x >> 3)};
+}
+
 // Candidate slot of member t (salt: its slot-hash salt) for the cell q of anchor v's block: the pair (t, v) owns
 // one 64-byte line of t's slot row, picked by a hash, and cell q goes to word (q + rotation) % 8 of it, where it
 // stays if it is the smaller (dist, id): one 64-bit atomic minimum, no order dependence.  All candidates one block
@@ -307,16 +320,16 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
     const u32 idmax = (u32)(g.n - 1);
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int64_t count = A.wl ? (int64_t)*A.wl_cnt : A.direct_count;
+    const ListShare part = list_share(A.wl ? (int64_t)*A.wl_cnt : A.direct_count, MODE == 0 && tg_use_order(g));
     if (MODE == 0) {
         for (int c = tid; c < TG_BLOCK_COLS * JOIN_CELLS; c += JOIN_THREADS) s_cell[c] = TG_EMPTY_KEY;
     }
     struct Block { int64_t v; const u32* bids; int nN, nT; };       // nT = 0: nothing to do
     auto block_at = [&](int64_t w) {
         Block b = {0, nullptr, 0, 0};
-        if (w >= count) return b;
+        if (w >= part.count) return b;
         u64 rec;
-        if (MODE == 0) rec = A.wl[w];
+        if (MODE == 0) rec = A.wl[part.first + w];
         else rec = tg_pack_rec((u32)w, A.xsizes[w * 2], A.xsizes[w * 2] + A.xsizes[w * 2 + 1]);
         const int nN = (int)((rec >> 32) & 0xFFu), nT = (int)((rec >> 40) & 0xFFu);
         b.v = (int64_t)(u32)rec;
@@ -371,18 +384,18 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
         }
     };
 
-    int64_t w = blockIdx.x;
-    if (w >= count) return;
+    int64_t w = part.index;
+    if (w >= part.count) return;
     Block cur = block_at(w);
     int buf = 0;
     if (tid < ROWS) s_idb[tid] = tid < cur.nT ? min(cur.bids[tid], idmax) : 0u;
     __syncthreads();
     issue(0, s_idb, cur.nT);
-    for (; w < count; w += gridDim.x) {
+    for (; w < part.count; w += part.workgroups) {
     const u32* s_ids = s_idb + buf * HW;
     const int64_t v = cur.v;
     const int nN = cur.nN, nT = cur.nT;
-    const Block nxt = block_at(w + gridDim.x);
+    const Block nxt = block_at(w + part.workgroups);
     if (tid < nT) {
         const u32 id = s_ids[tid];
         const u64 kth = MODE == 0 ? g.kth[id] : 0ull;        // threshold distance and norm in one word
@@ -635,8 +648,9 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
     WaveShared& sh = reinterpret_cast<WaveShared*>(wave_smem)[wave];
     const int r16 = lane & 15, q4 = lane >> 4;
     const float INF = __builtin_inff();
-    const int64_t count = wl ? (int64_t)*wl_cnt : direct_count;
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
+    const ListShare share = list_share(wl ? (int64_t)*wl_cnt : direct_count, MODE == 0 && tg_use_order(g));
+    const int64_t count = share.count;
+    const int64_t nwaves = share.workgroups * 4;
     const u32 idmax = (u32)(g.n - 1);
 
     // A record past the end of the list becomes an empty block at anchor 0, so that every load
@@ -645,7 +659,7 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
     auto load_rec = [&](int64_t w) -> u64 {
         const int64_t wc = w < count ? w : count - 1;
         u64 rec;
-        if (MODE == 0) rec = wl[wc];
+        if (MODE == 0) rec = wl[share.first + wc];
         else rec = tg_pack_rec((u32)wc, xsizes[wc * 2], xsizes[wc * 2] + xsizes[wc * 2 + 1]);
         return w < count ? rec : 0ull;
     };
@@ -733,7 +747,7 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
         __builtin_amdgcn_wave_barrier();
     };
 
-    int64_t w = (int64_t)blockIdx.x * 4 + wave;
+    int64_t w = share.index * 4 + wave;
     if (w >= count) return;
     WaveItem cur = decode(load_rec(w));
     WaveItem nxt = decode(load_rec(w + nwaves));

@@ -40,6 +40,7 @@ struct TgGraph {
     const uint8_t* Xq;  // n x ldq bytes: 8-bit codes of every row (phase-2 screening), or null
     const float* Xqm;   // the grid of the codes, three words: ordered bits of the smallest and of the largest value of X, float
                         // bits of the largest distance of a row from its grid point
+    const uint32_t* order;  // n: the nodes in an order that brings neighbours together (tg_launch_order), or null: by number
     int32_t ldq;        // d rounded up to 16: a row of codes never straddles more lines than it must
     const uint16_t* Xh; // n x ldhr: the rows for the local join, scaled and split into fp16 numbers (tg_split4): ldh high parts, then
                         // (unless `narrow`) ldh low parts; or null: the workgroup join splits the rows of X on their way into LDS
@@ -116,6 +117,12 @@ void tg_launch_dump_adj(const TgGraph& g, const TgSample& sm, int part, uint32_t
 void tg_launch_join(const TgGraph& g, const TgSample& sm, const TgCand& c, int part, int parts,
                     uint64_t hs_slot, unsigned long long* stat_bins /* 2 x TG_STAT_BINS or null */,
                     hipStream_t s);
+// exclusive prefix sum of n counts, off[n] = their sum; empties the join's work lists
+void tg_launch_scan(const uint32_t* cnt, int64_t n, unsigned long long* off, uint32_t* wl_cnt, hipStream_t s);
+// fills order (n); space: tg_order_space(n) bytes that nothing else needs now
+bool tg_order_pays(int64_t n, int ld);
+size_t tg_order_space(int64_t n);
+void tg_launch_order(const TgGraph& g, uint32_t* order, uint32_t* wl_cnt, void* space, hipStream_t s);
 void tg_launch_dump_blocks(const TgGraph& g, const TgSample& sm, int32_t* blk, int32_t* sizes, hipStream_t s);
 void tg_launch_join_distances(const TgGraph& g, const int32_t* blk, const int32_t* sizes, int64_t nb,
                               float* out, hipStream_t s);

@@ -938,6 +938,16 @@ __device__ __forceinline__ void phase2_body(const TgGraph& g, int m, int set_wor
 {
     if (screen_on && (*screen_on != 0u) != SCREEN) return;
     const int wave = threadIdx.x >> 6;
+    if (tg_use_order(g)) {
+        // an XCD takes every eighth workgroup: each has an eighth of the order to itself (the grid is a multiple of eight workgroups then)
+        const int64_t share = (g.n + 7) / 8, beg = (blockIdx.x & 7) * share, end = min(beg + share, g.n);
+        for (int64_t i = beg + (int64_t)(blockIdx.x >> 3) * LISTS_WAVES + wave; i < end; i += (int64_t)(gridDim.x >> 3) * LISTS_WAVES) {
+            phase2_node<SCREEN, false>(g, (int64_t)__builtin_amdgcn_readfirstlane((int)g.order[i]), m, set_words, updates, stat_bins, nullptr);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        return;
+    }
     for (int64_t v = (int64_t)blockIdx.x * LISTS_WAVES + wave; v < g.n; v += (int64_t)gridDim.x * LISTS_WAVES) {
         phase2_node<SCREEN, false>(g, v, m, set_words, updates, stat_bins, nullptr);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1045,6 +1055,7 @@ void tg_launch_phase2(const TgGraph& g, int m, u64* updates, u64* stat_bins, u32
     const size_t shm = phase2_lds(g, set_words);
     int64_t blocks = (g.n + LISTS_WAVES - 1) / LISTS_WAVES;
     if (blocks > PHASE2_GRID) blocks = PHASE2_GRID;
+    if (g.order) blocks = (blocks + 7) & ~7ll;
     if (g.Xq) {
         hipLaunchKernelGGL(phase2_screen_kernel, dim3((unsigned)blocks), dim3(64 * LISTS_WAVES), shm, s, g, m, set_words, updates, stat_bins,
                            (const u32*)screen_on);
@@ -1065,8 +1076,20 @@ __global__ __launch_bounds__(64 * LISTS_WAVES) void finalize_kernel(TgGraph g, i
 {
     extern __shared__ float smem[];
     const int wave = threadIdx.x >> 6, lane = tg_lane();
-    const int64_t v = v0 + (int64_t)blockIdx.x * LISTS_WAVES + wave;
-    if (v >= g.n) return;
+    // Where every fp32 sum of the norms, the inner products and their combination is exact, the distances in the lists are the
+    // directly computed ones already, bit for bit.
+    if (recompute && range && g.metric != 2 && tg_whole_exact(range, g.d)) recompute = 0;
+    int64_t v;
+    if (recompute && tg_use_order(g)) {
+        // an eighth of the launch's nodes for each XCD, as in phase2_body
+        const int64_t share = (int64_t)(gridDim.x >> 3) * LISTS_WAVES;
+        const int64_t i = v0 + (blockIdx.x & 7) * share + (int64_t)(blockIdx.x >> 3) * LISTS_WAVES + wave;
+        if (i >= g.n) return;
+        v = (int64_t)g.order[i];
+    } else {
+        v = v0 + (int64_t)blockIdx.x * LISTS_WAVES + wave;
+        if (v >= g.n) return;
+    }
     const int k = g.k;
     float* xs = smem + (size_t)wave * g.ld;
     u32* wscr = reinterpret_cast<u32*>(smem + (size_t)LISTS_WAVES * g.ld) + wave * 128;
@@ -1076,9 +1099,6 @@ __global__ __launch_bounds__(64 * LISTS_WAVES) void finalize_kernel(TgGraph g, i
         id = (int)(g.gid[v * k + lane] & TG_ID_MASK);
         dist = g.gdist[v * k + lane];
     }
-    // Where every fp32 sum of the norms, the inner products and their combination is exact, the distances in the lists are the
-    // directly computed ones already, bit for bit.
-    if (recompute && range && g.metric != 2 && tg_whole_exact(range, g.d)) recompute = 0;
     if (recompute) {
         stage_row(g, v, xs);
         const float rn_v = g.metric == 2 ? g.rnorm[v] : 1.0f;
@@ -1097,7 +1117,8 @@ void tg_launch_finalize(const TgGraph& g, int recompute, const uint32_t* range, 
 {
     size_t shm = (size_t)LISTS_WAVES * g.ld * sizeof(float) + LISTS_WAVES * 128 * sizeof(u32);
     tg_for_node_chunks(g.n, [&](int64_t v0, int64_t cnt) {
-        hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((cnt + LISTS_WAVES - 1) / LISTS_WAVES)), dim3(64 * LISTS_WAVES), shm, s, g,
+        // (a multiple of eight workgroups, for the order; a chunk's nodes are a multiple of eight workgroups' but for the last chunk)
+        hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)(((cnt + LISTS_WAVES - 1) / LISTS_WAVES + 7) & ~7ll)), dim3(64 * LISTS_WAVES), shm, s, g,
                            recompute, range, out_ids, out_dist, v0);
     });
 }

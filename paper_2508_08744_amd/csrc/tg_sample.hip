@@ -198,6 +198,14 @@ __device__ inline void assemble_block(const TgGraph& g, const TgSample& sm, int6
     if (lane == 0) sm.bsz[v] = (u32)nN | ((u32)nT << 8);
 }
 
+// the work list that takes anchor v's block, -1: nothing to join
+__device__ inline int work_list(const TgSample& sm, int64_t v, int nN, int nT)
+{
+    if (nN == 0 || nT < 2) return -1;
+    const int NT = (nT + 15) >> 4;
+    return ((int)v & (sm.parts - 1)) * 3 + (NT > 4 ? 2 : (NT == 4 || !sm.wave_ok) ? 1 : 0);
+}
+
 // One workgroup per bucket: its edges are counted per target in LDS, stored grouped by target (csr, at the
 // bucket's own place: one workgroup writes and reads it, so it stays in that workgroup's cache), and every
 // target's arrivals are then cut down to its reverse samples by one wave, which also assembles its block.
@@ -317,6 +325,7 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
         assemble_block(g, sm, u, w_list, (u32)best_new, min(tot_new, sm.R), (u32)best_old, min(tot_old, sm.R), asm_keys[wave], asm_tags[wave]);
         abeg = nbeg; aend = nend; e_first = e_next; w_list = w_next;
     }
+    if (tg_use_order(g)) return;        // wl_order_kernel writes the work lists
     // Work lists of the join: the bucket's anchors with something to join, by part of the round (v mod parts) and by block size.
     // List 0: at most 3 row groups, list 1: exactly 4, list 2: more.  Without the register-resident join (longer rows)
     // list 1 takes every block of at most 4 row groups and list 0 stays empty.  The list of (part, size class) is
@@ -332,11 +341,7 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
             const u32 z = sm.bsz[v];
             nN = (int)(z & 0xFFu);
             nT = (int)(z >> 8);
-            if (nN > 0 && nT >= 2) {
-                const int NT = (nT + 15) >> 4;
-                const int bin = NT > 4 ? 2 : (NT == 4 || !sm.wave_ok) ? 1 : 0;
-                list = ((int)v & (sm.parts - 1)) * 3 + bin;
-            }
+            list = work_list(sm, v, nN, nT);
         }
         const u32 mypos = list >= 0 ? atomicAdd(lcnt + list, 1u) : 0u;
         __syncthreads();
@@ -346,6 +351,37 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
         if (threadIdx.x < TG_WL_LISTS) lcnt[threadIdx.x] = 0u;
         __syncthreads();
     }
+}
+
+// The work lists in the nodes' order: a workgroup takes 1024 nodes of it and a run of every list.
+#define WLO_EACH 4
+__global__ __launch_bounds__(256) void wl_order_kernel(TgGraph g, TgSample sm)
+{
+    __shared__ u32 lcnt[TG_WL_LISTS], lbase[TG_WL_LISTS];
+    if (!tg_use_order(g)) return;
+    if (threadIdx.x < TG_WL_LISTS) lcnt[threadIdx.x] = 0u;
+    __syncthreads();
+    const int64_t cap = (g.n + sm.parts - 1) / sm.parts;
+    u32 v[WLO_EACH], z[WLO_EACH], pos[WLO_EACH];
+    int list[WLO_EACH];
+#pragma unroll
+    for (int j = 0; j < WLO_EACH; ++j) {
+        const int64_t i = ((int64_t)blockIdx.x * WLO_EACH + j) * 256 + threadIdx.x;
+        v[j] = i < g.n ? g.order[i] : 0u;
+        z[j] = i < g.n ? sm.bsz[v[j]] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < WLO_EACH; ++j) {
+        list[j] = work_list(sm, v[j], (int)(z[j] & 0xFFu), (int)(z[j] >> 8));
+        pos[j] = list[j] >= 0 ? atomicAdd(lcnt + list[j], 1u) : 0u;
+    }
+    __syncthreads();
+    if (threadIdx.x < TG_WL_LISTS) lbase[threadIdx.x] = lcnt[threadIdx.x] ? atomicAdd(sm.wl_cnt + threadIdx.x, lcnt[threadIdx.x]) : 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < WLO_EACH; ++j)
+        if (list[j] >= 0 && (int64_t)lbase[list[j]] + pos[j] < cap)
+            sm.wl[(int64_t)list[j] * cap + lbase[list[j]] + pos[j]] = tg_pack_rec(v[j], (int)(z[j] & 0xFFu), (int)(z[j] >> 8));
 }
 
 // blocks as stored -> the boundary's fixed n x 128 layout (padding -1) and (|NEW|, |OLD|)
@@ -371,6 +407,11 @@ void tg_launch_dump_blocks(const TgGraph& g, const TgSample& sm, int32_t* blk, i
     hipLaunchKernelGGL(dump_blocks_kernel, dim3((unsigned)grid), dim3(256), 0, s, g, sm, blk, sizes);
 }
 
+void tg_launch_scan(const uint32_t* cnt, int64_t n, unsigned long long* off, uint32_t* wl_cnt, hipStream_t s)
+{
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, cnt, n, off, wl_cnt);
+}
+
 void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hipStream_t s)
 {
     int kp = 1;
@@ -392,12 +433,12 @@ void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hi
                 hipLaunchKernelGGL(rev_bucket_kernel<true>, dim3(grid), dim3(REV_BUCKET_THREADS), 0, s, g, sm.S, kp, sm.bshift, b0, nb, chunk, sm.bcnt,
                                    (const u64*)sm.boff, sm.ebuf);
         }
-        if (pass == 0)
-            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, (const u32*)sm.bcnt, sm.nbuckets, sm.boff, sm.wl_cnt);
+        if (pass == 0) tg_launch_scan(sm.bcnt, sm.nbuckets, sm.boff, sm.wl_cnt, s);
     }
     for (int64_t bf = 0; bf < sm.nbuckets; bf += (1 << 20))
         hipLaunchKernelGGL(rev_select_kernel, dim3((unsigned)(sm.nbuckets - bf < (1 << 20) ? sm.nbuckets - bf : (1 << 20))), dim3(256), 0, s, g, sm,
                            hs_rev, bf);
+    if (g.order) hipLaunchKernelGGL(wl_order_kernel, dim3((unsigned)((g.n + 256 * WLO_EACH - 1) / (256 * WLO_EACH))), dim3(256), 0, s, g, sm);
 }
 // Buckets of 2^shift targets: the smallest (16 at least) of which one launch of the bucket step takes all, because a workgroup of
 // the selection serves a bucket and n / 2^shift of them have to fill the chip; at 1M nodes that is 128.  More where the bucket step would
