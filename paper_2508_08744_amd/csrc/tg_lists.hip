@@ -552,61 +552,6 @@ __device__ inline bool id_in_list(u32 id, u64 list_key, int k)
 }
 
 // ---------------------------------------------------------------------------------------
-// Algorithm 1, initialisation.  Node v draws ids floor(n * u_t), t = 0,1,2,..., from the tagged
-// hash and keeps the first k that differ from v and from all earlier draws.
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64 * LISTS_WAVES) void init_kernel(TgGraph g, u64 hs_init, int64_t v0)
-{
-    extern __shared__ float smem[];
-    const int wave = threadIdx.x >> 6, lane = tg_lane();
-    const int64_t v = v0 + (int64_t)blockIdx.x * LISTS_WAVES + wave;
-    if (v >= g.n) return;
-    float* xs = smem + (size_t)wave * g.ld;
-    u32* wscr = reinterpret_cast<u32*>(smem + (size_t)LISTS_WAVES * g.ld) + wave * 128;
-    const float aux_v = join_aux(g, v);          // asked for now, needed at the end
-    stage_row(g, v, xs);
-
-    int cnt = 0;
-    for (u64 t0 = 0; cnt < g.k; t0 += 64) {
-        const u32 c = (u32)(((tg_hash_xy(hs_init, (u64)v, t0 + (u64)lane) >> 32) * (u64)g.n) >> 32);
-        bool bad = (c == (u32)v);
-        for (int q = 0; q < cnt; ++q) bad |= (c == wscr[q]);
-        for (int q = 0; q < 63; ++q) {
-            u32 cq = (u32)__builtin_amdgcn_readlane((int)c, q);
-            bad |= (q < lane && cq == c);
-        }
-        const u64 ok = __ballot(!bad);
-        const int rank = cnt + __popcll(ok & tg_lanemask_lt());
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (!bad && rank < g.k) wscr[rank] = c;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        cnt = min(g.k, cnt + __popcll(ok));
-    }
-    const int cid = lane < g.k ? (int)wscr[lane] : -1;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const float rn_v = g.metric == 2 ? g.rnorm[v] : 1.0f;
-    const float dist = wave_direct_dist<8>(g, xs, rn_v, cid, wscr);
-    u64 key = lane < g.k ? tg_key(dist, (u32)cid, 1u) : TG_EMPTY_KEY;
-    key = tg_wave_sort(key);
-    if (lane < g.k) {
-        g.gid[v * g.k + lane] = tg_key_id(key) | 0x80000000u;
-        g.gdist[v * g.k + lane] = tg_key_dist(key);
-        if (lane == g.k - 1) g.kth[v] = join_word(aux_v, key);
-    }
-}
-void tg_launch_init(const TgGraph& g, uint64_t hs_init, hipStream_t s)
-{
-    size_t shm = (size_t)LISTS_WAVES * g.ld * sizeof(float) + LISTS_WAVES * 128 * sizeof(u32);
-    tg_for_node_chunks(g.n, [&](int64_t v0, int64_t cnt) {
-        hipLaunchKernelGGL(init_kernel, dim3((unsigned)((cnt + LISTS_WAVES - 1) / LISTS_WAVES)), dim3(64 * LISTS_WAVES), shm, s, g,
-                           hs_init, v0);
-    });
-}
-
-// ---------------------------------------------------------------------------------------
 // A set of node ids in LDS (open addressing, linear probing, `mask` + 1 words, always more
 // words than ids, so every probe sequence ends at a free word).  Inserts `id` for the lanes
 // with `active` and tells each whether the id was there already; of several lanes that bring
@@ -626,6 +571,117 @@ __device__ inline bool lds_set_insert(u32* tab, u32 mask, int shift, u32 id, boo
         }
     }
     return present;
+}
+
+// Squared distances of node v to one candidate per lane (lanes < k; ids in wscr) where X holds bytes: whole numbers from the 8-bit codes,
+// 128 bytes a row.  Eight lanes share a row, eight rows at a time, all of them on their way together.
+__device__ inline float wave_codes_dist(const TgGraph& g, int64_t v, int k, const u32* wscr)
+{
+    const int lane = tg_lane(), sub = lane & 7, c8 = lane >> 3;
+    const bool real = 16 * sub < g.ldq;
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+    const uint4 a = real ? *reinterpret_cast<const uint4*>(g.Xq + v * (int64_t)g.ldq + 16 * sub) : zero;
+    uint4 b[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int p = 8 * q + c8;
+        b[q] = zero;
+        if (8 * q < k) b[q] = *reinterpret_cast<const uint4*>(g.Xq + (int64_t)wscr[p < k ? p : 0] * g.ldq + (real ? 16 * sub : 0));
+    }
+    u32 mine = 0u;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if (!real) b[q] = zero;
+        const u32 wa[4] = {a.x, a.y, a.z, a.w}, wb[4] = {b[q].x, b[q].y, b[q].z, b[q].w};
+        u32 xy = 0u, ss = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            xy = __builtin_amdgcn_udot4(wa[i], wb[i], xy, false);
+            ss = __builtin_amdgcn_udot4(wb[i], wb[i], ss, false);
+            ss = __builtin_amdgcn_udot4(wa[i], wa[i], ss, false);
+        }
+        u32 t = ss - 2u * xy;                  // this lane's columns: sum (x - y)^2
+        t += dpp_u32<0xB1>(t);
+        t += dpp_u32<0x4E>(t);
+        t += dpp_u32<0x141>(t);
+        mine = sub == q ? t : mine;            // lane (c8, sub) has candidate 8 sub + c8
+    }
+    return (float)(u32)__shfl((int)mine, 8 * (lane & 7) + (lane >> 3));
+}
+
+// ---------------------------------------------------------------------------------------
+// Algorithm 1, initialisation.  Node v draws ids floor(n * u_t), t = 0,1,2,..., from the tagged
+// hash and keeps the first k that differ from v and from all earlier draws.
+// ---------------------------------------------------------------------------------------
+#define INIT_SET_WORDS 128
+template <bool CODES>
+__device__ __forceinline__ void init_body(const TgGraph& g, u64 hs_init, int64_t v0)
+{
+    if (g.bytes && tg_whole_bytes(g.bytes, g.d) != CODES) return;
+    extern __shared__ float smem[];
+    const int wave = threadIdx.x >> 6, lane = tg_lane();
+    const int64_t v = v0 + (int64_t)blockIdx.x * LISTS_WAVES + wave;
+    if (v >= g.n) return;
+    float* xs = smem + (size_t)wave * g.ld;
+    u32* wscr = reinterpret_cast<u32*>(smem + (size_t)LISTS_WAVES * g.ld) + wave * 128;
+    __shared__ u32 seen_s[LISTS_WAVES][INIT_SET_WORDS];
+    u32* seen = seen_s[wave];
+    const float aux_v = join_aux(g, v);          // asked for now, needed at the end
+    if (!CODES) stage_row(g, v, xs);
+
+    int cnt = 0;
+    for (u64 t0 = 0; cnt < g.k; t0 += 64) {
+        const u32 c = (u32)(((tg_hash_xy(hs_init, (u64)v, t0 + (u64)lane) >> 32) * (u64)g.n) >> 32);
+        bool bad = (c == (u32)v), repeats = true;
+        if (cnt == 0) {
+            // whether any id was drawn twice at all (rarely): an id set says so for far fewer instructions than the comparisons below
+            for (int i = lane; i < INIT_SET_WORDS; i += 64) seen[i] = TG_SET_FREE;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            repeats = __ballot(lds_set_insert(seen, INIT_SET_WORDS - 1, 33 - __ffs(INIT_SET_WORDS), c, true)) != 0ull;
+        }
+        if (repeats) {
+            for (int q = 0; q < cnt; ++q) bad |= (c == wscr[q]);
+            for (int q = 0; q < 63; ++q) {
+                u32 cq = (u32)__builtin_amdgcn_readlane((int)c, q);
+                bad |= (q < lane && cq == c);
+            }
+        }
+        const u64 ok = __ballot(!bad);
+        const int rank = cnt + __popcll(ok & tg_lanemask_lt());
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (!bad && rank < g.k) wscr[rank] = c;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        cnt = min(g.k, cnt + __popcll(ok));
+    }
+    const int cid = lane < g.k ? (int)wscr[lane] : -1;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const float rn_v = g.metric == 2 ? g.rnorm[v] : 1.0f;
+    const float dist = CODES ? wave_codes_dist(g, v, g.k, wscr) : wave_direct_dist<8>(g, xs, rn_v, cid, wscr);
+    u64 key = lane < g.k ? tg_key(dist, (u32)cid, 1u) : TG_EMPTY_KEY;
+    key = tg_wave_sort_first(key, g.k);
+    if (lane < g.k) {
+        g.gid[v * g.k + lane] = tg_key_id(key) | 0x80000000u;
+        g.gdist[v * g.k + lane] = tg_key_dist(key);
+        if (lane == g.k - 1) g.kth[v] = join_word(aux_v, key);
+    }
+}
+__global__ __launch_bounds__(64 * LISTS_WAVES) void init_kernel(TgGraph g, u64 hs_init, int64_t v0) { init_body<false>(g, hs_init, v0); }
+// Where X holds bytes the distances are whole numbers, and the 8-bit codes give them: a quarter of the bytes and of the registers (1M x 128,
+// k = 32: 2.45 -> 0.98 ms and 0.06 for the one that ends at once; in one kernel with the above, at four waves per SIMD, 1.35).
+__global__ __launch_bounds__(64 * LISTS_WAVES) __attribute__((amdgpu_waves_per_eu(8)))
+void init_codes_kernel(TgGraph g, u64 hs_init, int64_t v0) { init_body<true>(g, hs_init, v0); }
+void tg_launch_init(const TgGraph& g, uint64_t hs_init, hipStream_t s)
+{
+    size_t shm = (size_t)LISTS_WAVES * g.ld * sizeof(float) + LISTS_WAVES * 128 * sizeof(u32);
+    tg_for_node_chunks(g.n, [&](int64_t v0, int64_t cnt) {
+        const dim3 grid((unsigned)((cnt + LISTS_WAVES - 1) / LISTS_WAVES)), block(64 * LISTS_WAVES);
+        hipLaunchKernelGGL(init_kernel, grid, block, shm, s, g, hs_init, v0);
+        if (g.bytes) hipLaunchKernelGGL(init_codes_kernel, grid, block, shm, s, g, hs_init, v0);
+    });
 }
 
 // ---------------------------------------------------------------------------------------
