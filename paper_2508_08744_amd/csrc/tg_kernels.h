@@ -14,7 +14,8 @@
 // of lanes) of its own are therefore launched once per chunk of TG_LAUNCH_NODES nodes and told
 // where their chunk begins; the chunk size is a multiple of every such group size.
 #define TG_LAUNCH_NODES (1ll << 24)
-#define TG_REV_BUCKETS 8192      // buckets of reverse edges one launch counts in LDS
+#define TG_REV_BUCKETS 20480     // buckets of reverse edges one launch counts in LDS (80 KB: two workgroups of 1024 threads per CU)
+#define TG_REV_FINE 8192         // as many as buckets of up to 128 targets are made
 #define TG_REV_MAX_SHIFT 11      // a bucket holds at most 2048 targets
 #define TG_REV_MAX_W (1 << TG_REV_MAX_SHIFT)
 template <class F>

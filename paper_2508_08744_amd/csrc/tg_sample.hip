@@ -43,7 +43,7 @@ template <bool FILL>
 __global__ __launch_bounds__(REV_BUCKET_THREADS) void rev_bucket_kernel(TgGraph g, int S, int kp, int bshift, int64_t b0, int nb, int64_t chunk,
                                                          u32* bcnt, const u64* __restrict__ boff, u64* __restrict__ ebuf)
 {
-    __shared__ u32 hist[TG_REV_BUCKETS];
+    extern __shared__ u32 hist[];            // nb words
     for (int i = threadIdx.x; i < nb; i += REV_BUCKET_THREADS) hist[i] = 0u;
     __syncthreads();
     const int64_t vbeg = (int64_t)blockIdx.x * chunk, vend = vbeg + chunk < g.n ? vbeg + chunk : g.n;
@@ -423,14 +423,18 @@ void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hi
     if (chunk > (g.n + 255) / 256) chunk = (g.n + 255) / 256;
     chunk = (chunk + per_step - 1) / per_step * per_step;
     const unsigned grid = (unsigned)((g.n + chunk - 1) / chunk);
+    // (LDS beyond 64 KB per workgroup has to be asked for)
+    static const bool once = (hipFuncSetAttribute(reinterpret_cast<const void*>(rev_bucket_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, TG_REV_BUCKETS * sizeof(u32)),
+                              hipFuncSetAttribute(reinterpret_cast<const void*>(rev_bucket_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, TG_REV_BUCKETS * sizeof(u32)), true);
+    (void)once;
     for (int pass = 0; pass < 2; ++pass) {
         for (int64_t b0 = 0; b0 < sm.nbuckets; b0 += TG_REV_BUCKETS) {
             const int nb = (int)(sm.nbuckets - b0 < TG_REV_BUCKETS ? sm.nbuckets - b0 : TG_REV_BUCKETS);
             if (pass == 0)
-                hipLaunchKernelGGL(rev_bucket_kernel<false>, dim3(grid), dim3(REV_BUCKET_THREADS), 0, s, g, sm.S, kp, sm.bshift, b0, nb, chunk, sm.bcnt,
+                hipLaunchKernelGGL(rev_bucket_kernel<false>, dim3(grid), dim3(REV_BUCKET_THREADS), nb * sizeof(u32), s, g, sm.S, kp, sm.bshift, b0, nb, chunk, sm.bcnt,
                                    (const u64*)sm.boff, sm.ebuf);
             else
-                hipLaunchKernelGGL(rev_bucket_kernel<true>, dim3(grid), dim3(REV_BUCKET_THREADS), 0, s, g, sm.S, kp, sm.bshift, b0, nb, chunk, sm.bcnt,
+                hipLaunchKernelGGL(rev_bucket_kernel<true>, dim3(grid), dim3(REV_BUCKET_THREADS), nb * sizeof(u32), s, g, sm.S, kp, sm.bshift, b0, nb, chunk, sm.bcnt,
                                    (const u64*)sm.boff, sm.ebuf);
         }
         if (pass == 0) tg_launch_scan(sm.bcnt, sm.nbuckets, sm.boff, sm.wl_cnt, s);
@@ -446,7 +450,7 @@ void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hi
 int tg_rev_bucket_shift(int64_t n)
 {
     int sh = 4;
-    while (sh < 7 && ((n + (1ll << sh) - 1) >> sh) > TG_REV_BUCKETS) ++sh;
-    while (sh < TG_REV_MAX_SHIFT && ((n + (1ll << sh) - 1) >> sh) > 4 * TG_REV_BUCKETS) ++sh;
+    while (sh < 7 && ((n + (1ll << sh) - 1) >> sh) > TG_REV_FINE) ++sh;
+    while (sh < TG_REV_MAX_SHIFT && ((n + (1ll << sh) - 1) >> sh) > TG_REV_BUCKETS) ++sh;
     return sh;
 }
