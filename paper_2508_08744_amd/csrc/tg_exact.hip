@@ -2,7 +2,7 @@
 // rows with the smallest (distance, id), distances computed directly from the vectors in fp32.
 //
 // Measuring every pair that way is bound by the vector units (245 ms for 10 000 queries against 1M x 128, k = 32:
-// 10.5 TFLOP/s; this search takes 9.3 ms).  Here the matrix cores bound every pair from both sides first, and only pairs that may be
+// 10.5 TFLOP/s; this search takes 7.0 ms).  Here the matrix cores bound every pair from both sides first, and only pairs that may be
 // among the k nearest are measured directly:
 //   w(q, r) = |r|^2 / 2 - <q, r>  (squared L2; -<q, r> for the inner product, the same on unit vectors for the
 //   cosine) orders the rows for query q.  A tile of w is formed on the matrix cores, either from the rows
@@ -405,7 +405,7 @@ __device__ inline u32 ex_row(const ExScanArgs& a, u32 j)
 
 // ---------------------------------------------------------------------------------------
 // The scan.  A workgroup takes QT queries against a slice of the visited rows, 128 rows per tile, 128 bytes of
-// every row per step.  Four waves: QT = 128: each 64 queries x 64 rows; QT = 64: each 64 queries x 32 rows.  Rows
+// every row per step.  Eight waves: QT = 128: each 64 queries x 32 rows; QT = 64: each 64 queries x 16 rows.  Rows
 // and queries are staged in LDS, a row's eight 16-byte pieces permuted by (row mod 8) so that neither the
 // stores nor the operand reads meet in a bank; while a step is multiplied, the next one's rows travel.
 // Queries that fit (RES: at most 256 bytes each) stay in LDS for the whole slice, longer ones come again with
@@ -413,25 +413,30 @@ __device__ inline u32 ex_row(const ExScanArgs& a, u32 j)
 // is a register, and -|r|^2 / 2 is where the accumulator starts, so a tile costs three maxima, one compare and a
 // ballot unless something passes.  MODE: all rows (EX_FULL), a sample (EX_SAMPLE), or the first sample, of which everything
 // is kept (EX_FIRST: place = number of the visit).
-// 1M x 128 against 10 000 queries, fp16: 7.15 ms (358 TFLOP/s), waiting for rows: a step is 32 matrix instructions per wave and
-// the rows of the next one have only that long to arrive.  fp32: 1.0 ms for 256 queries (64 TFLOP/s).
+// What bounds it is the vector work of a tile (bounds, maxima, the pairs that pass; about as long as its matrix instructions twice over) and
+// waits for rows, which sixteen waves on a CU cover better than eight with twice the tile each: 1M x 128 against 10 000 queries, fp16: 7.15 -> 5.0 ms
+// (512 TFLOP/s), the whole search 9.3 -> 7.1; 50 000 x 96 against 64 (fp32): 66 -> 62 us.
 // ---------------------------------------------------------------------------------------
+#define EX_WAVES 8
 template <bool F16, int QT, bool RES, int MODE>
-__global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
+__global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
 {
+    constexpr int WAVES = EX_WAVES, THREADS = 64 * WAVES;
     constexpr bool ALL = MODE == EX_FIRST;
     constexpr bool SAMPLE = MODE != EX_FULL;
     extern __shared__ __align__(16) unsigned char ex_lds[];
     __shared__ __align__(16) float s_c0[2][EX_RT], s_c1[2][EX_RT];      // -|r|^2 / 2 (or 0; -inf past the end) and, fp32 cosine, 1 / |r|
     __shared__ float s_E[2][EX_RT / 16], s_R[2][EX_RT / 16];            // largest residual and norm of every 16 rows
-    __shared__ u64 s_queue[ALL ? 1 : 4][EX_QUEUE];                      // pairs on their way to the lists: ordered w << 32 | row of X ...
-    __shared__ u32 s_qof[ALL ? 1 : 4][EX_QUEUE];                        // ... and the query within the tile
+    __shared__ u64 s_queue[ALL ? 1 : WAVES][EX_QUEUE];                      // pairs on their way to the lists: ordered w << 32 | row of X ...
+    __shared__ u32 s_qof[ALL ? 1 : WAVES][EX_QUEUE];                        // ... and the query within the tile
     __shared__ u32 s_full[QT];                                          // the query's list is full: it is measured another way
-    constexpr int WI = QT == 128 ? 4 : 2;                               // 16-row tiles per wave
-    constexpr int AP = QT / 32;                                         // 16-byte pieces of a query step per thread
+    constexpr int WQ = QT / 64;                                         // waves side by side over the queries
+    constexpr int WI = EX_RT / 16 / (WAVES / WQ);                       // 16-row tiles per wave
+    constexpr int RP = THREADS / 8;                                     // rows whose step the threads fetch at once, a 16-byte piece each
+    constexpr int BP = EX_RT / RP, AP = QT / RP;                        // pieces of a step of the rows and of the queries per thread
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int r16 = lane & 15, q4 = lane >> 4;
-    const int wq = QT == 128 ? (wave & 1) : 0, wr = QT == 128 ? (wave >> 1) : wave;
+    const int wq = wave % WQ, wr = wave / WQ;
     const int qb = (int)(blockIdx.x % (unsigned)a.nqb);
     const int slice = (int)(blockIdx.x / (unsigned)a.nqb);
     const int tiles = (int)((a.nvisit + EX_RT - 1) / EX_RT);
@@ -458,15 +463,15 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
         if (q >= a.nq || qself[j] < 0) ntau[j] = __builtin_inff();      // no query: nothing passes
     }
 
-    floatx4 preB[4], preA[AP];
+    floatx4 preB[BP], preA[AP];
     float pre_rn = 0.0f, pre_er = 0.0f, pre_c1 = 1.0f;
-    const unsigned char* rp[4];
+    const unsigned char* rp[BP];
     const int nvisit = (int)a.nvisit;
     const int piece = tid & 7, prow = tid >> 3;
     auto fetch = [&](int t, int ch) __attribute__((always_inline)) {
         if (ch == 0) {
 #pragma unroll
-            for (int it = 0; it < 4; ++it) rp[it] = a.rows + (int64_t)ex_row<SAMPLE>(a, (u32)min(t * EX_RT + prow + 32 * it, nvisit - 1)) * a.rowbytes;
+            for (int it = 0; it < BP; ++it) rp[it] = a.rows + (int64_t)ex_row<SAMPLE>(a, (u32)min(t * EX_RT + prow + RP * it, nvisit - 1)) * a.rowbytes;
             if (tid < EX_RT) {
                 const u32 r = ex_row<SAMPLE>(a, (u32)min(t * EX_RT + tid, nvisit - 1));
                 pre_rn = a.rn[r];
@@ -477,22 +482,22 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
         const int off = ch * EX_CHUNK + piece * 16;
         const int offc = off < a.rowbytes ? off : 0;                    // beyond the row: any of its own values (the query is zero there)
 #pragma unroll
-        for (int it = 0; it < 4; ++it) preB[it] = *reinterpret_cast<const floatx4*>(rp[it] + offc);
+        for (int it = 0; it < BP; ++it) preB[it] = *reinterpret_cast<const floatx4*>(rp[it] + offc);
         if (!RES) {
 #pragma unroll
-            for (int it = 0; it < AP; ++it) preA[it] = *reinterpret_cast<const floatx4*>(qbase + (int64_t)(prow + 32 * it) * a.qbytes + off);
+            for (int it = 0; it < AP; ++it) preA[it] = *reinterpret_cast<const floatx4*>(qbase + (int64_t)(prow + RP * it) * a.qbytes + off);
         }
     };
     auto store = [&](int t, int ch, int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int row = prow + 32 * it;
+        for (int it = 0; it < BP; ++it) {
+            const int row = prow + RP * it;
             *reinterpret_cast<floatx4*>(lB + (size_t)buf * EX_RT * EX_CHUNK + row * EX_CHUNK + ((piece ^ (row & 7)) << 4)) = preB[it];
         }
         if (!RES) {
 #pragma unroll
             for (int it = 0; it < AP; ++it) {
-                const int row = prow + 32 * it;
+                const int row = prow + RP * it;
                 *reinterpret_cast<floatx4*>(lA + (size_t)buf * QT * EX_CHUNK + row * EX_CHUNK + ((piece ^ (row & 7)) << 4)) = preA[it];
             }
         }
@@ -518,14 +523,14 @@ __global__ __launch_bounds__(256, 2) void ex_scan_kernel(ExScanArgs a)
     };
 
     if (RES) {
-        for (int e = tid; e < QT * nch * 8; e += 256) {
+        for (int e = tid; e < QT * nch * 8; e += THREADS) {
             const int c = e & 7, row = (e >> 3) % QT, ch = (e >> 3) / QT;
             *reinterpret_cast<float4*>(lA + ((size_t)ch * QT + row) * EX_CHUNK + ((c ^ (row & 7)) << 4)) =
                 *reinterpret_cast<const float4*>(qbase + (int64_t)row * a.qbytes + ch * EX_CHUNK + c * 16);
         }
     }
     if (!ALL) {
-        for (int i = tid; i < QT; i += 256) s_full[i] = 0u;             // (seen by everyone behind the first barrier of the loop)
+        for (int i = tid; i < QT; i += THREADS) s_full[i] = 0u;             // (seen by everyone behind the first barrier of the loop)
     }
     // Pairs that pass wait in a queue of the wave's own and go to the lists up to 64 at a time: their places come from
     // one atomic per pair, and a wave that waited for those pair by pair did little else (the scan of 1M x 128 for 10 000
@@ -889,7 +894,7 @@ static void ex_launch_scan_t(const ExScanArgs& a, hipStream_t s)
     static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(ex_scan_kernel<F16, QT, RES, MODE>),
                                                   hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024), true);
     (void)once;
-    hipLaunchKernelGGL((ex_scan_kernel<F16, QT, RES, MODE>), dim3((unsigned)(a.nqb * a.nslices)), dim3(256), shm, s, a);
+    hipLaunchKernelGGL((ex_scan_kernel<F16, QT, RES, MODE>), dim3((unsigned)(a.nqb * a.nslices)), dim3(64 * EX_WAVES), shm, s, a);
 }
 template <bool F16, int MODE>
 static void ex_launch_scan_m(ExScanArgs a, hipStream_t s)
