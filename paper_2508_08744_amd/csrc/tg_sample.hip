@@ -298,7 +298,7 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
                 const u32 v = e & TG_ID_MASK;
                 key = (tg_hash_xy(hs_rev, (u64)v, (u64)u) & 0xFFFFFFFF00000000ull) | (u64)e;
             }
-            key = tg_wave_sort(key);
+            key = tg_wave_sort_first(key, (int)(aend - base < 64 ? aend - base : 64));
             const bool is_old = key != TG_EMPTY_KEY && (((u32)key) >> 31);
             const bool is_new = key != TG_EMPTY_KEY && !(((u32)key) >> 31);
             const u64 mn = __ballot(is_new), mo = __ballot(is_old);

@@ -1,0 +1,41 @@
+"""The prunings' products of rows split into two fp16 numbers per value, where splitting can go wrong: low parts that count in full,
+candidates far larger or smaller than the node (which take the fp32 products), a node at the origin, columns that end within a step.
+Whole numbers with squared norms of at most 2^23: bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2508_08744_amd import knn
+
+pytestmark = pytest.mark.gpu
+
+
+def _points(kind, n, d, rng):
+    if kind == "low parts":                    # beyond 2048 a value needs its low part
+        most = int(np.sqrt(2 ** 23 / d))
+        return rng.integers(most - most // 4, most + 1, (n, d)) * rng.choice([-1, 1], (n, d))
+    if kind == "scales":                       # values of 0..3 next to multiples of 512 (beyond fp16 on the small nodes' scale), and zeros
+        X = rng.integers(0, 4, (n, d))
+        X[::3] *= int(np.sqrt(2 ** 23 / d)) // 3
+        X[5::50] = 0
+        return X
+    return rng.integers(0, 40, (n, d))
+
+
+@pytest.mark.parametrize("kind,n,d,k,hops", [
+    ("low parts", 900, 1, 20, 1), ("low parts", 900, 1, 40, 1), ("low parts", 600, 1, 12, 2), ("low parts", 700, 1, 64, 1),
+    ("scales", 900, 4, 20, 1), ("scales", 900, 36, 40, 1), ("scales", 500, 3, 10, 2), ("scales", 600, 40, 64, 1),
+    ("steps", 700, 31, 32, 1), ("steps", 700, 32, 33, 1), ("steps", 700, 36, 16, 1), ("steps", 700, 68, 48, 1), ("steps", 700, 100, 49, 1),
+    ("steps", 400, 132, 8, 2)])
+def test_split_products(kind, n, d, k, hops):
+    rng = np.random.default_rng(n + d + k)
+    X = _points(kind, n, d, rng).astype(np.float32)
+    assert (X.astype(np.float64) ** 2).sum(1).max() <= 2 ** 23
+    ids = np.stack([rng.choice(n, k, replace=False) for _ in range(n)]).astype(np.int32)      # (neighbours of every scale)
+    Xg, ig = torch.from_numpy(X).cuda(), torch.from_numpy(ids).cuda()
+    d_out = max(1, k // 2)
+    for got, want in ((knn.prune_dist(Xg, ig, d_out, alpha=1.2, hops=hops), oracle.filter_dist(X, ids, hops, 64, 1.2, d_out)[0]),
+                      (knn.prune_angle(Xg, ig, d_out, gamma_deg=60.0, hops=hops), oracle.filter_angle(X, ids, hops, 64, 60.0, d_out)[0]),
+                      (knn.prune_dispersion(Xg, ig, d_out, hops=hops), oracle.filter_dpg(X, ids, hops, 64, d_out)[0])):
+        assert (got.cpu().numpy() == want).all()
