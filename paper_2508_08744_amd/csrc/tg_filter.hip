@@ -235,7 +235,7 @@ __device__ inline u32 filter_wave_max(u32 x)
 #define FILTER_RULE_DIST 0
 #define FILTER_RULE_ANGLE 1
 #define FILTER_RULE_DISPERSION 2
-// Whether the candidates' products are formed from split rows.  Not under the threshold rules within two hops: those instances have no registers
+// Whether the candidates' products can be formed from split rows.  Not under the threshold rules within two hops: those instances have no registers
 // for it at three waves per SIMD (250 000 x 128, k = 32: 8.41 -> 8.49 ms) and spend an eighth of their time on products.
 __host__ __device__ constexpr bool filter_split(int collect, int rule) { return collect == FILTER_ONE_HOP || rule == FILTER_RULE_DISPERSION; }
 // The neighbours under a threshold rule: 2.75 KB of LDS a wave are enough for arrays of their own, registers (three or four waves per
@@ -277,14 +277,13 @@ __host__ __device__ constexpr int filter_least_waves(int ng, int collect, int ru
     return rule == FILTER_RULE_DISPERSION ? 4 : 1;
 }
 
-template <int NG, int KS, bool FULL, bool VEC, int COLLECT, int RULE>
+template <int NG, int KS, bool FULL, bool VEC, int COLLECT, int RULE, bool SPLIT>
 __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) void filter_dist_kernel(FilterArgs A)
 {
     constexpr bool TWO_HOPS = COLLECT != FILTER_ONE_HOP;
     constexpr int PLACES = filter_set_places(COLLECT);
     constexpr int LOADS = filter_loads(VEC);
     constexpr bool ANGLE = RULE == FILTER_RULE_ANGLE;
-    constexpr bool SPLIT = filter_split(COLLECT, RULE);
     constexpr bool APART = filter_apart(COLLECT, RULE);
     constexpr bool ID_SET = filter_set_of_ids(COLLECT, RULE);
     constexpr int LDS_WORDS = filter_lds_words(NG, COLLECT, RULE);
@@ -311,9 +310,13 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
 
     for (int64_t p = (int64_t)blockIdx.x * FILTER_WAVES + wave; p < A.n; p += (int64_t)gridDim.x * FILTER_WAVES) {
         const float* xp = A.X + p * A.d;
-        u32 x_most = 0u;                       // bits of the lane's largest value of p (they order what is not negative; no number is the largest)
-        if (SPLIT)
-            for (int c = lane; c < A.d; c += 64) x_most = max(x_most, __float_as_uint(xp[c]) & 0x7FFFFFFFu);
+        u32 x_most = 0u, x_own[4] = {0u, 0u, 0u, 0u};      // bits of p's values, of which the largest sets the scale: asked for now, looked at behind the collection
+        if (SPLIT) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (lane + 64 * i < A.d) x_own[i] = __float_as_uint(xp[lane + 64 * i]);
+            for (int c = lane + 256; c < A.d; c += 64) x_most = max(x_most, __float_as_uint(xp[c]) & 0x7FFFFFFFu);
+        }
         int m = 0;
         // ---- Collect ----
         const int32_t u = lane < k ? A.ids[p * k + lane] : -1;
@@ -415,7 +418,11 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
         // fp32 matrix instructions and vector instructions took turns before (42 % and 56 % of the time at 200 000 x 200, k = 40,
         // dispersion rule): 1.84 -> 1.43 ms; 500 000 x 300, k = 64, distance rule 8.40 -> 7.04; 100 000 x 128, k = 32 273 -> 260 us.
         float us2 = 0.0f;                      // undoes the squared scale
-        if (SPLIT) x_most = filter_wave_max(x_most);
+        if (SPLIT) {                           // (bits order what is not negative; no number is the largest)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x_most = max(x_most, x_own[i] & 0x7FFFFFFFu);
+            x_most = filter_wave_max(x_most);
+        }
         if (SPLIT && x_most > 0u && x_most < 0x7F800000u) {
             const int e = min(max((int)(x_most >> 23) - 127, -50), 100);
             const float scale = tg_pow2(9 - e - 1);
@@ -478,6 +485,7 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
                         if (j >= groups) break;
 #pragma unroll
                         for (int s = 0; s < KS; ++s) {
+                            if (!FULL && c * 16 * KS + 16 * s >= A.d) break;
                             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].x, X[j][s].x, acc[i][j], 0, 0, 0);
                             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].y, X[j][s].y, acc[i][j], 0, 0, 0);
                             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].z, X[j][s].z, acc[i][j], 0, 0, 0);
@@ -656,9 +664,20 @@ static void launch_filter(const FilterArgs& A, bool vec, hipStream_t s)
     // four (three) waves per SIMD cover each other's loads
     constexpr int KS = NG > 2 ? 2 : 4;
     const bool full = vec && (A.d % (16 * KS) == 0);         // no column guards needed
-    if (full) filter_launch(filter_dist_kernel<NG, KS, true, true, COLLECT, RULE>, A, shm, s);
-    else if (vec) filter_launch(filter_dist_kernel<NG, KS, false, true, COLLECT, RULE>, A, shm, s);
-    else filter_launch(filter_dist_kernel<NG, KS, false, false, COLLECT, RULE>, A, shm, s);
+    constexpr bool CAN = filter_split(COLLECT, RULE);
+    // Short rows are multiplied in fp32 (steps beyond the row left out): the split takes registers, a wave per SIMD under the threshold rules,
+    // and is worth them from the second chunk of columns on (distance and angle rule, split / fp32: 13 000 x 64, k = 16 21.9 / 17.6 us, 40 000 x 33, k = 12
+    // 69.9 / 53.4, 300 000 x 64, k = 24 464 / 484, 6000 x 100, k = 24 19.3 / 25.3, 100 000 x 101, k = 32 451 / 543), under the dispersion rule, which has four
+    // waves either way, a little earlier (6000 x 50, k = 64 66.0 / 71.5; 10 000 x 33, k = 32 37.1 / 35.8).
+    if (CAN && A.d >= (RULE == FILTER_RULE_DISPERSION ? 48 : 65)) {
+        if (full) filter_launch(filter_dist_kernel<NG, KS, true, true, COLLECT, RULE, CAN>, A, shm, s);
+        else if (vec) filter_launch(filter_dist_kernel<NG, KS, false, true, COLLECT, RULE, CAN>, A, shm, s);
+        else filter_launch(filter_dist_kernel<NG, KS, false, false, COLLECT, RULE, CAN>, A, shm, s);
+    } else {
+        if (full) filter_launch(filter_dist_kernel<NG, KS, true, true, COLLECT, RULE, false>, A, shm, s);
+        else if (vec) filter_launch(filter_dist_kernel<NG, KS, false, true, COLLECT, RULE, false>, A, shm, s);
+        else filter_launch(filter_dist_kernel<NG, KS, false, false, COLLECT, RULE, false>, A, shm, s);
+    }
 }
 
 template <int RULE>

@@ -12,9 +12,10 @@ pytestmark = pytest.mark.gpu
 
 
 def _points(kind, n, d, rng):
-    if kind == "low parts":                    # beyond 2048 a value needs its low part
-        most = int(np.sqrt(2 ** 23 / d))
-        return rng.integers(most - most // 4, most + 1, (n, d)) * rng.choice([-1, 1], (n, d))
+    if kind == "low parts":                    # one value a row is beyond 2048: it needs its low part
+        X = rng.integers(0, 12, (n, d))
+        X[np.arange(n), rng.integers(0, min(d, 3), n)] = rng.integers(2048, 2850, n)
+        return X
     if kind == "scales":                       # values of 0..3 next to multiples of 512 (beyond fp16 on the small nodes' scale), and zeros
         X = rng.integers(0, 4, (n, d))
         X[::3] *= int(np.sqrt(2 ** 23 / d)) // 3
@@ -24,10 +25,10 @@ def _points(kind, n, d, rng):
 
 
 @pytest.mark.parametrize("kind,n,d,k,hops", [
-    ("low parts", 900, 1, 20, 1), ("low parts", 900, 1, 40, 1), ("low parts", 600, 1, 12, 2), ("low parts", 700, 1, 64, 1),
-    ("scales", 900, 4, 20, 1), ("scales", 900, 36, 40, 1), ("scales", 500, 3, 10, 2), ("scales", 600, 40, 64, 1),
-    ("steps", 700, 31, 32, 1), ("steps", 700, 32, 33, 1), ("steps", 700, 36, 16, 1), ("steps", 700, 68, 48, 1), ("steps", 700, 100, 49, 1),
-    ("steps", 400, 132, 8, 2)])
+    ("low parts", 900, 66, 20, 1), ("low parts", 900, 68, 40, 1), ("low parts", 600, 70, 12, 2), ("low parts", 700, 129, 64, 1), ("low parts", 500, 1, 9, 1),
+    ("scales", 900, 65, 20, 1), ("scales", 900, 68, 40, 1), ("scales", 500, 48, 10, 2), ("scales", 600, 100, 64, 1), ("scales", 500, 3, 12, 1),
+    ("steps", 700, 31, 32, 1), ("steps", 700, 47, 33, 1), ("steps", 700, 48, 16, 1), ("steps", 700, 64, 24, 1), ("steps", 700, 65, 48, 1), ("steps", 700, 96, 49, 1),
+    ("steps", 400, 97, 32, 1), ("steps", 400, 132, 8, 2)])
 def test_split_products(kind, n, d, k, hops):
     rng = np.random.default_rng(n + d + k)
     X = _points(kind, n, d, rng).astype(np.float32)
