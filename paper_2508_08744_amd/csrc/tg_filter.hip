@@ -424,9 +424,9 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
             x_most = filter_wave_max(x_most);
         }
         if (SPLIT && x_most > 0u && x_most < 0x7F800000u) {
-            const int e = min(max((int)(x_most >> 23) - 127, -50), 100);
-            const float scale = tg_pow2(9 - e - 1);
-            us2 = tg_pow2(2 * max(e - 8, -60));
+            const int e = min(max((int)(x_most >> 23) - 127, -50), 63);      // (squares beyond 2^126 are no numbers in fp32 either: such rows come out infinite)
+            const float scale = tg_pow2(8 - e);
+            us2 = tg_pow2(2 * (e - 8));
             for (int c = 0; c < nchunks; ++c) {
                 float4 X[NG][KS];
                 filter_load_chunk<NG, KS, FULL, VEC>(A, xp, cid, m, c * 16 * KS, X, dp);

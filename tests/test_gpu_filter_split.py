@@ -40,3 +40,14 @@ def test_split_products(kind, n, d, k, hops):
                       (knn.prune_angle(Xg, ig, d_out, gamma_deg=60.0, hops=hops), oracle.filter_angle(X, ids, hops, 64, 60.0, d_out)[0]),
                       (knn.prune_dispersion(Xg, ig, d_out, hops=hops), oracle.filter_dpg(X, ids, hops, 64, d_out)[0])):
         assert (got.cpu().numpy() == want).all()
+
+
+@pytest.mark.parametrize("power", [-55, -30, 30, 50])
+def test_a_power_of_two_changes_nothing(power):
+    rng = np.random.default_rng(9)
+    X = rng.integers(0, 40, (600, 80)).astype(np.float32)
+    ids = torch.from_numpy(np.stack([rng.choice(600, 24, replace=False) for _ in range(600)]).astype(np.int32)).cuda()
+    a, b = torch.from_numpy(X).cuda(), torch.from_numpy(X * np.float32(2.0 ** power)).cuda()
+    assert torch.equal(knn.prune_dist(a, ids, 12), knn.prune_dist(b, ids, 12))
+    assert torch.equal(knn.prune_angle(a, ids, 12), knn.prune_angle(b, ids, 12))
+    assert torch.equal(knn.prune_dispersion(a, ids, 12), knn.prune_dispersion(b, ids, 12))
