@@ -42,12 +42,15 @@ def test_split_products(kind, n, d, k, hops):
         assert (got.cpu().numpy() == want).all()
 
 
-@pytest.mark.parametrize("power", [-55, -30, 30, 50])
+@pytest.mark.parametrize("power", [-55, -35, 20, 50])
 def test_a_power_of_two_changes_nothing(power):
+    """The angle rules multiply two squared lengths (of at most 2^17 here): with 4 power + 34 outside fp32's exponents the products are no
+    longer the same numbers whatever forms the lengths, so they are asked at the two moderate powers only."""
     rng = np.random.default_rng(9)
     X = rng.integers(0, 40, (600, 80)).astype(np.float32)
     ids = torch.from_numpy(np.stack([rng.choice(600, 24, replace=False) for _ in range(600)]).astype(np.int32)).cuda()
     a, b = torch.from_numpy(X).cuda(), torch.from_numpy(X * np.float32(2.0 ** power)).cuda()
     assert torch.equal(knn.prune_dist(a, ids, 12), knn.prune_dist(b, ids, 12))
-    assert torch.equal(knn.prune_angle(a, ids, 12), knn.prune_angle(b, ids, 12))
-    assert torch.equal(knn.prune_dispersion(a, ids, 12), knn.prune_dispersion(b, ids, 12))
+    if -40 < power < 24:
+        assert torch.equal(knn.prune_angle(a, ids, 12), knn.prune_angle(b, ids, 12))
+        assert torch.equal(knn.prune_dispersion(a, ids, 12), knn.prune_dispersion(b, ids, 12))
