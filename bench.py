@@ -5,7 +5,7 @@
 One "step" is one whole build (norms, random lists, it1 phase-1 rounds, it2 phase-2 rounds,
 finalize) of the 1M x 128 fp32, k = 32 workload (synthetic stand-in for SIFT-1M) with the
 vectors already resident in HBM.  Prints ONE JSON line: points/s at recall@32 >= 0.95, the
-local join's share of the matrix and memory peaks (timed with HIP events on the launch stream), and
+local join's fraction of the fp32 MFMA peak (timed with HIP events on the launch stream), and
 the CPU oracle timed on a bounded sample of the same workload.
 """
 from __future__ import annotations
@@ -20,7 +20,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-MFMA_F16_PEAK_TFLOPS = 2500.0      # MI355X dense fp16 matrix peak
+MFMA_FP32_PEAK_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
 MFMA_I8_PEAK_TOPS = 5000.0         # and 8-bit
 HBM_PEAK_GBS = 8000.0
 
@@ -76,21 +76,21 @@ def joins_codes(X, metric, prm):
     return hi - lo <= 255.0 and 2.0 * d * max(abs(lo), abs(hi)) ** 2 <= 2.0 ** 24
 
 
-def join_figures(stats, d, codes, halves=False):
+def join_figures(stats, d, codes):
     """The phase-1 join of the builds that left these stats: multiplying kernels of one round, on average."""
     r1 = stats[0]["rounds_phase1"]
     launches = r1 * len(stats)
     ms = sum(sum(s["ms_join"][:r1]) for s in stats) / max(launches, 1)
     # algorithmic operations: 2 d per needed pair (new-new and new-old pairs of every block)
     ops = 2.0 * d * sum(sum(s["join_pairs"][:r1]) for s in stats) / max(launches, 1)
-    # a row as the join reads it: its codes, or two fp16 numbers per value (one where every value is an fp16 number; three products or one)
-    row = float((d + 15) // 16 * 16) if codes else (2.0 if halves else 4.0) * ((d + 31) // 32 * 32)
+    row = float((d + 15) // 16 * 16) if codes else 4.0 * d
     gather = row * sum(sum(s["join_vectors"][:r1]) for s in stats) / max(launches, 1)
-    peak = MFMA_I8_PEAK_TOPS if codes else MFMA_F16_PEAK_TFLOPS
+    peak = MFMA_I8_PEAK_TOPS if codes else MFMA_FP32_PEAK_TFLOPS
     rate = ops / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
     gbs = gather / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
-    # far from the rate of the matrix instructions: what the kernel moves is nearer its bound
-    out = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS}
+    out = {"bound": "mfma", "achieved": rate, "peak": peak, "unit": "TFLOP/s", "frac": rate / peak}
+    if codes:           # far from the rate of the i8 instructions: what the kernel moves is nearer its bound
+        out = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS}
     return dict(out, avg_launch_ms=ms, launches=launches, matrix_tops=rate, matrix_peak_tops=peak, gather_GBps=gbs, hbm_gather_frac=gbs / HBM_PEAK_GBS)
 
 
@@ -158,7 +158,7 @@ def main():
 
     # dominant kernel: the phase-1 local join (the kernels that multiply); duration from the HIP events the library
     # records on the launch stream around each join launch.  Byte-valued rows are joined on their 8-bit codes (a code row per
-    # vector, i8 matrix instructions; the few blocks of more than 64 members as fp16 numbers), others split into fp16 numbers.
+    # vector, i8 matrix instructions; the few blocks of more than 64 members as fp16 numbers), others in fp32.
     r1 = stats[0]["rounds_phase1"]
     codes = joins_codes(Xg, metric, prm)
     join = join_figures(stats, d, codes)
@@ -194,7 +194,7 @@ def main():
         "join_mfma_pct": 100.0 * join["matrix_tops"] / join["matrix_peak_tops"],
         "roofline": dict({"kernel": "phase-1 local join of one round, every part: " +
                                     ("join_bytes_kernel (i8 matrix instructions on the 8-bit codes), join_kernel for blocks of more than 64 members"
-                                     if codes else "join_wave_kernel<3>, <4> and join_kernel (fp16 matrix instructions on split rows)") +
+                                     if codes else "join_wave_kernel<3>, <4> and join_kernel (fp32 matrix instructions)") +
                                     "; adj_kernel, which runs before them, is timed apart",
                           "traffic": traffic, "traffic_source": traffic_source}, **join),
         "breakdown_ms": {"norms": last["ms_norms"], "init": last["ms_init"], "finalize": last["ms_finalize"],
@@ -219,8 +219,8 @@ def main():
             out["cpu_baseline"] = cpu_baseline(args.config, prm, min(args.cpu_sample, n))
         print(json.dumps(out))
         return
-    # the same points moved by a quarter: no bytes any more, so the local join multiplies split rows (join_f16 = 0; a quarter more than a byte is
-    # an fp16 number, so there are no low parts) or rounded ones (join_f16 = 1; the list update measures arrivals again).  Not part of `value`; the distances of the points, and so the truth,
+    # the same points moved by a quarter: no bytes any more, so the local join multiplies fp32 rows (join_f16 = 0) or their fp16
+    # copies (join_f16 = 1; a quarter more than a byte is an fp16 number).  Not part of `value`; the distances of the points, and so the truth,
     # are the same but for rounding
     if args.config == "C2" and n == cfg["n"]:
         Xr = Xg + 0.25
@@ -241,7 +241,7 @@ def main():
             out[name] = {"ms_per_step": ms_r, "points_per_s": n / (ms_r * 1e-3), "ms_join": sum(st_r[-1]["ms_join"][:r1]),
                          "recall_at_k": oracle.recall(ids_r[rows_g].cpu().numpy(), truth.cpu().numpy())}
             if not f16:
-                out[name]["roofline"] = join_figures(st_r, d, False, True)
+                out[name]["roofline"] = join_figures(st_r, d, False)
             del ws_r, ids_r
         del Xr
     # the next step after the hot path: rank-based pruning of the graph just built (outside `value`).

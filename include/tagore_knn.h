@@ -82,20 +82,23 @@ typedef enum { TG_METRIC_L2 = 0, TG_METRIC_IP = 1, TG_METRIC_COSINE = 2 } tg_met
  *            Where X holds whole numbers within 255 of each other, small enough that every fp32 sum is exact (see finalize), at
  *            most 128 of them a row and TG_METRIC_L2, the copy is X itself, and the local join of phase 1 takes its
  *            (exact) products from it as well: the graph is the same bit for bit
- *   join_f16 0: the local join of phase 1 forms its inner products from the vectors as given: every value as the
- *            sum of two fp16 numbers (of its row times a power of two), multiplied on the fp16 matrix instructions
- *            and accumulated in fp32.  The sums are at least as close to the exact ones as fp32 sums are, and exact
- *            where those are.  (Rows of at most 128 values: n x (d rounded up to 32) x 4 bytes of workspace, up to 48 GiB.)
- *            1: from a copy of the vectors rounded to fp16 (round to nearest even;
- *            n x (d rounded up to 32) x 2 bytes of workspace), accumulating in fp32; norms,
+ *   join_f16 1: the local join of phase 1 forms its inner products on the fp16 matrix
+ *            instructions from a copy of the vectors rounded to fp16 (round to nearest even;
+ *            n x (64, 96, 128, or d rounded up to 32) x 2 bytes of workspace), accumulating in fp32; norms,
  *            thresholds, phase 2 and the reported distances stay fp32.  Where every value is an
- *            fp16 number (byte-valued features, say) the copy is exact;
- *            elsewhere the join ranks its candidates on rounded vectors (11 significant
+ *            fp16 number (byte-valued features, say) the copy is exact (see 2 for what that
+ *            means for the graph); elsewhere the join ranks its candidates on rounded vectors (11 significant
  *            bits), and the list update measures every candidate that enters a list again in fp32
  *            from the vectors, so lists and thresholds hold exact distances.  Values
  *            beyond +-65504 have no fp16 number: such data must not use 1; the rows that hold such a
- *            value are counted in tg_knn_stats.undefined_rows.
- *            2: as 0, which by itself leaves out the second fp16 numbers where all of them are zero.  Default 0
+ *            value are counted in tg_knn_stats.undefined_rows (their lists stay well-formed and hold
+ *            exact distances, but which candidates reach them is unspecified).
+ *            2: as 1, but only if every value of X turned out to be an fp16 number when the copy
+ *            was made (a flag on the device; both variants of the join are launched and the one
+ *            whose turn it is not ends at once).  No operand is rounded then, so the join's
+ *            products are those of the fp32 join exactly; its fp32 sums are taken in another
+ *            order, so the graph is the same as with 0 bit for bit where those sums are exact
+ *            (integer-valued data below 2^24) and equally accurate elsewhere.  Default 0
  */
 typedef struct tg_knn_params {
     int32_t k;

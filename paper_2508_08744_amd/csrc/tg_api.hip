@@ -103,15 +103,14 @@ struct tg_knn_handle {
     float* xqm;          // its grid (three words, see TgGraph)
     u32* d_screen_on;    // device flags, one per phase-2 round: screening still pays (decided after each screened round for the next)
     u32* d_undefined;    // device counter: rows of X without a defined distance (written with the norms)
-    uint16_t* xh;        // split copy of X for the local join (short rows; join_f16 = 1: of any rows, high parts only), or null
+    uint16_t* xh;        // fp16 copy of X for the local join (join_f16 = 1, 2)
+    u32* d_f16_ok;       // join_f16 = 2: device flag, 1 while every value of X is an fp16 number
     int round;           // rounds run so far (both phases)
     int rounds1, rounds2;
     u32* gid_phase2;     // the second array of lists, which phase 2 alone has
     u32* order;          // see tg_launch_order
     bool phase2;
     bool norms_done;
-    bool xq_shared;      // the codes lie where the split copy was ...
-    bool split_lost;     // ... and have been written over it
     bool lists_ready;    // tg_knn_init or tg_knn_import has written the lists
     bool timed;          // record events around the steps (for the stats)
     std::vector<hipEvent_t> ev;
@@ -137,22 +136,19 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->g.gdist = c.take<float>((size_t)n * p.k);
     h->g.kth = c.take<u64>(n);
     h->g.ldq = (d + 15) & ~15;
-    h->g.narrow = p.join_f16 == 1 ? 1 : 0;
-    h->g.ldh = (d + 31) & ~31;
-    h->g.ldhr = h->g.narrow ? h->g.ldh : 2 * h->g.ldh;
-    h->xh = h->g.narrow || tg_join_wave_ok(n, ld) ? c.take<uint16_t>((size_t)n * h->g.ldhr) : nullptr;
-    h->g.Xh = h->xh;
-    // The codes and the split copy (4 bytes per value, so it is the larger one) share a place.  Where X holds bytes and phase 1 reads codes,
-    // the split copy is not written; elsewhere phase 1 reads the split copy, and the codes are written at the phase switch.
-    h->xq_shared = p.screen && h->xh && !h->g.narrow;
-    h->xq = !p.screen ? nullptr : h->xq_shared ? reinterpret_cast<uint8_t*>(h->xh) : c.take<uint8_t>((size_t)n * h->g.ldq);
+    h->xq = p.screen ? c.take<uint8_t>((size_t)n * h->g.ldq) : nullptr;
     h->xqm = c.take<float>(64);          // also where the norms leave the range of the values
     h->g.Xq = h->xq;
     h->g.Xqm = h->xqm;
-    h->g.low = h->xh ? reinterpret_cast<const uint32_t*>(h->xqm) + TG_RANGE_LOW : nullptr;
     h->g.bytes = h->xq && tg_join_bytes_possible(n, ld, p.metric) ? reinterpret_cast<const uint32_t*>(h->xqm) : nullptr;
     h->d_screen_on = c.take<u32>(TG_MAX_ROUNDS + 1);
     h->d_undefined = c.take<u32>(64);
+    // the register-resident join reads 64, 96 or 128 columns per row (4, 6 or 8 steps of 16); longer rows are whole steps of 32
+    h->g.ldh = ld <= 64 ? 64 : ld <= 96 ? 96 : ld <= 128 ? 128 : (d + 31) & ~31;
+    h->xh = p.join_f16 ? c.take<uint16_t>((size_t)n * h->g.ldh) : nullptr;
+    h->d_f16_ok = p.join_f16 == 2 ? c.take<u32>(64) : nullptr;
+    h->g.f16_ok = h->d_f16_ok;
+    h->g.Xh = h->xh;
     h->sm.S = p.S; h->sm.R = p.R;
     h->sm.bshift = tg_rev_bucket_shift(n);
     h->sm.nbuckets = (n + (1ll << h->sm.bshift) - 1) >> h->sm.bshift;
@@ -166,7 +162,7 @@ static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* 
     h->sm.bsz = c.take<u32>(n);
     h->sm.wl = c.take<u64>((size_t)3 * (n + TG_MAX_PARTS));
     h->sm.wl_cnt = c.take<u32>(TG_WL_LISTS);
-    h->sm.wave_ok = tg_join_wave_ok(n, ld) ? 1 : 0;
+    h->sm.wave_ok = tg_join_wave_ok(ld) ? 1 : 0;
     h->sm.parts = p.parts;
     h->sm.parts_shift = p.parts == 8 ? 3 : p.parts == 4 ? 2 : p.parts == 2 ? 1 : 0;
     h->sm.adj_words = h->sm.BC > 96 ? 4 : h->sm.BC > 64 ? 3 : 2;
@@ -251,7 +247,6 @@ extern "C" int tg_knn_create(tg_knn_handle** out, const float* X, int64_t n, int
     h->round = h->rounds1 = h->rounds2 = 0;
     h->phase2 = false;
     h->norms_done = false;
-    h->split_lost = false;
     h->lists_ready = false;
     h->timed = true;
     if (h->x_padded) tg_launch_pad_rows(X, n, d, h->x_padded, h->g.ld, h->stream);
@@ -264,6 +259,7 @@ extern "C" int tg_knn_create(tg_knn_handle** out, const float* X, int64_t n, int
     z.nbuckets = (size_t)h->sm.nbuckets;
     z.range = reinterpret_cast<uint32_t*>(h->xqm);
     z.undefined = h->d_undefined;
+    z.f16_ok = h->d_f16_ok;
     tg_launch_setup(z, h->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -301,11 +297,9 @@ static void ensure_norms(tg_knn_handle* h)
 {
     if (h->norms_done) return;
     int sp = begin_span(h, SPAN_NORMS, 0);
-    uint32_t* range = reinterpret_cast<uint32_t*>(h->xqm);
-    const bool on_the_way = h->xh && !h->g.narrow && !h->g.bytes;      // the split copy: written by the kernel of the norms
-    tg_launch_norms(h->g, range, h->d_undefined, on_the_way ? h->xh : nullptr, h->stream);
-    // (join_f16 = 1: a row with a value beyond +-65504 is counted)
-    if (h->xh && !on_the_way) tg_launch_split(h->g, h->xh, range, h->g.narrow ? h->d_undefined : nullptr, h->stream);
+    tg_launch_norms(h->g, reinterpret_cast<uint32_t*>(h->xqm), h->d_undefined, h->stream);
+    // rounding every row whatever its values (join_f16 = 1): a row with a value beyond +-65504 has no fp16 copy to rank on, and is counted
+    if (h->xh) tg_launch_narrow(h->g, h->xh, h->d_f16_ok, h->d_f16_ok ? nullptr : h->d_undefined, h->stream);
     if (h->g.bytes) tg_launch_quantize(h->g, h->xq, h->xqm, true, h->stream);      // bytes: the join reads the codes
     end_span(h, sp);
     h->norms_done = true;
@@ -354,10 +348,6 @@ static int phase1_round(tg_knn_handle* h, int64_t* updates)
     if (h->phase2) return fail(TG_ERR_INVALID_ARG, "phase 1 round after the switch to phase 2");
     if (h->round >= TG_MAX_ROUNDS) return fail(TG_ERR_INVALID_ARG, "more than %d rounds", TG_MAX_ROUNDS);
     const int r = h->round;
-    if (h->split_lost) {         // lists built anew on a handle that had come to phase 2
-        tg_launch_split(h->g, h->xh, reinterpret_cast<uint32_t*>(h->xqm), nullptr, h->stream);
-        h->split_lost = false;
-    }
     int sp = begin_span(h, SPAN_SAMPLE, r);
     if (r >= 3) make_order(h);           // (the lists of the first rounds are too random to say who is near whom)
     tg_launch_reverse(h->g, h->sm, tg_hash_seed(h->p.seed, TG_TAG_REV(r)), h->stream);
@@ -393,7 +383,6 @@ extern "C" int tg_knn_begin_phase2(tg_knn_handle* h)
         ensure_norms(h);
         int sp = begin_span(h, SPAN_NORMS, 0);
         tg_launch_quantize(h->g, h->xq, h->xqm, false, h->stream);      // (bytes: done together with the norms)
-        h->split_lost = h->xq_shared;
         tg_launch_phase2_probe(h->g, h->p.m, h->d_undefined + 32, h->d_screen_on + h->rounds2, h->stream);
         end_span(h, sp);
     }
@@ -548,9 +537,7 @@ extern "C" int tg_knn_join_distances(tg_knn_handle* h, const int32_t* blk, const
         }
     }
     ensure_norms(h);
-    TgGraph g = h->g;
-    if (h->split_lost) g.Xh = nullptr;           // (the workgroup kernel reads X)
-    tg_launch_join_distances(g, blk, sizes, nb, out, h->stream);
+    tg_launch_join_distances(h->g, blk, sizes, nb, out, h->stream);
     return launch_status("join distances");
 }
 
@@ -749,7 +736,7 @@ extern "C" int tg_exact_knn_static(const float* X, int64_t n, int32_t d, int32_t
     if (metric == 2) {
         g.nrm = w.take<float>(n);
         g.rnorm = w.take<float>(n);
-        tg_launch_norms(g, nullptr, nullptr, nullptr, s);  // writes every word it later reads
+        tg_launch_norms(g, nullptr, nullptr, s);           // writes every word it later reads
     }
     u64* partial = w.take<u64>((size_t)nq * slices * k);   // every word read by the merge is written by the scan
     tg_launch_exact_knn(g.X, g.ld, g.rnorm, n, k, metric, query_rows, nq, 0, nullptr, nullptr, out_ids, out_dist, partial, slices, s);

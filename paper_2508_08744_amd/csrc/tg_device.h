@@ -10,7 +10,6 @@ typedef unsigned int u32;
 
 #define TG_WAVE 64
 #define TG_RANGE_NONINT 8        // word of the range buffer: set when a value of X is not a whole number
-#define TG_RANGE_LOW 9           // word of the range buffer: set when a row of the split copy has a low part (tg_split)
 #define TG_EMPTY_KEY 0xFFFFFFFFFFFFFFFFull
 #define TG_GOLDEN 0x9E3779B97F4A7C15ull
 #define TG_ID_MASK 0x7FFFFFFFu     // list word: id in bits 0..30, "fresh" mark in bit 31
@@ -210,20 +209,8 @@ __device__ inline bool tg_whole_bytes(const u32* __restrict__ range, int d)
     return tg_whole_exact(range, d) && tg_unord(range[1]) - tg_unord(range[0]) <= 255.0f;
 }
 
-// ---- Rows for the fp16 matrix instructions of the local join.  A row is multiplied by a power of two of its own, which brings its
-// norm below 2^14, and every value is split into two fp16 numbers: the nearest one and the nearest one to what is left.  Together
-// they hold 22 bits of the value (24 where the low one has few), whatever the row's scale: nothing is lost to the exponent range before
-// values 2^-38 times the row's norm.  The scale follows from the word the join has of a node anyway: its squared norm (cosine: its inverse norm).
-__device__ inline int tg_row_exp(float aux, int metric)
-{
-    const int e = (int)((__float_as_uint(aux) >> 23) & 0xFFu) - 127;
-    const int p = metric == 2 ? -e : (e + 2) >> 1;              // norm at most 2^p
-    return min(max(p, -100), 100);
-}
 __device__ inline float tg_pow2(int e) { return __uint_as_float((u32)(e + 127) << 23); }
-__device__ inline float tg_row_scale(float aux, int metric) { return tg_pow2(14 - tg_row_exp(aux, metric)); }
-__device__ inline float tg_row_unscale(float aux, int metric) { return tg_pow2(tg_row_exp(aux, metric) - 14); }
-// four values of a row, scaled: high and low parts, two to a word
+// four values, scaled, as sums of two fp16 numbers (22 bits): high and low parts, two to a word
 __device__ inline void tg_split4(float4 x, float scale, uint2& hi, uint2& lo)
 {
     typedef _Float16 half2v __attribute__((ext_vector_type(2)));

@@ -959,7 +959,7 @@ void tg_launch_exact_screened(const float* X, int ld, int64_t n, int d, int k, i
         TgGraph g = {};
         g.n = n; g.d = d; g.ld = ld; g.k = k; g.metric = metric;
         g.X = X; g.nrm = rn; g.rnorm = rnorm;
-        tg_launch_norms(g, nullptr, nullptr, nullptr, s);
+        tg_launch_norms(g, nullptr, nullptr, s);
         a.rows = reinterpret_cast<const unsigned char*>(X);
         a.rowbytes = 4 * ld;
     }

@@ -9,7 +9,7 @@
 //      would drop it anyway, but in the join it would take the place of a useful one).
 // Either join kernel then
 //   2. gathers the block's vectors (into registers, or into LDS a slab of columns at a time);
-//   3. accumulates the Gram tile NEW x (NEW ++ OLD) with v_mfma_f32_16x16x32_f16 on split rows and turns it
+//   3. accumulates the Gram tile NEW x (NEW ++ OLD) with v_mfma_f32_16x16x4_f32 and turns it
 //      into distances |x|^2 + |y|^2 - 2<x,y>  (or -<x,y>, or 1 - cos);
 //   4. retention: every member keeps, for each group of eight consecutive block positions, the
 //      closest candidate under its threshold (the paper keeps one per node and warp sub-tile),
@@ -52,16 +52,14 @@ __device__ inline void groupmin8(u32& dist, u32& id)
     dist = m;
     id = c;
 }
-// Gram value of two scaled rows -> distance.  us undoes a row's scale (a power of two: nothing is rounded by it).  aux = squared norms
-// (L2) or what the Gram value is multiplied by: us (inner product), inverse norm times us (cosine).
+// Gram value -> distance.  aux = squared norms (L2) or inverse norms (cosine).
 template <int METRIC>
-__device__ inline float gram_to_dist(float gram, float aux_a, float aux_b, float us_a, float us_b)
+__device__ inline float gram_to_dist(float gram, float aux_a, float aux_b)
 {
-    if (METRIC == 0) return fmaxf(0.0f, fmaf(-2.0f * us_a, gram * us_b, aux_a + aux_b));
-    if (METRIC == 1) return -(gram * (aux_a * aux_b)) + 0.0f;
+    if (METRIC == 0) return fmaxf(0.0f, fmaf(-2.0f, gram, aux_a + aux_b));
+    if (METRIC == 1) return -gram + 0.0f;
     return 1.0f - gram * (aux_a * aux_b) + 0.0f;   // symmetric in the two nodes, bit for bit
 }
-__device__ inline float join_row_aux(float aux, float us, int metric) { return metric == 0 ? aux : metric == 1 ? us : aux * us; }
 // A candidate may precede the target's last list entry when its distance does not exceed that entry's.  The id of
 // that entry is not looked at: a candidate at exactly that distance with a larger id passes too, and the list update,
 // which keeps the k smallest (distance, id), drops it again; nothing that belongs in the list is held back.
@@ -261,19 +259,16 @@ __device__ inline void emit_candidate(const TgCand& cd, u32 t, u32 tmax, u32 sal
 // Workgroup kernel.  MODE 0: emit candidates for the stored blocks.  MODE 1: write the distance tile of
 // caller-given blocks.
 // SRC, where the rows come from:
-//   ROWS_F32    X.  Scaled and split into two fp16 numbers per value on the way from the registers into LDS (tg_split4; DK high
-//               parts, then DK low parts per row and slab: the bytes of the fp32 values), and a tile of 32 columns is three
-//               v_mfma_f32_16x16x32_f16: high x high, high x low, low x high (and low x low for rows of at most 32 values).
-//               What is left out is 2^-22 of a product, with either sign (measured: 0.6 of the error of fp32 sums), and the matrix
-//               pipe takes 48 cycles for the 256 of the fp32 instruction, whose datapath the vector instructions share.
-//   ROWS_HALF   the fp16 copy of the rows (g.narrow): high parts only.
+//   ROWS_F32    X, multiplied with v_mfma_f32_16x16x4_f32.
+//   ROWS_HALF   the fp16 copy of the rows: a slab holds twice the columns in the same bytes, and a step of 32 columns is one
+//               v_mfma_f32_16x16x32_f16 per tile.
 //   ROWS_CODES  the 8-bit codes, where X turned out to hold bytes: exact fp16 numbers once the codes are moved back.
 // ROWS: the most members a block may have here, 64 or 128.
 // The walk over the work list is pipelined across blocks: the ids of block w + 1 travel while block w is multiplied, and its first slab
 // while block w is evaluated and handed over.
 // LDS: header (salt, threshold, norms, ids of two blocks), the adjacency words, the cells, the tile.
 // ---------------------------------------------------------------------------------------
-#define JOIN_HDR_BYTES (6 * (TG_BLOCK_COLS + 4) * 4)
+#define JOIN_HDR_BYTES (5 * (TG_BLOCK_COLS + 4) * 4)
 #define JOIN_ADJ_BYTES (TG_BLOCK_COLS * 4 * 4)
 enum { ROWS_F32, ROWS_HALF, ROWS_CODES };
 struct JoinArgs {
@@ -299,9 +294,8 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
     constexpr int HW = TG_BLOCK_COLS + 4;                               // words per header array
     u32* s_salt = reinterpret_cast<u32*>(smem_raw);                     // slot-hash salt of each member
     u32* s_okd = s_salt + HW;                                           // threshold: ordered distance of the member's last entry
-    float* s_aux = reinterpret_cast<float*>(s_okd + HW);                // see gram_to_dist
-    float* s_us = s_aux + HW;                                           // undoes the row's scale
-    u32* s_idb = reinterpret_cast<u32*>(s_us + HW);                     // ids, of the block in hand and of the next one
+    float* s_aux = reinterpret_cast<float*>(s_okd + HW);                // squared norm (or 1/|x| for cosine)
+    u32* s_idb = reinterpret_cast<u32*>(s_aux + HW);                    // ids, of the block in hand and of the next one
     u32* s_adj = reinterpret_cast<u32*>(smem_raw + JOIN_HDR_BYTES);     // member p: four words, bit x = position x is in p's list
     u64* s_cell = reinterpret_cast<u64*>(smem_raw + JOIN_HDR_BYTES + JOIN_ADJ_BYTES);   // candidates of the block in hand
     unsigned char* tile = smem_raw + JOIN_HDR_BYTES + JOIN_ADJ_BYTES + JOIN_CELL_BYTES;
@@ -313,7 +307,6 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
     constexpr int PER = ROWS * F4 / JOIN_THREADS > 0 ? ROWS * F4 / JOIN_THREADS : 1;   // pieces per thread and slab, at most
     constexpr int TJ = ROWS / 32;                                       // column tiles per wave
     const int ldx = SRC == ROWS_F32 ? g.ld : SRC == ROWS_HALF ? g.ldh : g.ldq;   // values per stored row
-    const bool lo = SRC == ROWS_F32 && (g.ld <= 32 || !g.low || *g.low != 0u);   // the rows have low parts
     const float qlo = SRC == ROWS_CODES ? tg_unord(g.bytes[0]) : 0.0f;           // what the codes are moved by
     const unsigned char* xbase = SRC == ROWS_F32 ? reinterpret_cast<const unsigned char*>(g.X)
                                : SRC == ROWS_HALF ? reinterpret_cast<const unsigned char*>(g.Xh) : g.Xq;
@@ -359,15 +352,8 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
             const int row = (tid + JOIN_THREADS * it) / F4;
             if (row >= nT) continue;
             unsigned char* out = tile + row * LDTB;
-            if (SRC == ROWS_HALF) {
+            if (SRC != ROWS_CODES) {
                 *reinterpret_cast<uint4*>(out + piece * 16) = pre[it];
-            } else if (SRC == ROWS_F32) {
-                uint2 hi, low;
-                const float4 x = make_float4(__uint_as_float(pre[it].x), __uint_as_float(pre[it].y), __uint_as_float(pre[it].z), __uint_as_float(pre[it].w));
-                // (the reciprocal of a power of two; the member data of the block are in LDS before its first slab is)
-                tg_split4(x, __uint_as_float((254u << 23) - __float_as_uint(s_us[row])), hi, low);
-                *reinterpret_cast<uint2*>(out + piece * 8) = hi;
-                if (lo) *reinterpret_cast<uint2*>(out + 2 * DK + piece * 8) = low;
             } else {
                 const u32 word[4] = {pre[it].x, pre[it].y, pre[it].z, pre[it].w};
 #pragma unroll
@@ -400,9 +386,7 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
         const u32 id = s_ids[tid];
         const u64 kth = MODE == 0 ? g.kth[id] : 0ull;        // threshold distance and norm in one word
         const float aux = MODE == 0 ? __uint_as_float((u32)kth) : (g.metric == 2 ? g.rnorm[id] : g.nrm[id]);
-        const float us = SRC == ROWS_CODES ? 1.0f : tg_row_unscale(aux, g.metric);
-        s_us[tid] = us;
-        s_aux[tid] = join_row_aux(aux, us, g.metric);
+        s_aux[tid] = aux;
         if (MODE == 0) {
             s_okd[tid] = (u32)(kth >> 32);
             s_salt[tid] = (u32)tg_mix64(A.hs_slot + (u64)id);
@@ -449,38 +433,49 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
         commit(ks, nT);
         __syncthreads();
         if (ks + CS < ldx) issue(ks + CS, s_ids, nT);
-        // lane (r, q) reads the 8 consecutive columns 32 s + 8 q .. + 7 of its row
-        auto half8 = [&](int row0, int col, int part) {
-            return __builtin_bit_cast(halfx8, *reinterpret_cast<const float4*>(tile + (row0 * 16 + c16) * LDTB + part * 2 * DK + (col + 8 * g4) * 2));
-        };
-        const int kend = min(CS, (ldx - ks + 31) & ~31);
+        if (SRC == ROWS_F32) {
+            const int kend = min(CS, (ldx - ks + 15) & ~15);
+            // Lane (r, q) = (lane % 16, lane / 16) reads 4 consecutive columns 16*s + 4*q .. +3 of its
+            // row; step t of the four MFMAs then contracts columns {16*s + 4*q + t : q = 0..3}.  The
+            // same column permutation is applied to both operands, so the sum is the full dot product.
 #pragma unroll 1
-        for (int kk = 0; kk < kend; kk += 32) {
-            halfx8 ah[2], bh[TJ], al[2], bl[TJ];
+            for (int kk = 0; kk < kend; kk += 16) {
+                float4 av[2], bv[TJ];
 #pragma unroll
-            for (int ti = 0; ti < 2; ++ti)
-                if (wr + 2 * ti < MT) {
-                    ah[ti] = half8(wr + 2 * ti, kk, 0);
-                    if (lo) al[ti] = half8(wr + 2 * ti, kk, 1);
-                }
-#pragma unroll
-            for (int tj = 0; tj < TJ; ++tj)
-                if (wc + 2 * tj < NT) {
-                    bh[tj] = half8(wc + 2 * tj, kk, 0);
-                    if (lo) bl[tj] = half8(wc + 2 * tj, kk, 1);
-                }
-#pragma unroll
-            for (int ti = 0; ti < 2; ++ti)
+                for (int ti = 0; ti < 2; ++ti)
+                    if (wr + 2 * ti < MT) av[ti] = *reinterpret_cast<const float4*>(tile + ((wr + 2 * ti) * 16 + c16) * LDTB + (kk + 4 * g4) * 4);
 #pragma unroll
                 for (int tj = 0; tj < TJ; ++tj)
-                    if (act[ti][tj]) {
-                        if (lo) {
-                            if (g.ld <= 32) acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[ti], bl[tj], acc[ti][tj], 0, 0, 0);
-                            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[ti], bh[tj], acc[ti][tj], 0, 0, 0);
-                            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[ti], bl[tj], acc[ti][tj], 0, 0, 0);
+                    if (wc + 2 * tj < NT) bv[tj] = *reinterpret_cast<const float4*>(tile + ((wc + 2 * tj) * 16 + c16) * LDTB + (kk + 4 * g4) * 4);
+#pragma unroll
+                for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+                    for (int tj = 0; tj < TJ; ++tj)
+                        if (act[ti][tj]) {
+                            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ti].x, bv[tj].x, acc[ti][tj], 0, 0, 0);
+                            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ti].y, bv[tj].y, acc[ti][tj], 0, 0, 0);
+                            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ti].z, bv[tj].z, acc[ti][tj], 0, 0, 0);
+                            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ti].w, bv[tj].w, acc[ti][tj], 0, 0, 0);
                         }
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[ti], bh[tj], acc[ti][tj], 0, 0, 0);
-                    }
+            }
+        } else {
+            // lane (r, q) reads the 8 consecutive columns 32 s + 8 q .. + 7 of its row: one matrix instruction per step
+            const int kend = min(CS, (ldx - ks + 31) & ~31);
+#pragma unroll 1
+            for (int kk = 0; kk < kend; kk += 32) {
+                halfx8 av[2], bv[TJ];
+#pragma unroll
+                for (int ti = 0; ti < 2; ++ti)
+                    if (wr + 2 * ti < MT) av[ti] = *reinterpret_cast<const halfx8*>(tile + ((wr + 2 * ti) * 16 + c16) * LDTB + (kk + 8 * g4) * 2);
+#pragma unroll
+                for (int tj = 0; tj < TJ; ++tj)
+                    if (wc + 2 * tj < NT) bv[tj] = *reinterpret_cast<const halfx8*>(tile + ((wc + 2 * tj) * 16 + c16) * LDTB + (kk + 8 * g4) * 2);
+#pragma unroll
+                for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+                    for (int tj = 0; tj < TJ; ++tj)
+                        if (act[ti][tj]) acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[ti], bv[tj], acc[ti][tj], 0, 0, 0);
+            }
         }
     }
     // the next block's first slab starts travelling (its half of the ids was last read before the first barrier above)
@@ -496,14 +491,13 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
     for (int ti = 0; ti < 2; ++ti) {
         const int i = wr + 2 * ti;
         if (i >= MT) continue;
-        float aux_a[4], us_a[4];
+        float aux_a[4];
         u32 id_a[4], okd_a[4], adj_a[4][TJ];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int a = 16 * i + 4 * g4 + e;
             const int aa = a < nN ? a : 0;
             aux_a[e] = s_aux[aa];
-            us_a[e] = s_us[aa];
             id_a[e] = (u32)s_ids[aa];
             if (MODE == 0) {
                 okd_a[e] = a < nN ? s_okd[aa] : 0u;             // rows past the NEW part pass nothing
@@ -520,7 +514,7 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
             const int b = 16 * j + c16;
             const bool b_ok = b < nT;
             const int bb = b_ok ? b : 0;
-            const float aux_b = s_aux[bb], us_b = s_us[bb];
+            const float aux_b = s_aux[bb];
             const u32 id_b = (u32)s_ids[bb];
             u32 o[4];
 #pragma unroll
@@ -528,9 +522,9 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
                 const int a = 16 * i + 4 * g4 + e;
                 const bool ok = b_ok & (a < nN) & (b > a);
                 const float gram = acc[ti][tj][e];
-                const float dist = g.metric == 0 ? gram_to_dist<0>(gram, aux_a[e], aux_b, us_a[e], us_b)
-                                 : g.metric == 1 ? gram_to_dist<1>(gram, aux_a[e], aux_b, us_a[e], us_b)
-                                                 : gram_to_dist<2>(gram, aux_a[e], aux_b, us_a[e], us_b);
+                const float dist = g.metric == 0 ? gram_to_dist<0>(gram, aux_a[e], aux_b)
+                                 : g.metric == 1 ? gram_to_dist<1>(gram, aux_a[e], aux_b)
+                                                 : gram_to_dist<2>(gram, aux_a[e], aux_b);
                 if (MODE == 1) {
                     if (ok) A.xout[((int64_t)v * TG_BLOCK_ROWS + a) * TG_BLOCK_COLS + b] = dist;
                 }
@@ -591,36 +585,32 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
     buf ^= 1;
     }   // work-list loop
 }
-// (200 000 x 960, k = 32, blocks of at most 64 members: slabs of 64 columns with four waves per SIMD; slabs of 128 with three: a build takes 60.0 ms
-// instead of 54.5, the fp32 instruction on slabs of 128 columns: 70.8)
-template <int DK, int MODE, bool NARROW, int ROWS>
+// (200 000 x 960, k = 32, blocks of at most 64 members: slabs of 64 columns with four waves per SIMD: a build takes 54.8 ms; slabs of 128 with
+// three: 60.7; these, two of them on their way and nothing across blocks, taken by number: 70.9)
+// Bytes are joined on their codes whatever copy there is; COPY: there is an fp16 copy of the rows, which serves where it is exact or asked
+// for whatever it rounds (join_f16 = 1).
+template <int DK, int MODE, bool COPY, int ROWS>
 __global__ __launch_bounds__(JOIN_THREADS, ROWS <= 64 ? 4 : 2) void join_kernel(JoinArgs A)
 {
-    if (NARROW) join_body<DK, MODE, ROWS_HALF, ROWS>(A);
-    else if (MODE == 0 && A.g.bytes && A.g.d > 1 && tg_whole_bytes(A.g.bytes, A.g.d)) join_body<DK, MODE, ROWS_CODES, ROWS>(A);
+    if (MODE == 0 && A.g.bytes && A.g.d > 1 && tg_whole_bytes(A.g.bytes, A.g.d)) join_body<DK, MODE, ROWS_CODES, ROWS>(A);
+    else if (COPY && (!A.g.f16_ok || *A.g.f16_ok != 0u)) join_body<DK, MODE, ROWS_HALF, ROWS>(A);
     else join_body<DK, MODE, ROWS_F32, ROWS>(A);
 }
 
 
 // ---------------------------------------------------------------------------------------
 // Register-resident variant for small blocks and d <= 128: one wave per anchor, no LDS tile
-// and no barrier.  The wave keeps the whole block in VGPRs in MFMA operand layout, from the split copy of the rows (g.Xh): lane
-// (r, q) = (lane % 16, lane / 16) holds, for every 16-row group t < GMAX and step of 32 columns s < KS, the high parts of columns
-// 32 s + 8 q .. + 7 of row 16 t + r and (LO) their low parts, so that one load instruction reads 64
+// and no barrier.  The wave keeps the whole block in VGPRs in MFMA operand layout: lane
+// (r, q) = (lane % 16, lane / 16) holds, for every 16-row group t < GMAX and column step
+// s < KS, columns 16 s + 4 q .. + 3 of row 16 t + r, so that one load instruction reads 64
 // contiguous bytes of each of 16 rows (a step-major split would touch four lines per row).
-// Tile (i, j) is then 3 KS v_mfma_f32_16x16x32_f16 on registers: high x high, high x low, low x high (KS = 1: low x low, too, so that every
-// product of whole numbers below 2^22 counts in full: rows of one value can hold numbers beyond the high part's 2048 under sums that are
-// exact, longer ones cannot).  Without LO, where no row has a low part, it is KS of them on half the bytes.
-// In place of 8 KS v_mfma_f32_16x16x4_f32 of 32 cycles: a step is 48 cycles instead of 256, and the vector
-// instructions of the epilogue, which share the fp32 matrix instructions' datapath, can run beside these.  The error against 64-bit
-// sums (rms, relative to the norms) is 0.4 to 0.9 of what it was in fp32, the bytes gathered are the same.  What bounds the kernel is the
-// rows and the candidates' lines: 10M x 96, cosine: 246 -> 235 ms of joins per build (3 TB/s of rows and about as much of lines);
-// 10 000 x 32: 23.9 -> 17 us a launch.
+// Tile (i, j) is then 4 KS v_mfma_f32_16x16x4_f32 on registers X[i][s], X[j][s]: both operands
+// use the same column permutation, so the sum is the full dot product.
 //
 // Waves walk a work list of anchors whose blocks have at most GMAX row groups, and the walk
 // is software pipelined: while block w is multiplied, the ids, thresholds, norms and adjacency
 // words of block w + 1 are fetched, and as soon as tile row i of block w is finished its
-// registers are refilled with row group i of block w + 1.  MODE as in join_kernel.
+// registers X[i] are refilled with row group i of block w + 1.  MODE as in join_kernel.
 // ---------------------------------------------------------------------------------------
 struct WaveItem {
     int64_t v;
@@ -633,21 +623,26 @@ struct WaveShared {
     u32 okd[2][64];
     int ids[2][64];
     float aux[2][64];
-    float us[2][64];           // undoes the row's scale
     u32 adj[2][64][2];         // member p, bit x: position x of the block is in p's list already
     u64 cell[2][64 * JOIN_CELLS];   // candidates of one block, one cell per (member, group of positions); handed over a block later
 };
 
-template <int GMAX, int MODE, int METRIC, int KS, bool LO>
-__device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample& sm, const TgCand& cd, u64 hs_slot, u64* stat_bins,
-                                               const int32_t* xblk, const int32_t* xsizes, float* xout,
-                                               const u64* __restrict__ wl, const u32* __restrict__ wl_cnt, int64_t direct_count, int gmin)
+// NARROW: the rows come from the fp16 copy (g.Xh, rows of 32 KS values, zero padded): a register
+// then holds eight values, columns 32 s + 8 q .. + 7, and a tile step is one
+// v_mfma_f32_16x16x32_f16 (fp32 accumulation) in place of eight fp32 matrix instructions.
+template <int GMAX, int MODE, int METRIC, int KS, bool FULL, bool NARROW>
+__global__ __launch_bounds__(256) void join_wave_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins,
+                                                        const int32_t* xblk, const int32_t* xsizes, float* xout,
+                                                        const u64* __restrict__ wl, const u32* __restrict__ wl_cnt,
+                                                        int64_t direct_count, int gmin)
 {
     extern __shared__ __align__(16) unsigned char wave_smem[];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = tg_lane();
     WaveShared& sh = reinterpret_cast<WaveShared*>(wave_smem)[wave];
     const int r16 = lane & 15, q4 = lane >> 4;
     const float INF = __builtin_inff();
+    if (g.f16_ok && (*g.f16_ok != 0u) != NARROW) return;      // the other variant's turn
+    if (MODE == 0 && g.bytes && tg_whole_bytes(g.bytes, g.d)) return;      // join_bytes_kernel's
     const ListShare share = list_share(wl ? (int64_t)*wl_cnt : direct_count, MODE == 0 && tg_use_order(g));
     const int64_t count = share.count;
     const int64_t nwaves = share.workgroups * 4;
@@ -685,14 +680,28 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
             idr[t] = min(it.bids[row < it.nT ? row : 0], idmax);      // (a row past the block may hold anything)
         }
     };
-    constexpr int PARTS = LO ? 2 : 1;
-    halfx8 X[GMAX][PARTS][KS];
+    float4 X[GMAX][KS];
     auto load_group = [&](int t, u32 id) {      // t is a compile-time constant at every call site
-        const uint16_t* xh = g.Xh + (int64_t)id * g.ldhr;
+        if (NARROW) {
+            const uint16_t* xh = g.Xh + (int64_t)id * g.ldh;
 #pragma unroll
-        for (int part = 0; part < PARTS; ++part)
+            for (int s8 = 0; s8 < KS; ++s8) X[t][s8] = *reinterpret_cast<const float4*>(xh + 32 * s8 + 8 * q4);
+            return;
+        }
+        const float* x = g.X + (int64_t)id * g.ld;
 #pragma unroll
-            for (int s8 = 0; s8 < KS; ++s8) X[t][part][s8] = *reinterpret_cast<const halfx8*>(xh + part * (32 * KS) + 32 * s8 + 8 * q4);
+        for (int s8 = 0; s8 < KS; ++s8) {
+            const int col = 16 * s8 + 4 * q4;
+            if (FULL) {
+                // rows of exactly 16 KS floats: nothing to mask
+                X[t][s8] = *reinterpret_cast<const float4*>(x + col);
+            } else {
+                // unconditional load at a clamped column, zeroed afterwards when the column is padding
+                const bool real = col < g.ld;
+                const float4 val = *reinterpret_cast<const float4*>(x + (real ? col : 0));
+                X[t][s8] = real ? val : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
     };
     // per-member data (one member per lane): fetched into registers, parked in LDS one block ahead
     // the threshold of a member's list and its norm come in one word (MODE 1 has no lists: the norm alone)
@@ -710,10 +719,8 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
     };
     auto park_member = [&](const WaveItem& it, int id, float aux, u64 kth, u64 adj, int buf) {
         if (lane < it.nT) {
-            const float us = tg_row_unscale(aux, METRIC);
             sh.ids[buf][lane] = id;
-            sh.aux[buf][lane] = join_row_aux(aux, us, METRIC);
-            if (METRIC == 0) sh.us[buf][lane] = us;
+            sh.aux[buf][lane] = aux;
             if (MODE == 0) {
                 sh.okd[buf][lane] = (u32)(kth >> 32);
                 sh.salt[buf][lane] = (u32)tg_mix64(hs_slot + (u64)id);
@@ -786,7 +793,6 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
         const u32* s_okd = sh.okd[buf];
         const int* s_ids = sh.ids[buf];
         const float* s_aux = sh.aux[buf];
-        const float* s_us = sh.us[buf];
         const int64_t v = cur.v;
         const int nN = cur.nN, nT = cur.nT, MT = cur.MT, NT = cur.NT;
         u64* cells = sh.cell[buf];
@@ -807,7 +813,7 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
             // a = 16 i + 4 q4 + e.  Everything below works on "ordered" distances (tg_ord:
             // unsigned order = float order); a pair that must not count gets +inf added, so
             // no validity masks have to be carried around.
-            float aux_a[4], pen_a[4], us_a[4] = {0.f, 0.f, 0.f, 0.f};
+            float aux_a[4], pen_a[4];
             u32 ida_key[4], okd_a[4], adj_a[4] = {0u, 0u, 0u, 0u};
             const int rowc = (16 * i + 4 * q4) * JOIN_CELLS + (r16 >> 3);      // cell (first of the lane's rows, column group 0) of this lane's half of a tile
             if (i < MT) {
@@ -818,7 +824,6 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
                     pen_a[e] = a < nN ? 0.f : INF;
                     // L2: the penalty rides on the norm (norm + 0 is the norm, bit for bit)
                     aux_a[e] = METRIC == 0 ? s_aux[aa] + pen_a[e] : s_aux[aa];
-                    if (METRIC == 0) us_a[e] = s_us[aa];
                     ida_key[e] = ((u32)s_ids[aa] << 2) | 3u;
                     okd_a[e] = (MODE == 0 && a < nN) ? s_okd[aa] : 0u;
                 }
@@ -838,27 +843,28 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
                     }
                     if (j >= NT) continue;
                     floatx4 acc = (floatx4){0.f, 0.f, 0.f, 0.f};
-                    if (LO) {
 #pragma unroll
-                        for (int s8 = 0; s8 < KS; ++s8) {
-                            if (KS == 1) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[i][PARTS - 1][s8], X[j][PARTS - 1][s8], acc, 0, 0, 0);
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[i][PARTS - 1][s8], X[j][0][s8], acc, 0, 0, 0);
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[i][0][s8], X[j][PARTS - 1][s8], acc, 0, 0, 0);
+                    for (int s8 = 0; s8 < KS; ++s8) {
+                        if (NARROW) {
+                            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, X[i][s8]),
+                                                                          __builtin_bit_cast(halfx8, X[j][s8]), acc, 0, 0, 0);
+                        } else {
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s8].x, X[j][s8].x, acc, 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s8].y, X[j][s8].y, acc, 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s8].z, X[j][s8].z, acc, 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s8].w, X[j][s8].w, acc, 0, 0, 0);
                         }
                     }
-#pragma unroll
-                    for (int s8 = 0; s8 < KS; ++s8) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[i][0][s8], X[j][0][s8], acc, 0, 0, 0);
                     // column side: lane (r16, .) is column b = 16 j + r16
                     const int b = 16 * j + r16;
                     const int bb = b < nT ? b : 0;
                     const float pen_b = b < nT ? 0.f : INF;
                     const float aux_b = METRIC == 0 ? s_aux[bb] + pen_b : s_aux[bb];
-                    const float us_b = METRIC == 0 ? s_us[bb] : 0.f;
                     const u32 id_b = (u32)s_ids[bb];
                     u32 o[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        float dist = gram_to_dist<METRIC>(acc[e], aux_a[e], aux_b, us_a[e], us_b);
+                        float dist = gram_to_dist<METRIC>(acc[e], aux_a[e], aux_b);
                         if (METRIC != 0) dist += pen_a[e] + pen_b;
                         // only the diagonal tile has pairs on or below the diagonal to drop
                         if (i == j) dist += (r16 > 4 * q4 + e) ? 0.f : INF;
@@ -925,17 +931,6 @@ __device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample&
         buf ^= 1;
     }
     if (MODE == 0 && prev_nT > 0) flush_cells(buf ^ 1, prev_v, prev_nT);
-}
-
-template <int GMAX, int MODE, int METRIC, int KS>
-__global__ __launch_bounds__(256) void join_wave_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins,
-                                                        const int32_t* xblk, const int32_t* xsizes, float* xout,
-                                                        const u64* __restrict__ wl, const u32* __restrict__ wl_cnt,
-                                                        int64_t direct_count, int gmin)
-{
-    if (MODE == 0 && g.bytes && tg_whole_bytes(g.bytes, g.d)) return;      // join_bytes_kernel's
-    if (!g.narrow && *g.low != 0u) join_wave_body<GMAX, MODE, METRIC, KS, true>(g, sm, cd, hs_slot, stat_bins, xblk, xsizes, xout, wl, wl_cnt, direct_count, gmin);
-    else join_wave_body<GMAX, MODE, METRIC, KS, false>(g, sm, cd, hs_slot, stat_bins, xblk, xsizes, xout, wl, wl_cnt, direct_count, gmin);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1157,7 +1152,7 @@ static void launch_join_list(const TgGraph& g, const TgSample& sm, const TgCand&
     A.g = g; A.sm = sm; A.cd = c; A.hs_slot = hs_slot; A.stat_bins = stat_bins;
     A.wl = sm.wl + (int64_t)list * cap;
     A.wl_cnt = sm.wl_cnt + list;
-    const auto kernel = g.narrow ? join_kernel<DK, 0, true, ROWS> : join_kernel<DK, 0, false, ROWS>;
+    const auto kernel = g.Xh ? join_kernel<DK, 0, true, ROWS> : join_kernel<DK, 0, false, ROWS>;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(JOIN_THREADS), join_lds_bytes(DK, rows), s, A);
 }
 // wave_done: the register-resident kernel has served the classes 0 and 1
@@ -1178,9 +1173,20 @@ static void launch_wave_k(const TgGraph& g, const TgSample& sm, const TgCand& c,
     const int64_t wgs = (cap + 3) / 4;
     const unsigned grid = (unsigned)(wgs < JOIN_GRID ? wgs : JOIN_GRID);
     const size_t shm = 4 * sizeof(WaveShared);
-    hipLaunchKernelGGL((join_wave_kernel<GMAX, 0, METRIC, KS>), dim3(grid), dim3(256), shm, s, g, sm, c, hs_slot, stat_bins,
-                       (const int32_t*)nullptr, (const int32_t*)nullptr, (float*)nullptr, (const u64*)(sm.wl + (int64_t)list * cap),
-                       (const u32*)(sm.wl_cnt + list), (int64_t)0, 0);
+    // with the device flag both variants are launched, and the one it does not name ends at once
+    if (g.Xh)       // rows of the fp16 copy are whole steps of 32 values: KS / 2 of them
+        hipLaunchKernelGGL((join_wave_kernel<GMAX, 0, METRIC, KS / 2, true, true>), dim3(grid), dim3(256), shm, s, g, sm, c, hs_slot, stat_bins,
+                           (const int32_t*)nullptr, (const int32_t*)nullptr, (float*)nullptr, (const u64*)(sm.wl + (int64_t)list * cap),
+                           (const u32*)(sm.wl_cnt + list), (int64_t)0, 0);
+    if (g.Xh && !g.f16_ok) return;
+    if (g.ld == 16 * KS)
+        hipLaunchKernelGGL((join_wave_kernel<GMAX, 0, METRIC, KS, true, false>), dim3(grid), dim3(256), shm, s, g, sm, c, hs_slot, stat_bins,
+                           (const int32_t*)nullptr, (const int32_t*)nullptr, (float*)nullptr, (const u64*)(sm.wl + (int64_t)list * cap),
+                           (const u32*)(sm.wl_cnt + list), (int64_t)0, 0);
+    else
+        hipLaunchKernelGGL((join_wave_kernel<GMAX, 0, METRIC, KS, false, false>), dim3(grid), dim3(256), shm, s, g, sm, c, hs_slot, stat_bins,
+                           (const int32_t*)nullptr, (const int32_t*)nullptr, (float*)nullptr, (const u64*)(sm.wl + (int64_t)list * cap),
+                           (const u32*)(sm.wl_cnt + list), (int64_t)0, 0);
 }
 template <int GMAX, int METRIC, int KS>
 static void launch_wave_dump_k(const TgGraph& g, const int32_t* blk, const int32_t* sizes, int64_t nb, float* out, int gmin,
@@ -1190,18 +1196,21 @@ static void launch_wave_dump_k(const TgGraph& g, const int32_t* blk, const int32
     TgCand c = {};
     const int64_t wgs = (nb + 3) / 4;
     const size_t shm = 4 * sizeof(WaveShared);
-    hipLaunchKernelGGL((join_wave_kernel<GMAX, 1, METRIC, KS>), dim3((unsigned)(wgs < JOIN_GRID ? wgs : JOIN_GRID)),
-                       dim3(256), shm, s, g, sm, c, 0ull, (u64*)nullptr, blk, sizes, out, (const u64*)nullptr, (const u32*)nullptr, nb, gmin);
+    if (g.Xh)
+        hipLaunchKernelGGL((join_wave_kernel<GMAX, 1, METRIC, KS / 2, true, true>), dim3((unsigned)(wgs < JOIN_GRID ? wgs : JOIN_GRID)),
+                           dim3(256), shm, s, g, sm, c, 0ull, (u64*)nullptr, blk, sizes, out, (const u64*)nullptr, (const u32*)nullptr, nb, gmin);
+    if (!g.Xh || g.f16_ok)
+        hipLaunchKernelGGL((join_wave_kernel<GMAX, 1, METRIC, KS, false, false>), dim3((unsigned)(wgs < JOIN_GRID ? wgs : JOIN_GRID)),
+                           dim3(256), shm, s, g, sm, c, 0ull, (u64*)nullptr, blk, sizes, out, (const u64*)nullptr, (const u32*)nullptr, nb, gmin);
 }
-// a step holds 32 columns of the split copy
+// rows of at most 64 / 96 / 128 floats take 4 / 6 / 8 column steps per lane quarter
 template <int GMAX, int METRIC>
 static void launch_wave_m(const TgGraph& g, const TgSample& sm, const TgCand& c, u64 hs_slot, u64* stat_bins, int list, int parts,
                           hipStream_t s)
 {
-    if (g.ldh == 32) launch_wave_k<GMAX, METRIC, 1>(g, sm, c, hs_slot, stat_bins, list, parts, s);
-    else if (g.ldh == 64) launch_wave_k<GMAX, METRIC, 2>(g, sm, c, hs_slot, stat_bins, list, parts, s);
-    else if (g.ldh == 96) launch_wave_k<GMAX, METRIC, 3>(g, sm, c, hs_slot, stat_bins, list, parts, s);
-    else launch_wave_k<GMAX, METRIC, 4>(g, sm, c, hs_slot, stat_bins, list, parts, s);
+    if (g.ld <= 64) launch_wave_k<GMAX, METRIC, 4>(g, sm, c, hs_slot, stat_bins, list, parts, s);
+    else if (g.ld <= 96) launch_wave_k<GMAX, METRIC, 6>(g, sm, c, hs_slot, stat_bins, list, parts, s);
+    else launch_wave_k<GMAX, METRIC, 8>(g, sm, c, hs_slot, stat_bins, list, parts, s);
 }
 template <int GMAX>
 static void launch_wave_t(const TgGraph& g, const TgSample& sm, const TgCand& c, u64 hs_slot, u64* stat_bins, int list, int parts,
@@ -1215,16 +1224,17 @@ template <int GMAX, int METRIC>
 static void launch_wave_dump(const TgGraph& g, const int32_t* blk, const int32_t* sizes, int64_t nb, float* out, int gmin,
                              hipStream_t s)
 {
-    if (g.ldh == 32) launch_wave_dump_k<GMAX, METRIC, 1>(g, blk, sizes, nb, out, gmin, s);
-    else if (g.ldh == 64) launch_wave_dump_k<GMAX, METRIC, 2>(g, blk, sizes, nb, out, gmin, s);
-    else if (g.ldh == 96) launch_wave_dump_k<GMAX, METRIC, 3>(g, blk, sizes, nb, out, gmin, s);
-    else launch_wave_dump_k<GMAX, METRIC, 4>(g, blk, sizes, nb, out, gmin, s);
+    if (g.ld <= 64) launch_wave_dump_k<GMAX, METRIC, 4>(g, blk, sizes, nb, out, gmin, s);
+    else if (g.ld <= 96) launch_wave_dump_k<GMAX, METRIC, 6>(g, blk, sizes, nb, out, gmin, s);
+    else launch_wave_dump_k<GMAX, METRIC, 8>(g, blk, sizes, nb, out, gmin, s);
 }
+
+static bool wave_path(const TgGraph& g) { return tg_join_wave_ok(g.ld); }
 
 void tg_launch_join(const TgGraph& g, const TgSample& sm, const TgCand& c, int part, int parts, uint64_t hs_slot,
                     unsigned long long* stat_bins, hipStream_t s)
 {
-    const bool wv = sm.wave_ok != 0;
+    const bool wv = wave_path(g);
     if (g.bytes) {
         const int64_t cap = wl_cap(g.n, parts);
         const dim3 grid(JOIN_BYTES_GRID), block(256);
@@ -1245,8 +1255,7 @@ void tg_launch_join_distances(const TgGraph& g, const int32_t* blk, const int32_
                         allow_large_lds(join_kernel<64, 1, true, TG_BLOCK_COLS>, join_lds_bytes(64, TG_BLOCK_COLS)), true);
     (void)once;
     int skip_le = 0;
-    // same routing by block size as the production join (the split copy is left out where X turns out to hold bytes)
-    if (g.Xh && tg_join_wave_ok(g.n, g.ld) && (g.narrow || !g.bytes)) {
+    if (wave_path(g)) {      // same routing by block size as the production join
         if (g.metric == 0) { launch_wave_dump<3, 0>(g, blk, sizes, nb, out, 0, s); launch_wave_dump<4, 0>(g, blk, sizes, nb, out, 4, s); }
         else if (g.metric == 1) { launch_wave_dump<3, 1>(g, blk, sizes, nb, out, 0, s); launch_wave_dump<4, 1>(g, blk, sizes, nb, out, 4, s); }
         else { launch_wave_dump<3, 2>(g, blk, sizes, nb, out, 0, s); launch_wave_dump<4, 2>(g, blk, sizes, nb, out, 4, s); }
@@ -1254,6 +1263,6 @@ void tg_launch_join_distances(const TgGraph& g, const int32_t* blk, const int32_
     }
     JoinArgs A = {};
     A.g = g; A.xblk = blk; A.xsizes = sizes; A.xout = out; A.direct_count = nb; A.skip_le = skip_le;
-    const auto kernel = g.narrow ? join_kernel<64, 1, true, TG_BLOCK_COLS> : join_kernel<64, 1, false, TG_BLOCK_COLS>;
+    const auto kernel = g.Xh ? join_kernel<64, 1, true, TG_BLOCK_COLS> : join_kernel<64, 1, false, TG_BLOCK_COLS>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(nb < JOIN_GRID ? nb : JOIN_GRID)), dim3(JOIN_THREADS), join_lds_bytes(64, TG_BLOCK_COLS), s, A);
 }

@@ -43,14 +43,12 @@ struct TgGraph {
                         // bits of the largest distance of a row from its grid point
     const uint32_t* order;  // n: the nodes in an order that brings neighbours together (tg_launch_order), or null: by number
     int32_t ldq;        // d rounded up to 16: a row of codes never straddles more lines than it must
-    const uint16_t* Xh; // n x ldhr: the rows for the local join, scaled and split into fp16 numbers (tg_split4): ldh high parts, then
-                        // (unless `narrow`) ldh low parts; or null: the workgroup join splits the rows of X on their way into LDS
-    int32_t ldh;        // d rounded up to 32: columns d..ldh-1 are zero
-    int32_t ldhr;       // fp16 numbers per row of Xh: ldh or 2 ldh
-    int32_t narrow;     // 1: the join ranks on rows rounded to fp16 (no low parts), and the list update measures arrivals again
-    const uint32_t* low;    // device flag, or null (taken as 1): some row of Xh has a low part that is not zero
+    const uint16_t* Xh; // n x ldh: the rows rounded to fp16 for the local join, or null (join in fp32)
+    int32_t ldh;        // 64, 96 or 128 (the smallest that holds d), d rounded up to 32 beyond: columns d..ldh-1 are zero
     const uint32_t* bytes;  // the range of X, or null: set when the join on the 8-bit codes is launched too.  If X turns out to hold bytes
                             // (tg_whole_bytes) the blocks of at most 64 members are its work and the other variants leave them alone
+    const uint32_t* f16_ok; // device flag, or null: 1 while every value of X has turned out to be an fp16 number.  When set,
+                            // both variants of the join are launched and the one the flag does not name ends at once
 };
 
 struct TgSample {
@@ -90,26 +88,24 @@ struct TgSetup {
     size_t nbuckets;
     uint32_t* range;                // see tg_launch_norms and tg_launch_quantize
     uint32_t* undefined;            // this word and three of the next line
+    uint32_t* f16_ok;               // 1, or null
 };
 void tg_launch_setup(const TgSetup& z, hipStream_t s);
 // range: two words for the smallest and largest value of X (which start at ordered +infinity and -infinity) and the flag at TG_RANGE_NONINT, or NULL; undefined: a word to which the rows without a defined distance are added, or NULL
-// Xh: where the split rows go, or null (and always null for rows of more than 128 floats)
-void tg_launch_norms(const TgGraph& g, uint32_t* range, uint32_t* undefined, uint16_t* Xh, hipStream_t s);
+void tg_launch_norms(const TgGraph& g, uint32_t* range, uint32_t* undefined, hipStream_t s);
 void tg_launch_init(const TgGraph& g, uint64_t hs_init, hipStream_t s);
 // when: the codes are wanted now if X holds bytes (true) or if it does not (false), or in any case (null range in g.bytes)
 void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, bool when_bytes, hipStream_t s);
-// the copy g.Xh on its own, behind the norms (nothing where X turned out to hold bytes and g.bytes is set)
-void tg_launch_split(const TgGraph& g, uint16_t* Xh, uint32_t* range /* its flag TG_RANGE_LOW is set, or null */,
-                     uint32_t* overflow_rows /* counts the rows with a finite value beyond fp16's range, or null */, hipStream_t s);
+void tg_launch_narrow(const TgGraph& g, uint16_t* Xh, uint32_t* exact_flag /* cleared when a value is no fp16 number, or null */,
+                      uint32_t* overflow_rows /* counts the rows with a finite value beyond fp16's range, or null */, hipStream_t s);
 void tg_launch_fill_u32(uint32_t* p, size_t count, uint32_t v, hipStream_t s);
 void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hipStream_t s);
 int tg_rev_bucket_shift(int64_t n);
 // whether the join on the 8-bit codes is worth its launches: they cost about 4 us a part where X turns out to hold no bytes (a round
 // of 65 536 nodes takes 0.4 ms)
 static inline bool tg_join_bytes_possible(int64_t n, int ld, int metric) { return n >= 65536 && ld <= 128 && metric == 0; }
-// Rows the register-resident join takes: short ones, of which the workspace holds a split copy.  Beyond 48 GiB of copy the workgroup join,
-// which splits X on the way, takes every block: such sets fill the memory of the device as it is.
-static inline bool tg_join_wave_ok(int64_t n, int ld) { return ld <= 128 && n * ((ld + 31) & ~31) * 4 <= (int64_t)48 << 30; }
+// rows the register-resident join takes
+static inline bool tg_join_wave_ok(int ld) { return ld <= 128; }
 // which members of a block sit in which member's list, for the anchors of one part: sm.adj (to run before tg_launch_join of that part);
 // the same, copied to n x 128 x 4 words for inspection
 void tg_launch_adj(const TgGraph& g, const TgSample& sm, int part, hipStream_t s);

@@ -5,6 +5,7 @@
 // Ownership rule that makes the update lock-free: exactly one wavefront reads and
 // rewrites a given list in a given kernel; other nodes reach a list only through its
 // candidate slots (atomic minimum) or through the previous round's snapshot.
+#include <hip/hip_fp16.h>
 #include "tg_kernels.h"
 #include "tg_device.h"
 
@@ -45,9 +46,9 @@ __global__ __launch_bounds__(256) void setup_kernel(TgSetup z)
         z.range[1] = 0x007FFFFFu;            // ordered -infinity
         z.range[2] = 0u;                     // largest distance of a row from its grid point
         z.range[TG_RANGE_NONINT] = 0u;
-        z.range[TG_RANGE_LOW] = 0u;
         *z.undefined = 0u;
         for (int i = 0; i < 3; ++i) z.undefined[32 + i] = 0u;      // (of the phase-2 probe)
+        if (z.f16_ok) *z.f16_ok = 1u;
     }
 }
 void tg_launch_setup(const TgSetup& z, hipStream_t s)
@@ -79,24 +80,20 @@ void tg_launch_pad_rows(const float* X, int64_t n, int d, float* Xp, int ld, hip
 // value is not a whole number (finalize_kernel asks).  With `undefined`, rows that have no
 // defined distance are counted there: a squared norm that is not a finite number (an infinite or
 // undefined value in the row, or an overflow), and a zero norm where the reciprocal is asked for.
-// SPLIT (rows of at most 128 floats): the row is still in registers when its norm is known, and its split copy is written from there.
 // ---------------------------------------------------------------------------------------
-template <bool SPLIT>
 __global__ __launch_bounds__(256) void norms_kernel(const float* __restrict__ X, int64_t n, int d, int ld,
                                                     float* __restrict__ nrm, float* __restrict__ rnorm, u32* __restrict__ range,
-                                                    u32* __restrict__ undefined, int metric, uint16_t* __restrict__ Xh, int ldh)
+                                                    u32* __restrict__ undefined)
 {
     __shared__ u32 s_lo[16], s_hi[16];
     const int sub = threadIdx.x & 15;
     float lo = __builtin_inff(), hi = -__builtin_inff();
-    bool nonint = false, low = false;
+    bool nonint = false;
     for (int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); row < n; row += (int64_t)gridDim.x * 16) {
         const float* x = X + row * (int64_t)ld;
         float acc = 0.0f;
-        float4 keep[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
         for (int c = sub * 4; c < ld; c += 64) {
             const float4 v = *reinterpret_cast<const float4*>(x + c);
-            if (SPLIT) { if (c < 64) keep[0] = v; else keep[1] = v; }
             acc += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
             if (range) {
                 const float e[4] = {v.x, v.y, v.z, v.w};
@@ -114,24 +111,8 @@ __global__ __launch_bounds__(256) void norms_kernel(const float* __restrict__ X,
             if (rnorm) rnorm[row] = 1.0f / sqrtf(acc);
             if (undefined && (!(acc < __builtin_inff()) || (rnorm && !(acc > 0.0f)))) atomicAdd(undefined, 1u);
         }
-        if (SPLIT) {
-            const float scale = tg_row_scale(metric == 2 ? 1.0f / sqrtf(acc) : acc, metric);
-            uint16_t* out = Xh + row * (int64_t)(2 * ldh);
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int c = sub * 4 + 64 * p;
-                if (c < ldh) {
-                    uint2 hi, lo;
-                    tg_split4(keep[p], scale, hi, lo);
-                    *reinterpret_cast<uint2*>(out + c) = hi;
-                    *reinterpret_cast<uint2*>(out + ldh + c) = lo;
-                    low |= ((lo.x | lo.y) & 0x7FFF7FFFu) != 0u;
-                }
-            }
-        }
     }
     if (!range) return;
-    if (SPLIT && __ballot(low) != 0ull && tg_lane() == 0 && range[TG_RANGE_LOW] == 0u) range[TG_RANGE_LOW] = 1u;
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) {
         lo = fminf(lo, __shfl_xor(lo, o));
@@ -148,15 +129,15 @@ __global__ __launch_bounds__(256) void norms_kernel(const float* __restrict__ X,
     }
     if (__ballot(nonint) != 0ull && tg_lane() == 0 && range[TG_RANGE_NONINT] == 0u) range[TG_RANGE_NONINT] = 1u;
 }
-void tg_launch_norms(const TgGraph& g, uint32_t* range, uint32_t* undefined, uint16_t* Xh, hipStream_t s)
+void tg_launch_norms(const TgGraph& g, uint32_t* range, uint32_t* undefined, hipStream_t s)
 {
     // with the range asked for, few workgroups at small n: they all end at once and would queue at its two words (10 000 x 32: 28 us
     // with 625 workgroups, 37 511 x 52: 106 us with 2048)
     const int64_t wgs = (g.n + 15) / 16;
     int64_t most = 2048;
     if (range && g.n * g.ld < (int64_t)1 << 25) most = 256;
-    hipLaunchKernelGGL(Xh ? norms_kernel<true> : norms_kernel<false>, dim3((unsigned)(wgs < most ? wgs : most)), dim3(256), 0, s, g.X, g.n, g.d, g.ld,
-                       g.nrm, g.metric == 2 ? g.rnorm : (float*)nullptr, range, undefined, (int)g.metric, Xh, (int)g.ldh);
+    hipLaunchKernelGGL(norms_kernel, dim3((unsigned)(wgs < most ? wgs : most)), dim3(256), 0, s, g.X, g.n, g.d, g.ld, g.nrm,
+                       g.metric == 2 ? g.rnorm : (float*)nullptr, range, undefined);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -237,47 +218,44 @@ void tg_launch_quantize(const TgGraph& g, uint8_t* Xq, float* Xqm, bool when_byt
 }
 
 // ---------------------------------------------------------------------------------------
-// The split copy of the rows (tg_split4) on its own, four values per thread: where the kernel of the norms cannot write it on its way,
-// because X may still turn out to hold bytes (the join then reads the 8-bit codes, and nothing is written), or for rows of any length
-// (g.narrow: high parts only).
+// fp16 copy of the rows for the local join: round to nearest even, eight values per thread,
+// zero beyond column d.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void split_kernel(TgGraph g, uint16_t* __restrict__ Xh, u32* range, u32* overflow_rows)
+__global__ __launch_bounds__(256) void narrow_kernel(TgGraph g, uint16_t* __restrict__ Xh, u32* exact_flag, u32* overflow_rows)
 {
-    if (!g.narrow && g.bytes && tg_whole_bytes(g.bytes, g.d)) return;
-    bool low = false;
-    const int per_row = g.ldh >> 2;
+    bool inexact = false;
+    const int per_row = g.ldh >> 3;
     const size_t total = (size_t)g.n * per_row;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
         const size_t row = i / per_row;
-        const int c0 = (int)(i - row * per_row) * 4;
+        const int c0 = (int)(i - row * per_row) * 8;
         const float* x = g.X + row * (size_t)g.ld;
-        const float4 v = c0 < g.ld ? *reinterpret_cast<const float4*>(x + c0) : make_float4(0.f, 0.f, 0.f, 0.f);
-        uint2 hi, lo;
-        tg_split4(v, tg_row_scale(g.metric == 2 ? g.rnorm[row] : g.nrm[row], g.metric), hi, lo);
-        uint16_t* out = Xh + row * (size_t)g.ldhr + c0;
-        *reinterpret_cast<uint2*>(out) = hi;
-        if (!g.narrow) {
-            *reinterpret_cast<uint2*>(out + g.ldh) = lo;
-            low |= ((lo.x | lo.y) & 0x7FFF7FFFu) != 0u;
+        u32 h[8];
+        bool over = false;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float val = c0 + e < g.d ? x[c0 + e] : 0.f;
+            const __half hv = __float2half_rn(val);
+            inexact |= __half2float(hv) != val;
+            over |= fabsf(val) <= 3.4028234e38f && fabsf(__half2float(hv)) > 65504.f;      // a finite value that fp16 cannot hold
+            h[e] = (u32)__half_as_ushort(hv);
         }
-        if (overflow_rows) {
-            const float most = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
-            if (most >= 65520.f) {            // (what rounds to more than 65504)
-                // such a row is counted once: by the piece that holds its first such finite value (rare: the row is read again)
-                int first = -1;
-                for (int c = 0; c < g.d && first < 0; ++c)
-                    if (fabsf(x[c]) >= 65520.f && fabsf(x[c]) <= 3.4028234e38f) first = c;
-                if (first >= c0 && first < c0 + 4) atomicAdd(overflow_rows, 1u);
-            }
+        if (over && overflow_rows) {
+            // such a row is counted once: by the piece that holds its first such value (rare: the columns before are read again)
+            bool first = true;
+            for (int c = 0; c < c0 && first; ++c) first = !(fabsf(x[c]) > 65504.f && fabsf(x[c]) <= 3.4028234e38f);
+            if (first) atomicAdd(overflow_rows, 1u);
         }
+        *reinterpret_cast<uint4*>(Xh + row * (size_t)g.ldh + c0) =
+            make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
     }
-    // one store per wave that met such a row, and none once the flag is up
-    if (range && __ballot(low) != 0ull && tg_lane() == 0 && range[TG_RANGE_LOW] == 0u) range[TG_RANGE_LOW] = 1u;
+    // one store per wave that met such a value, and none once the flag is down
+    if (exact_flag && __ballot(inexact) != 0ull && tg_lane() == 0 && *exact_flag != 0u) *exact_flag = 0u;
 }
-void tg_launch_split(const TgGraph& g, uint16_t* Xh, uint32_t* range, uint32_t* overflow_rows, hipStream_t s)
+void tg_launch_narrow(const TgGraph& g, uint16_t* Xh, uint32_t* exact_flag, uint32_t* overflow_rows, hipStream_t s)
 {
-    hipLaunchKernelGGL(split_kernel, dim3(grid_for((size_t)g.n * (g.ldh >> 2), 256)), dim3(256), 0, s, g, Xh, range, overflow_rows);
+    hipLaunchKernelGGL(narrow_kernel, dim3(grid_for((size_t)g.n * (g.ldh >> 3), 256)), dim3(256), 0, s, g, Xh, exact_flag, overflow_rows);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -813,8 +791,8 @@ __global__ __launch_bounds__(64 * LISTS_WAVES) void update_kernel(TgGraph g, int
 void tg_launch_update(const TgGraph& g, const TgSample& sm, const TgCand& c, u64* updates, bool flip, hipStream_t s)
 {
     if (c.C > UPDATE_MAX_C) return;    // the boundary refuses such C; the queue in LDS holds no more
-    // rows rounded for the join: measure arrivals again
-    const bool remeasure = g.narrow != 0;
+    // rows rounded for the join whatever their values (not the mode that narrows only where that is exact): measure arrivals again
+    const bool remeasure = g.Xh && !g.f16_ok;
     const size_t shm = remeasure ? (size_t)LISTS_WAVES * g.ld * sizeof(float) + LISTS_WAVES * 128 * sizeof(u32) : 0;
     tg_for_node_chunks(g.n, [&](int64_t v0, int64_t cnt) {
         const dim3 grid((unsigned)((cnt + LISTS_WAVES - 1) / LISTS_WAVES));

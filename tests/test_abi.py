@@ -182,3 +182,20 @@ def test_exact_scratch_gets_smaller_with_every_attempt(n, ld, metric, nq, padded
     assert seen[-1][1] == min(nq, 64) and not seen[-1][0]
     # the squared norms, the inverse ones, and per query (of two tiles) a list of 2048 places, its packed row and a few words
     assert seen[-1][2] <= padded + 8 * n + 64 * 2048 * 8 + 128 * (4 * (ld + 32) + 96) + 4096
+
+
+def test_workspace_holds_no_copy_that_was_not_asked_for():
+    """What a caller has to provide: the codes cost n x (d rounded up to 16) bytes, the fp16 copy of join_f16 = 1 and 2 two bytes a value at
+    any length of row, and the default join has no copy of the rows; sets that fill a device fit as they did (100M x 96 in 180.4 GB,
+    100M x 128 in 132.4)."""
+    from paper_2508_08744_amd import knn
+
+    def need(n, d, k, **kw):
+        return knn.workspace_bytes(n, d, knn.default_params(k, 8, **kw))
+    assert need(100_000_000, 96, 32, parts=8, C=64) <= 180.4e9
+    assert need(100_000_000, 128, 10, parts=8, C=64) <= 132.4e9
+    assert need(50_000_000, 128, 16) <= 171.8e9
+    for n, d, ldh in ((1_000_000, 40, 64), (1_000_000, 96, 96), (1_000_000, 97, 128), (300_000, 200, 224), (300_000, 960, 960)):
+        assert abs(need(n, d, 32) - need(n, d, 32, screen=0) - n * ((d + 15) // 16 * 16)) < 4096
+        for f16 in (1, 2):
+            assert abs(need(n, d, 32, join_f16=f16) - need(n, d, 32) - 2 * n * ldh) < 4096
