@@ -579,8 +579,8 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
                 emit_candidate(A.cd, s_ids[c >> 3], idmax, s_salt[c >> 3], key, (u32)v, c & 7);
             }
         }
-        __syncthreads();          // the member data and the cells are the next block's from here on
     }
+    __syncthreads();              // the member data and the cells are the next block's from here on
     cur = nxt;
     buf ^= 1;
     }   // work-list loop

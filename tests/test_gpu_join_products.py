@@ -89,6 +89,26 @@ def test_a_pair_has_one_distance(d, metric):
     b.close()
 
 
+@pytest.mark.parametrize("d", [20, 128, 132])
+def test_more_blocks_than_workgroups(d):
+    """5000 blocks in one call, so that every workgroup (2048 of them) walks several: the tiles are those of the same blocks in calls of at most
+    2000, each of which has a workgroup to itself.  A block's member data must stay until all its waves have used them."""
+    rng = np.random.default_rng(d)
+    nb = 5000
+    X = rng.standard_normal((3000, d)).astype(np.float32) * np.exp(rng.normal(0, 2, (3000, 1))).astype(np.float32)
+    blk = np.argsort(rng.random((nb, 3000), dtype=np.float32), axis=1)[:, :128].astype(np.int32)
+    new = rng.integers(1, 65, nb)
+    sizes = np.stack([new, 128 - new], axis=1).astype(np.int32)
+    sizes[::7] = [20, 30]                                                  # (of at most 64 members: a wave's for short rows)
+    sizes[5::11] = [64, 64]
+    b = knn.Builder(torch.from_numpy(X).cuda(), knn.default_params(8, 4))
+    whole = b.join_distances(torch.from_numpy(blk), torch.from_numpy(sizes)).nan_to_num()
+    for s in range(0, nb, 2000):
+        part = b.join_distances(torch.from_numpy(blk[s:s + 2000]), torch.from_numpy(sizes[s:s + 2000])).nan_to_num()
+        assert torch.equal(whole[s:s + 2000], part)
+    b.close()
+
+
 @pytest.mark.parametrize("d,most", [(1, 2896), (2, 2048), (32, 500), (33, 500), (128, 255)])
 def test_whole_numbers_under_exact_sums_are_exact(d, most):
     """2 d most^2 <= 2^24: every fp32 sum over products or squares is exact, so a distance is
