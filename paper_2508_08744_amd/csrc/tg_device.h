@@ -209,19 +209,6 @@ __device__ inline bool tg_whole_bytes(const u32* __restrict__ range, int d)
     return tg_whole_exact(range, d) && tg_unord(range[1]) - tg_unord(range[0]) <= 255.0f;
 }
 
-__device__ inline float tg_pow2(int e) { return __uint_as_float((u32)(e + 127) << 23); }
-// four values, scaled, as sums of two fp16 numbers (22 bits): high and low parts, two to a word
-__device__ inline void tg_split4(float4 x, float scale, uint2& hi, uint2& lo)
-{
-    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-    const float e[4] = {x.x * scale, x.y * scale, x.z * scale, x.w * scale};
-    const half2v h0 = {(_Float16)e[0], (_Float16)e[1]}, h1 = {(_Float16)e[2], (_Float16)e[3]};
-    const half2v l0 = {(_Float16)(e[0] - (float)h0.x), (_Float16)(e[1] - (float)h0.y)};
-    const half2v l1 = {(_Float16)(e[2] - (float)h1.x), (_Float16)(e[3] - (float)h1.y)};
-    hi = make_uint2(__builtin_bit_cast(u32, h0), __builtin_bit_cast(u32, h1));
-    lo = make_uint2(__builtin_bit_cast(u32, l0), __builtin_bit_cast(u32, l1));
-}
-
 // whether the nodes are taken in g.order (not where X holds bytes and phase 1 reads 128 of them a row: the kernels that would make the
 // order end at once then; 1M x 128 bytes, four rounds: 0.25 ms for the order, 0.1 gained)
 template <class G>

@@ -14,7 +14,7 @@
 // One wave per node.  Section 5.2 evaluates a batch of candidates against the neighbour that
 // was inserted last, one batch per insertion.  Here the candidate rows (at most 64) are loaded
 // once into registers in matrix-core operand layout and ALL their pairwise products are
-// formed at once (a Gram matrix on the matrix cores, upper triangle of 16 x 16 tiles);
+// formed at once (a Gram matrix on v_mfma_f32_16x16x4_f32, upper triangle of 16 x 16 tiles);
 // what remains of the serial rule is bit arithmetic: every candidate gets the 64-bit set of
 // the candidates in front of it that would occlude it, and the set of inserted candidates is the
 // fixed point of "inserted iff no inserted candidate occludes me", found in a few passes.  The rows are the only large HBM traffic
@@ -45,7 +45,6 @@ __host__ __device__ constexpr int filter_loads(bool vec) { return vec ? 8 : 2; }
 #define FILTER_FREE 0xFFFFFFFFu
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 struct FilterArgs {
     const float* X;
@@ -235,9 +234,6 @@ __device__ inline u32 filter_wave_max(u32 x)
 #define FILTER_RULE_DIST 0
 #define FILTER_RULE_ANGLE 1
 #define FILTER_RULE_DISPERSION 2
-// Whether the candidates' products can be formed from split rows.  Not under the threshold rules within two hops: those instances have no registers
-// for it at three waves per SIMD (250 000 x 128, k = 32: 8.41 -> 8.49 ms) and spend an eighth of their time on products.
-__host__ __device__ constexpr bool filter_split(int collect, int rule) { return collect == FILTER_ONE_HOP || rule == FILTER_RULE_DISPERSION; }
 // The neighbours under a threshold rule: 2.75 KB of LDS a wave are enough for arrays of their own, registers (three or four waves per
 // SIMD) are what limits the waves, and a wait before the keys replace the distances is saved: 100 000 x 300, k = 32: 680 -> 671 us,
 // 60 000 x 37, k = 64: 348 -> 344 us.
@@ -264,20 +260,19 @@ __host__ __device__ constexpr int filter_lds_words(int ng, int collect, int rule
 }
 
 // Waves per SIMD that the compiler must leave room for.  Four for the neighbours under the dispersion rule, which is bound by what a
-// wave does in sequence (products, angles, the greedy): 200 000 x 200, k = 40, d_out = 20: 2.65 ms with 64 rows and two waves, 1.84 ms
-// with 48 rows and four, 1.43 with split products; two with 64 rows (100 000 x 400, k = 64: four spill, 3.30 ms; 2.07).  No demand on the
+// wave does in sequence (products, angles, the greedy): 200 000 x 200, k = 40, d_out = 20: 2.65 ms with 64 rows and two waves, 1.85 ms
+// with 48 rows and four; and for 33..48 neighbours under the others, which have the registers (111) anyway.  No demand on the other
 // threshold instances, which wait for rows: asked for four, that of up to 32 neighbours gets fewer loads on their way (100 000 x 128,
-// k = 32: 310 us against 274), that of 33..48 spills (200 000 x 200, k = 48: 1294 against 1222 us) and so does that of 49..64.  Three for two hops, which wait for
+// k = 32: 310 us against 274) and that of 49..64 spills (60 000 x 37, k = 64: 353 against 344 us).  Three for two hops, which wait for
 // rows too (4 d bytes per distinct id, 5.5 TB/s): with four the compiler spills, 250 000 x 128, k = 32: 8.62 against 8.45 ms (9.17 with
 // two waves and the rows of ids read one at a time), and none where rows come value by value (18 595 x 279, k = 12: 1298 -> 1280 us).
 __host__ __device__ constexpr int filter_least_waves(int ng, int collect, int rule, bool vec)
 {
     if (collect != FILTER_ONE_HOP) return vec ? 3 : 1;
-    if (ng == 4) return rule == FILTER_RULE_DISPERSION ? 2 : 1;
-    return rule == FILTER_RULE_DISPERSION ? 4 : 1;
+    return rule == FILTER_RULE_DISPERSION || ng == 3 ? 4 : 1;
 }
 
-template <int NG, int KS, bool FULL, bool VEC, int COLLECT, int RULE, bool SPLIT>
+template <int NG, int KS, bool FULL, bool VEC, int COLLECT, int RULE>
 __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) void filter_dist_kernel(FilterArgs A)
 {
     constexpr bool TWO_HOPS = COLLECT != FILTER_ONE_HOP;
@@ -310,13 +305,6 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
 
     for (int64_t p = (int64_t)blockIdx.x * FILTER_WAVES + wave; p < A.n; p += (int64_t)gridDim.x * FILTER_WAVES) {
         const float* xp = A.X + p * A.d;
-        u32 x_most = 0u, x_own[4] = {0u, 0u, 0u, 0u};      // bits of p's values, of which the largest sets the scale: asked for now, looked at behind the collection
-        if (SPLIT) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (lane + 64 * i < A.d) x_own[i] = __float_as_uint(xp[lane + 64 * i]);
-            for (int c = lane + 256; c < A.d; c += 64) x_most = max(x_most, __float_as_uint(xp[c]) & 0x7FFFFFFFu);
-        }
         int m = 0;
         // ---- Collect ----
         const int32_t u = lane < k ? A.ids[p * k + lane] : -1;
@@ -410,73 +398,19 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
 #pragma unroll
         for (int t = 0; t < NG; ++t) dp[t] = 0.f;
         const int groups = (m + 15) >> 4;
-        // Products of the rows split into two fp16 numbers per value (tg_split4), all four of a pair, so that values of up to 22 bits count
-        // in full: 64 cycles of matrix pipe for 32 columns of a tile, 256 with the fp32 instruction, which moreover shares the vector
-        // instructions' datapath.  One power of two for all rows of a node, which brings p's largest value to 2^9; candidates more than 64 times
-        // that large come out infinite (and a p of zeros says nothing): such a node takes the fp32 instruction.  A candidate far below p's scale
-        // loses digits below 2^-33 of p's largest value, beside which its distances to p are large: no decision sees them.
-        // fp32 matrix instructions and vector instructions took turns before (42 % and 56 % of the time at 200 000 x 200, k = 40,
-        // dispersion rule): 1.84 -> 1.43 ms; 500 000 x 300, k = 64, distance rule 8.40 -> 7.04; 100 000 x 128, k = 32 273 -> 260 us.
-        float us2 = 0.0f;                      // undoes the squared scale
-        if (SPLIT) {                           // (bits order what is not negative; no number is the largest)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) x_most = max(x_most, x_own[i] & 0x7FFFFFFFu);
-            x_most = filter_wave_max(x_most);
-        }
-        if (SPLIT && x_most > 0u && x_most < 0x7F800000u) {
-            const int e = min(max((int)(x_most >> 23) - 127, -50), 63);      // (squares beyond 2^126 are no numbers in fp32 either: such rows come out infinite)
-            const float scale = tg_pow2(8 - e);
-            us2 = tg_pow2(2 * (e - 8));
-            for (int c = 0; c < nchunks; ++c) {
-                float4 X[NG][KS];
-                filter_load_chunk<NG, KS, FULL, VEC>(A, xp, cid, m, c * 16 * KS, X, dp);
-#pragma unroll
-                for (int s = 0; s < KS; s += 2) {
-                    if (!FULL && c * 16 * KS + 16 * s >= A.d) break;          // uniform: nothing but zeros from here on
-                    halfx8 hi[NG], lo[NG];
-#pragma unroll
-                    for (int t = 0; t < NG; ++t) {
-                        uint2 h0, l0, h1, l1;
-                        tg_split4(X[t][s], scale, h0, l0);
-                        tg_split4(X[t][s + 1], scale, h1, l1);
-                        hi[t] = __builtin_bit_cast(halfx8, make_uint4(h0.x, h0.y, h1.x, h1.y));
-                        lo[t] = __builtin_bit_cast(halfx8, make_uint4(l0.x, l0.y, l1.x, l1.y));
-                    }
-#pragma unroll
-                    for (int i = 0; i < NG; ++i) {
-                        if (i >= groups) break;                   // uniform
-#pragma unroll
-                        for (int j = i; j < NG; ++j) {
-                            if (j >= groups) break;
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo[i], lo[j], acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo[i], hi[j], acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi[i], lo[j], acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi[i], hi[j], acc[i][j], 0, 0, 0);
-                        }
-                    }
-                }
-            }
-            bool finite = true;                // of the squared norms, on the diagonals
-#pragma unroll
-            for (int t = 0; t < NG; ++t) {
-                const floatx4 a = acc[t][t];
-                const float lo = (r16 & 1) ? a.y : a.x, hi = (r16 & 1) ? a.w : a.z;
-                finite &= q4 != (r16 >> 2) || fabsf((r16 & 2) ? hi : lo) < __builtin_inff();
-            }
-            if (__ballot(!finite) != 0ull) us2 = 0.0f;
-        }
-        if (us2 == 0.0f) {                     // uniform
-            us2 = 1.0f;
-#pragma unroll
-            for (int i = 0; i < NG; ++i)
-#pragma unroll
-                for (int j = 0; j < NG; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int t = 0; t < NG; ++t) dp[t] = 0.f;
-#pragma unroll 1
-            for (int c = 0; c < nchunks; ++c) {
-                float4 X[NG][KS];
-                filter_load_chunk<NG, KS, FULL, VEC>(A, xp, cid, m, c * 16 * KS, X, dp);
+        for (int c = 0; c < nchunks; ++c) {
+            float4 X[NG][KS];
+            filter_load_chunk<NG, KS, FULL, VEC>(A, xp, cid, m, c * 16 * KS, X, dp);
+            auto multiply = [&](int i, int j, int s) __attribute__((always_inline)) {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].x, X[j][s].x, acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].y, X[j][s].y, acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].z, X[j][s].z, acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].w, X[j][s].w, acc[i][j], 0, 0, 0);
+            };
+            // Steps beyond the row hold nothing but zeros and are left out (500 000 x 16, k = 32: 767 -> 522 us, 100 000 x 101, k = 32: 594 -> 501),
+            // so they come outermost: one test each.  Whole chunks take a tile at a time (300 000 x 64, k = 24: 488 us, steps outermost 500).
+            // A tile's sum takes its columns in the same order either way.
+            if (FULL) {
 #pragma unroll
                 for (int i = 0; i < NG; ++i) {
                     if (i >= groups) break;                           // uniform
@@ -484,12 +418,20 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
                     for (int j = i; j < NG; ++j) {
                         if (j >= groups) break;
 #pragma unroll
-                        for (int s = 0; s < KS; ++s) {
-                            if (!FULL && c * 16 * KS + 16 * s >= A.d) break;
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].x, X[j][s].x, acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].y, X[j][s].y, acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].z, X[j][s].z, acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[i][s].w, X[j][s].w, acc[i][j], 0, 0, 0);
+                        for (int s = 0; s < KS; ++s) multiply(i, j, s);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    if (c * 16 * KS + 16 * s >= A.d) break;           // uniform
+#pragma unroll
+                    for (int i = 0; i < NG; ++i) {
+                        if (i >= groups) break;
+#pragma unroll
+                        for (int j = i; j < NG; ++j) {
+                            if (j >= groups) break;
+                            multiply(i, j, s);
                         }
                     }
                 }
@@ -525,10 +467,10 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
                 const float nC = nrm[16 * j + r16];
                 const float dC = dp[j];
                 const floatx4 g = acc[i][j];
-                const float rc0 = us2 * ((nR.x + nC) - 2.0f * g.x);        // dis(R, C)
-                const float rc1 = us2 * ((nR.y + nC) - 2.0f * g.y);
-                const float rc2 = us2 * ((nR.z + nC) - 2.0f * g.z);
-                const float rc3 = us2 * ((nR.w + nC) - 2.0f * g.w);
+                const float rc0 = (nR.x + nC) - 2.0f * g.x;        // dis(R, C)
+                const float rc1 = (nR.y + nC) - 2.0f * g.y;
+                const float rc2 = (nR.z + nC) - 2.0f * g.z;
+                const float rc3 = (nR.w + nC) - 2.0f * g.w;
                 if (RULE == FILTER_RULE_DISPERSION) {
                     // the angle of every pair, stored both ways round (row R, column C and the reverse)
                     const int R = 16 * i + 4 * q4, C = 16 * j + r16;
@@ -664,20 +606,9 @@ static void launch_filter(const FilterArgs& A, bool vec, hipStream_t s)
     // four (three) waves per SIMD cover each other's loads
     constexpr int KS = NG > 2 ? 2 : 4;
     const bool full = vec && (A.d % (16 * KS) == 0);         // no column guards needed
-    constexpr bool CAN = filter_split(COLLECT, RULE);
-    // Short rows are multiplied in fp32 (steps beyond the row left out): the split takes registers, a wave per SIMD under the threshold rules,
-    // and is worth them from the second chunk of columns on (distance and angle rule, split / fp32: 13 000 x 64, k = 16 21.9 / 17.6 us, 40 000 x 33, k = 12
-    // 69.9 / 53.4, 300 000 x 64, k = 24 464 / 484, 6000 x 100, k = 24 19.3 / 25.3, 100 000 x 101, k = 32 451 / 543), under the dispersion rule, which has four
-    // waves either way, a little earlier (6000 x 50, k = 64 66.0 / 71.5; 10 000 x 33, k = 32 37.1 / 35.8).
-    if (CAN && A.d >= (RULE == FILTER_RULE_DISPERSION ? 48 : 65)) {
-        if (full) filter_launch(filter_dist_kernel<NG, KS, true, true, COLLECT, RULE, CAN>, A, shm, s);
-        else if (vec) filter_launch(filter_dist_kernel<NG, KS, false, true, COLLECT, RULE, CAN>, A, shm, s);
-        else filter_launch(filter_dist_kernel<NG, KS, false, false, COLLECT, RULE, CAN>, A, shm, s);
-    } else {
-        if (full) filter_launch(filter_dist_kernel<NG, KS, true, true, COLLECT, RULE, false>, A, shm, s);
-        else if (vec) filter_launch(filter_dist_kernel<NG, KS, false, true, COLLECT, RULE, false>, A, shm, s);
-        else filter_launch(filter_dist_kernel<NG, KS, false, false, COLLECT, RULE, false>, A, shm, s);
-    }
+    if (full) filter_launch(filter_dist_kernel<NG, KS, true, true, COLLECT, RULE>, A, shm, s);
+    else if (vec) filter_launch(filter_dist_kernel<NG, KS, false, true, COLLECT, RULE>, A, shm, s);
+    else filter_launch(filter_dist_kernel<NG, KS, false, false, COLLECT, RULE>, A, shm, s);
 }
 
 template <int RULE>
