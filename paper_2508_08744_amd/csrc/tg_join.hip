@@ -314,6 +314,8 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const ListShare part = list_share(A.wl ? (int64_t)*A.wl_cnt : A.direct_count, MODE == 0 && tg_use_order(g));
+    int64_t w = part.index;
+    if (w >= part.count) return;
     if (MODE == 0) {
         for (int c = tid; c < TG_BLOCK_COLS * JOIN_CELLS; c += JOIN_THREADS) s_cell[c] = TG_EMPTY_KEY;
     }
@@ -370,8 +372,6 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
         }
     };
 
-    int64_t w = part.index;
-    if (w >= part.count) return;
     Block cur = block_at(w);
     int buf = 0;
     if (tid < ROWS) s_idb[tid] = tid < cur.nT ? min(cur.bids[tid], idmax) : 0u;
