@@ -119,6 +119,8 @@ struct tg_knn_handle {
 };
 enum { SPAN_NORMS, SPAN_INIT, SPAN_SAMPLE, SPAN_ADJ, SPAN_JOIN, SPAN_UPDATE, SPAN_FINALIZE };
 
+bool tg_lds_unasked(uint64_t asked, int device) { return device < 0 || device >= 64 || !((asked >> device) & 1u); }
+
 static int round_up4(int d) { return (d + 3) & ~3; }
 
 static void carve(tg_knn_handle* h, const float* X, int64_t n, int32_t d, void* ws, size_t* need)

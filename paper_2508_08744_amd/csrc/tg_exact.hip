@@ -226,9 +226,7 @@ void tg_launch_exact_knn(const float* X, int ld, const float* rnorm, int64_t n, 
     const int64_t groups = (nq + EXQ - 1) / EXQ;
     const int waves = ld <= 1024 ? 4 : ld <= 2048 ? 2 : 1;     // independent waves per workgroup, bounded by LDS
     const size_t shm = (size_t)waves * ((size_t)EXQ * ld * sizeof(float) + (size_t)EXQ * EX_BUF * sizeof(u64));
-    static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(exact_scan_kernel),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256), true);
-    (void)once;
+    tg_allow_lds<exact_scan_kernel>(160 * 1024 - 256);
     const int64_t across = (groups + waves - 1) / waves;
     if (list && across * waves * nslices < EX_LIST_WAVES) nslices = (int)((EX_LIST_WAVES / waves + across - 1) / across);
     const dim3 grid((unsigned)across, (unsigned)nslices);
@@ -891,9 +889,7 @@ static void ex_launch_scan_t(const ExScanArgs& a, hipStream_t s)
 {
     const int nch = a.qbytes / EX_CHUNK;
     const size_t shm = (size_t)(RES ? nch : 2) * QT * EX_CHUNK + 2 * EX_RT * EX_CHUNK;
-    static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(ex_scan_kernel<F16, QT, RES, MODE>),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024), true);
-    (void)once;
+    tg_allow_lds<ex_scan_kernel<F16, QT, RES, MODE>>(64 * 1024);
     hipLaunchKernelGGL((ex_scan_kernel<F16, QT, RES, MODE>), dim3((unsigned)(a.nqb * a.nslices)), dim3(64 * EX_WAVES), shm, s, a);
 }
 template <bool F16, int MODE>

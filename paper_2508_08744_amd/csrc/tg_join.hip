@@ -1125,13 +1125,6 @@ static size_t join_lds_bytes(int DK, int rows)
     return JOIN_HDR_BYTES + JOIN_ADJ_BYTES + JOIN_CELL_BYTES + (size_t)rows * (DK + 4) * sizeof(float);
 }
 
-// LDS beyond 64 KB per workgroup has to be asked for once per kernel
-template <class K>
-static void allow_large_lds(K kernel, size_t bytes)
-{
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
 #define JOIN_BYTES_GRID 1536
 #define JOIN_GRID 2048     // persistent launches: workgroups walk the work list with this stride
 
@@ -1142,9 +1135,8 @@ template <int DK, int ROWS>
 static void launch_join_list(const TgGraph& g, const TgSample& sm, const TgCand& c, u64 hs_slot, u64* stat_bins, int list, int parts,
                              hipStream_t s)
 {
-    static bool once = (allow_large_lds(join_kernel<DK, 0, false, ROWS>, join_lds_bytes(DK, ROWS)),
-                        allow_large_lds(join_kernel<DK, 0, true, ROWS>, join_lds_bytes(DK, ROWS)), true);
-    (void)once;
+    tg_allow_lds<join_kernel<DK, 0, false, ROWS>>(join_lds_bytes(DK, ROWS));
+    tg_allow_lds<join_kernel<DK, 0, true, ROWS>>(join_lds_bytes(DK, ROWS));
     const int rows = sm.BC < ROWS ? sm.BC : ROWS;   // a stored block never exceeds BC rows
     const int64_t cap = wl_cap(g.n, parts);
     const unsigned grid = (unsigned)(cap < JOIN_GRID ? cap : JOIN_GRID);
@@ -1251,9 +1243,8 @@ void tg_launch_join(const TgGraph& g, const TgSample& sm, const TgCand& c, int p
 void tg_launch_join_distances(const TgGraph& g, const int32_t* blk, const int32_t* sizes, int64_t nb, float* out,
                               hipStream_t s)
 {
-    static bool once = (allow_large_lds(join_kernel<64, 1, false, TG_BLOCK_COLS>, join_lds_bytes(64, TG_BLOCK_COLS)),
-                        allow_large_lds(join_kernel<64, 1, true, TG_BLOCK_COLS>, join_lds_bytes(64, TG_BLOCK_COLS)), true);
-    (void)once;
+    tg_allow_lds<join_kernel<64, 1, false, TG_BLOCK_COLS>>(join_lds_bytes(64, TG_BLOCK_COLS));
+    tg_allow_lds<join_kernel<64, 1, true, TG_BLOCK_COLS>>(join_lds_bytes(64, TG_BLOCK_COLS));
     int skip_le = 0;
     if (wave_path(g)) {      // same routing by block size as the production join
         if (g.metric == 0) { launch_wave_dump<3, 0>(g, blk, sizes, nb, out, 0, s); launch_wave_dump<4, 0>(g, blk, sizes, nb, out, 4, s); }

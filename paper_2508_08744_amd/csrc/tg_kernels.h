@@ -3,12 +3,27 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 
 #define TG_BLOCK_COLS 128   // a join block holds at most 64 NEW rows and 128 rows in total
 #define TG_BLOCK_ROWS 64
 #define TG_STAT_BINS 1024   // spread of the per-round statistics counters
 #define TG_MAX_PARTS 8      // a phase-1 round is carried out in at most this many parts
 #define TG_WL_LISTS (3 * TG_MAX_PARTS)   // join work lists of a round: one per part and block-size class
+
+// More LDS than a kernel may have unasked has to be asked for, kernel by kernel, on every device that launches it.
+// asked: the devices that have been (one bit each; a device beyond the 64th is asked at every launch).
+bool tg_lds_unasked(uint64_t asked, int device);
+template <auto KERNEL>
+static inline void tg_allow_lds(size_t bytes)
+{
+    static std::atomic<uint64_t> asked{0};
+    int device = -1;
+    (void)hipGetDevice(&device);
+    if (!tg_lds_unasked(asked.load(std::memory_order_acquire), device)) return;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (device >= 0 && device < 64) asked.fetch_or(1ull << device, std::memory_order_release);
+}
 
 // One launch carries fewer than 2^32 work-items.  Kernels that give every node a wave (or a group
 // of lanes) of its own are therefore launched once per chunk of TG_LAUNCH_NODES nodes and told

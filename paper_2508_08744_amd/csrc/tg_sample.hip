@@ -423,10 +423,9 @@ void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hi
     if (chunk > (g.n + 255) / 256) chunk = (g.n + 255) / 256;
     chunk = (chunk + per_step - 1) / per_step * per_step;
     const unsigned grid = (unsigned)((g.n + chunk - 1) / chunk);
-    // LDS beyond 64 KB per workgroup has to be asked for (on the device in use)
     if (sm.nbuckets * sizeof(u32) > 65536) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(rev_bucket_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, TG_REV_BUCKETS * sizeof(u32));
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(rev_bucket_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, TG_REV_BUCKETS * sizeof(u32));
+        tg_allow_lds<rev_bucket_kernel<false>>(TG_REV_BUCKETS * sizeof(u32));
+        tg_allow_lds<rev_bucket_kernel<true>>(TG_REV_BUCKETS * sizeof(u32));
     }
     for (int pass = 0; pass < 2; ++pass) {
         for (int64_t b0 = 0; b0 < sm.nbuckets; b0 += TG_REV_BUCKETS) {

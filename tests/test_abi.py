@@ -199,3 +199,15 @@ def test_workspace_holds_no_copy_that_was_not_asked_for():
         assert abs(need(n, d, 32) - need(n, d, 32, screen=0) - n * ((d + 15) // 16 * 16)) < 4096
         for f16 in (1, 2):
             assert abs(need(n, d, 32, join_f16=f16) - need(n, d, 32) - 2 * n * ldh) < 4096
+
+
+def test_lds_is_asked_for_on_every_device():
+    """Kernels with more LDS than a launch may have unasked ask once per device, and at every launch beyond the 64th (an internal function
+    of the library: a process that moves on to a second device must ask there too)."""
+    from paper_2508_08744_amd import knn
+    f = knn.lib()._Z14tg_lds_unaskedmi
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_uint64, ctypes.c_int]
+    for device in (0, 1, 7, 63):
+        others = (2 ** 64 - 1) ^ (1 << device)
+        assert f(0, device) and f(others, device) and not f(1 << device, device) and not f(2 ** 64 - 1, device)
+    assert f(2 ** 64 - 1, 64) and f(2 ** 64 - 1, -1)
