@@ -118,9 +118,35 @@ def test_more_nodes_than_one_launch_can_carry():
 
 
 def test_reverse_samples_over_several_launches_of_the_bucket_step():
-    # 1.3 M nodes are 10 157 buckets of 128 targets, more than one launch of the bucket step counts in LDS (8 192):
-    # the step runs twice, each launch taking the edges whose targets it covers.  Tiny rows and lists keep the oracle
-    # fast; blocks around the border between the two launches and at both ends, then a whole round, bit for bit.
+    # More than 20 480 buckets of 2 048 targets, the widest there are, take two launches of the bucket step, each of which takes the edges
+    # whose targets it covers.  Every list is fresh, shorter than S, and nobody has more than R arrivals, so nothing is sampled away: a
+    # block holds exactly the node's own list and the nodes that list it.  Both ends and the border between the launches.
+    border = 20480 * 2048
+    n, d, k = border + 700_001, 4, 4
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    Xg = torch.randint(0, 64, (n, d), generator=gen, device="cuda").to(torch.float32)
+    prm = knn.default_params(k, 2, seed=3, C=16, parts=8)
+    b = knn.Builder(Xg, prm)
+    b.init()
+    ids = b.graph()[0].long()
+    blk, sizes = b.sample_blocks()
+    b.close()
+    assert int(sizes[:, 1].max()) == 0
+    for lo, hi in ((0, 3000), (border - 3000, border + 3000), (n - 3000, n)):
+        src, col = torch.nonzero((ids >= lo) & (ids < hi), as_tuple=True)
+        arrivals = torch.stack([ids[src, col], src], dim=1)
+        assert int(torch.bincount(arrivals[:, 0] - lo).max()) <= prm.R
+        own = torch.stack([torch.arange(lo, hi, device="cuda").repeat_interleave(k), ids[lo:hi].reshape(-1)], dim=1)
+        want = torch.unique(torch.cat([arrivals, own]), dim=0)
+        members = torch.arange(128, device="cuda")[None, :] < sizes[lo:hi, :1]
+        row, at = torch.nonzero(members, as_tuple=True)
+        got = torch.stack([row + lo, blk[lo:hi][row, at].long()], dim=1)
+        assert len(got) == len(want) and torch.equal(torch.unique(got, dim=0), want), lo
+
+
+def test_reverse_samples_of_ten_thousand_buckets():
+    # 1.3 M nodes are 10 157 buckets of 128 targets (with 40 KB of counters a launch).  Tiny rows and lists keep the oracle
+    # fast; blocks around the middle and at both ends, then a whole round, bit for bit.
     n, d, k = 1_300_000, 4, 4
     X = np.random.Generator(np.random.PCG64(11)).integers(0, 64, size=(n, d)).astype(np.float32)
     prm = knn.default_params(k, 2, seed=3, C=16)
