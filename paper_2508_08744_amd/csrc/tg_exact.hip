@@ -413,7 +413,9 @@ __device__ inline u32 ex_row(const ExScanArgs& a, u32 j)
 // is kept (EX_FIRST: place = number of the visit).
 // What bounds it is the vector work of a tile (bounds, maxima, the pairs that pass; about as long as its matrix instructions twice over) and
 // waits for rows, which sixteen waves on a CU cover better than eight with twice the tile each: 1M x 128 against 10 000 queries, fp16: 7.15 -> 5.0 ms
-// (512 TFLOP/s), the whole search 9.3 -> 7.1; 50 000 x 96 against 64 (fp32): 66 -> 62 us.
+// (512 TFLOP/s), the whole search 9.3 -> 7.1; 50 000 x 96 against 64 (fp32): 66 -> 62 us.  Where the queries come again (not RES, 128 of them) three to
+// seven registers spill at four waves per SIMD, which still is the better side: whole searches with four waves a workgroup / eight / eight, two per SIMD
+// and no spill: 200 000 x 960 against 2000 (fp16): 2.33 / 2.19 / 2.81 ms; 200 000 x 200 against 4000: 1.83 / 1.54 / 2.08; 1M x 96 against 100 (fp32): 543 / 531 / 571 us.
 // ---------------------------------------------------------------------------------------
 #define EX_WAVES 8
 template <bool F16, int QT, bool RES, int MODE>

@@ -4,9 +4,9 @@
 // A node's label is the smallest node number it can reach in a few steps over the first entries of the lists (a step takes the smallest label of
 // the node and of its closest neighbours, and the label's own label): nodes of one dense region share it.  The nodes are
 // then brought together by a hash of their label, in buckets of about a thousand.
-// 10M x 96 (cosine, 4 + 1 rounds): 4.8 ms for the order; fourth round's joins 57 -> 47, phase 2 40.6 -> 30, finalize 24.9 -> 13.3 ms.  200 000 x 960 (4 + 4):
-// 0.06 ms; a phase-2 round 2.6 -> 1.65, finalize 3.6 -> 1.5.  With ids sorted by the clusters the points were drawn from, which is
-// as good as an order gets: 23 and 11 ms, 1.45 and 1.3.
+// 10M x 96 (cosine, 4 + 1 rounds): 5 ms for the order; fourth round's joins 58.9 -> 53.5 ms, phase 2 40.5 -> 29.5, finalize 24.8 -> 13.4, the build
+// 526 -> 506.  200 000 x 960 (4 + 4): 0.07 ms; a phase-2 round 2.55 -> 1.66, finalize 3.6 -> 1.5, the build 61.3 -> 55.7.  With ids sorted by the clusters
+// the points were drawn from, which is as good as an order gets: phase 2 and finalize 23 and 11 ms, 1.45 and 1.3.
 // Measured choices (10M x 96: phase 2 / finalize): three steps over 4 entries 32.6 / 15.6, four over 4 31.1 / 14.2, six over 4 30.1 / 13.2 (200 000 x 960: 1.6 / 1.43),
 // three over 8 31.0 / 14.2, four over 8 30.0 / 13.3 and the fewest launches; over 2 entries worse with any number of steps.
 #include "tg_kernels.h"
@@ -60,8 +60,9 @@ __global__ __launch_bounds__(ORDER_THREADS) void order_kernel(TgGraph g, const u
     for (int64_t v = beg + threadIdx.x; v < end; v += ORDER_THREADS) order[atomicAdd(&hist[bucket(v)], 1u)] = (u32)v;
 }
 
-// Rows of at least 96 values, 8 M values in all: 100 000 x 128 builds in 6.48 -> 6.31 ms, 30 000 x 500 5.19 -> 4.91, 1M x 128 70.7 -> 67.7 (5 + 5 rounds);
-// below, the order costs what it gives (30 000 x 128: 0.995 of the time before, 300 000 x 64 1.007, 1M x 32 1.03).
+// Rows of at least 96 values, 8 M values in all: 100 000 x 128 builds in 7.03 -> 6.94 ms, 30 000 x 500 6.46 -> 5.58, 1M x 128 76.1 -> 74.3 (5 + 5 rounds).
+// Below, it is worth less the shorter the rows and costs what it gives: 400 000 x 92 24.1 -> 23.6, 300 000 x 64 15.60 -> 15.63, 1M x 32 49.0 -> 49.6; and at few
+// values 87 382 x 96 5.75 -> 5.73, 30 000 x 128 2.62 -> 2.63.
 bool tg_order_pays(int64_t n, int ld) { return ld >= 96 && n * ld >= (int64_t)8 << 20; }
 // in bytes: the two arrays of labels, the buckets' places and counts
 size_t tg_order_space(int64_t n) { return (size_t)(2 * n + 3 * ORDER_MAX_BUCKETS + 4) * sizeof(u32); }

@@ -445,8 +445,9 @@ void tg_launch_reverse(const TgGraph& g, const TgSample& sm, uint64_t hs_rev, hi
     if (g.order) hipLaunchKernelGGL(wl_order_kernel, dim3((unsigned)((g.n + 256 * WLO_EACH - 1) / (256 * WLO_EACH))), dim3(256), 0, s, g, sm);
 }
 // Buckets of 2^shift targets: the smallest (16 at least) of which one launch of the bucket step takes all, because a workgroup of
-// the selection serves a bucket and n / 2^shift of them have to fill the chip; at 1M nodes that is 128.  More where the bucket step would
-// otherwise need more than four launches, each of which reads every list.
+// the selection serves a bucket and n / 2^shift of them have to fill the chip; at 1M nodes that is 128.  More where one launch of the
+// bucket step could not take them (n > 2.6 M): a second one reads every list again.  A round's samples and blocks, against buckets half as wide in two
+// launches: 3M nodes, k = 32: 4.6 / 5.1 ms; 4M, k = 16: 3.65 / 4.2; 6M, k = 32: 9.45 / 10.4; 8M, k = 16: 7.5 / 8.2.
 int tg_rev_bucket_shift(int64_t n)
 {
     int sh = 4;
