@@ -941,8 +941,8 @@ __global__ __launch_bounds__(256) void join_wave_kernel(TgGraph g, TgSample sm, 
 // matrix instructions of 16 cycles instead of 32 of 32, a block of 64 members 32 registers instead of 128.
 // One wave per anchor, blocks of at most 64 members (lists 1 and 0 of the part); register layout, cells and hand-over
 // as in join_wave_kernel.  |c|^2 of every member comes off the diagonal of its group's own tile.
-// 1M x 128, k = 32: the joins of the four rounds take 4.7 + 2.5 + 2.6 + 3.6 ms (8.9 + 5.9 + 6.0 + 6.9 in fp32, 5.8 + 3.3 + 3.5 + 4.9 on the
-// fp16 copy); in the first round what bounds it is the minima in LDS, eight lanes at a time on one cell.
+// 1M x 128, k = 32: the joins of the four rounds take 4.7 + 2.5 + 2.7 + 2.9 ms, blocks of more than 64 members among them (the same points moved by a
+// quarter: 27.4 ms in fp32, 15.4 on the fp16 copy); in the first round what bounds it is the minima in LDS, eight lanes at a time on one cell.
 // ---------------------------------------------------------------------------------------
 typedef int intx4 __attribute__((ext_vector_type(4)));
 #define BYTES_FAR (1 << 28)          // the norm of a row that must not count: its distances are beyond BYTES_MOST
