@@ -17,6 +17,7 @@ struct ExScanArgs {
     int32_t metric;
     int32_t rowbytes, qbytes;        // bytes of a stored row; of a packed query (whole chunks)
     int32_t nqb, nslices;            // query tiles and row slices of the launch
+    int32_t wqs;                     // ex_scan_wave_kernel: waves of a workgroup side by side over the queries
     float c1;                        // see ex_margin
     const unsigned char* rows;       // fp16 or fp32 rows
     const float* rn;                 // squared norm of every row, in the units of `rows`

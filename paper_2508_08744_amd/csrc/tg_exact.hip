@@ -672,6 +672,174 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
     if (!ALL) flush();
 }
 
+// ---------------------------------------------------------------------------------------
+// The scan of fp16 rows of at most 256 bytes, all rows (EX_FULL) or a sample of them.  A wave keeps 64 queries in registers, in matrix
+// operand layout (lane (r, q) holds piece 4 s + q of query 16 j + r: 16 KS registers), and meets one group of 16 rows after the other;
+// only the rows go through LDS, 64 at a time in two buffers, a row's 16-byte pieces permuted so that neither the stores nor the
+// operand reads meet in a bank.  The four waves of a workgroup stand side by side over the queries, or over two or four shares of the
+// rows of a tile where there are fewer queries (a.wqs: waves over the queries).
+// A group of 16 x 64 pairs costs 4 KS matrix instructions, KS operand reads, and on the vector units two maxima and a compare for each
+// 16 queries: the thresholds are taken for the 64 rows of a tile (the bound of a pair is made of the largest norm and the largest
+// residual among them: a little looser than a row's own, no pair is lost).
+// Pairs that pass wait in a queue of the wave's own and go to the lists up to 64 at a time and more (see ex_scan_kernel).
+// 1M x 128 against 10 000 queries: 5.75 ms with the queries in LDS and each row read for 128 of them, 0.73 the sample; now both 3.95, of
+// which 1.2 go to the pairs that pass (700 a query in either), the rest runs at 1.0 PFLOP/s (matrix units busy half the cycles; a
+// library product of this size: 1.15).  Rows 128 at a time with two waves per SIMD: 0.2 ms more; the next group's operands asked for ahead: no
+// gain with two waves, spills with three.
+// ---------------------------------------------------------------------------------------
+#define EXG_RT 64            // rows of a tile
+#define EXG_QUEUE 320        // pairs a wave collects before they go to the lists: 64 and the 256 of a 16 x 16 tile
+template <int KS, bool SAMPLE>
+__global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
+{
+    constexpr int PIECES = 4 * KS;                                      // of a row
+    constexpr int UNITS = EXG_RT * PIECES / 256;                        // pieces of a tile per thread
+    __shared__ floatx4 s_tile[2][EXG_RT * PIECES];
+    __shared__ __align__(16) float s_c0[2][EXG_RT];                     // where a row's sums start: -|r|^2 / 2 (or 0; -inf past the end)
+    __shared__ float s_R[2], s_E[2];
+    __shared__ u64 s_queue[4][EXG_QUEUE];                               // ordered w << 32 | visit within the slice << 6 | query within the wave's
+    __shared__ u32 s_full[256];                                         // the query's list is full: it is measured another way
+    __shared__ int s_self[256];                                         // the query's own row
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int r16 = lane & 15, q4 = lane >> 4;
+    const int wqs = a.wqs, wq = wave & (wqs - 1), wr = wave / wqs;
+    const int qb = (int)(blockIdx.x % (unsigned)a.nqb), slice = (int)(blockIdx.x / (unsigned)a.nqb);
+    const int tiles = (int)((a.nvisit + EXG_RT - 1) / EXG_RT);
+    const int per = (tiles + a.nslices - 1) / a.nslices;
+    const int t0 = slice * per, t1 = min(tiles, t0 + per);
+    if (t0 >= t1) return;
+    const int nvisit = (int)a.nvisit;
+    const int64_t q0 = (int64_t)qb * (64 * wqs);                        // the workgroup's first query, and this wave's first among them
+    const int qw = wq * 64;
+
+    halfx8 fq[4][KS];
+    float ntau[4], qa[4], qe[4], kq[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int64_t q = q0 + qw + 16 * j + r16;
+        const bool some = q < a.nq;
+        const int64_t qc = some ? q : 0;
+        const float4 m = a.qmeta[qc];
+        qa[j] = m.x; qe[j] = m.y; kq[j] = a.c1 * m.z;
+        ntau[j] = -__builtin_inff();
+        if (!(m.z < __builtin_inff())) qa[j] = qe[j] = kq[j] = 0.0f;    // a query without a defined norm: everything passes
+        else ntau[j] = -a.tau[qc];
+        if (!some || a.qrow[qc] < 0) ntau[j] = __builtin_inff();        // no query: nothing passes
+        const unsigned char* src = a.Q + qc * (int64_t)a.qbytes + q4 * 16;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) fq[j][s] = *reinterpret_cast<const halfx8*>(src + 64 * s);
+    }
+
+    // the rows of the next tile: registers first, LDS once the tile before the last is done with
+    floatx4 pre[UNITS];
+    float pre_rn = 0.0f, pre_er = 0.0f;
+    auto row_of = [&](int j) __attribute__((always_inline)) { return ex_row<SAMPLE>(a, (u32)min(j, nvisit - 1)); };
+    // sixteen rows' pieces of one number lie in the sixteen 16-byte columns of the 64 banks
+    auto swizzle = [](int row) __attribute__((always_inline)) { return KS == 4 ? row & 15 : KS == 2 ? (row >> 1) & 7 : (row >> 2) & 3; };
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < UNITS; ++it) {
+            const int u = tid + 256 * it, row = u / PIECES, off = ((u - row * PIECES) ^ swizzle(row)) * 16;
+            pre[it] = *reinterpret_cast<const floatx4*>(a.rows + (int64_t)row_of(t * EXG_RT + row) * (64 * KS) + off);
+        }
+        if (tid < EXG_RT) {
+            const u32 r = row_of(t * EXG_RT + tid);
+            pre_rn = a.rn[r];
+            pre_er = a.er[r];
+        }
+    };
+    auto store = [&](int t, int par) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < UNITS; ++it) s_tile[par][tid + 256 * it] = pre[it];
+        if (tid < EXG_RT) {
+            const bool real = t * EXG_RT + tid < nvisit;
+            // a row without a defined norm: EX_ALWAYS takes it past any threshold, and its neighbours keep theirs (see ex_scan_kernel)
+            const bool undefined = !(pre_rn < __builtin_inff());
+            s_c0[par][tid] = !real ? -__builtin_inff() : undefined ? EX_ALWAYS : a.metric == 0 ? -0.5f * pre_rn : 0.0f;
+            float R = undefined ? 0.0f : sqrtf(pre_rn), E = undefined ? 0.0f : pre_er;
+#pragma unroll
+            for (int o = 1; o < EXG_RT; o <<= 1) {
+                R = fmaxf(R, __shfl_xor(R, o));
+                E = fmaxf(E, __shfl_xor(E, o));
+            }
+            if (tid == 0) { s_R[par] = R * 1.0001f; s_E[par] = E; }
+        }
+    };
+
+    s_full[tid] = 0u;                                                   // (seen by everyone behind the first barrier of the loop)
+    s_self[tid] = tid < 64 * wqs && q0 + tid < a.nq ? a.qrow[q0 + tid] : -1;
+    int nqueue = 0;
+    auto flush = [&]() __attribute__((always_inline)) {
+        ex_sync();
+        for (int b = 0; b < nqueue; b += 64) {
+            if (b + lane < nqueue) {
+                const u64 e = s_queue[wave][b + lane];
+                const u32 ql = (u32)qw + ((u32)e & 63u), visit = (u32)(t0 * EXG_RT) + ((u32)e >> 6);
+                const int64_t q = q0 + ql;
+                const u32 r = row_of((int)visit);
+                if (visit < (u32)nvisit && r != (u32)s_self[ql]) {
+                    const u32 pos = atomicAdd(a.cnt + q * EX_CSTRIDE, 1u);
+                    if (pos < EX_CAP) a.buf[q * EX_CAP + pos] = (e & 0xFFFFFFFF00000000ull) | r;
+                    else s_full[ql] = 1u;
+                }
+            }
+        }
+        nqueue = 0;
+        ex_sync();
+    };
+
+    const u64 below = tg_lanemask_lt();
+    fetch(t0);
+    for (int t = t0; t < t1; ++t) {
+        const int par = (t - t0) & 1;
+        store(t, par);
+        __syncthreads();
+        if (t + 1 < t1) fetch(t + 1);
+        float thr[4];
+        {
+            const float R = s_R[par], E = s_E[par];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) thr[j] = ntau[j] - ex_margin(qa[j], qe[j], kq[j], R, E, a.c1);
+        }
+#pragma unroll 1
+        for (int i = wr * wqs; i < (wr + 1) * wqs; ++i) {              // (64 rows are four groups: wqs of them for each of the 4 / wqs shares)
+            const int row = 16 * i + r16;
+            halfx8 fr[KS];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) fr[s] = __builtin_bit_cast(halfx8, s_tile[par][row * PIECES + ((4 * s + q4) ^ swizzle(row))]);
+            const floatx4 c0 = *reinterpret_cast<const floatx4*>(&s_c0[par][16 * i + 4 * q4]);
+            floatx4 acc[4];
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr[s], fq[j][s], s ? acc[j] : c0, 0, 0, 0);
+            // -w of every pair against -tau - m
+            u64 hit[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) hit[j] = __ballot(fmaxf(fmaxf(acc[j][0], acc[j][1]), fmaxf(acc[j][2], acc[j][3])) >= thr[j]);
+            if ((hit[0] | hit[1] | hit[2] | hit[3]) == 0ull) continue;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (hit[j] == 0ull) continue;
+                if (nqueue > EXG_QUEUE - 256) flush();
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool pass = acc[j][e] >= thr[j];
+                    const u64 m = __ballot(pass);
+                    if (m == 0ull) continue;
+                    const u32 tag = (u32)(((t - t0) * EXG_RT + 16 * i + 4 * q4 + e) << 6) | (u32)(16 * j + r16);
+                    if (pass) s_queue[wave][nqueue + __popcll(m & below)] = ((u64)tg_ord(-acc[j][e]) << 32) | tag;
+                    nqueue += __popcll(m);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (s_full[qw + 16 * j + r16]) ntau[j] = __builtin_inff();
+    }
+    flush();
+}
+
 // The k-th smallest of count keys key_of(i), found by the four waves of a workgroup: waves take every fourth batch of
 // 64, batches without a key below the wave's k-th so far are passed over, the four sorted lists are merged.  s_top: 3 x 64 words.
 // Wave 0 returns the 64 smallest keys, ascending; the others an empty list.
@@ -894,9 +1062,36 @@ static void ex_launch_scan_t(const ExScanArgs& a, hipStream_t s)
     tg_allow_lds<ex_scan_kernel<F16, QT, RES, MODE>>(64 * 1024);
     hipLaunchKernelGGL((ex_scan_kernel<F16, QT, RES, MODE>), dim3((unsigned)(a.nqb * a.nslices)), dim3(64 * EX_WAVES), shm, s, a);
 }
+template <bool SAMPLE>
+static void ex_launch_scan_wave(ExScanArgs a, hipStream_t s)
+{
+    // 256, 128 or 64 queries to a workgroup (rows are fetched once for all of them): the most that need at most a fifteenth more places
+    auto padded = [&](int wqs) { return (a.nq + 64 * wqs - 1) / (64 * wqs) * (64 * wqs); };
+    a.wqs = 4;
+    while (padded(a.wqs) * 15 > padded(1) * 16) a.wqs /= 2;
+    a.nqb = (int)(padded(a.wqs) / (64 * a.wqs));
+    const int64_t tiles = (a.nvisit + EXG_RT - 1) / EXG_RT;
+    // three workgroups per CU at a time, three times over; a place in a slice has 26 bits in the queue, and 16384 queries leave 36 slices
+    int64_t slices = 2304 / a.nqb;
+    if (slices < 1) slices = 1;
+    a.nslices = (int)(slices < tiles ? slices : tiles);
+    const dim3 grid((unsigned)(a.nqb * a.nslices)), block(256);
+    switch (a.rowbytes >> 6) {
+    case 1: hipLaunchKernelGGL((ex_scan_wave_kernel<1, SAMPLE>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((ex_scan_wave_kernel<2, SAMPLE>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((ex_scan_wave_kernel<3, SAMPLE>), grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL((ex_scan_wave_kernel<4, SAMPLE>), grid, block, 0, s, a); break;
+    }
+}
 template <bool F16, int MODE>
 static void ex_launch_scan_m(ExScanArgs a, hipStream_t s)
 {
+    if constexpr (F16 && MODE != EX_FIRST) {
+        if (a.qbytes <= 2 * EX_CHUNK) {
+            ex_launch_scan_wave<MODE == EX_SAMPLE>(a, s);
+            return;
+        }
+    }
     const bool wide = a.nq > 64;
     const int qt = wide ? 128 : 64;
     a.nqb = (int)((a.nq + qt - 1) / qt);
@@ -904,14 +1099,15 @@ static void ex_launch_scan_m(ExScanArgs a, hipStream_t s)
     int64_t slices = (2048 + a.nqb - 1) / a.nqb;                       // two workgroups per CU at a time, a few times over
     a.nslices = (int)(slices < tiles ? slices : tiles);
     if (a.nslices < 1) a.nslices = 1;
-    const bool res = a.qbytes <= 2 * EX_CHUNK;
-    if (wide) {
-        if (res) ex_launch_scan_t<F16, 128, true, MODE>(a, s);
-        else ex_launch_scan_t<F16, 128, false, MODE>(a, s);
-    } else {
-        if (res) ex_launch_scan_t<F16, 64, true, MODE>(a, s);
-        else ex_launch_scan_t<F16, 64, false, MODE>(a, s);
+    if constexpr (!F16 || MODE == EX_FIRST) {
+        if (a.qbytes <= 2 * EX_CHUNK) {
+            if (wide) ex_launch_scan_t<F16, 128, true, MODE>(a, s);
+            else ex_launch_scan_t<F16, 64, true, MODE>(a, s);
+            return;
+        }
     }
+    if (wide) ex_launch_scan_t<F16, 128, false, MODE>(a, s);
+    else ex_launch_scan_t<F16, 64, false, MODE>(a, s);
 }
 template <bool F16>
 static void ex_launch_scan_f(const ExScanArgs& a, int mode, hipStream_t s)

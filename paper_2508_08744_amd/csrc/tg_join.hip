@@ -630,8 +630,10 @@ struct WaveShared {
 // NARROW: the rows come from the fp16 copy (g.Xh, rows of 32 KS values, zero padded): a register
 // then holds eight values, columns 32 s + 8 q .. + 7, and a tile step is one
 // v_mfma_f32_16x16x32_f16 (fp32 accumulation) in place of eight fp32 matrix instructions.
+// Waves per SIMD that the compiler must leave room for.
+__host__ __device__ constexpr int wave_least(int gmax, int ks) { return gmax * ks <= 18 ? 3 : 2; }
 template <int GMAX, int MODE, int METRIC, int KS, bool FULL, bool NARROW>
-__global__ __launch_bounds__(256) void join_wave_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins,
+__global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins,
                                                         const int32_t* xblk, const int32_t* xsizes, float* xout,
                                                         const u64* __restrict__ wl, const u32* __restrict__ wl_cnt,
                                                         int64_t direct_count, int gmin)
@@ -954,7 +956,7 @@ struct BytesShared {
     u32 adj[64][2];
 };
 template <int KS>
-__global__ __launch_bounds__(256) void join_bytes_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins, int part, int64_t cap)
+__global__ __launch_bounds__(256, 4) void join_bytes_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins, int part, int64_t cap)
 {
     __shared__ __align__(16) BytesShared shs[4];
     if (!tg_whole_bytes(g.bytes, g.d)) return;
@@ -1125,7 +1127,7 @@ static size_t join_lds_bytes(int DK, int rows)
     return JOIN_HDR_BYTES + JOIN_ADJ_BYTES + JOIN_CELL_BYTES + (size_t)rows * (DK + 4) * sizeof(float);
 }
 
-#define JOIN_BYTES_GRID 1536
+#define JOIN_BYTES_GRID 2048
 #define JOIN_GRID 2048     // persistent launches: workgroups walk the work list with this stride
 
 static int64_t wl_cap(int64_t n, int parts) { return (n + parts - 1) / parts; }
@@ -1163,7 +1165,8 @@ static void launch_wave_k(const TgGraph& g, const TgSample& sm, const TgCand& c,
 {
     const int64_t cap = wl_cap(g.n, parts);
     const int64_t wgs = (cap + 3) / 4;
-    const unsigned grid = (unsigned)(wgs < JOIN_GRID ? wgs : JOIN_GRID);
+    constexpr int most = wave_least(GMAX, KS) * 768;          // whole rounds of the workgroups that are resident together
+    const unsigned grid = (unsigned)(wgs < most ? wgs : most);
     const size_t shm = 4 * sizeof(WaveShared);
     // with the device flag both variants are launched, and the one it does not name ends at once
     if (g.Xh)       // rows of the fp16 copy are whole steps of 32 values: KS / 2 of them

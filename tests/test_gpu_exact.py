@@ -166,10 +166,11 @@ def test_exact_f16_neighbours_of_rows_without_a_bound(metric, kind):
 
 
 # The search on fp16 rows: every query against the search on fp32 rows (static, which never narrows), some against the oracle.  Rows of less than
-# a step, of whole steps, of one value more, queries too long to stay in LDS, and queries that end within a tile.
+# a step, of one to four whole steps, of one value more, queries too long to stay in LDS, queries that end within a tile, and 64, 128 and 256
+# queries to a workgroup.
 @pytest.mark.parametrize("n,d,k,nq,metric", [
     (140000, 16, 64, 1000, "l2"), (80000, 32, 1, 1000, "ip"), (60001, 36, 33, 999, "cosine"), (40000, 96, 10, 640, "l2"),
-    (33001, 128, 32, 513, "ip"), (33001, 132, 32, 513, "l2"), (20000, 300, 16, 400, "cosine"), (9001, 500, 5, 500, "ip"), (12000, 1200, 10, 150, "l2")])
+    (33001, 128, 32, 513, "ip"), (200003, 64, 20, 160, "l2"), (100001, 100, 3, 300, "ip"), (70001, 68, 50, 500, "cosine"), (33001, 132, 32, 513, "l2"), (20000, 300, 16, 400, "cosine"), (9001, 500, 5, 500, "ip"), (12000, 1200, 10, 150, "l2")])
 @pytest.mark.parametrize("whole", [True, False])
 def test_exact_f16_edges(n, d, k, nq, metric, whole):
     rng = np.random.default_rng(n + d)
