@@ -108,50 +108,31 @@ __device__ inline u64 tg_sort_level(u64 key, int lane)
     if (SIZE >= 4) key = tg_cmpx(key, tg_partner<1>(key), (lane & 1) == 0);
     return key;
 }
-// Ascending bitonic sort of one key per lane across the wave.
-__device__ inline u64 tg_wave_sort(u64 key)
+// The lane's number, worked out where it is asked for: its six masks, kept across the loop around a network, cost phase 2 and the
+// two-hop collection the registers that they have least of.
+__device__ inline int tg_lane_here()
 {
-    const int lane = tg_lane();
+    int lane = tg_lane();
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+// Ascending bitonic sort of one key per lane across the wave (HALVES: across each half of it), every exchange on whole keys.
+template <bool HALVES>
+__device__ inline u64 tg_wave_sort_whole(u64 key)
+{
+    const int lane = tg_lane_here();
     key = tg_sort_level<2>(key, lane);
     key = tg_sort_level<4>(key, lane);
     key = tg_sort_level<8>(key, lane);
     key = tg_sort_level<16>(key, lane);
     key = tg_sort_level<32>(key, lane);
-    key = tg_sort_level<64>(key, lane);
+    if (!HALVES) key = tg_sort_level<64>(key, lane);
     return key;
 }
 
-// The same where only the first `count` lanes (uniform) hold keys and the others the empty key, which stays behind: the
-// levels that reach across rows of 16 lanes go through the LDS crossbar and are left out when they have nothing to do.
-// (The list updates of a 1M x 128 build: 6.97 -> 6.86 ms; they are bound by their slot rows, 4.3 TB/s in the first round.)
-__device__ inline u64 tg_wave_sort_first(u64 key, int count)
-{
-    const int lane = tg_lane();
-    key = tg_sort_level<2>(key, lane);
-    key = tg_sort_level<4>(key, lane);
-    key = tg_sort_level<8>(key, lane);
-    key = tg_sort_level<16>(key, lane);
-    if (count > 16) key = tg_sort_level<32>(key, lane);
-    if (count > 32) key = tg_sort_level<64>(key, lane);
-    return key;
-}
-
-// a and b are ascending across the wave; returns the 64 smallest keys of their union,
-// ascending (the wave-level form of the rank merge of section 4.2).
-__device__ inline u64 tg_wave_merge_low(u64 a, u64 b)
-{
-    const int lane = tg_lane();
-    u64 x = tg_min64(a, tg_partner<63>(b));
-    x = tg_cmpx(x, tg_partner<32>(x), (lane & 32) == 0);
-    x = tg_cmpx(x, tg_partner<16>(x), (lane & 16) == 0);
-    x = tg_cmpx(x, tg_partner<8>(x), (lane & 8) == 0);
-    x = tg_cmpx(x, tg_partner<4>(x), (lane & 4) == 0);
-    x = tg_cmpx(x, tg_partner<2>(x), (lane & 2) == 0);
-    x = tg_cmpx(x, tg_partner<1>(x), (lane & 1) == 0);
-    return x;
-}
-
-// The same network on 32-bit keys: compare-exchange is one v_min / v_max with a DPP operand.
+// ---- networks on 32-bit keys: an exchange is a move (DPP inside a row of 16 lanes, a lane swap across rows) and a median of three, the
+// third being 0 in the lane that keeps the smaller key and all ones in the one that keeps the larger.  (A whole key takes two moves, a
+// compare, a mask operation and two selects, across rows two trips through the LDS crossbar.)
 template <int CTRL>
 __device__ inline u32 tg_dpp32(u32 x)
 {
@@ -162,36 +143,119 @@ __device__ inline u32 tg_partner32(u32 x)
 {
     if (XOR == 1) return tg_dpp32<0xB1>(x);
     if (XOR == 2) return tg_dpp32<0x4E>(x);
-    if (XOR == 3) return tg_dpp32<0x1B>(x);
-    if (XOR == 4) return tg_dpp32<0x1B>(tg_dpp32<0x141>(x));
     if (XOR == 7) return tg_dpp32<0x141>(x);
-    if (XOR == 8) return tg_dpp32<0x128>(x);
-    if (XOR == 15) return tg_dpp32<0x140>(x);
-    return (u32)__shfl_xor((int)x, XOR);
+    return tg_dpp32<0x140>(x);          // 15
 }
-__device__ inline u32 tg_cmpx32(u32 key, u32 other, bool keep_min) { return keep_min ? min(key, other) : max(key, other); }
-template <int SIZE>
-__device__ inline u32 tg_sort_level32(u32 key, int lane)
+__device__ inline u32 tg_median32(u32 a, u32 b, u32 c) { return max(min(a, b), min(max(a, b), c)); }
+// all ones where bit J of the lane is set
+template <int J>
+__device__ inline u32 tg_lane_bit(int lane) { return (lane & J) ? 0xFFFFFFFFu : 0u; }
+// lane ^ J for J = 1, 2, 4, 8, 16, 32; lane ^ J mirrored inside its group for J = 3, 7, 15; the lane with the upper half of bits keeps the larger key
+template <int J>
+__device__ inline u32 tg_exchange32(u32 x, int lane)
 {
-    key = tg_cmpx32(key, tg_partner32<SIZE - 1>(key), (lane & (SIZE >> 1)) == 0);
-    if (SIZE >= 64) key = tg_cmpx32(key, tg_partner32<16>(key), (lane & 16) == 0);
-    if (SIZE >= 32) key = tg_cmpx32(key, tg_partner32<8>(key), (lane & 8) == 0);
-    if (SIZE >= 16) key = tg_cmpx32(key, tg_partner32<4>(key), (lane & 4) == 0);
-    if (SIZE >= 8) key = tg_cmpx32(key, tg_partner32<2>(key), (lane & 2) == 0);
-    if (SIZE >= 4) key = tg_cmpx32(key, tg_partner32<1>(key), (lane & 1) == 0);
-    return key;
+    if (J == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return tg_median32(r[0], r[1], tg_lane_bit<32>(lane));
+    }
+    if (J == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return tg_median32(r[0], r[1], tg_lane_bit<16>(lane));
+    }
+    if (J == 15) return tg_median32(x, tg_dpp32<0x140>(x), tg_lane_bit<8>(lane));
+    if (J == 8) return tg_median32(x, tg_dpp32<0x128>(x), tg_lane_bit<8>(lane));
+    if (J == 7) return tg_median32(x, tg_dpp32<0x141>(x), tg_lane_bit<4>(lane));
+    if (J == 4) return tg_median32(x, tg_dpp32<0x1B>(tg_dpp32<0x141>(x)), tg_lane_bit<4>(lane));
+    if (J == 3) return tg_median32(x, tg_dpp32<0x1B>(x), tg_lane_bit<2>(lane));
+    if (J == 2) return tg_median32(x, tg_dpp32<0x4E>(x), tg_lane_bit<2>(lane));
+    return tg_median32(x, tg_dpp32<0xB1>(x), tg_lane_bit<1>(lane));
 }
-// Ascending bitonic sort of one 32-bit key per lane across the wave.
-__device__ inline u32 tg_wave_sort32(u32 key)
+// sorts every group of 2 J lanes whose keys are bitonic
+template <int J>
+__device__ inline u32 tg_clean32(u32 x, int lane)
 {
-    const int lane = tg_lane();
-    key = tg_sort_level32<2>(key, lane);
-    key = tg_sort_level32<4>(key, lane);
-    key = tg_sort_level32<8>(key, lane);
-    key = tg_sort_level32<16>(key, lane);
-    key = tg_sort_level32<32>(key, lane);
-    key = tg_sort_level32<64>(key, lane);
-    return key;
+    if (J >= 32) x = tg_exchange32<32>(x, lane);
+    if (J >= 16) x = tg_exchange32<16>(x, lane);
+    if (J >= 8) x = tg_exchange32<8>(x, lane);
+    if (J >= 4) x = tg_exchange32<4>(x, lane);
+    if (J >= 2) x = tg_exchange32<2>(x, lane);
+    return tg_exchange32<1>(x, lane);
+}
+// Ascending sort across the wave of the keys of the first `count` lanes (uniform), the others holding all ones or at least nothing smaller.
+__device__ inline u32 tg_wave_sort32_first(u32 x, int count)
+{
+    const int lane = tg_lane_here();
+    // (odd rows run backwards, by inverted keys, for the level of 32, the upper half for the level of 64)
+    if (count > 16) x ^= tg_lane_bit<16>(lane);
+    x = tg_exchange32<1>(x, lane);
+    x = tg_exchange32<1>(tg_exchange32<3>(x, lane), lane);
+    x = tg_clean32<2>(tg_exchange32<7>(x, lane), lane);
+    x = tg_clean32<4>(tg_exchange32<15>(x, lane), lane);
+    if (count > 16) {
+        x ^= tg_lane_bit<16>(lane);
+        if (count > 32) x ^= tg_lane_bit<32>(lane);
+        x = tg_clean32<16>(x, lane);
+        if (count > 32) x = tg_clean32<32>(x ^ tg_lane_bit<32>(lane), lane);
+    }
+    return x;
+}
+__device__ inline u32 tg_wave_sort32(u32 x) { return tg_wave_sort32_first(x, 64); }
+
+// the key of the lane before (the first: 0) and behind (the last: all ones); HALVES: the two halves of the wave are strangers
+template <bool HALVES>
+__device__ inline u64 tg_lane_before(u64 x)
+{
+    const u32 lo = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)x, 0x138, 0xF, 0xF, false);
+    const u32 hi = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)(x >> 32), 0x138, 0xF, 0xF, false);
+    const u64 y = ((u64)hi << 32) | lo;
+    return HALVES && tg_lane() == 32 ? 0ull : y;
+}
+template <bool HALVES>
+__device__ inline u64 tg_lane_behind(u64 x)
+{
+    const u32 lo = (u32)__builtin_amdgcn_update_dpp(-1, (int)(u32)x, 0x130, 0xF, 0xF, false);
+    const u32 hi = (u32)__builtin_amdgcn_update_dpp(-1, (int)(u32)(x >> 32), 0x130, 0xF, 0xF, false);
+    const u64 y = ((u64)hi << 32) | lo;
+    return HALVES && tg_lane() == 31 ? ~0ull : y;
+}
+// Whole keys by a network on 32-bit ones: the upper 26 bits of a key (of a distance: sign, exponent, 17 bits) with its lane below are
+// sorted, the keys fetched in that order, and looked over: keys that agree in those bits may still stand the wrong way round.  One or
+// two exchanges of neighbours put a pair or three of them right; more (masses of equal distances) go through the network of whole keys.
+__device__ inline u32 tg_short_key(u64 key) { return ((u32)(key >> 32) & ~63u) | (u32)tg_lane(); }
+template <bool HALVES>
+__device__ inline u64 tg_fetch_sorted(u64 key, u32 order)
+{
+    const int at = (int)(order << 2) & 252;
+    const u32 lo = (u32)__builtin_amdgcn_ds_bpermute(at, (int)(u32)key);
+    const u32 hi = (u32)__builtin_amdgcn_ds_bpermute(at, (int)(u32)(key >> 32));
+    u64 x = ((u64)hi << 32) | lo;
+    if (__ballot(x < tg_lane_before<HALVES>(x)) == 0ull) return x;
+    const bool odd = (tg_lane() & 1) != 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        x = odd ? tg_min64(x, tg_lane_behind<HALVES>(x)) : tg_max64(x, tg_lane_before<HALVES>(x));
+        x = tg_cmpx(x, tg_partner<1>(x), !odd);
+    }
+    if (__ballot(x < tg_lane_before<HALVES>(x)) == 0ull) return x;
+    return tg_wave_sort_whole<HALVES>(x);
+}
+// Ascending sort across the wave where only the first `count` lanes (uniform) hold keys and the others the empty key, which stays behind.
+__device__ inline u64 tg_wave_sort_first(u64 key, int count) { return tg_fetch_sorted<false>(key, tg_wave_sort32_first(tg_short_key(key), count)); }
+__device__ inline u64 tg_wave_sort(u64 key) { return tg_wave_sort_first(key, 64); }
+
+// a and b are ascending across the wave; returns the 64 smallest keys of their union,
+// ascending (the wave-level form of the rank merge of section 4.2).
+__device__ inline u64 tg_wave_merge_low(u64 a, u64 b)
+{
+    const u64 x = tg_min64(a, tg_partner<63>(b));
+    return tg_fetch_sorted<false>(x, tg_clean32<32>(tg_short_key(x), tg_lane_here()));
+}
+// the same two for each half of the wave by itself: 32 keys a half
+__device__ inline u64 tg_half_sort(u64 key) { return tg_fetch_sorted<true>(key, tg_wave_sort32_first(tg_short_key(key), 32)); }
+__device__ inline u64 tg_half_merge_low(u64 a, u64 b)
+{
+    const u64 x = tg_min64(a, tg_partner<31>(b));
+    return tg_fetch_sorted<true>(x, tg_clean32<16>(tg_short_key(x), tg_lane_here()));
 }
 
 __device__ inline u64 tg_lanemask_lt() { return (1ull << tg_lane()) - 1ull; }

@@ -672,14 +672,63 @@ void tg_launch_init(const TgGraph& g, uint64_t hs_init, hipStream_t s)
 // ---------------------------------------------------------------------------------------
 #define UPDATE_MAX_C 256
 #define UPDATE_SET_WORDS 512     // more than 64 + UPDATE_MAX_C ids
+#define UPDATE_PLACES 1024       // update_settle: places that ids are hashed to, a byte each
+// The lanes in `drop` give up their keys, those behind close up, the empty key comes in from the end.
+__device__ inline u64 update_close_up(u64 x, u64 drop)
+{
+    const u64 lt = tg_lanemask_lt(), keep = ~drop;
+    const bool out = (drop >> tg_lane()) & 1ull;
+    if (out) x = TG_EMPTY_KEY;
+    const int to = 4 * (out ? __popcll(keep) + __popcll(drop & lt) : __popcll(keep & lt));
+    const u32 lo = (u32)__builtin_amdgcn_ds_permute(to, (int)(u32)x);
+    const u32 hi = (u32)__builtin_amdgcn_ds_permute(to, (int)(u32)(x >> 32));
+    return ((u64)hi << 32) | lo;
+}
+// x: ascending across the wave.  A candidate that several blocks found has the same key each time (a pair has one distance wherever it
+// meets), so its repeats are neighbours; all but one go.
+__device__ inline u64 update_once(u64 x)
+{
+    const u64 repeats = __ballot(x == tg_lane_before<false>(x) && x != TG_EMPTY_KEY);
+    return repeats ? update_close_up(x, repeats) : x;
+}
+// The same, and the first k entries' ids are different whatever their keys: each lane writes its number to the place its id is hashed to,
+// and a lane that does not find itself there (1 list in 2 has one, by chance) looks for its id among the others.
+__device__ inline u64 update_settle(u64 x, int k, volatile unsigned char* place)
+{
+    const int lane = tg_lane();
+    x = update_once(x);
+    for (;;) {
+        const u32 id = tg_key_id(x);
+        const bool on = lane < k && x != TG_EMPTY_KEY;
+        volatile unsigned char* mine = place + ((id * 0x9E3779B1u) >> 22);      // (read back from LDS, not from what was written)
+        if (on) *mine = (unsigned char)lane;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        u64 clash = __ballot(on && *mine != (unsigned char)lane), twice = 0ull;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        while (clash) {
+            const u32 c = (u32)__builtin_amdgcn_readlane((int)id, __ffsll((unsigned long long)clash) - 1);
+            clash &= clash - 1;
+            const u64 same = __ballot(on && id == c);
+            twice |= same & (same - 1);
+        }
+        if (twice == 0ull) return x;
+        x = update_close_up(x, twice);
+    }
+}
 // REMEASURE (the join ranked on rows rounded to fp16): every arrival is measured again in fp32 from the
 // vectors before the list is written, so the lists and their thresholds hold exact distances.
-template <bool REMEASURE>
+// SMALL: lists of at most 32 entries.  No candidate is in the list already (the join leaves out pairs that are listed as the part begins,
+// and lists change in this kernel only), so what has to be found are repeats among the candidates, and sorting brings those together: list
+// and candidates are sorted in one network where they are at most 64, else 64 candidates at a time are sorted and merged.  Longer lists could
+// lose entries to repeats in a merge that keeps 64, and look every id up in a set.
+template <bool REMEASURE, bool SMALL>
 __global__ __launch_bounds__(64 * LISTS_WAVES) void update_kernel(TgGraph g, int S, TgCand cd, u64* updates, int flip, int64_t v0)
 {
     extern __shared__ float smem[];      // REMEASURE: a row of X and 128 words of scratch per wave
     __shared__ u64 queue[LISTS_WAVES][UPDATE_MAX_C];
-    __shared__ u32 seen_s[LISTS_WAVES][UPDATE_SET_WORDS];
+    __shared__ u32 seen_s[LISTS_WAVES][SMALL ? UPDATE_PLACES / 4 : UPDATE_SET_WORDS];
     const int wave = threadIdx.x >> 6, lane = tg_lane();
     const int64_t v = v0 + (int64_t)blockIdx.x * LISTS_WAVES + wave;
     if (v >= g.n) return;
@@ -723,9 +772,52 @@ __global__ __launch_bounds__(64 * LISTS_WAVES) void update_kernel(TgGraph g, int
 
     const bool any_cand = nq > 0;
     if (any_cand) {
+        u32* seen = seen_s[wave];
+        // More than two batches (the first parts of the early rounds): the first merge has tightened the list, and most of
+        // what waits cannot precede its last entry any more.  What still can is closed up, usually into one batch.
+        auto close_up_queue = [&]() __attribute__((always_inline)) {
+            const u64 last = tg_shfl64(L, k - 1);
+            int wr = 64;
+            for (int r0 = 64; r0 < nq; r0 += 64) {
+                const u64 c = r0 + lane < nq ? queue[wave][r0 + lane] : TG_EMPTY_KEY;
+                const bool keep = c < last;
+                const u64 mk = __ballot(keep);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                if (keep) queue[wave][wr + __popcll(mk & lt)] = c;       // (never ahead of what has been read)
+                wr += __popcll(mk);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            nq = wr;
+        };
+        if (SMALL) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            unsigned char* place = reinterpret_cast<unsigned char*>(seen);
+            if (k + nq <= 64) {
+                u64 x = L;
+                if (lane >= k && lane < k + nq) x = queue[wave][lane - k];
+                if (lane >= k && tg_key_id(x) == (u32)v) x = TG_EMPTY_KEY;
+                L = update_settle(tg_wave_sort_first(x, k + nq), k, place);
+                if (lane >= k) L = TG_EMPTY_KEY;
+            } else {
+                for (int q0 = 0; q0 < nq; q0 += 64) {
+                    u64 ck = q0 + lane < nq ? queue[wave][q0 + lane] : TG_EMPTY_KEY;
+                    if (tg_key_id(ck) == (u32)v) ck = TG_EMPTY_KEY;
+                    if (q0 > 0) {
+                        if (!(ck < tg_shfl64(L, k - 1))) ck = TG_EMPTY_KEY;      // cannot precede the last entry of the list as merged so far
+                        if (__ballot(ck != TG_EMPTY_KEY) == 0) continue;
+                    }
+                    ck = update_once(tg_wave_sort_first(ck, nq - q0));
+                    L = update_settle(tg_wave_merge_low(L, ck), k, place);
+                    if (lane >= k) L = TG_EMPTY_KEY;
+                    if (q0 == 0 && nq > 128) close_up_queue();
+                }
+            }
+        } else {
         // ids of G[v], then every candidate: a candidate that is listed, or a repeat (the same
         // candidate may sit in several slots, one per block that found it), finds its id there
-        u32* seen = seen_s[wave];
         int set_words = 128;
         while (set_words * 2 < 3 * (k + nq)) set_words *= 2;          // at most UPDATE_SET_WORDS
         const u32 set_mask = (u32)set_words - 1u;
@@ -747,24 +839,8 @@ __global__ __launch_bounds__(64 * LISTS_WAVES) void update_kernel(TgGraph g, int
             ck = tg_wave_sort_first(ck, nq - q0);
             L = tg_wave_merge_low(L, ck);
             if (lane >= k) L = TG_EMPTY_KEY;
-            if (q0 == 0 && nq > 128) {
-                // More than two batches (the first parts of the early rounds): the first merge has tightened the list, and most of
-                // what waits cannot precede its last entry any more.  What still can is closed up, usually into one batch.
-                const u64 last = tg_shfl64(L, k - 1);
-                int wr = 64;
-                for (int r0 = 64; r0 < nq; r0 += 64) {
-                    const u64 c = r0 + lane < nq ? queue[wave][r0 + lane] : TG_EMPTY_KEY;
-                    const bool keep = c < last;
-                    const u64 mk = __ballot(keep);
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    if (keep) queue[wave][wr + __popcll(mk & lt)] = c;       // (never ahead of what has been read)
-                    wr += __popcll(mk);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                nq = wr;
-            }
+            if (q0 == 0 && nq > 128) close_up_queue();
+        }
         }
         if (REMEASURE) {
             const bool arrival = lane < k && (L & 2ull) != 0ull;
@@ -796,10 +872,9 @@ void tg_launch_update(const TgGraph& g, const TgSample& sm, const TgCand& c, u64
     const size_t shm = remeasure ? (size_t)LISTS_WAVES * g.ld * sizeof(float) + LISTS_WAVES * 128 * sizeof(u32) : 0;
     tg_for_node_chunks(g.n, [&](int64_t v0, int64_t cnt) {
         const dim3 grid((unsigned)((cnt + LISTS_WAVES - 1) / LISTS_WAVES));
-        if (remeasure)
-            hipLaunchKernelGGL(update_kernel<true>, grid, dim3(64 * LISTS_WAVES), shm, s, g, sm.S, c, updates, flip ? 1 : 0, v0);
-        else
-            hipLaunchKernelGGL(update_kernel<false>, grid, dim3(64 * LISTS_WAVES), 0, s, g, sm.S, c, updates, flip ? 1 : 0, v0);
+        const auto kernel = remeasure ? (g.k <= 32 ? update_kernel<true, true> : update_kernel<true, false>)
+                                      : (g.k <= 32 ? update_kernel<false, true> : update_kernel<false, false>);
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * LISTS_WAVES), shm, s, g, sm.S, c, updates, flip ? 1 : 0, v0);
     });
 }
 

@@ -64,18 +64,12 @@ __device__ inline bool merge_ascending(u64 key, int lane)
     return __ballot((lane & (W - 1)) > 0 && prev > key) == 0ull;
 }
 template <int W>
-__device__ inline u64 merge_sort(u64 key) { return W == 64 ? tg_wave_sort(key) : tg_wave_sort_first(key, 32); }
+__device__ inline u64 merge_sort(u64 key) { return W == 64 ? tg_wave_sort(key) : tg_half_sort(key); }
 // a and b ascend across the node's lanes: the W smallest keys of their union, ascending
 template <int W>
-__device__ inline u64 merge_low(u64 a, u64 b, int lane)
+__device__ inline u64 merge_low(u64 a, u64 b)
 {
-    if (W == 64) return tg_wave_merge_low(a, b);
-    u64 x = tg_min64(a, tg_partner<31>(b));
-    x = tg_cmpx(x, tg_partner<16>(x), (lane & 16) == 0);
-    x = tg_cmpx(x, tg_partner<8>(x), (lane & 8) == 0);
-    x = tg_cmpx(x, tg_partner<4>(x), (lane & 4) == 0);
-    x = tg_cmpx(x, tg_partner<2>(x), (lane & 2) == 0);
-    return tg_cmpx(x, tg_partner<1>(x), (lane & 1) == 0);
+    return W == 64 ? tg_wave_merge_low(a, b) : tg_half_merge_low(a, b);
 }
 
 template <int W>
@@ -121,7 +115,7 @@ __global__ __launch_bounds__(256) void merge_local_kernel(int32_t* __restrict__ 
         kb = merge_close_up<W>(kb, reinterpret_cast<u64*>(keys) + W, lane);
         if (!merge_ascending<W>(ka, lane)) ka = merge_sort<W>(ka);
         if (!merge_ascending<W>(kb, lane)) kb = merge_sort<W>(kb);
-        const u64 m = merge_low<W>(ka, kb, lane);
+        const u64 m = merge_low<W>(ka, kb);
         if (a_on) {
             const bool none = m == TG_EMPTY_KEY;
             g_ids[v * k + r] = none ? -1 : (int32_t)tg_key_id(m);

@@ -115,8 +115,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(const u32* __restric
 // ---- per node: keep the R smallest (priority, source) of each class, then assemble the block --
 // Block of anchor v:  NEW = new_fwd ++ (new_rev not yet there),
 //                     OLD = (old_fwd not in NEW) ++ (old_rev in neither).
-// fwd entries sit one per lane (lanes < k), rn / ro are the kept reverse arrivals, ascending
-// by (priority, source), one per lane (lanes < cn / co).
+// fwd entries sit one per lane (lanes < k); rid: the kept reverse arrivals (where `has`), ascending
+// by (priority, source), the new ones in the lanes from 0, the old ones in those from 32 (at most 32 of either: R is no more).
 // A small id -> tag map in LDS for the cross checks between the forward and the reverse samples
 // (open addressing, 256 words for at most 64 ids; ids inside one list are distinct).
 #define ASM_WORDS 256
@@ -150,8 +150,8 @@ __device__ inline int asm_find(const u32* keys, u32 id, bool active)
     }
     return slot;
 }
-__device__ inline void assemble_block(const TgGraph& g, const TgSample& sm, int64_t v, u32 w /* list entry of lane < k */, u32 rn, int cn,
-                                      u32 ro, int co, u32* keys, u32* tags)
+__device__ inline void assemble_block(const TgGraph& g, const TgSample& sm, int64_t v, u32 w /* list entry of lane < k */, u32 rid, bool has,
+                                      u32* keys, u32* tags)
 {
     const int lane = tg_lane();
     const int k = g.k, S = sm.S;
@@ -164,37 +164,34 @@ __device__ inline void assemble_block(const TgGraph& g, const TgSample& sm, int6
     const u32 fid = w & TG_ID_MASK;
     const u64 m_nf = __ballot(is_nf);
     // forward samples into the map: tag 1 = new, 2 = old (4 is added when a reverse-new arrival repeats it)
-    for (int i = lane; i < ASM_WORDS; i += 64) keys[i] = ASM_FREE;
+    reinterpret_cast<uint4*>(keys)[lane] = make_uint4(ASM_FREE, ASM_FREE, ASM_FREE, ASM_FREE);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const int fslot = asm_insert(keys, fid, is_nf || is_of);
     if (fslot >= 0) tags[fslot] = is_nf ? 1u : 2u;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const int sn = asm_find(keys, rn, lane < cn);
-    const int so = asm_find(keys, ro, lane < co);
-    const u32 tn = sn >= 0 ? tags[sn] : 0u;
-    const bool rn_dup = tn == 1u;                       // already there as a new forward sample
-    const bool ro_dup = so >= 0;                        // already there as a forward sample of either class
+    const bool rev_new = lane < 32;
+    const int rslot = asm_find(keys, rid, has);
+    const u32 tag = rslot >= 0 ? tags[rslot] : 0u;
+    // a new arrival is there already as a new forward sample, an old one as a forward sample of either class
+    const bool keep_r = has && (rev_new ? tag != 1u : rslot < 0);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (tn == 2u) tags[sn] = 6u;                        // the old forward sample is NEW through the reverse side
+    if (rev_new && tag == 2u) tags[rslot] = 6u;         // the old forward sample is NEW through the reverse side
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const bool of_drop = is_of && (tags[fslot >= 0 ? fslot : 0] & 4u);
-    const bool keep_rn = lane < cn && !rn_dup;
     const bool keep_of = is_of && !of_drop;
-    const bool keep_ro = lane < co && !ro_dup;
-    const u64 m_krn = __ballot(keep_rn), m_kof = __ballot(keep_of), m_kro = __ballot(keep_ro);
-    const int n_nf = __popcll(m_nf);
-    const int nN = n_nf + __popcll(m_krn);
+    const u64 m_kr = __ballot(keep_r), m_kof = __ballot(keep_of);
+    const int n_nf = __popcll(m_nf), n_krn = __popc((u32)m_kr);
+    const int nN = n_nf + n_krn;
     const int n_kof = __popcll(m_kof);
-    const int nT = nN + n_kof + __popcll(m_kro);
+    const int nT = nN + n_kof + __popcll(m_kr >> 32);
     u32* ids = sm.blk + v * (int64_t)sm.BC;
     if (is_nf) ids[__popcll(m_nf & lt)] = fid;
-    if (keep_rn) ids[n_nf + __popcll(m_krn & lt)] = rn;
     if (keep_of) ids[nN + __popcll(m_kof & lt)] = fid;
-    if (keep_ro) ids[nN + n_kof + __popcll(m_kro & lt)] = ro;
+    if (keep_r) ids[__popcll(m_kr & lt) + (rev_new ? n_nf : nN + n_kof - n_krn)] = rid;
     if (lane == 0) sm.bsz[v] = (u32)nN | ((u32)nT << 8);
 }
 
@@ -213,7 +210,8 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
 {
     __shared__ u32 tpos[TG_REV_MAX_W];
     __shared__ u64 part[4][2][64];
-    __shared__ u32 asm_keys[4][ASM_WORDS], asm_tags[4][ASM_WORDS];
+    __shared__ __align__(16) u32 asm_keys[4][ASM_WORDS];
+    __shared__ u32 asm_tags[4][ASM_WORDS];
     __shared__ u32 lcnt[TG_WL_LISTS], lbase[TG_WL_LISTS];
     const int lane = tg_lane(), wave = threadIdx.x >> 6;
     const int64_t b = bfirst + blockIdx.x;
@@ -287,42 +285,69 @@ __global__ __launch_bounds__(256) void rev_select_kernel(TgGraph g, TgSample sm,
             e_next = nbeg + lane < nend ? sm.csr[nbeg + lane] : 0u;
             w_next = lane < k ? g.gid[(u + 4) * k + lane] : 0u;
         }
-        u64 best_new = TG_EMPTY_KEY, best_old = TG_EMPTY_KEY;   // ascending across the wave
-        int tot_new = 0, tot_old = 0;
-        for (u64 base = abeg; base < aend; base += 64) {
-            // key = priority | class << 31 | source: one sort orders both classes; the class bit sits
-            // below the priority, so inside a class the order is (priority, source)
-            u64 key = TG_EMPTY_KEY;
-            if (base + lane < aend) {
-                const u32 e = base == abeg ? e_first : sm.csr[base + lane];
-                const u32 v = e & TG_ID_MASK;
-                key = (tg_hash_xy(hs_rev, (u64)v, (u64)u) & 0xFFFFFFFF00000000ull) | (u64)e;
+        // Up to 64 arrivals, the usual case: sorted by class, then the upper 25 bits of their priority, in one network on 32-bit keys.
+        u32 rid = 0u;
+        int cn = 0, co = 0;
+        bool settled = false;
+        const int count = (int)min(aend - abeg, (u64)65);
+        if (count <= 64) {
+            const u32 prio = (u32)(tg_hash_xy(hs_rev, (u64)(e_first & TG_ID_MASK), (u64)u) >> 32);
+            u32 order = lane < count ? (e_first & 0x80000000u) | ((prio >> 7) << 6) | (u32)lane : 0xFFFFFFFFu;
+            order = tg_wave_sort32_first(order, count);
+            const u32 before = (u32)__builtin_amdgcn_update_dpp(-1, (int)order, 0x138, 0xF, 0xF, false);
+            // two that agree in those bits (1 target in 60 000): the lower ones decide, below
+            if (__ballot(lane > 0 && lane < count && ((order ^ before) >> 6) == 0u) == 0ull) {
+                const u32 e = (u32)__builtin_amdgcn_ds_bpermute((int)(order << 2) & 252, (int)e_first);
+                co = __popcll(__ballot(lane < count && (e >> 31)));
+                cn = count - co;
+                const int from = lane < 32 ? lane : cn + lane - 32;
+                rid = (u32)__builtin_amdgcn_ds_bpermute(4 * from, (int)e) & TG_ID_MASK;
+                settled = true;
             }
-            key = tg_wave_sort_first(key, (int)(aend - base < 64 ? aend - base : 64));
-            const bool is_old = key != TG_EMPTY_KEY && (((u32)key) >> 31);
-            const bool is_new = key != TG_EMPTY_KEY && !(((u32)key) >> 31);
-            const u64 mn = __ballot(is_new), mo = __ballot(is_old);
-            const int cn = __popcll(mn), co = __popcll(mo);
-            // split into two ascending runs through LDS
-            if (is_new) part[wave][0][__popcll(mn & lt)] = key;
-            if (is_old) part[wave][1][__popcll(mo & lt)] = key & ~0x80000000ull;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const u64 kn = lane < cn ? part[wave][0][lane] : TG_EMPTY_KEY;
-            const u64 ko = lane < co ? part[wave][1][lane] : TG_EMPTY_KEY;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            if (base == abeg) {
-                best_new = kn;
-                best_old = ko;
-            } else {
-                if (cn) best_new = tg_wave_merge_low(best_new, kn);
-                if (co) best_old = tg_wave_merge_low(best_old, ko);
-            }
-            tot_new += cn;
-            tot_old += co;
         }
-        assemble_block(g, sm, u, w_list, (u32)best_new, min(tot_new, sm.R), (u32)best_old, min(tot_old, sm.R), asm_keys[wave], asm_tags[wave]);
+        if (!settled) {
+            u64 best_new = TG_EMPTY_KEY, best_old = TG_EMPTY_KEY;   // ascending across the wave
+            int tot_new = 0, tot_old = 0;
+            for (u64 base = abeg; base < aend; base += 64) {
+                // key = priority | class << 31 | source: one sort orders both classes; the class bit sits
+                // below the priority, so inside a class the order is (priority, source)
+                u64 key = TG_EMPTY_KEY;
+                if (base + lane < aend) {
+                    const u32 e = base == abeg ? e_first : sm.csr[base + lane];
+                    const u32 v = e & TG_ID_MASK;
+                    key = (tg_hash_xy(hs_rev, (u64)v, (u64)u) & 0xFFFFFFFF00000000ull) | (u64)e;
+                }
+                key = tg_wave_sort_first(key, (int)(aend - base < 64 ? aend - base : 64));
+                const bool is_old = key != TG_EMPTY_KEY && (((u32)key) >> 31);
+                const bool is_new = key != TG_EMPTY_KEY && !(((u32)key) >> 31);
+                const u64 mn = __ballot(is_new), mo = __ballot(is_old);
+                const int mine_new = __popcll(mn), mine_old = __popcll(mo);
+                // split into two ascending runs through LDS
+                if (is_new) part[wave][0][__popcll(mn & lt)] = key;
+                if (is_old) part[wave][1][__popcll(mo & lt)] = key & ~0x80000000ull;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const u64 kn = lane < mine_new ? part[wave][0][lane] : TG_EMPTY_KEY;
+                const u64 ko = lane < mine_old ? part[wave][1][lane] : TG_EMPTY_KEY;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                if (base == abeg) {
+                    best_new = kn;
+                    best_old = ko;
+                } else {
+                    if (mine_new) best_new = tg_wave_merge_low(best_new, kn);
+                    if (mine_old) best_old = tg_wave_merge_low(best_old, ko);
+                }
+                tot_new += mine_new;
+                tot_old += mine_old;
+            }
+            const u32 old_id = (u32)__shfl((int)(u32)best_old, lane & 31);       // (every lane takes part)
+            rid = lane < 32 ? (u32)best_new : old_id;
+            cn = tot_new;
+            co = tot_old;
+        }
+        const bool has = lane < 32 ? lane < min(cn, sm.R) : lane - 32 < min(co, sm.R);
+        assemble_block(g, sm, u, w_list, rid, has, asm_keys[wave], asm_tags[wave]);
         abeg = nbeg; aend = nend; e_first = e_next; w_list = w_next;
     }
     if (tg_use_order(g)) return;        // wl_order_kernel writes the work lists
