@@ -23,8 +23,10 @@
 #define JOIN_THREADS 256
 #define JOIN_CELLS 8                                   // cells per member: one per group of eight positions (mod 8)
 #define JOIN_CELL_BYTES (TG_BLOCK_COLS * JOIN_CELLS * 8)   // workgroup kernel: all cells of a block
-#define T8_SLOTS 4096                                  // table of a block's ids: hash -> block position, one byte each
-#define T8_FREE 255u                                   // "no member" (positions are 0..127)
+#define T8_BITS 11
+#define T8_SLOTS (1 << T8_BITS)                        // table of a block's ids: hash -> block position, one byte each
+#define T8_FREE 127u                                   // a free place: it names position 127, which is in no other place (see adj_kernel)
+#define T8_PAST 128u                                   // of a taken place: a member whose place it would have been is further on
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
@@ -68,27 +70,31 @@ __device__ inline float gram_to_dist(float gram, float aux_a, float aux_b)
 // Which members of a block sit in which member's list already: sm.adj, per anchor of the part
 // (slot v / parts) and member p, tg_adj_words words whose bit x says "the node at position x of
 // the block is in p's list".  One wave per anchor.  The block's ids (distinct) go into an
-// open-addressed table in LDS, T8[hash(id) + probes] = block position, a byte each.  The members'
+// open-addressed table in LDS, T8[hash(id) + probes] = block position, a byte each, with a mark where
+// a member had to go past the place.  The members'
 // lists are then read as one run of 16-byte pieces, 64 pieces per load, so consecutive lanes
 // read consecutive pieces of one list; every id of a piece is looked up (hash, table byte, the
-// id at that position, the next byte while the place is taken by another id) and a hit sets its
-// bit in LDS, from where the words go out in one run.
+// id at that position) and a hit sets its bit in LDS, from where the words go out in one run.
+// One look is all, with no branch: a free place names position 127, which no place is taken by (its member, in a block of 128,
+// is whatever a walk from its place finds behind taken ones: a free place), so a comparison is right wherever it lands, and only
+// beyond marked places (one block in two has one) the walk goes on.  Before, every id's walk was a loop that ended at a free place, at
+// 18 vector and as many scalar instructions an id.  With 2048 places and two pieces a lane on their way eight waves share a SIMD and cover the
+// loads; 4096 and eight pieces leave six or five.  1M x 128, k = 32: 5.64 -> 4.10 ms a build of four rounds (5.1 TB/s of list entries;
+// 4096 places and 8, 4, 2 pieces: 4.76, 4.20, 4.63; 2048 and 6, 4: 4.44, 4.52), 37 511 x 50, k = 20: 322 -> 216 us.
 // The lists are read as they stand when this part of the round begins.
 // ---------------------------------------------------------------------------------------
 __device__ inline u32 t8_hash(u32 id)
 {
-    const u32 x = id ^ (id >> 11);
-    return (u32)__umul24(x, 0x9E3779u) >> 20;      // 12 bits of a 24 x 24 bit product (the intrinsic's type is signed)
+    return (u32)__umul24(id, 0x9E3779u) >> (32 - T8_BITS);     // of a 24 x 24 bit product (the intrinsic's type is signed)
 }
 #define ADJ_WAVES 4
-#define ADJ_UNROLL 8
 struct AdjShared {
-    int ids[TG_BLOCK_COLS + 4];
+    int ids[TG_BLOCK_COLS];
     u32 adjw[(TG_BLOCK_COLS + 1) * 4];      // the last row takes what lanes past the end of the block look up
     unsigned char T8[T8_SLOTS];
 };
 template <bool VEC>
-__global__ __launch_bounds__(64 * ADJ_WAVES) void adj_kernel(TgGraph g, TgSample sm, int part, int64_t nslots)
+__global__ __launch_bounds__(64 * ADJ_WAVES, 8) void adj_kernel(TgGraph g, TgSample sm, int part, int64_t nslots)
 {
     __shared__ AdjShared shs[ADJ_WAVES];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = tg_lane();
@@ -96,14 +102,14 @@ __global__ __launch_bounds__(64 * ADJ_WAVES) void adj_kernel(TgGraph g, TgSample
     const int k = g.k;
     const u32 idmax = (u32)(g.n - 1);
     constexpr int W = VEC ? 4 : 1;                 // ids per piece; VEC: rows of the lists are 16-byte aligned (k % 4 == 0)
+    constexpr int EACH = VEC ? 2 : 8;              // pieces on their way at a time
     const int per = k / W;                         // pieces per list
     const int per_sh = (per & (per - 1)) == 0 ? __ffs(per) - 1 : -1;
     auto lds_fence = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
-    for (int c = lane; c < T8_SLOTS / 4; c += 64) reinterpret_cast<u32*>(sh.T8)[c] = 0xFFFFFFFFu;
-    if (lane < 4) sh.ids[TG_BLOCK_COLS + lane] = -1;
+    for (int c = lane; c < T8_SLOTS / 4; c += 64) reinterpret_cast<u32*>(sh.T8)[c] = T8_FREE * 0x01010101u;
     u32 my_s[2] = {0u, 0u};
     bool my_in[2] = {false, false};
     for (int64_t a = (int64_t)blockIdx.x * ADJ_WAVES + wave; a < nslots; a += (int64_t)gridDim.x * ADJ_WAVES) {
@@ -133,24 +139,38 @@ __global__ __launch_bounds__(64 * ADJ_WAVES) void adj_kernel(TgGraph g, TgSample
         }
         for (int h = 0; h < (nT > 64 ? 2 : 1); ++h) {
             const u32 p = (u32)(lane + 64 * h);
-            bool pending = my_in[h];
+            bool pending = my_in[h] && p != T8_FREE;
             while (__ballot(pending)) {                  // at most nT turns: the table has room for every member
                 if (pending && T8v[my_s[h]] == T8_FREE) T8v[my_s[h]] = (unsigned char)p;
                 lds_fence();
+                const u32 got = T8v[my_s[h]];
+                lds_fence();
                 if (pending) {
-                    if (T8v[my_s[h]] == p) pending = false;
-                    else my_s[h] = (my_s[h] + 1u) & (T8_SLOTS - 1);
+                    if ((got & ~T8_PAST) == p) pending = false;
+                    else {
+                        T8v[my_s[h]] = (unsigned char)(got | T8_PAST);
+                        my_s[h] = (my_s[h] + 1u) & (T8_SLOTS - 1);
+                    }
                 }
                 lds_fence();
             }
         }
+        if (nT == TG_BLOCK_COLS) {
+            // the member at position 127 has no place of its own: its walk ends at the free one it meets
+            if (lane == 63) {
+                while (T8v[my_s[1]] != T8_FREE) {
+                    T8v[my_s[1]] = (unsigned char)(T8v[my_s[1]] | T8_PAST);
+                    my_s[1] = (my_s[1] + 1u) & (T8_SLOTS - 1);
+                }
+            }
+        }
         lds_fence();
         const int total = nT * per;
-        for (int base = 0; base < total; base += 64 * ADJ_UNROLL) {
-            u32 lid[ADJ_UNROLL][W];
-            int mm[ADJ_UNROLL];
+        for (int base = 0; base < total; base += 64 * EACH) {
+            u32 lid[EACH][W];
+            int mm[EACH];
 #pragma unroll
-            for (int u = 0; u < ADJ_UNROLL; ++u) {
+            for (int u = 0; u < EACH; ++u) {
                 const int idx = base + 64 * u + lane;
                 const bool ok = idx < total;
                 const int ii = ok ? idx : 0;
@@ -166,22 +186,31 @@ __global__ __launch_bounds__(64 * ADJ_WAVES) void adj_kernel(TgGraph g, TgSample
                 mm[u] = ok ? m : TG_BLOCK_COLS;
             }
 #pragma unroll
-            for (int u = 0; u < ADJ_UNROLL; ++u) {
+            for (int u = 0; u < EACH; ++u) {
                 if (base + 64 * u >= total) break;       // (wave-uniform)
+                u32 at[W], there[W], past = 0u;
 #pragma unroll
                 for (int w = 0; w < W; ++w) {
-                    const u32 cid = lid[u][w] & TG_ID_MASK;
-                    u32 s = t8_hash(cid);
-                    u32 e = (u32)sh.T8[s];
-                    while (e != T8_FREE) {               // ends at a free place: the table is never full
-                        if ((u32)sh.ids[e] == cid) {
-                            atomicOr(&sh.adjw[mm[u] * 4 + (int)(e >> 5)], 1u << (e & 31u));
-                            break;
+                    lid[u][w] &= TG_ID_MASK;
+                    at[w] = (u32)sh.T8[t8_hash(lid[u][w])];
+                    past |= at[w];
+                }
+                if (__ballot((past & T8_PAST) != 0u) != 0ull) {
+#pragma unroll
+                    for (int w = 0; w < W; ++w) {
+                        u32 s = t8_hash(lid[u][w]);
+                        while ((at[w] & T8_PAST) && (u32)sh.ids[at[w] & ~T8_PAST] != lid[u][w]) {     // ends at a free place at the latest
+                            s = (s + 1u) & (T8_SLOTS - 1);
+                            at[w] = sh.T8[s];
                         }
-                        s = (s + 1u) & (T8_SLOTS - 1);
-                        e = sh.T8[s];
+                        at[w] &= ~T8_PAST;
                     }
                 }
+#pragma unroll
+                for (int w = 0; w < W; ++w) there[w] = (u32)sh.ids[at[w]];
+#pragma unroll
+                for (int w = 0; w < W; ++w)
+                    if (there[w] == lid[u][w]) atomicOr(&sh.adjw[mm[u] * 4 + (int)(at[w] >> 5)], 1u << (at[w] & 31u));
             }
         }
         lds_fence();
