@@ -255,6 +255,11 @@ void tg_launch_dump_adj(const TgGraph& g, const TgSample& sm, int part, uint32_t
     hipLaunchKernelGGL(dump_adj_kernel, dim3(1024), dim3(256), 0, s, sm, g.n, part, out);
 }
 
+// a use of the value's registers: what is still on its way into them is waited for
+template <class V>
+__device__ inline void wait_here(const V& v) { asm volatile("" ::"v"(v) : "memory"); }
+__device__ inline void wait_here(const float4& v) { asm volatile("" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w) : "memory"); }
+
 // The part of a work list that a workgroup walks.  A list written in the nodes' order (g.order) is cut into eight shares, one for
 // each XCD, which takes every eighth workgroup: what an XCD's waves have in hand at one time are then neighbours.
 struct ListShare {
@@ -268,19 +273,23 @@ __device__ inline ListShare list_share(int64_t count, bool ordered)
     return {first, min(share, count - first), (int64_t)(blockIdx.x >> 3), (int64_t)(gridDim.x >> 3)};
 }
 
-// Candidate slot of member t (salt: its slot-hash salt) for the cell q of anchor v's block: the pair (t, v) owns
+// Candidate slots of member t for anchor v's block: the pair (t, v) owns
 // one 64-byte line of t's slot row, picked by a hash, and cell q goes to word (q + rotation) % 8 of it, where it
 // stays if it is the smaller (dist, id): one 64-bit atomic minimum, no order dependence.  All candidates one block
-// has for t share a line, so they travel in one memory transaction.
-__device__ inline void emit_candidate(const TgCand& cd, u32 t, u32 tmax, u32 salt, u64 key, u32 v, int q)
+// has for t share a line, so they travel in one memory transaction.  slot_line is worked out once a member (salt: t's slot-hash salt):
+// the line's first slot, and the rotation in the three bits that are zero in it.
+__device__ inline u32 slot_line(const TgCand& cd, u32 salt, u32 v)
 {
-    if (t > tmax) return;                            // (no id from LDS becomes an address unchecked)
     u32 h = (salt + v) * 0x9E3779B1u;
     h ^= h >> 15;
     h *= 0x85EBCA77u;
     h ^= h >> 13;
-    const u32 line = h >> (36 - __ffs(cd.C));        // C / 8 lines
-    const u32 slot = line * 8u + ((u32)(q + (int)(h & 7u)) & 7u);
+    return ((h >> (36 - __ffs(cd.C))) << 3) | (h & 7u);          // (C / 8 lines)
+}
+__device__ inline void emit_candidate(const TgCand& cd, u32 t, u32 tmax, u32 line, u64 key, int q)
+{
+    if (t > tmax) return;                            // (no id from LDS becomes an address unchecked)
+    const u32 slot = (line & ~7u) | (((u32)q + line) & 7u);
     atomicMin(cd.slots + (int64_t)t * cd.C + slot, key);
 }
 
@@ -295,7 +304,7 @@ __device__ inline void emit_candidate(const TgCand& cd, u32 t, u32 tmax, u32 sal
 // ROWS: the most members a block may have here, 64 or 128.
 // The walk over the work list is pipelined across blocks: the ids of block w + 1 travel while block w is multiplied, and its first slab
 // while block w is evaluated and handed over.
-// LDS: header (salt, threshold, norms, ids of two blocks), the adjacency words, the cells, the tile.
+// LDS: header (slot line, threshold, norms, ids of two blocks), the adjacency words, the cells, the tile.
 // ---------------------------------------------------------------------------------------
 #define JOIN_HDR_BYTES (5 * (TG_BLOCK_COLS + 4) * 4)
 #define JOIN_ADJ_BYTES (TG_BLOCK_COLS * 4 * 4)
@@ -321,8 +330,8 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
     const TgSample& sm = A.sm;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int HW = TG_BLOCK_COLS + 4;                               // words per header array
-    u32* s_salt = reinterpret_cast<u32*>(smem_raw);                     // slot-hash salt of each member
-    u32* s_okd = s_salt + HW;                                           // threshold: ordered distance of the member's last entry
+    u32* s_line = reinterpret_cast<u32*>(smem_raw);                     // slot_line of each member
+    u32* s_okd = s_line + HW;                                           // threshold: ordered distance of the member's last entry
     float* s_aux = reinterpret_cast<float*>(s_okd + HW);                // squared norm (or 1/|x| for cosine)
     u32* s_idb = reinterpret_cast<u32*>(s_aux + HW);                    // ids, of the block in hand and of the next one
     u32* s_adj = reinterpret_cast<u32*>(smem_raw + JOIN_HDR_BYTES);     // member p: four words, bit x = position x is in p's list
@@ -418,7 +427,7 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
         s_aux[tid] = aux;
         if (MODE == 0) {
             s_okd[tid] = (u32)(kth >> 32);
-            s_salt[tid] = (u32)tg_mix64(A.hs_slot + (u64)id);
+            s_line[tid] = slot_line(A.cd, (u32)tg_mix64(A.hs_slot + (u64)id), (u32)v);
         }
     }
     if (MODE == 0 && A.stat_bins && tid == 0 && nT > 0) {
@@ -605,7 +614,7 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
             const u64 key = s_cell[c];
             if (key != TG_EMPTY_KEY) {
                 s_cell[c] = TG_EMPTY_KEY;
-                emit_candidate(A.cd, s_ids[c >> 3], idmax, s_salt[c >> 3], key, (u32)v, c & 7);
+                emit_candidate(A.cd, s_ids[c >> 3], idmax, s_line[c >> 3], key, c & 7);
             }
         }
     }
@@ -648,7 +657,7 @@ struct WaveItem {
 };
 
 struct WaveShared {
-    u32 salt[2][64];
+    u32 line[2][64];           // slot_line of each member
     u32 okd[2][64];
     int ids[2][64];
     float aux[2][64];
@@ -754,7 +763,7 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
             sh.aux[buf][lane] = aux;
             if (MODE == 0) {
                 sh.okd[buf][lane] = (u32)(kth >> 32);
-                sh.salt[buf][lane] = (u32)tg_mix64(hs_slot + (u64)id);
+                sh.line[buf][lane] = slot_line(cd, (u32)tg_mix64(hs_slot + (u64)id), (u32)it.v);
                 sh.adj[buf][lane][0] = (u32)adj;
                 sh.adj[buf][lane][1] = (u32)(adj >> 32);
             }
@@ -765,14 +774,14 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
     // neighbouring lanes and their slots share a 64-byte line, so the atomics of one member travel
     // as one transaction.
     constexpr int CELLS = 64 * JOIN_CELLS;
-    auto flush_cells = [&](int fbuf, u32 fv, int fnT) {
+    auto flush_cells = [&](int fbuf, int fnT) {
         const u64* cells = sh.cell[fbuf];
 #pragma unroll
         for (int s8 = 0; s8 < 8; ++s8) {
             const int p = 8 * s8 + (lane >> 3), q = lane & 7;
             if (8 * s8 < fnT) {
                 const u64 key = p < fnT ? cells[p * JOIN_CELLS + q] : TG_EMPTY_KEY;
-                if (key != TG_EMPTY_KEY) emit_candidate(cd, (u32)sh.ids[fbuf][p], idmax, sh.salt[fbuf][p], key, fv, q);
+                if (key != TG_EMPTY_KEY) emit_candidate(cd, (u32)sh.ids[fbuf][p], idmax, sh.line[fbuf][p], key, q);
             }
         }
     };
@@ -806,17 +815,19 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
         mid = (int)min(nxt.bids[lane < nxt.nT ? lane : 0], idmax);
     }
     int buf = 0;
-    u32 prev_v = 0;
     int prev_nT = 0;      // members of the block whose cells still wait in LDS
 
     // In round w: block w is multiplied, the rows, norms, thresholds and lists of block w + 1 are
     // fetched (their ids came in one round earlier), and the ids of block w + 2 start travelling.
     for (; w < count; w += nwaves) {
+        // The rows are waited for here, in front of the hand-over below: loads and atomics count down together, so a wait behind the
+        // atomics, of which any number may have been issued, would be a wait for them too.
+#pragma unroll
+        for (int t = 0; t < GMAX; ++t)
+#pragma unroll
+            for (int s8 = 0; s8 < KS; ++s8) wait_here(X[t][s8]);
         const WaveItem nxt2 = decode(rec2);
         rec2 = load_rec(w + 3 * nwaves);
-        u32 idn2[GMAX];
-        fetch_row_ids(nxt2, idn2);
-        const int mid2 = (int)min(nxt2.bids[lane < nxt2.nT ? lane : 0], idmax);
         float m_aux = 0.f;
         u64 m_kth = 0, m_adj = 0;
 
@@ -828,10 +839,13 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
         const int nN = cur.nN, nT = cur.nT, MT = cur.MT, NT = cur.NT;
         u64* cells = sh.cell[buf];
         if (MODE == 0) {
-            if (prev_nT > 0) flush_cells(buf ^ 1, prev_v, prev_nT);
+            if (prev_nT > 0) flush_cells(buf ^ 1, prev_nT);
             clear_cells(buf);
             lds_fence();
         }
+        u32 idn2[GMAX];
+        fetch_row_ids(nxt2, idn2);
+        const int mid2 = (int)min(nxt2.bids[lane < nxt2.nT ? lane : 0], idmax);
         if (MODE == 0 && stat_bins && lane == 0 && MT > 0) {
             const u64 pairs = (u64)nN * (u64)(nN - 1) / 2 + (u64)nN * (u64)(nT - nN);
             atomicAdd(stat_bins + (v & (TG_STAT_BINS - 1)), pairs);
@@ -950,7 +964,6 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
         if (MODE == 0) {
             // the block's cells wait in LDS for one more round; its member data are needed for
             // that, so the next block's member data go to the buffer of the block before
-            prev_v = (u32)v;
             prev_nT = MT > 0 ? nT : 0;
         }
         park_member(nxt, mid, m_aux, m_kth, m_adj, buf ^ 1);
@@ -961,7 +974,7 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
         mid = mid2;
         buf ^= 1;
     }
-    if (MODE == 0 && prev_nT > 0) flush_cells(buf ^ 1, prev_v, prev_nT);
+    if (MODE == 0 && prev_nT > 0) flush_cells(buf ^ 1, prev_nT);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -979,9 +992,9 @@ typedef int intx4 __attribute__((ext_vector_type(4)));
 #define BYTES_FAR (1 << 28)          // the norm of a row that must not count: its distances are beyond BYTES_MOST
 #define BYTES_MOST 1e8f              // thresholds are cut to this (the distances are at most 2^24)
 struct BytesShared {
-    u64 cell[64 * JOIN_CELLS];       // all empty between blocks
+    u64 cell[2][64 * JOIN_CELLS];    // of the block in hand, and of the one before until they are handed over; else empty
     int nrm[64], thr[64], id[64];
-    u32 salt[64];
+    u32 line[64];                    // slot_line of each member
     u32 adj[64][2];
 };
 template <int KS>
@@ -1035,9 +1048,20 @@ __global__ __launch_bounds__(256, 4) void join_bytes_kernel(TgGraph g, TgSample 
                 X[t][s] = *reinterpret_cast<const intx4*>(g.Xq + (int64_t)idr[t] * g.ldq + (col < g.ldq ? col : 0));
             }
     };
-    for (int c = lane; c < 64 * JOIN_CELLS; c += 64) sh.cell[c] = TG_EMPTY_KEY;
+    for (int c = lane; c < 64 * JOIN_CELLS; c += 64) sh.cell[0][c] = sh.cell[1][c] = TG_EMPTY_KEY;
     int64_t w = (int64_t)blockIdx.x * 4 + wave;
     if (w >= count) return;
+    int buf = 0, prev_nT = 0;         // members of the block whose cells still wait in the other buffer
+    auto hand_over = [&](u64* cells, int members) __attribute__((always_inline)) {
+        for (int p0 = 0; p0 < members; p0 += 8) {
+            const int p = p0 + (lane >> 3), q = lane & 7;
+            const u64 key = cells[p * JOIN_CELLS + q];
+            if (key != TG_EMPTY_KEY) {
+                cells[p * JOIN_CELLS + q] = TG_EMPTY_KEY;
+                emit_candidate(cd, (u32)sh.id[p], idmax, sh.line[p], key, q);
+            }
+        }
+    };
     Item cur = decode(load_rec(w)), nxt = decode(load_rec(w + nwaves));
     u32 idn[4];
     fetch_ids(cur, idn);
@@ -1050,11 +1074,25 @@ __global__ __launch_bounds__(256, 4) void join_bytes_kernel(TgGraph g, TgSample 
     for (; w < count; w += nwaves) {
         const u64 rec2 = load_rec(w + 2 * nwaves);
         const int nN = cur.nN, nT = cur.nT, MT = (nN + 15) >> 4, NT = (nT + 15) >> 4;
+        // Everything that was asked for is waited for here, in front of the last block's hand-over: loads and atomics count down together,
+        // and any number of atomics may be issued.  They have this block's time to land.
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) wait_here(X[t][s]);
+            wait_here(idn[t]);
+        }
+        wait_here(m_kth);
+        wait_here(m_adj);
+        wait_here(midn);
+        hand_over(sh.cell[buf ^ 1], prev_nT);
+        lds_fence();
+        u64* const cells = sh.cell[buf];
         // the block's member data: one member per lane
         sh.id[lane] = mid;
         // one more than the distance of the list's last entry (a whole number, unless the caller imported another list)
         sh.thr[lane] = (int)fmaxf(0.0f, floorf(fminf(tg_unord((u32)(m_kth >> 32)), BYTES_MOST)) + 1.0f);
-        sh.salt[lane] = (u32)tg_mix64(hs_slot + (u64)(u32)mid);
+        sh.line[lane] = slot_line(cd, (u32)tg_mix64(hs_slot + (u64)(u32)mid), cur.v);
         sh.adj[lane][0] = (u32)m_adj;
         sh.adj[lane][1] = (u32)(m_adj >> 32);
         // codes -> signed, and the squared norms off the diagonals
@@ -1119,12 +1157,12 @@ __global__ __launch_bounds__(256, 4) void join_bytes_kernel(TgGraph g, TgSample 
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const u64 hi = (u64)(__float_as_uint((float)dist[e]) | 0x80000000u) << 32;
-                    if (prow[e]) atomicMin(&sh.cell[(a0 + e) * JOIN_CELLS + 2 * j + (r16 >> 3)], hi | idb);
-                    if (pcol[e]) atomicMin(&sh.cell[b * JOIN_CELLS + 2 * i + (q4 >> 1)], hi | (u64)(((u32)ida[e] << 2) | 3u));
+                    if (prow[e]) atomicMin(&cells[(a0 + e) * JOIN_CELLS + 2 * j + (r16 >> 3)], hi | idb);
+                    if (pcol[e]) atomicMin(&cells[b * JOIN_CELLS + 2 * i + (q4 >> 1)], hi | (u64)(((u32)ida[e] << 2) | 3u));
                 }
             }
         }
-        // the next block's rows and member data start travelling, then this block's candidates leave
+        // the next block's rows and member data start travelling
         const Item nxt2 = decode(rec2);
         fetch_rows(idn);
         const u64 k_next = g.kth[midn];
@@ -1133,15 +1171,8 @@ __global__ __launch_bounds__(256, 4) void join_bytes_kernel(TgGraph g, TgSample 
         fetch_ids(nxt2, idn);
         const int midn2 = (int)min(nxt2.bids[lane < nxt2.nT ? lane : 0], idmax);
         lds_fence();
-        for (int p0 = 0; p0 < nT; p0 += 8) {
-            const int p = p0 + (lane >> 3), q = lane & 7;
-            const u64 key = sh.cell[p * JOIN_CELLS + q];
-            if (key != TG_EMPTY_KEY) {
-                sh.cell[p * JOIN_CELLS + q] = TG_EMPTY_KEY;
-                emit_candidate(cd, (u32)sh.id[p], idmax, sh.salt[p], key, cur.v, q);
-            }
-        }
-        lds_fence();
+        prev_nT = nT;
+        buf ^= 1;
         cur = nxt;
         nxt = nxt2;
         mid = midn;
@@ -1149,6 +1180,7 @@ __global__ __launch_bounds__(256, 4) void join_bytes_kernel(TgGraph g, TgSample 
         m_kth = k_next;
         m_adj = adj_next;
     }
+    hand_over(sh.cell[buf ^ 1], prev_nT);
 }
 
 static size_t join_lds_bytes(int DK, int rows)
@@ -1156,7 +1188,7 @@ static size_t join_lds_bytes(int DK, int rows)
     return JOIN_HDR_BYTES + JOIN_ADJ_BYTES + JOIN_CELL_BYTES + (size_t)rows * (DK + 4) * sizeof(float);
 }
 
-#define JOIN_BYTES_GRID 2048
+#define JOIN_BYTES_GRID 3072
 #define JOIN_GRID 2048     // persistent launches: workgroups walk the work list with this stride
 
 static int64_t wl_cap(int64_t n, int parts) { return (n + parts - 1) / parts; }
