@@ -347,19 +347,47 @@ __global__ __launch_bounds__(256) void ex_half_kernel(const float* __restrict__ 
 // The queries of this batch, packed: rows of whole chunks, zero padded (so that what the scan reads beyond the
 // end of a row of X counts for nothing), zero rows up to a multiple of the tile.  One wave per query.
 // qmeta: |q|, residual norm, squared norm; qrow: its row of X (-1: no query); the query's counter is cleared.
+// Where the scan is on the fp32 rows a query's norm is formed here, as norms_kernel forms it, and the workgroups behind those of the
+// queries form the norms of all rows (first batch): one launch, not two (64 queries against 50 000 x 96: 54.1 -> 51.2 us).
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void ex_query_kernel(ExScanArgs a, int f16, const int64_t* __restrict__ rows, int64_t q_first, int64_t nqpad,
-                                                       const float* __restrict__ rnorm)
+// |x|^2 of a row by each 16 lanes of a wave
+__device__ inline float ex_row_norm(const float* __restrict__ x, int ld)
 {
-    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    float acc = 0.0f;
+    for (int c = (threadIdx.x & 15) * 4; c < ld; c += 64) {
+        const float4 v = *reinterpret_cast<const float4*>(x + c);
+        acc += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    }
+    acc += __shfl_xor(acc, 1);
+    acc += __shfl_xor(acc, 2);
+    acc += __shfl_xor(acc, 4);
+    acc += __shfl_xor(acc, 8);
+    return acc;
+}
+__global__ __launch_bounds__(256) void ex_query_kernel(ExScanArgs a, int f16, const int64_t* __restrict__ rows, int64_t q_first, int64_t nqpad,
+                                                       int ld, float* __restrict__ nrm, float* __restrict__ rnorm)
+{
     const int lane = tg_lane();
+    if ((int64_t)blockIdx.x * 4 >= nqpad) {
+        const int64_t groups = gridDim.x - nqpad / 4, group = blockIdx.x - nqpad / 4;
+        for (int64_t row = group * 16 + (threadIdx.x >> 4); row < a.n; row += groups * 16) {
+            const float acc = ex_row_norm(reinterpret_cast<const float*>(a.rows) + row * (int64_t)ld, ld);
+            if ((threadIdx.x & 15) == 0) {
+                nrm[row] = acc;
+                if (a.metric == 2) rnorm[row] = 1.0f / sqrtf(acc);
+            }
+        }
+        return;
+    }
+    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (q == 0 && lane == 0) *a.fb_n = 0u;
-    if (q >= nqpad) return;
     int64_t row = -1;
     if (q < a.nq) row = rows ? rows[q_first + q] : q_first + q;
     if (row >= a.n || row < 0) row = -1;
+    float qn = 0.0f;
+    if (row >= 0) qn = f16 ? a.rn[row] : ex_row_norm(reinterpret_cast<const float*>(a.rows) + row * (int64_t)ld, ld);
     const int words = a.qbytes >> 4;
-    const float s = (!f16 && a.metric == 2 && row >= 0) ? rnorm[row] : 1.0f;
+    const float s = (!f16 && a.metric == 2 && row >= 0) ? 1.0f / sqrtf(qn) : 1.0f;
     for (int c = lane; c < words; c += 64) {
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
         if (row >= 0 && c * 16 < a.rowbytes) {
@@ -374,7 +402,7 @@ __global__ __launch_bounds__(256) void ex_query_kernel(ExScanArgs a, int f16, co
         *reinterpret_cast<uint4*>(a.Q + q * (int64_t)a.qbytes + c * 16) = v;
     }
     if (lane == 0) {
-        const float qn = row >= 0 ? ((!f16 && a.metric == 2) ? 1.0f : a.rn[row]) : 0.0f;
+        if (!f16 && a.metric == 2 && row >= 0) qn = 1.0f;
         a.qmeta[q] = make_float4(sqrtf(qn), row >= 0 && a.er ? a.er[row] : 0.0f, qn, 0.0f);
         a.qrow[q] = (int32_t)row;
         if (q < a.nq) a.cnt[q * EX_CSTRIDE] = 0u;
@@ -430,6 +458,7 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
     __shared__ u64 s_queue[ALL ? 1 : WAVES][EX_QUEUE];                      // pairs on their way to the lists: ordered w << 32 | row of X ...
     __shared__ u32 s_qof[ALL ? 1 : WAVES][EX_QUEUE];                        // ... and the query within the tile
     __shared__ u32 s_full[QT];                                          // the query's list is full: it is measured another way
+    __shared__ u32 s_row[ALL ? 2 : 1][ALL ? EX_RT : 1];                 // the rows' numbers in X
     constexpr int WQ = QT / 64;                                         // waves side by side over the queries
     constexpr int WI = EX_RT / 16 / (WAVES / WQ);                       // 16-row tiles per wave
     constexpr int RP = THREADS / 8;                                     // rows whose step the threads fetch at once, a 16-byte piece each
@@ -465,6 +494,7 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
 
     floatx4 preB[BP], preA[AP];
     float pre_rn = 0.0f, pre_er = 0.0f, pre_c1 = 1.0f;
+    u32 pre_row = 0u;
     const unsigned char* rp[BP];
     const int nvisit = (int)a.nvisit;
     const int piece = tid & 7, prow = tid >> 3;
@@ -474,6 +504,7 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
             for (int it = 0; it < BP; ++it) rp[it] = a.rows + (int64_t)ex_row<SAMPLE>(a, (u32)min(t * EX_RT + prow + RP * it, nvisit - 1)) * a.rowbytes;
             if (tid < EX_RT) {
                 const u32 r = ex_row<SAMPLE>(a, (u32)min(t * EX_RT + tid, nvisit - 1));
+                pre_row = r;
                 pre_rn = a.rn[r];
                 pre_er = F16 ? a.er[r] : 0.0f;
                 if (!F16 && a.metric == 2) pre_c1 = a.rnorm[r];
@@ -507,6 +538,7 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
             const bool undefined = !(pre_rn < __builtin_inff()) || !(pre_c1 < __builtin_inff());
             s_c0[par][tid] = !real ? -__builtin_inff() : F16 && undefined ? EX_ALWAYS : a.metric == 0 ? -0.5f * pre_rn : 0.0f;
             if (!F16) s_c1[par][tid] = pre_c1;
+            if (ALL) s_row[ALL ? par : 0][ALL ? tid : 0] = pre_row;
             float R = (!F16 && a.metric == 2) ? 1.0f : sqrtf(pre_rn), E = pre_er;
             // A row without a defined norm is bounded by nothing.  fp32: nor are its neighbours in the tile then (a maximum alone would pass
             // over a NaN).  fp16: EX_ALWAYS takes it past any threshold, and its neighbours keep theirs (with an infinite norm among the
@@ -615,13 +647,31 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
             }
             return v;
         };
+        if (ALL) {
+            // every value is kept, at the number of its visit
+#pragma unroll
+            for (int i = 0; i < WI; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const floatx4 v = value(i, j);
+                    const int at = 16 * (wr * WI + i) + 4 * q4;
+                    if (ntau[j] > 0.0f) continue;                               // no query
+                    u64* out = a.buf + ((int64_t)qb * QT + wq * 64 + 16 * j + r16) * EX_CAP + t * EX_RT + at;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const u32 row = s_row[ALL ? par : 0][ALL ? at + e : 0];
+                        if (t * EX_RT + at + e < nvisit) out[e] = row == (u32)qself[j] ? TG_EMPTY_KEY : ((u64)tg_ord(-v[e]) << 32) | row;
+                    }
+                }
+            continue;
+        }
 #pragma unroll
         for (int i = 0; i < WI; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const floatx4 v = value(i, j);
                 const float best = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
-                hits |= (ALL || __ballot(F16 ? best >= threshold(i, j) : !(best < threshold(i, j))) != 0ull) ? 1u << (4 * i + j) : 0u;
+                hits |= __ballot(F16 ? best >= threshold(i, j) : !(best < threshold(i, j))) != 0ull ? 1u << (4 * i + j) : 0u;
             }
         // ... and those tiles one by one (one copy of the code for all of them: unrolled it drowned the loop above)
         while (hits) {
@@ -635,32 +685,26 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
             for (int i = 0; i < WI; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (at == 4 * i + j) { v = value(i, j); thr = threshold(i, j); self = qself[j]; live = ntau[j] < __builtin_inff(); if (ALL && ntau[j] > 0.0f) self = -2; }
+                    if (at == 4 * i + j) { v = value(i, j); thr = threshold(i, j); self = qself[j]; live = ntau[j] < __builtin_inff(); }
             const int ql = wq * 64 + 16 * (at & 3) + r16;
 #pragma unroll 1
             for (int e = 0; e < 4; ++e) {
                 const float ve = e == 0 ? v[0] : e == 1 ? v[1] : e == 2 ? v[2] : v[3];
                 const int jv = t * EX_RT + 16 * (wr * WI + (at >> 2)) + 4 * q4 + e;
                 const u64 key_hi = (u64)tg_ord(-ve) << 32;
-                if (ALL) {
-                    if (jv >= nvisit || self == -2) continue;                       // (no row; no query)
-                    const u32 row = ex_row<SAMPLE>(a, (u32)jv);
-                    a.buf[((int64_t)qb * QT + ql) * EX_CAP + jv] = row == (u32)self ? TG_EMPTY_KEY : key_hi | row;
-                } else {
-                    bool pass = (F16 ? ve >= thr : !(ve < thr) && live) && jv < nvisit;     // fp32: an undefined bound rules nothing out
-                    if (__ballot(pass) == 0ull) continue;
-                    const u32 row = ex_row<SAMPLE>(a, (u32)jv);
-                    pass = pass && row != (u32)self;
-                    const u64 m = __ballot(pass);
-                    const int more = __popcll(m);
-                    if (nqueue + more > EX_QUEUE) flush();
-                    if (pass) {
-                        const int put = nqueue + __popcll(m & tg_lanemask_lt());
-                        s_queue[wave][put] = key_hi | row;
-                        s_qof[wave][put] = (u32)ql;
-                    }
-                    nqueue += more;
+                bool pass = (F16 ? ve >= thr : !(ve < thr) && live) && jv < nvisit;     // fp32: an undefined bound rules nothing out
+                if (__ballot(pass) == 0ull) continue;
+                const u32 row = ex_row<SAMPLE>(a, (u32)jv);
+                pass = pass && row != (u32)self;
+                const u64 m = __ballot(pass);
+                const int more = __popcll(m);
+                if (nqueue + more > EX_QUEUE) flush();
+                if (pass) {
+                    const int put = nqueue + __popcll(m & tg_lanemask_lt());
+                    s_queue[wave][put] = key_hi | row;
+                    s_qof[wave][put] = (u32)ql;
                 }
+                nqueue += more;
             }
         }
         if (!ALL) {
@@ -840,26 +884,37 @@ __global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
     flush();
 }
 
-// The k-th smallest of count keys key_of(i), found by the four waves of a workgroup: waves take every fourth batch of
-// 64, batches without a key below the wave's k-th so far are passed over, the four sorted lists are merged.  s_top: 3 x 64 words.
-// Wave 0 returns the 64 smallest keys, ascending; the others an empty list.
-template <class F>
+// The waves' lists of 64 keys, ascending, become one, in wave 0 (the others return what they have): halves of the waves that are left meet
+// until one is.  s_top: WAVES / 2 x 64 words.
+template <int WAVES>
+__device__ inline u64 ex_waves_merge(u64 top, u64 (*s_top)[64])
+{
+    const int wave = threadIdx.x >> 6, lane = tg_lane();
+#pragma unroll
+    for (int h = WAVES / 2; h > 0; h /= 2) {
+        __syncthreads();
+        if (wave >= h && wave < 2 * h) s_top[wave - h][lane] = top;
+        __syncthreads();
+        if (wave < h) top = tg_wave_merge_low(top, s_top[wave][lane]);
+    }
+    return top;
+}
+// The k-th smallest of count keys key_of(i), found by the waves of a workgroup: waves take a batch of
+// 64 in turn, batches without a key below the wave's k-th so far are passed over, the sorted lists are merged.
+// Wave 0 returns the 64 smallest keys, ascending.
+template <int WAVES, class F>
 __device__ inline u64 ex_block_smallest(int count, int k, u64 (*s_top)[64], F key_of)
 {
     const int wave = threadIdx.x >> 6, lane = tg_lane();
     u64 top = TG_EMPTY_KEY, last = TG_EMPTY_KEY;
-    for (int b = wave * 64; b < count; b += 256) {
+    for (int b = wave * 64; b < count; b += 64 * WAVES) {
         u64 key = b + lane < count ? key_of(b + lane) : TG_EMPTY_KEY;
         if (__ballot(key < last) == 0ull) continue;
-        top = tg_wave_merge_low(top, tg_wave_sort(key));
+        key = tg_wave_sort(key);
+        top = b == wave * 64 ? key : tg_wave_merge_low(top, key);
         last = tg_shfl64(top, k - 1);
     }
-    __syncthreads();
-    if (wave > 0) s_top[wave - 1][lane] = top;
-    __syncthreads();
-    if (wave > 0) return TG_EMPTY_KEY;
-    for (int i = 0; i < 3 && i * 64 + 64 < count; ++i) top = tg_wave_merge_low(top, s_top[i][lane]);
-    return top;
+    return ex_waves_merge<WAVES>(top, s_top);
 }
 // upper bound of an entry's value: w + m with the row's own norm and residual (unit rows in the fp32 cosine scan)
 __device__ inline u64 ex_upper_key(const ExScanArgs& a, u64 e, float4 qm, float kq, bool unit)
@@ -872,16 +927,19 @@ __device__ inline u64 ex_upper_key(const ExScanArgs& a, u64 e, float4 qm, float 
     if (up != up) return TG_EMPTY_KEY;                                  // an undefined distance bounds no other
     return ((u64)tg_ord(up) << 32) | row;
 }
-// tau of every query from the entries of a sample: one workgroup per query
-__global__ __launch_bounds__(256) void ex_select_kernel(ExScanArgs a, int k, int fixed_count, int unit)
+// tau of every query from the entries of a sample: one workgroup per query, of sixteen waves where there are few queries and the time of
+// one is the time of all (64 queries: 9.5 -> 5.9 us; the answers below got no faster, 11.1 -> 12.3), of four where they fill the chip.
+#define EX_FEW 512
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void ex_select_kernel(ExScanArgs a, int k, int fixed_count, int unit)
 {
-    __shared__ u64 s_top[3][64];
+    __shared__ u64 s_top[WAVES / 2][64];
     const int64_t q = blockIdx.x;
     if (a.qrow[q] < 0) return;
     const int count = fixed_count ? fixed_count : (int)min(a.cnt[q * EX_CSTRIDE], (u32)EX_CAP);
     const float4 qm = a.qmeta[q];
     const u64* e = a.buf + q * EX_CAP;
-    const u64 top = ex_block_smallest(count, k, s_top, [&](int i) { return ex_upper_key(a, e[i], qm, a.c1 * qm.z, unit != 0); });
+    const u64 top = ex_block_smallest<WAVES>(count, k, s_top, [&](int i) { return ex_upper_key(a, e[i], qm, a.c1 * qm.z, unit != 0); });
     if (threadIdx.x < 64) {
         const u64 kth = tg_shfl64(top, k - 1);
         if (threadIdx.x == 0) {
@@ -894,12 +952,13 @@ __global__ __launch_bounds__(256) void ex_select_kernel(ExScanArgs a, int k, int
 
 // The answer of a query from its list: entries that cannot be among the k nearest by the list's own k-th smallest upper
 // bound fall out, the others are measured directly (16 lanes per row, the sum taken as exact_scan_kernel takes it), sorted, written.
-__global__ __launch_bounds__(256) void ex_answer_kernel(ExScanArgs a, const float* __restrict__ X, int ld, const float* __restrict__ rnorm, int k,
+#define EX_ANSWER_WAVES 4
+__global__ __launch_bounds__(64 * EX_ANSWER_WAVES) void ex_answer_kernel(ExScanArgs a, const float* __restrict__ X, int ld, const float* __restrict__ rnorm, int k,
                                                         int fixed_count, int unit, int32_t* __restrict__ out_ids, float* __restrict__ out_dist)
 {
     extern __shared__ __align__(16) float s_q[];
-    __shared__ u64 s_top[3][64];
-    __shared__ u64 s_key[256];
+    __shared__ u64 s_top[EX_ANSWER_WAVES / 2][64];
+    __shared__ u64 s_key[64 * EX_ANSWER_WAVES];
     __shared__ u32 s_row[EX_CAP];
     __shared__ float s_tau;
     __shared__ u32 s_n;
@@ -916,7 +975,7 @@ __global__ __launch_bounds__(256) void ex_answer_kernel(ExScanArgs a, const floa
         return;
     }
     const float* xq = X + (int64_t)qrow * ld;
-    for (int c = tid * 4; c < ld; c += 1024) *reinterpret_cast<float4*>(s_q + c) = *reinterpret_cast<const float4*>(xq + c);
+    for (int c = tid * 4; c < ld; c += 256 * EX_ANSWER_WAVES) *reinterpret_cast<float4*>(s_q + c) = *reinterpret_cast<const float4*>(xq + c);
     const int count = (int)cnt;
     const float4 qm = a.qmeta[q];
     const float kq = a.c1 * qm.z;
@@ -925,7 +984,7 @@ __global__ __launch_bounds__(256) void ex_answer_kernel(ExScanArgs a, const floa
     u64 top = TG_EMPTY_KEY;
     float tau = __builtin_inff();
     if (count > k) {
-        top = ex_block_smallest(count, k, s_top, [&](int i) { return ex_upper_key(a, ent[i], qm, kq, unit != 0); });
+        top = ex_block_smallest<EX_ANSWER_WAVES>(count, k, s_top, [&](int i) { return ex_upper_key(a, ent[i], qm, kq, unit != 0); });
         if (wave == 0) {
             const u64 kth = tg_shfl64(top, k - 1);
             if (lane == 0) s_tau = kth == TG_EMPTY_KEY ? __builtin_inff() : tg_unord((u32)(kth >> 32));
@@ -935,7 +994,7 @@ __global__ __launch_bounds__(256) void ex_answer_kernel(ExScanArgs a, const floa
     } else {
         __syncthreads();
     }
-    for (int i = tid; i < count; i += 256) {
+    for (int i = tid; i < count; i += 64 * EX_ANSWER_WAVES) {
         const u64 e = ent[i];
         if (e == TG_EMPTY_KEY) continue;
         const u32 row = (u32)e;
@@ -950,7 +1009,7 @@ __global__ __launch_bounds__(256) void ex_answer_kernel(ExScanArgs a, const floa
     u64 last = TG_EMPTY_KEY;
     // a wave measures 64 rows (16 per quarter, four of them on their way at a time), then folds them into its list
     u64* mine = s_key + wave * 64;
-    for (int b = wave * 64; b < m; b += 256) {
+    for (int b = wave * 64; b < m; b += 64 * EX_ANSWER_WAVES) {
         mine[lane] = TG_EMPTY_KEY;
         ex_sync();
         for (int p0 = 0; p0 < 64 && b + p0 < m; p0 += 16) {
@@ -991,19 +1050,15 @@ __global__ __launch_bounds__(256) void ex_answer_kernel(ExScanArgs a, const floa
             }
         }
         ex_sync();
-        const u64 key = mine[lane];
+        u64 key = mine[lane];
         ex_sync();
         if (__ballot(key < last) == 0ull) continue;
-        top = tg_wave_merge_low(top, tg_wave_sort(key));
+        key = tg_wave_sort(key);
+        top = b == wave * 64 ? key : tg_wave_merge_low(top, key);
         last = tg_shfl64(top, k - 1);
     }
-    __syncthreads();
-    if (wave > 0) s_top[wave - 1][lane] = top;
-    __syncthreads();
-    if (wave == 0) {
-        for (int i = 0; i < 3 && i * 64 + 64 < m; ++i) top = tg_wave_merge_low(top, s_top[i][lane]);
-        ex_write_row(top, k, q, out_ids, out_dist);
-    }
+    top = ex_waves_merge<EX_ANSWER_WAVES>(top, s_top);
+    if (wave == 0) ex_write_row(top, k, q, out_ids, out_dist);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1150,10 +1205,6 @@ void tg_launch_exact_screened(const float* X, int ld, int64_t n, int d, int k, i
         a.rowbytes = 2 * ldh;
         a.er = er;
     } else {
-        TgGraph g = {};
-        g.n = n; g.d = d; g.ld = ld; g.k = k; g.metric = metric;
-        g.X = X; g.nrm = rn; g.rnorm = rnorm;
-        tg_launch_norms(g, nullptr, nullptr, s);
         a.rows = reinterpret_cast<const unsigned char*>(X);
         a.rowbytes = 4 * ld;
     }
@@ -1189,23 +1240,28 @@ void tg_launch_exact_screened(const float* X, int ld, int64_t n, int d, int k, i
         a.tau = reinterpret_cast<float*>(tb((size_t)pad * 4));
         a.fb_list = reinterpret_cast<u32*>(tb((size_t)pad * 4 + 4));
         a.fb_n = a.fb_list + a.nq;
-        hipLaunchKernelGGL(ex_query_kernel, dim3((unsigned)(pad / 4)), dim3(256), 0, s, a, f16 ? 1 : 0, rows, q0, pad, (const float*)rnorm);
+        const int64_t norm_wgs = f16 || q0 ? 0 : (n + 15) / 16 < 2048 ? (n + 15) / 16 : 2048;
+        hipLaunchKernelGGL(ex_query_kernel, dim3((unsigned)(pad / 4 + norm_wgs)), dim3(256), 0, s, a, f16 ? 1 : 0, rows, q0, pad, ld, rn, rnorm);
         const int first = (int)(n < EX_CAP ? n : EX_CAP);
+        const bool few = a.nq <= EX_FEW;
+        auto select = [&](int fixed) {
+            hipLaunchKernelGGL((few ? ex_select_kernel<16> : ex_select_kernel<4>), dim3((unsigned)a.nq), dim3(few ? 1024 : 256), 0, s, a, k, fixed, unit);
+        };
         a.nvisit = first;
         a.step = n > EX_CAP ? step : 1;                                // (fewer rows than places: all of them in order)
         a.step_by_n = (double)a.step / (double)n;
         ex_launch_scan(a, f16, EX_FIRST, s);
         if (n > EX_CAP) {
-            hipLaunchKernelGGL(ex_select_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a, k, first, unit);
+            select(first);
             for (int i = 0; i < levels; ++i) {
                 a.nvisit = level[i];
                 ex_launch_scan(a, f16, EX_SAMPLE, s);
-                hipLaunchKernelGGL(ex_select_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a, k, 0, unit);
+                select(0);
             }
             a.nvisit = n;
             ex_launch_scan(a, f16, EX_FULL, s);
         }
-        hipLaunchKernelGGL(ex_answer_kernel, dim3((unsigned)a.nq), dim3(256), shm_q, s, a, X, ld, (const float*)rnorm, k, n > EX_CAP ? 0 : first, unit,
+        hipLaunchKernelGGL(ex_answer_kernel, dim3((unsigned)a.nq), dim3(64 * EX_ANSWER_WAVES), shm_q, s, a, X, ld, (const float*)rnorm, k, n > EX_CAP ? 0 : first, unit,
                            out_ids + q0 * k, out_dist ? out_dist + q0 * k : nullptr);
         if (n > EX_CAP) {
             // queries whose list overflowed, if any (the lists are free by now: they take the partial results)
