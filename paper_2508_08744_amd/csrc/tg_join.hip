@@ -266,11 +266,11 @@ struct ListShare {
     int64_t first, count;        // records
     int64_t index, workgroups;   // this workgroup, among those that walk the share
 };
-__device__ inline ListShare list_share(int64_t count, bool ordered)
+__device__ inline ListShare list_share(int64_t count, bool ordered, u32 wg, u32 wgs)
 {
-    if (!ordered || (gridDim.x & 7u)) return {0, count, (int64_t)blockIdx.x, (int64_t)gridDim.x};
-    const int64_t share = (count + 7) >> 3, first = (int64_t)(blockIdx.x & 7u) * share;
-    return {first, min(share, count - first), (int64_t)(blockIdx.x >> 3), (int64_t)(gridDim.x >> 3)};
+    if (!ordered || (wgs & 7u)) return {0, count, (int64_t)wg, (int64_t)wgs};
+    const int64_t share = (count + 7) >> 3, first = (int64_t)(wg & 7u) * share;
+    return {first, min(share, count - first), (int64_t)(wg >> 3), (int64_t)(wgs >> 3)};
 }
 
 // Candidate slots of member t for anchor v's block: the pair (t, v) owns
@@ -323,8 +323,9 @@ struct JoinArgs {
     int64_t direct_count;
     int skip_le;
 };
+// wg of wgs: the workgroup's number among those that walk the list
 template <int DK, int MODE, int SRC, int ROWS>
-__device__ __forceinline__ void join_body(const JoinArgs& A)
+__device__ __forceinline__ void join_body(const JoinArgs& A, u32 wg, u32 wgs)
 {
     const TgGraph& g = A.g;
     const TgSample& sm = A.sm;
@@ -351,7 +352,7 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
     const u32 idmax = (u32)(g.n - 1);
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const ListShare part = list_share(A.wl ? (int64_t)*A.wl_cnt : A.direct_count, MODE == 0 && tg_use_order(g));
+    const ListShare part = list_share(A.wl ? (int64_t)*A.wl_cnt : A.direct_count, MODE == 0 && tg_use_order(g), wg, wgs);
     int64_t w = part.index;
     if (w >= part.count) return;
     if (MODE == 0) {
@@ -630,9 +631,9 @@ __device__ __forceinline__ void join_body(const JoinArgs& A)
 template <int DK, int MODE, bool COPY, int ROWS>
 __global__ __launch_bounds__(JOIN_THREADS, ROWS <= 64 ? 4 : 2) void join_kernel(JoinArgs A)
 {
-    if (MODE == 0 && A.g.bytes && A.g.d > 1 && tg_whole_bytes(A.g.bytes, A.g.d)) join_body<DK, MODE, ROWS_CODES, ROWS>(A);
-    else if (COPY && (!A.g.f16_ok || *A.g.f16_ok != 0u)) join_body<DK, MODE, ROWS_HALF, ROWS>(A);
-    else join_body<DK, MODE, ROWS_F32, ROWS>(A);
+    if (MODE == 0 && A.g.bytes && A.g.d > 1 && tg_whole_bytes(A.g.bytes, A.g.d)) join_body<DK, MODE, ROWS_CODES, ROWS>(A, blockIdx.x, gridDim.x);
+    else if (COPY && (!A.g.f16_ok || *A.g.f16_ok != 0u)) join_body<DK, MODE, ROWS_HALF, ROWS>(A, blockIdx.x, gridDim.x);
+    else join_body<DK, MODE, ROWS_F32, ROWS>(A, blockIdx.x, gridDim.x);
 }
 
 
@@ -670,11 +671,13 @@ struct WaveShared {
 // v_mfma_f32_16x16x32_f16 (fp32 accumulation) in place of eight fp32 matrix instructions.
 // Waves per SIMD that the compiler must leave room for.
 __host__ __device__ constexpr int wave_least(int gmax, int ks) { return gmax * ks <= 18 ? 3 : 2; }
-template <int GMAX, int MODE, int METRIC, int KS, bool FULL, bool NARROW>
-__global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins,
-                                                        const int32_t* xblk, const int32_t* xsizes, float* xout,
-                                                        const u64* __restrict__ wl, const u32* __restrict__ wl_cnt,
-                                                        int64_t direct_count, int gmin)
+// TWO: two lists, the one of blocks of four groups first.
+template <int GMAX, int MODE, int METRIC, int KS, bool FULL, bool NARROW, bool TWO>
+__device__ __forceinline__ void join_wave_body(const TgGraph& g, const TgSample& sm, const TgCand& cd, u64 hs_slot, u64* stat_bins,
+                                               const int32_t* xblk, const int32_t* xsizes, float* xout,
+                                               const u64* __restrict__ wl, const u32* __restrict__ wl_cnt,
+                                               const u64* __restrict__ wl_more, const u32* __restrict__ wl_more_cnt,
+                                               int64_t direct_count, int gmin, u32 wg, u32 wgs)
 {
     extern __shared__ __align__(16) unsigned char wave_smem[];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = tg_lane();
@@ -683,7 +686,9 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
     const float INF = __builtin_inff();
     if (g.f16_ok && (*g.f16_ok != 0u) != NARROW) return;      // the other variant's turn
     if (MODE == 0 && g.bytes && tg_whole_bytes(g.bytes, g.d)) return;      // join_bytes_kernel's
-    const ListShare share = list_share(wl ? (int64_t)*wl_cnt : direct_count, MODE == 0 && tg_use_order(g));
+    const int64_t count_first = wl ? (int64_t)*wl_cnt : direct_count;
+    const ListShare share = TWO ? ListShare{0, count_first + (int64_t)*wl_more_cnt, (int64_t)wg, (int64_t)wgs}
+                                : list_share(count_first, MODE == 0 && tg_use_order(g), wg, wgs);
     const int64_t count = share.count;
     const int64_t nwaves = share.workgroups * 4;
     const u32 idmax = (u32)(g.n - 1);
@@ -694,7 +699,8 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
     auto load_rec = [&](int64_t w) -> u64 {
         const int64_t wc = w < count ? w : count - 1;
         u64 rec;
-        if (MODE == 0) rec = wl[share.first + wc];
+        if (TWO) rec = wc < count_first ? wl[wc] : wl_more[wc - count_first];
+        else if (MODE == 0) rec = wl[share.first + wc];
         else rec = tg_pack_rec((u32)wc, xsizes[wc * 2], xsizes[wc * 2] + xsizes[wc * 2 + 1]);
         return w < count ? rec : 0ull;
     };
@@ -975,6 +981,31 @@ __global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(Tg
         buf ^= 1;
     }
     if (MODE == 0 && prev_nT > 0) flush_cells(buf ^ 1, prev_nT);
+}
+
+template <int GMAX, int MODE, int METRIC, int KS, bool FULL, bool NARROW>
+__global__ __launch_bounds__(256, wave_least(GMAX, KS)) void join_wave_kernel(TgGraph g, TgSample sm, TgCand cd, u64 hs_slot, u64* stat_bins,
+                                                                              const int32_t* xblk, const int32_t* xsizes, float* xout,
+                                                                              const u64* __restrict__ wl, const u32* __restrict__ wl_cnt,
+                                                                              int64_t direct_count, int gmin)
+{
+    join_wave_body<GMAX, MODE, METRIC, KS, FULL, NARROW, false>(g, sm, cd, hs_slot, stat_bins, xblk, xsizes, xout, wl, wl_cnt, nullptr, nullptr,
+                                                                direct_count, gmin, blockIdx.x, gridDim.x);
+}
+
+// All three lists of a part in one launch, for builds whose launches are short: the first workgroups take the blocks of more than 64
+// members, the others the rest (blocks of up to 48 members fetch a row group more than in a kernel of their own, which hardly counts here).
+// A: with the list of the large blocks; its neighbours in the work lists are the other two.
+template <int METRIC, int KS>
+__global__ __launch_bounds__(256, wave_least(4, KS)) void join_all_kernel(JoinArgs A, u32 large_wgs, int64_t cap)
+{
+    if (blockIdx.x < large_wgs) {
+        if (A.g.bytes && A.g.d > 1 && tg_whole_bytes(A.g.bytes, A.g.d)) join_body<64, 0, ROWS_CODES, TG_BLOCK_COLS>(A, blockIdx.x, large_wgs);
+        else join_body<64, 0, ROWS_F32, TG_BLOCK_COLS>(A, blockIdx.x, large_wgs);
+    } else {
+        join_wave_body<4, 0, METRIC, KS, false, false, true>(A.g, A.sm, A.cd, A.hs_slot, A.stat_bins, nullptr, nullptr, nullptr, A.wl - cap, A.wl_cnt - 1,
+                                                             A.wl - 2 * cap, A.wl_cnt - 2, 0, 0, blockIdx.x - large_wgs, gridDim.x - large_wgs);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1287,6 +1318,29 @@ static void launch_wave_dump(const TgGraph& g, const int32_t* blk, const int32_t
 
 static bool wave_path(const TgGraph& g) { return tg_join_wave_ok(g.ld); }
 
+// One launch for the three lists of a part where they are short: the two of small blocks and the mostly empty one of large blocks took 23 + 9 + 8 us
+// one after another in a build of 10 000 x 32.  Whole builds of eight rounds, three launches / one, us: 10 000 x 32, k = 16: 728 / 645; 3000 x 24,
+// k = 32: 575 / 489; 20 000 x 128 bytes: 1609 / 1518; 37 511 x 50, k = 20: 2186 / 2115; 80 000 x 64, k = 24: 3593 / 3548; 60 000 x 20, k = 10: 1993 / 1994.
+#define JOIN_ALL_MOST 40000      // anchors of a part
+#define JOIN_ALL_LARGE 512       // workgroups for the blocks of more than 64 members
+template <int METRIC, int KS>
+static void launch_join_all_k(const JoinArgs& A, int64_t cap, hipStream_t s)
+{
+    const size_t large = join_lds_bytes(64, A.sm.BC), shm = large > 4 * sizeof(WaveShared) ? large : 4 * sizeof(WaveShared);
+    constexpr int most = wave_least(4, KS) * 768;
+    const unsigned large_wgs = (unsigned)(cap < JOIN_ALL_LARGE ? cap : JOIN_ALL_LARGE);
+    const int64_t wgs = (cap + 3) / 4;
+    tg_allow_lds<join_all_kernel<METRIC, KS>>(join_lds_bytes(64, TG_BLOCK_COLS));
+    hipLaunchKernelGGL((join_all_kernel<METRIC, KS>), dim3(large_wgs + (unsigned)(wgs < most ? wgs : most)), dim3(256), shm, s, A, large_wgs, cap);
+}
+template <int METRIC>
+static void launch_join_all(const JoinArgs& A, int64_t cap, hipStream_t s)
+{
+    if (A.g.ld <= 64) launch_join_all_k<METRIC, 4>(A, cap, s);
+    else if (A.g.ld <= 96) launch_join_all_k<METRIC, 6>(A, cap, s);
+    else launch_join_all_k<METRIC, 8>(A, cap, s);
+}
+
 void tg_launch_join(const TgGraph& g, const TgSample& sm, const TgCand& c, int part, int parts, uint64_t hs_slot,
                     unsigned long long* stat_bins, hipStream_t s)
 {
@@ -1296,6 +1350,17 @@ void tg_launch_join(const TgGraph& g, const TgSample& sm, const TgCand& c, int p
         const dim3 grid(JOIN_BYTES_GRID), block(256);
         if (g.ldq <= 64) hipLaunchKernelGGL(join_bytes_kernel<1>, grid, block, 0, s, g, sm, c, hs_slot, stat_bins, part, cap);
         else hipLaunchKernelGGL(join_bytes_kernel<2>, grid, block, 0, s, g, sm, c, hs_slot, stat_bins, part, cap);
+    }
+    if (wv && !g.Xh && !g.order && wl_cap(g.n, parts) <= JOIN_ALL_MOST) {
+        const int64_t cap = wl_cap(g.n, parts);
+        JoinArgs A = {};
+        A.g = g; A.sm = sm; A.cd = c; A.hs_slot = hs_slot; A.stat_bins = stat_bins;
+        A.wl = sm.wl + (int64_t)(part * 3 + 2) * cap;
+        A.wl_cnt = sm.wl_cnt + part * 3 + 2;
+        if (g.metric == 0) launch_join_all<0>(A, cap, s);
+        else if (g.metric == 1) launch_join_all<1>(A, cap, s);
+        else launch_join_all<2>(A, cap, s);
+        return;
     }
     if (wv) {
         launch_wave_t<3>(g, sm, c, hs_slot, stat_bins, part * 3 + 0, parts, s);
