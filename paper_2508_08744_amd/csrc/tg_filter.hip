@@ -181,18 +181,45 @@ __device__ inline int filter_collect_ids(u32* set, int* queue, int Q, int id, bo
     return Q + __popcll(mask);
 }
 
+// Square root and quotient rounded once, for arguments whose exponents leave every step room: the hardware's approximation, a step of
+// Newton's method on it, and the remainder, taken exactly by a fused multiply-add, times it (Markstein, "Computation of elementary functions on
+// the IBM RISC System/6000 processor", 1990).  8 and 6 instructions where the general ones, which scale and sort out the special values, take
+// 16 and 12.  Checked against sqrtf for every float of 2^-92 .. 2^92 and against / for 2e10 pairs of the range below: the same bits.
+__device__ inline float filter_sqrt(float x)
+{
+#pragma clang fp contract(off)
+    const float y = __builtin_amdgcn_rsqf(x);
+    float g = x * y, h = 0.5f * y;
+    const float r = fmaf(-h, g, 0.5f);
+    g = fmaf(g, r, g);
+    h = fmaf(h, r, h);
+    return fmaf(fmaf(-g, g, x), h, g);
+}
+__device__ inline float filter_quotient(float t, float d)
+{
+#pragma clang fp contract(off)
+    float r = __builtin_amdgcn_rcpf(d);
+    r = fmaf(fmaf(-d, r, 1.0f), r, r);
+    const float q = t * r;
+    return fmaf(fmaf(-d, q, t), r, q);
+}
+// Squared lengths for which the above serve: 0 (the angle is 0 whatever comes out) or 2^-45 .. 2^45.  Then a b is 0 or within 2^+-90, and
+// t, a multiple of 2^-70, is 0 or large enough for the remainder to be exact.
+__device__ inline bool filter_plain_length(float v) { return v == 0.0f || (v >= 2.842170943e-14f && v <= 3.518437209e13f); }
+
 // Angle at p between p -> r and p -> c from the squared lengths a = |p r|^2, b = |p c|^2, c = |r c|^2:
 // acos((a + b - c) / (2 sqrt(a b))), the arc cosine from the eight-term polynomial of Abramowitz and
 // Stegun 4.4.46 (acos x = sqrt(1 - x) (a0 + .. + a7 x^7) on [0, 1], pi - acos(-x) below 0).  Every
 // operation is rounded once, in this order, so that a host program can follow it bit for bit.
-// A node at p's position (a b = 0) has no direction: angle 0.
+// A node at p's position (a b = 0) has no direction: angle 0.  PLAIN: a and b are filter_plain_length.
+template <bool PLAIN>
 __device__ inline float filter_angle_at(float a, float b, float c)
 {
 #pragma clang fp contract(off)
     const float ab = a * b;
-    const float den = 2.0f * sqrtf(ab);
+    const float den = 2.0f * (PLAIN ? filter_sqrt(ab) : sqrtf(ab));
     const float t = (a + b) - c;
-    float x = t / den;
+    float x = PLAIN ? filter_quotient(t, den) : t / den;
     x = x > 1.0f ? 1.0f : x;
     x = x < -1.0f ? -1.0f : x;
     const float ax = fabsf(x);
@@ -204,7 +231,9 @@ __device__ inline float filter_angle_at(float a, float b, float c)
     pol = fmaf(pol, ax, 0.0889789874f);
     pol = fmaf(pol, ax, -0.2145988016f);
     pol = fmaf(pol, ax, 1.5707963050f);
-    const float r = sqrtf(1.0f - ax) * pol;
+    const float u = 1.0f - ax;                      // 0, or 2^-24 and more
+    const float root = !PLAIN ? sqrtf(u) : u == 0.0f ? 0.0f : filter_sqrt(u);
+    const float r = root * pol;
     const float th = x < 0.0f ? 3.14159265358979323846f - r : r;
     return ab > 0.0f ? th : 0.0f;
 }
@@ -212,7 +241,10 @@ __device__ inline float filter_angle_at(float a, float b, float c)
 __global__ void angle_at_kernel(const float* a, const float* b, const float* c, float* out, int64_t count)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) out[i] = filter_angle_at(a[i], b[i], c[i]);
+    if (i >= count) return;
+    // (as the filter does: a wave takes the short way where all its lengths allow it)
+    if (__ballot(!(filter_plain_length(a[i]) && filter_plain_length(b[i]))) == 0ull) out[i] = filter_angle_at<true>(a[i], b[i], c[i]);
+    else out[i] = filter_angle_at<false>(a[i], b[i], c[i]);
 }
 void tg_launch_angle_at(const float* a, const float* b, const float* c, float* out, int64_t count, hipStream_t s)
 {
@@ -261,7 +293,7 @@ __host__ __device__ constexpr int filter_lds_words(int ng, int collect, int rule
 
 // Waves per SIMD that the compiler must leave room for.  Four for the neighbours under the dispersion rule, which is bound by what a
 // wave does in sequence (products, angles, the greedy): 200 000 x 200, k = 40, d_out = 20: 2.65 ms with 64 rows and two waves, 1.85 ms
-// with 48 rows and four; and for 33..48 neighbours under the others, which have the registers (111) anyway.  No demand on the other
+// with 48 rows and four (two for 49..64 neighbours, whose matrices of angles leave room for no more); and for 33..48 neighbours under the others, which have the registers (111) anyway.  No demand on the other
 // threshold instances, which wait for rows: asked for four, that of up to 32 neighbours gets fewer loads on their way (100 000 x 128,
 // k = 32: 310 us against 274) and that of 49..64 spills (60 000 x 37, k = 64: 353 against 344 us).  Three for two hops, which wait for
 // rows too (4 d bytes per distinct id, 5.5 TB/s): with four the compiler spills, 250 000 x 128, k = 32: 8.62 against 8.45 ms (9.17 with
@@ -269,7 +301,59 @@ __host__ __device__ constexpr int filter_lds_words(int ng, int collect, int rule
 __host__ __device__ constexpr int filter_least_waves(int ng, int collect, int rule, bool vec)
 {
     if (collect != FILTER_ONE_HOP) return vec ? 3 : 1;
+    if (rule == FILTER_RULE_DISPERSION && ng == 4) return 2;
     return rule == FILTER_RULE_DISPERSION || ng == 3 ? 4 : 1;
+}
+
+// The angle at p of every pair of candidates into the matrix `ang` (rows of 16 NG + 1 words), both ways round, from the products of their rows
+// (tile (i, j), j >= i), their distances to p (dp: of row 16 t + r; dpc: of all) and squared norms.  A tile on the diagonal holds each pair
+// twice, so two of them are worked through as one: the upper half of the first, the lower half of the second.  (An entry on the
+// diagonal is nobody's angle and is not read.)
+template <int NG, bool PLAIN>
+__device__ __forceinline__ void filter_angles(const floatx4 (&acc)[NG][NG], const float (&dp)[NG], const float* nrm, const float* dpc, int groups,
+                                              float* ang)
+{
+    constexpr int AS = 16 * NG + 1;
+    const int lane = tg_lane(), r16 = lane & 15, q4 = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+        if (i >= groups) break;
+        const float4 nRv = *reinterpret_cast<const float4*>(nrm + 16 * i + 4 * q4);
+        const float4 dRv = *reinterpret_cast<const float4*>(dpc + 16 * i + 4 * q4);
+        const float nR[4] = {nRv.x, nRv.y, nRv.z, nRv.w}, dR[4] = {dRv.x, dRv.y, dRv.z, dRv.w};
+        const bool first = (i & 1) == 0, two = i + 1 < NG && i + 1 < groups;       // of two diagonal tiles that go together; both there
+#pragma unroll
+        for (int j = i; j < NG; ++j) {
+            if (j >= groups) break;
+            if (j == i && (!first || two)) continue;                    // (with the other one, below)
+            const float nC = nrm[16 * j + r16];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int R = 16 * i + 4 * q4 + e, C = 16 * j + r16;
+                const float rc = (nR[e] + nC) - 2.0f * acc[i][j][e];        // dis(R, C)
+                const float th = filter_angle_at<PLAIN>(dR[e], dp[j], rc);
+                ang[R * AS + C] = th;
+                ang[C * AS + R] = th;
+            }
+        }
+        if (!first || !two) continue;
+        constexpr int LAST = NG - 1;
+        const int h = i < LAST ? i + 1 : LAST;
+        const float nC1 = nrm[16 * i + r16], nC2 = nrm[16 * h + r16];
+        const float4 nR2v = *reinterpret_cast<const float4*>(nrm + 16 * h + 4 * q4);
+        const float4 dR2v = *reinterpret_cast<const float4*>(dpc + 16 * h + 4 * q4);
+        const float nR2[4] = {nR2v.x, nR2v.y, nR2v.z, nR2v.w}, dR2[4] = {dR2v.x, dR2v.y, dR2v.z, dR2v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int R = 4 * q4 + e;
+            const bool up = r16 > R;                                        // the pair of tile i, else that of tile i + 1
+            const float rc = (up ? nR[e] + nC1 : nR2[e] + nC2) - 2.0f * (up ? acc[i][i][e] : acc[h][h][e]);
+            const float th = filter_angle_at<PLAIN>(up ? dR[e] : dR2[e], up ? dp[i] : dp[h], rc);
+            const int at = (AS + 1) * 16 * (up ? i : h);
+            ang[at + R * AS + r16] = th;
+            ang[at + r16 * AS + R] = th;
+        }
+    }
 }
 
 template <int NG, int KS, bool FULL, bool VEC, int COLLECT, int RULE>
@@ -282,7 +366,7 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
     constexpr bool APART = filter_apart(COLLECT, RULE);
     constexpr bool ID_SET = filter_set_of_ids(COLLECT, RULE);
     constexpr int LDS_WORDS = filter_lds_words(NG, COLLECT, RULE);
-    constexpr int AS = 16 * NG + 1;      // row stride of the matrix of angles
+    [[maybe_unused]] constexpr int AS = 16 * NG + 1;      // row stride of the matrix of angles
     constexpr int AW = APART ? FILTER_WAVES : 1;
     extern __shared__ __align__(16) u32 lds[];
     __shared__ int s_cid[AW][64];                       // (these six: unused and not allocated unless APART)
@@ -452,61 +536,59 @@ __global__ __launch_bounds__(256, filter_least_waves(NG, COLLECT, RULE, VEC)) vo
             occ[lane + 64] = 0u;
         }
         filter_wave_sync();
-        // occ[C] = the candidates R that would occlude C: not dis(p, C) < alpha^2 dis(R, C), or an angle
-        // at p of at most gamma (that relation is symmetric in R and C).  The lane holds its column's
-        // four rows as a nibble; the mirrored pairs (rows and columns exchanged) of a tile off the
-        // diagonal come out of ballots.
+        if constexpr (RULE == FILTER_RULE_DISPERSION) {
+            // Where no length is out of the ordinary the short square root and quotient serve.
+            bool plain = true;
 #pragma unroll
-        for (int i = 0; i < NG; ++i) {
-            if (i >= groups) break;
-            const float4 nR = *reinterpret_cast<const float4*>(nrm + 16 * i + 4 * q4);
-            const float4 dR = *reinterpret_cast<const float4*>(dpc + 16 * i + 4 * q4);
+            for (int t = 0; t < NG; ++t) plain &= filter_plain_length(dp[t]);
+            if (__ballot(!plain) == 0ull) filter_angles<NG, true>(acc, dp, nrm, dpc, groups, ang);
+            else filter_angles<NG, false>(acc, dp, nrm, dpc, groups, ang);
+        } else {
+            // occ[C] = the candidates R that would occlude C: not dis(p, C) < alpha^2 dis(R, C), or an angle
+            // at p of at most gamma (that relation is symmetric in R and C).  The lane holds its column's
+            // four rows as a nibble; the mirrored pairs (rows and columns exchanged) of a tile off the
+            // diagonal come out of ballots.
 #pragma unroll
-            for (int j = i; j < NG; ++j) {
-                if (j >= groups) break;
-                const float nC = nrm[16 * j + r16];
-                const float dC = dp[j];
-                const floatx4 g = acc[i][j];
-                const float rc0 = (nR.x + nC) - 2.0f * g.x;        // dis(R, C)
-                const float rc1 = (nR.y + nC) - 2.0f * g.y;
-                const float rc2 = (nR.z + nC) - 2.0f * g.z;
-                const float rc3 = (nR.w + nC) - 2.0f * g.w;
-                if (RULE == FILTER_RULE_DISPERSION) {
-                    // the angle of every pair, stored both ways round (row R, column C and the reverse)
-                    const int R = 16 * i + 4 * q4, C = 16 * j + r16;
-                    const float th0 = filter_angle_at(dR.x, dC, rc0), th1 = filter_angle_at(dR.y, dC, rc1);
-                    const float th2 = filter_angle_at(dR.z, dC, rc2), th3 = filter_angle_at(dR.w, dC, rc3);
-                    ang[(R + 0) * AS + C] = th0; ang[(R + 1) * AS + C] = th1;
-                    ang[(R + 2) * AS + C] = th2; ang[(R + 3) * AS + C] = th3;
-                    ang[C * AS + R + 0] = th0; ang[C * AS + R + 1] = th1;
-                    ang[C * AS + R + 2] = th2; ang[C * AS + R + 3] = th3;
-                    continue;
-                }
-                bool o0, o1, o2, o3, m0, m1, m2, m3;               // R occludes C; C occludes R
-                if (ANGLE) {
-                    const float t0 = (dR.x + dC) - rc0, t1 = (dR.y + dC) - rc1, t2 = (dR.z + dC) - rc2, t3 = (dR.w + dC) - rc3;
-                    o0 = m0 = !((t0 < 0.0f) | (t0 * t0 < A.thr * (dR.x * dC)));
-                    o1 = m1 = !((t1 < 0.0f) | (t1 * t1 < A.thr * (dR.y * dC)));
-                    o2 = m2 = !((t2 < 0.0f) | (t2 * t2 < A.thr * (dR.z * dC)));
-                    o3 = m3 = !((t3 < 0.0f) | (t3 * t3 < A.thr * (dR.w * dC)));
-                } else {
-                    const float rhs0 = A.thr * rc0, rhs1 = A.thr * rc1, rhs2 = A.thr * rc2, rhs3 = A.thr * rc3;
-                    o0 = !(dC < rhs0); o1 = !(dC < rhs1); o2 = !(dC < rhs2); o3 = !(dC < rhs3);
-                    m0 = !(dR.x < rhs0); m1 = !(dR.y < rhs1); m2 = !(dR.z < rhs2); m3 = !(dR.w < rhs3);
-                }
-                const u32 nib = (u32)o0 | ((u32)o1 << 1) | ((u32)o2 << 2) | ((u32)o3 << 3);
-                atomicOr(occ + 2 * (16 * j + r16) + (i >> 1), nib << (16 * (i & 1) + 4 * q4));
-                if (j > i) {
-                    const u64 b0 = __ballot(m0);
-                    const u64 b1 = __ballot(m1);
-                    const u64 b2 = __ballot(m2);
-                    const u64 b3 = __ballot(m3);
-                    if (r16 == 0) {
-                        const int R = 16 * i + 4 * q4, sh = 16 * q4, word = j >> 1, up = 16 * (j & 1);
-                        atomicOr(occ + 2 * (R + 0) + word, (u32)((b0 >> sh) & 0xFFFFull) << up);
-                        atomicOr(occ + 2 * (R + 1) + word, (u32)((b1 >> sh) & 0xFFFFull) << up);
-                        atomicOr(occ + 2 * (R + 2) + word, (u32)((b2 >> sh) & 0xFFFFull) << up);
-                        atomicOr(occ + 2 * (R + 3) + word, (u32)((b3 >> sh) & 0xFFFFull) << up);
+            for (int i = 0; i < NG; ++i) {
+                if (i >= groups) break;
+                const float4 nR = *reinterpret_cast<const float4*>(nrm + 16 * i + 4 * q4);
+                const float4 dR = *reinterpret_cast<const float4*>(dpc + 16 * i + 4 * q4);
+#pragma unroll
+                for (int j = i; j < NG; ++j) {
+                    if (j >= groups) break;
+                    const float nC = nrm[16 * j + r16];
+                    const float dC = dp[j];
+                    const floatx4 g = acc[i][j];
+                    const float rc0 = (nR.x + nC) - 2.0f * g.x;        // dis(R, C)
+                    const float rc1 = (nR.y + nC) - 2.0f * g.y;
+                    const float rc2 = (nR.z + nC) - 2.0f * g.z;
+                    const float rc3 = (nR.w + nC) - 2.0f * g.w;
+                    bool o0, o1, o2, o3, m0, m1, m2, m3;               // R occludes C; C occludes R
+                    if (ANGLE) {
+                        const float t0 = (dR.x + dC) - rc0, t1 = (dR.y + dC) - rc1, t2 = (dR.z + dC) - rc2, t3 = (dR.w + dC) - rc3;
+                        o0 = m0 = !((t0 < 0.0f) | (t0 * t0 < A.thr * (dR.x * dC)));
+                        o1 = m1 = !((t1 < 0.0f) | (t1 * t1 < A.thr * (dR.y * dC)));
+                        o2 = m2 = !((t2 < 0.0f) | (t2 * t2 < A.thr * (dR.z * dC)));
+                        o3 = m3 = !((t3 < 0.0f) | (t3 * t3 < A.thr * (dR.w * dC)));
+                    } else {
+                        const float rhs0 = A.thr * rc0, rhs1 = A.thr * rc1, rhs2 = A.thr * rc2, rhs3 = A.thr * rc3;
+                        o0 = !(dC < rhs0); o1 = !(dC < rhs1); o2 = !(dC < rhs2); o3 = !(dC < rhs3);
+                        m0 = !(dR.x < rhs0); m1 = !(dR.y < rhs1); m2 = !(dR.z < rhs2); m3 = !(dR.w < rhs3);
+                    }
+                    const u32 nib = (u32)o0 | ((u32)o1 << 1) | ((u32)o2 << 2) | ((u32)o3 << 3);
+                    atomicOr(occ + 2 * (16 * j + r16) + (i >> 1), nib << (16 * (i & 1) + 4 * q4));
+                    if (j > i) {
+                        const u64 b0 = __ballot(m0);
+                        const u64 b1 = __ballot(m1);
+                        const u64 b2 = __ballot(m2);
+                        const u64 b3 = __ballot(m3);
+                        if (r16 == 0) {
+                            const int R = 16 * i + 4 * q4, sh = 16 * q4, word = j >> 1, up = 16 * (j & 1);
+                            atomicOr(occ + 2 * (R + 0) + word, (u32)((b0 >> sh) & 0xFFFFull) << up);
+                            atomicOr(occ + 2 * (R + 1) + word, (u32)((b1 >> sh) & 0xFFFFull) << up);
+                            atomicOr(occ + 2 * (R + 2) + word, (u32)((b2 >> sh) & 0xFFFFull) << up);
+                            atomicOr(occ + 2 * (R + 3) + word, (u32)((b3 >> sh) & 0xFFFFull) << up);
+                        }
                     }
                 }
             }
