@@ -121,6 +121,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(const u32* __restric
 // (open addressing, 256 words for at most 64 ids; ids inside one list are distinct).
 #define ASM_WORDS 256
 #define ASM_FREE 0xFFFFFFFFu
+#define ASM_PAST 0x80000000u      // of a taken place (ids have 30 bits): an id whose place it would have been is further on
 __device__ inline int asm_insert(u32* keys, u32 id, bool active)
 {
     int slot = -1;
@@ -130,25 +131,25 @@ __device__ inline int asm_insert(u32* keys, u32 id, bool active)
         if (pending) {
             const u32 old = atomicCAS(keys + h, ASM_FREE, id);
             if (old == ASM_FREE) { slot = (int)h; pending = false; }
-            else h = (h + 1) & (ASM_WORDS - 1);
+            else { atomicOr(keys + h, ASM_PAST); h = (h + 1) & (ASM_WORDS - 1); }
         }
     }
     return slot;
 }
+// (one look, and a walk only from a place that an id went past)
 __device__ inline int asm_find(const u32* keys, u32 id, bool active)
 {
-    int slot = -1;
-    bool pending = active;
     u32 h = (id * 0x9E3779B1u) >> 24;
+    u32 t = keys[h];
+    bool pending = active && t != ASM_FREE && (t & ASM_PAST) && (t & ~ASM_PAST) != id;
     while (__ballot(pending)) {
         if (pending) {
-            const u32 t = keys[h];
-            if (t == id) { slot = (int)h; pending = false; }
-            else if (t == ASM_FREE) pending = false;
-            else h = (h + 1) & (ASM_WORDS - 1);
+            h = (h + 1) & (ASM_WORDS - 1);
+            t = keys[h];
+            pending = t != ASM_FREE && (t & ASM_PAST) && (t & ~ASM_PAST) != id;
         }
     }
-    return slot;
+    return active && (t & ~ASM_PAST) == id ? (int)h : -1;
 }
 __device__ inline void assemble_block(const TgGraph& g, const TgSample& sm, int64_t v, u32 w /* list entry of lane < k */, u32 rid, bool has,
                                       u32* keys, u32* tags)
