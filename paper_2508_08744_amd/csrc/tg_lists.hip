@@ -14,11 +14,16 @@
 // ---------------------------------------------------------------------------------------
 // small utilities
 // ---------------------------------------------------------------------------------------
-__global__ void fill_u32_kernel(u32* p, size_t count, u32 v)
+// 16 bytes a store where the words allow it, `head` words in front of the first such place (500 000 lists of 32, both arrays cleared: 37 -> 23 us)
+__global__ void fill_u32_kernel(u32* p, size_t count, u32 v, u32 head)
 {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < count; i += stride) p[i] = v;
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    const size_t wide = (count - head) / 4;
+    uint4* w = reinterpret_cast<uint4*>(p + head);
+    for (size_t i = i0; i < wide; i += stride) w[i] = make_uint4(v, v, v, v);
+    if (i0 < head) p[i0] = v;
+    const size_t tail = head + 4 * wide;
+    if (i0 < count - tail) p[tail + i0] = v;
 }
 static int grid_for(size_t count, int block)
 {
@@ -29,7 +34,10 @@ static int grid_for(size_t count, int block)
 }
 void tg_launch_fill_u32(u32* p, size_t count, u32 v, hipStream_t s)
 {
-    if (count) hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(count, 256)), dim3(256), 0, s, p, count, v);
+    if (!count) return;
+    const size_t to_aligned = ((16 - (reinterpret_cast<uintptr_t>(p) & 15)) & 15) / sizeof(u32);
+    const u32 head = (u32)(to_aligned < count ? to_aligned : count);
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for((count + 3) / 4, 256)), dim3(256), 0, s, p, count, v, head);
 }
 
 // What a build expects in its workspace before the first step, in one launch (11 launches of 2-6 us each otherwise: 48 us of a
