@@ -2,7 +2,7 @@
 // rows with the smallest (distance, id), distances computed directly from the vectors in fp32.
 //
 // Measuring every pair that way is bound by the vector units (245 ms for 10 000 queries against 1M x 128, k = 32:
-// 10.5 TFLOP/s; this search takes 7.0 ms).  Here the matrix cores bound every pair from both sides first, and only pairs that may be
+// 10.5 TFLOP/s; this search takes 4.2 ms).  Here the matrix cores bound every pair from both sides first, and only pairs that may be
 // among the k nearest are measured directly:
 //   w(q, r) = |r|^2 / 2 - <q, r>  (squared L2; -<q, r> for the inner product, the same on unit vectors for the
 //   cosine) orders the rows for query q.  A tile of w is formed on the matrix cores, either from the rows
@@ -440,8 +440,8 @@ __device__ inline u32 ex_row(const ExScanArgs& a, u32 j)
 // ballot unless something passes.  MODE: all rows (EX_FULL), a sample (EX_SAMPLE), or the first sample, of which everything
 // is kept (EX_FIRST: place = number of the visit).
 // What bounds it is the vector work of a tile (bounds, maxima, the pairs that pass; about as long as its matrix instructions twice over) and
-// waits for rows, which sixteen waves on a CU cover better than eight with twice the tile each: 1M x 128 against 10 000 queries, fp16: 7.15 -> 5.0 ms
-// (512 TFLOP/s), the whole search 9.3 -> 7.1; 50 000 x 96 against 64 (fp32): 66 -> 62 us.  Where the queries come again (not RES, 128 of them) three to
+// waits for rows, which sixteen waves on a CU cover better than eight with twice the tile each: 1M x 128 against 10 000 queries, fp16 (which
+// ex_scan_wave_kernel takes now): 7.15 -> 5.0 ms; 50 000 x 96 against 64 (fp32): 66 -> 62 us.  Where the queries come again (not RES, 128 of them) three to
 // seven registers spill at four waves per SIMD, which still is the better side: whole searches with four waves a workgroup / eight / eight, two per SIMD
 // and no spill: 200 000 x 960 against 2000 (fp16): 2.33 / 2.19 / 2.81 ms; 200 000 x 200 against 4000: 1.83 / 1.54 / 2.08; 1M x 96 against 100 (fp32): 543 / 531 / 571 us.
 // ---------------------------------------------------------------------------------------
@@ -726,9 +726,9 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
 // 16 queries: the thresholds are taken for the 64 rows of a tile (the bound of a pair is made of the largest norm and the largest
 // residual among them: a little looser than a row's own, no pair is lost).
 // Pairs that pass wait in a queue of the wave's own and go to the lists up to 64 at a time and more (see ex_scan_kernel).
-// 1M x 128 against 10 000 queries: 5.75 ms with the queries in LDS and each row read for 128 of them, 0.73 the sample; now both 3.95, of
-// which 1.2 go to the pairs that pass (700 a query in either), the rest runs at 1.0 PFLOP/s (matrix units busy half the cycles; a
-// library product of this size: 1.15).  Rows 128 at a time with two waves per SIMD: 0.2 ms more; the next group's operands asked for ahead: no
+// 1M x 128 against 10 000 queries: 5.75 ms with the queries in LDS and each row read for 128 of them, 0.73 its sample; now 2.88 and 0.37, of
+// which about 1.2 go to the pairs that pass (700 a query in either); without those the scan runs at 1.0 PFLOP/s (a library product of
+// 8192 cubed: 1.15).  Rows 128 at a time with two waves per SIMD: 0.2 ms more; the next group's operands asked for ahead: no
 // gain with two waves, spills with three.
 // ---------------------------------------------------------------------------------------
 #define EXG_RT 64            // rows of a tile

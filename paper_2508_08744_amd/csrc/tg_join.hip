@@ -669,7 +669,8 @@ struct WaveShared {
 // NARROW: the rows come from the fp16 copy (g.Xh, rows of 32 KS values, zero padded): a register
 // then holds eight values, columns 32 s + 8 q .. + 7, and a tile step is one
 // v_mfma_f32_16x16x32_f16 (fp32 accumulation) in place of eight fp32 matrix instructions.
-// Waves per SIMD that the compiler must leave room for.
+// Waves per SIMD that the compiler must leave room for: three where the block's rows take at most 72 registers (blocks of 48 members and rows of
+// 96 values: 174 registers left alone, two waves): 10M x 96 cosine 501 -> 496 ms, 37 511 x 50 2487 -> 2454 us.
 __host__ __device__ constexpr int wave_least(int gmax, int ks) { return gmax * ks <= 18 ? 3 : 2; }
 // TWO: two lists, the one of blocks of four groups first.
 template <int GMAX, int MODE, int METRIC, int KS, bool FULL, bool NARROW, bool TWO>
@@ -1016,8 +1017,9 @@ __global__ __launch_bounds__(256, wave_least(4, KS)) void join_all_kernel(JoinAr
 // matrix instructions of 16 cycles instead of 32 of 32, a block of 64 members 32 registers instead of 128.
 // One wave per anchor, blocks of at most 64 members (lists 1 and 0 of the part); register layout, cells and hand-over
 // as in join_wave_kernel.  |c|^2 of every member comes off the diagonal of its group's own tile.
-// 1M x 128, k = 32: the joins of the four rounds take 4.7 + 2.5 + 2.7 + 2.9 ms, blocks of more than 64 members among them (the same points moved by a
-// quarter: 27.4 ms in fp32, 15.4 on the fp16 copy); in the first round what bounds it is the minima in LDS, eight lanes at a time on one cell.
+// Four waves per SIMD (three when the compiler took 129 registers: 11.55 -> 10.95 ms a build; five: 11.9), a block handed over one block later: 10.65.
+// 1M x 128, k = 32: the joins of the four rounds take 4.4 + 2.3 + 2.4 + 2.7 ms, blocks of more than 64 members among them (the same points moved by a
+// quarter: 26.7 ms in fp32, 14.1 on the fp16 copy); in the first round what bounds it is the minima in LDS, eight lanes at a time on one cell.
 // ---------------------------------------------------------------------------------------
 typedef int intx4 __attribute__((ext_vector_type(4)));
 #define BYTES_FAR (1 << 28)          // the norm of a row that must not count: its distances are beyond BYTES_MOST

@@ -731,6 +731,8 @@ __device__ inline u64 update_settle(u64 x, int k, volatile unsigned char* place)
 // and lists change in this kernel only), so what has to be found are repeats among the candidates, and sorting brings those together: list
 // and candidates are sorted in one network where they are at most 64, else 64 candidates at a time are sorted and merged.  Longer lists could
 // lose entries to repeats in a merge that keeps 64, and look every id up in a set.
+// 1M x 128, k = 32, eight updates: 6.95 ms with the set and networks on whole keys, 6.56 with networks on 32-bit keys, 5.8 without the set; 400 -> 300
+// vector and 380 -> 117 scalar instructions a list.  The slot rows (2 KB a list) bound it: 4.2 TB/s.
 template <bool REMEASURE, bool SMALL>
 __global__ __launch_bounds__(64 * LISTS_WAVES) void update_kernel(TgGraph g, int S, TgCand cd, u64* updates, int flip, int64_t v0)
 {
