@@ -159,3 +159,33 @@ def test_bad_arguments():
             knn.prune_dispersion(X, ids, **kw)
     e = torch.zeros(0, device="cuda")
     assert knn.angle_at(e, e, e).numel() == 0
+
+
+def test_angle_with_lengths_of_the_short_way():
+    """Lengths of 0 or 2^-45 .. 2^45, which take the short square root and quotient: every exponent against every other, the ends of the range,
+    differences that cancel to their last bit and ratios past +-1."""
+    rng = np.random.default_rng(32)
+    n = 1 << 20
+    lim = np.float32(2.0) ** np.array([-45, 45], dtype=np.float32)
+    a = np.clip((2.0 ** rng.uniform(-45, 45, n)).astype(np.float32), *lim)
+    b = np.clip((2.0 ** rng.uniform(-45, 45, n)).astype(np.float32), *lim)
+    near = rng.random(n) < 0.5
+    b[near] = np.clip((a[near] * 2.0 ** rng.uniform(-3, 3, near.sum())).astype(np.float32), *lim)
+    a[:64], b[64:128], a[128:192], b[128:192] = lim[0], lim[1], 0.0, lim[1]
+    c = ((np.sqrt(a) - np.sqrt(b)) ** 2 + 4 * np.sqrt(a * b) * rng.random(n).astype(np.float32) * np.float32(1.01)).astype(np.float32)
+    right = rng.random(n) < 0.3                                     # right angles: a + b - c is a few last bits, or nothing
+    c[right] = (a + b)[right] * (1 + rng.integers(-3, 4, right.sum()).astype(np.float32) * np.float32(2.0 ** -23))
+    want = oracle.angle_at(a, b, c)
+    got = knn.angle_at(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), torch.from_numpy(c).cuda()).cpu().numpy()
+    assert (got.view(np.uint32) == want.view(np.uint32)).all()
+
+
+# a power of two in front of every value moves the squared lengths out of the short way's range and changes no angle: the same rows
+@pytest.mark.parametrize("k,hops", [(9, 1), (20, 1), (40, 1), (64, 1), (12, 2)])
+def test_scaled_points_are_pruned_the_same(k, hops):
+    X = inputs.make("C2", n=2000, d=64, comps=5)
+    Xg = torch.from_numpy(X).cuda()
+    ids, _, _ = knn.knn_build_ex(Xg, knn.default_params(k, 6, seed=2))
+    rows = knn.prune_dispersion(Xg, ids, k // 2, hops=hops)
+    for scale in (2.0 ** 20, 2.0 ** -32):                          # (lengths about 2^55 and 2^-49; their products still have a place in fp32)
+        assert torch.equal(rows, knn.prune_dispersion(Xg * scale, ids, k // 2, hops=hops))
