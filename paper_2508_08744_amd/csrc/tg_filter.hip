@@ -203,8 +203,9 @@ __device__ inline float filter_quotient(float t, float d)
     const float q = t * r;
     return fmaf(fmaf(-d, q, t), r, q);
 }
-// Squared lengths for which the above serve: 0 (the angle is 0 whatever comes out) or 2^-45 .. 2^45.  Then a b is 0 or within 2^+-90, and
-// t, a multiple of 2^-70, is 0 or large enough for the remainder to be exact.
+// Squared lengths a and b for which the above serve: 0 (the angle is 0 whatever comes out) or 2^-45 .. 2^45.  Then a b is 0 or within 2^+-90, and
+// t, a multiple of 2^-70 unless it is larger than 2^-46, is 0 or large enough for the remainder to be exact.  Nothing is asked of c, which bounds t
+// from above: a t beyond the divisor is taken for it before the division, not the quotient for 1 behind it.
 __device__ inline bool filter_plain_length(float v) { return v == 0.0f || (v >= 2.842170943e-14f && v <= 3.518437209e13f); }
 
 // Angle at p between p -> r and p -> c from the squared lengths a = |p r|^2, b = |p c|^2, c = |r c|^2:
@@ -218,10 +219,17 @@ __device__ inline float filter_angle_at(float a, float b, float c)
 #pragma clang fp contract(off)
     const float ab = a * b;
     const float den = 2.0f * (PLAIN ? filter_sqrt(ab) : sqrtf(ab));
-    const float t = (a + b) - c;
-    float x = PLAIN ? filter_quotient(t, den) : t / den;
-    x = x > 1.0f ? 1.0f : x;
-    x = x < -1.0f ? -1.0f : x;
+    float t = (a + b) - c, x;
+    if (PLAIN) {
+        // (the quotient of an infinite or huge t would be infinity less infinity; a rounded quotient is beyond 1 exactly where t is beyond den)
+        t = t > den ? den : t;
+        t = t < -den ? -den : t;
+        x = filter_quotient(t, den);
+    } else {
+        x = t / den;
+        x = x > 1.0f ? 1.0f : x;
+        x = x < -1.0f ? -1.0f : x;
+    }
     const float ax = fabsf(x);
     float pol = -0.0012624911f;
     pol = fmaf(pol, ax, 0.0066700901f);

@@ -180,6 +180,25 @@ def test_angle_with_lengths_of_the_short_way():
     assert (got.view(np.uint32) == want.view(np.uint32)).all()
 
 
+def test_angle_with_any_third_length():
+    """a and b of the short way with a c that has nothing to do with them: negative, zero, of every exponent up to the largest float, infinite, not a
+    number.  Rows of the wave's 64: all of them such, or every third one an ordinary triple, which must not notice."""
+    rng = np.random.default_rng(33)
+    n = 1 << 18
+    a, b = ((2.0 ** rng.uniform(-45, 45, n)).astype(np.float32).clip(2.0 ** -45, 2.0 ** 45) for _ in range(2))
+    c = (2.0 ** rng.uniform(-149, 128, n) * rng.choice([-1.0, 1.0], n)).astype(np.float32)
+    odd = np.array([np.inf, -np.inf, np.nan, np.finfo(np.float32).max, np.finfo(np.float32).min, 0.0, -0.0, 1e-45], dtype=np.float32)
+    c[::7] = rng.choice(odd, c[::7].size)
+    a[:5], b[:5], c[:5] = [1, 1, 0.1, 1e-6, 0], [1, 1, 0.1, 1e-6, 1], [np.inf, -np.inf, 3e38, 1e34, np.inf]
+    half = n // 2
+    c[half::3] = (a + b - np.sqrt(a * b) * rng.uniform(-2.02, 2.02, n).astype(np.float32))[half::3]
+    want = oracle.angle_at(a, b, c)
+    got = knn.angle_at(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), torch.from_numpy(c).cuda()).cpu().numpy()
+    same = (got.view(np.uint32) == want.view(np.uint32)) | (np.isnan(got) & np.isnan(want))
+    assert same.all(), (np.nonzero(~same)[0].size, a[~same][:5], b[~same][:5], c[~same][:5], got[~same][:5], want[~same][:5])
+    assert (np.isnan(want) == (np.isnan(c) & (a * b > 0))).all()
+
+
 # a power of two in front of every value moves the squared lengths out of the short way's range and changes no angle: the same rows
 @pytest.mark.parametrize("k,hops", [(9, 1), (20, 1), (40, 1), (64, 1), (12, 2)])
 def test_scaled_points_are_pruned_the_same(k, hops):
