@@ -724,14 +724,19 @@ __global__ __launch_bounds__(64 * EX_WAVES, 4) void ex_scan_kernel(ExScanArgs a)
 // rows of a tile where there are fewer queries (a.wqs: waves over the queries).
 // A group of 16 x 64 pairs costs 4 KS matrix instructions, KS operand reads, and on the vector units two maxima and a compare for each
 // 16 queries: the thresholds are taken for the 64 rows of a tile (the bound of a pair is made of the largest norm and the largest
-// residual among them: a little looser than a row's own, no pair is lost).
+// residual among them: a little looser than a row's own, no pair is lost), or for each group where those of the groups differ (EXG_UNEVEN): one row
+// far from the others would loosen the bounds of 63, pairs pass that need not, lists fill up and their queries are measured directly.  300 000 x 128
+// against 2000, one row of a hundred times the norm in every 64: 4.34 ms by the tile, 1.09 by the group (1.24 in ex_scan_kernel, by 16 rows); 500 000 x 96
+// against 4000, norms spread over e^+-1: 7.3, 1.98 (2.55).  By the group always this kernel takes 3.1 ms for the
+// 2.83 below, with the choice 2.83 still: the maxima by DPP and in scalar registers pay for it.
 // Pairs that pass wait in a queue of the wave's own and go to the lists up to 64 at a time and more (see ex_scan_kernel).
-// 1M x 128 against 10 000 queries: 5.75 ms with the queries in LDS and each row read for 128 of them, 0.73 its sample; now 2.88 and 0.37, of
+// 1M x 128 against 10 000 queries: 5.75 ms with the queries in LDS and each row read for 128 of them, 0.73 its sample; now 2.83 and 0.37, of
 // which about 1.2 go to the pairs that pass (700 a query in either); without those the scan runs at 1.0 PFLOP/s (a library product of
 // 8192 cubed: 1.15).  Rows 128 at a time with two waves per SIMD: 0.2 ms more; the next group's operands asked for ahead: no
 // gain with two waves, spills with three.
 // ---------------------------------------------------------------------------------------
 #define EXG_RT 64            // rows of a tile
+#define EXG_UNEVEN 1.5f      // a tile whose largest norm or residual is more than this many times the largest of one of its groups takes thresholds by the group
 #define EXG_QUEUE 320        // pairs a wave collects before they go to the lists: 64 and the 256 of a 16 x 16 tile
 template <int KS, bool SAMPLE>
 __global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
@@ -740,7 +745,8 @@ __global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
     constexpr int UNITS = EXG_RT * PIECES / 256;                        // pieces of a tile per thread
     __shared__ floatx4 s_tile[2][EXG_RT * PIECES];
     __shared__ __align__(16) float s_c0[2][EXG_RT];                     // where a row's sums start: -|r|^2 / 2 (or 0; -inf past the end)
-    __shared__ float s_R[2], s_E[2];
+    __shared__ float s_R[2][5], s_E[2][5];                              // largest norm and residual of every 16 rows, and of the tile
+    __shared__ u32 s_uneven[2];
     __shared__ u64 s_queue[4][EXG_QUEUE];                               // ordered w << 32 | visit within the slice << 6 | query within the wave's
     __shared__ u32 s_full[256];                                         // the query's list is full: it is measured another way
     __shared__ int s_self[256];                                         // the query's own row
@@ -757,18 +763,20 @@ __global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
     const int qw = wq * 64;
 
     halfx8 fq[4][KS];
-    float ntau[4], qa[4], qe[4], kq[4];
+    // A pair passes where -w >= -tau - m, m as in ex_margin: of a query, -tau less its own share of m, |q| + e_q, e_q.  (Four roundings more than
+    // ex_margin has are in c1; |tau| counts for no more than the pair's norms do, since nothing but a w about as large is near it.)
+    const float c1 = a.c1 + 2.4e-7f;
+    float base[4], qs[4], qe[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int64_t q = q0 + qw + 16 * j + r16;
         const bool some = q < a.nq;
         const int64_t qc = some ? q : 0;
         const float4 m = a.qmeta[qc];
-        qa[j] = m.x; qe[j] = m.y; kq[j] = a.c1 * m.z;
-        ntau[j] = -__builtin_inff();
-        if (!(m.z < __builtin_inff())) qa[j] = qe[j] = kq[j] = 0.0f;    // a query without a defined norm: everything passes
-        else ntau[j] = -a.tau[qc];
-        if (!some || a.qrow[qc] < 0) ntau[j] = __builtin_inff();        // no query: nothing passes
+        base[j] = -__builtin_inff();                                    // a query without a defined norm: everything passes
+        qs[j] = qe[j] = 0.0f;
+        if (m.z < __builtin_inff()) { base[j] = -a.tau[qc] - c1 * m.z; qs[j] = m.x + m.y; qe[j] = m.y; }
+        if (!some || a.qrow[qc] < 0) base[j] = __builtin_inff();        // no query: nothing passes
         const unsigned char* src = a.Q + qc * (int64_t)a.qbytes + q4 * 16;
 #pragma unroll
         for (int s = 0; s < KS; ++s) fq[j][s] = *reinterpret_cast<const halfx8*>(src + 64 * s);
@@ -800,13 +808,22 @@ __global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
             // a row without a defined norm: EX_ALWAYS takes it past any threshold, and its neighbours keep theirs (see ex_scan_kernel)
             const bool undefined = !(pre_rn < __builtin_inff());
             s_c0[par][tid] = !real ? -__builtin_inff() : undefined ? EX_ALWAYS : a.metric == 0 ? -0.5f * pre_rn : 0.0f;
-            float R = undefined ? 0.0f : sqrtf(pre_rn), E = undefined ? 0.0f : pre_er;
-#pragma unroll
-            for (int o = 1; o < EXG_RT; o <<= 1) {
-                R = fmaxf(R, __shfl_xor(R, o));
-                E = fmaxf(E, __shfl_xor(E, o));
+            const float R = undefined ? 0.0f : sqrtf(pre_rn), E = undefined ? 0.0f : pre_er;
+            // (as bits, which order them: neither is negative)
+            u32 r = __float_as_uint(R), e = __float_as_uint(E);
+            r = max(r, tg_partner32<1>(r));   e = max(e, tg_partner32<1>(e));
+            r = max(r, tg_partner32<2>(r));   e = max(e, tg_partner32<2>(e));
+            r = max(r, tg_partner32<7>(r));   e = max(e, tg_partner32<7>(e));
+            r = max(r, tg_partner32<15>(r));  e = max(e, tg_partner32<15>(e));
+            if ((tid & 15) == 0) { s_R[par][tid >> 4] = __uint_as_float(r) * 1.0001f; s_E[par][tid >> 4] = __uint_as_float(e); }
+            auto of = [](u32 x, int group) __attribute__((always_inline)) { return (u32)__builtin_amdgcn_readlane((int)x, 16 * group); };
+            const u32 r_most = max(max(of(r, 0), of(r, 1)), max(of(r, 2), of(r, 3))), r_least = min(min(of(r, 0), of(r, 1)), min(of(r, 2), of(r, 3)));
+            const u32 e_most = max(max(of(e, 0), of(e, 1)), max(of(e, 2), of(e, 3))), e_least = min(min(of(e, 0), of(e, 1)), min(of(e, 2), of(e, 3)));
+            if (tid == 0) {
+                s_R[par][4] = __uint_as_float(r_most) * 1.0001f;
+                s_E[par][4] = __uint_as_float(e_most);
+                s_uneven[par] = __uint_as_float(r_most) > EXG_UNEVEN * __uint_as_float(r_least) || __uint_as_float(e_most) > EXG_UNEVEN * __uint_as_float(e_least);
             }
-            if (tid == 0) { s_R[par] = R * 1.0001f; s_E[par] = E; }
         }
     };
 
@@ -840,13 +857,12 @@ __global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
         __syncthreads();
         if (t + 1 < t1) fetch(t + 1);
         float thr[4];
-        {
-            const float R = s_R[par], E = s_E[par];
+        auto bound_by = [&](int group) __attribute__((always_inline)) {
+            const float R = s_R[par][group], E = s_E[par][group], own = c1 * R * R;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) thr[j] = ntau[j] - ex_margin(qa[j], qe[j], kq[j], R, E, a.c1);
-        }
-#pragma unroll 1
-        for (int i = wr * wqs; i < (wr + 1) * wqs; ++i) {              // (64 rows are four groups: wqs of them for each of the 4 / wqs shares)
+            for (int j = 0; j < 4; ++j) thr[j] = fmaf(-qs[j], E, fmaf(-qe[j], R, base[j] - own));
+        };
+        auto meet = [&](int i) __attribute__((always_inline)) {
             const int row = 16 * i + r16;
             halfx8 fr[KS];
 #pragma unroll
@@ -861,7 +877,7 @@ __global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
             u64 hit[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) hit[j] = __ballot(fmaxf(fmaxf(acc[j][0], acc[j][1]), fmaxf(acc[j][2], acc[j][3])) >= thr[j]);
-            if ((hit[0] | hit[1] | hit[2] | hit[3]) == 0ull) continue;
+            if ((hit[0] | hit[1] | hit[2] | hit[3]) == 0ull) return;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (hit[j] == 0ull) continue;
@@ -876,10 +892,20 @@ __global__ __launch_bounds__(256, 3) void ex_scan_wave_kernel(ExScanArgs a)
                     nqueue += __popcll(m);
                 }
             }
+        };
+        // (64 rows are four groups: wqs of them for each of the 4 / wqs shares)
+        const bool uneven = __builtin_amdgcn_readfirstlane((int)s_uneven[par]) != 0;
+        const int last = (wr + 1) * wqs;
+#pragma unroll 1
+        for (int i = wr * wqs; i < last;) {
+            bound_by(uneven ? i : 4);
+            const int upto = uneven ? i + 1 : last;
+#pragma unroll 1
+            for (; i < upto; ++i) meet(i);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (s_full[qw + 16 * j + r16]) ntau[j] = __builtin_inff();
+            if (s_full[qw + 16 * j + r16]) base[j] = __builtin_inff();
     }
     flush();
 }

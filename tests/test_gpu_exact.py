@@ -180,6 +180,24 @@ def test_exact_f16_edges(n, d, k, nq, metric, whole):
     _check_f16(X, k, metric, rng.choice(n, size=nq, replace=False).astype(np.int64), 24)
 
 
+# Tiles of 64 rows whose groups of 16 have norms (and residuals) of their own size get thresholds by the group, others one for the tile: one row far
+# from the rest in every 64, in every 1000 (both kinds of tile), norms that grow from group to group, no two alike; one to four steps to a row,
+# one, two and four waves side by side over the queries.
+@pytest.mark.parametrize("n,d,k,nq,metric", [(140000, 28, 10, 900, "l2"), (200003, 64, 20, 160, "ip"), (70001, 96, 32, 300, "l2"), (50001, 128, 5, 500, "l2")])
+@pytest.mark.parametrize("kind", ["one in 64", "one in 1000", "steps", "spread"])
+def test_exact_f16_uneven_norms(n, d, k, nq, metric, kind):
+    rng = np.random.default_rng(n + d)
+    X = rng.normal(0, 1, size=(n, d)).astype(np.float32)
+    if kind == "spread":
+        X *= np.exp(rng.normal(0, 1, size=(n, 1))).astype(np.float32)
+    elif kind == "steps":
+        X *= (1 + np.arange(n) // 16 % 4)[:, None].astype(np.float32)
+    else:
+        X[11::64 if kind == "one in 64" else 1000] *= 100
+    assert _takes_f16(n, d, nq)
+    _check_f16(X, k, metric, rng.choice(n, size=nq, replace=False).astype(np.int64), 16)
+
+
 @pytest.mark.parametrize("kind", ["tiny", "huge", "offset", "outlier", "twins"])
 @pytest.mark.parametrize("metric", ["l2", "ip", "cosine"])
 def test_exact_f16_number_ranges(kind, metric):
