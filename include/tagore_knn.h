@@ -215,7 +215,7 @@ int tg_knn_join_distances(tg_knn_handle* h, const int32_t* blk, const int32_t* s
  * Exact k-NN of selected rows by exhaustive search on the GPU (ground truth for the
  * recall of section 7.1).  query_rows: device int64[nq] row indices into X (NULL = rows
  * 0..nq-1); out_ids device nq x k, out_dist device nq x k (may be NULL).  Order (dist, id).
- * A row index outside [0, n) is refused (checked on the host: with query_rows the call waits for the stream once,
+ * A row index outside [0, n) is refused (checked on the host: with query_rows the call takes its scratch, then waits for the stream once,
  * before it enqueues the search).  The search itself and the release of its scratch (hipMallocAsync / hipFreeAsync:
  * an fp16 copy of X where more than 128 queries make that worth while, and 16 KB per query) are only enqueued: outputs are
  * valid, and X and query_rows free to change, once `stream` has got past the call; errors of the kernels surface

@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -636,27 +637,39 @@ extern "C" int tg_exact_knn(const float* X, int64_t n, int32_t d, int32_t k, int
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
         return fail(TG_ERR_UNSUPPORTED, "tg_exact_knn takes scratch memory and cannot be captured: use tg_exact_knn_static");
-    if (query_rows) {   // the row indices come from the caller: check them before a kernel uses them
-        std::vector<int64_t> hr((size_t)nq);
-        HIP_TRY(hipMemcpyAsync(hr.data(), query_rows, hr.size() * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        for (int64_t r : hr)
-            if (r < 0 || r >= n) return fail(TG_ERR_INVALID_ARG, "query row %lld out of range", (long long)r);
-    } else if (nq > n) {
-        return fail(TG_ERR_INVALID_ARG, "nq > n without query_rows");
-    }
+    if (!query_rows && nq > n) return fail(TG_ERR_INVALID_ARG, "nq > n without query_rows");
     const int ld = round_up4(d);
     const bool pad = (ld != d) || ((reinterpret_cast<uintptr_t>(X) & 15) != 0);
     // The scratch lives in stream order, like the workspace of tg_knn_build; where it cannot be had, less of it is asked for.
     TgExactPlan plan = {};
     const size_t padded = pad ? ((size_t)n * ld * sizeof(float) + 255) & ~(size_t)255 : 0;
     char* ws = nullptr;
-    for (int attempt = 0; ; ++attempt) {
-        if (!tg_exact_plan(n, ld, metric, nq, padded, attempt, &plan))
-            return fail(TG_ERR_OUT_OF_MEMORY, "scratch of %zu bytes could not be allocated", plan.bytes);
-        if (hipMallocAsync(reinterpret_cast<void**>(&ws), plan.bytes, s) == hipSuccess) break;
-        (void)hipGetLastError();
+    auto take = [&](int attempt) {       // false: there is no such plan
+        if (!tg_exact_plan(n, ld, metric, nq, padded, attempt, &plan)) return false;
+        if (hipMallocAsync(reinterpret_cast<void**>(&ws), plan.bytes, s) != hipSuccess) {
+            (void)hipGetLastError();
+            ws = nullptr;
+        }
+        return true;
+    };
+    // It is asked for in front of the wait for the row indices: a wait hands to the system what the last call has given back in stream order, and
+    // asking behind it would map the same memory anew (1M x 128 against 10 000 queries, calls queued: 4.4 ms a call, 16 where a large build went before; now 3.9 in either).
+    (void)take(0);
+    if (query_rows) {   // the row indices come from the caller: check them before a kernel uses them
+        std::unique_ptr<int64_t[]> hr(new (std::nothrow) int64_t[(size_t)nq]);
+        hipError_t e = hr ? hipMemcpyAsync(hr.get(), query_rows, (size_t)nq * sizeof(int64_t), hipMemcpyDeviceToHost, s) : hipErrorOutOfMemory;
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        int64_t bad = 0;
+        while (e == hipSuccess && bad < nq && hr[bad] >= 0 && hr[bad] < n) ++bad;
+        if (e != hipSuccess || bad < nq) {
+            if (ws) (void)hipFreeAsync(ws, s);
+            if (e != hipSuccess) return fail(TG_ERR_HIP, "reading the query rows failed: %s", hipGetErrorString(e));
+            return fail(TG_ERR_INVALID_ARG, "query row %lld out of range", (long long)hr[bad]);
+        }
     }
+    // (again, if it could not be had: the wait may have freed some)
+    for (int attempt = 0; !ws; ++attempt)
+        if (!take(attempt)) return fail(TG_ERR_OUT_OF_MEMORY, "scratch of %zu bytes could not be allocated", plan.bytes);
     float* xp = reinterpret_cast<float*>(ws);
     if (pad) tg_launch_pad_rows(X, n, d, xp, ld, s);
     tg_launch_exact_screened(pad ? xp : X, ld, n, d, k, metric, query_rows, nq, plan.f16 != 0, ws + padded, ws + padded + plan.fixed, plan.batch, out_ids,

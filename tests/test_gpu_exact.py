@@ -1,5 +1,6 @@
 """The screened exact k-NN at the edges of its samples, tiles and number ranges, against the brute-force oracle."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -226,3 +227,47 @@ def test_exact_overflowing_queries(n, d, k, nq, f16, listed):
     for f in (knn.exact_knn, knn.exact_knn_static):
         ids, dist = f(torch.from_numpy(X).cuda(), k, "l2", torch.from_numpy(rows).cuda())
         assert (ids.cpu().numpy()[pick] == oi).all() and (dist.cpu().numpy()[pick] == od).all()      # (every sum is exact)
+
+
+def _pool_bytes_in_use():
+    """Bytes that stream-ordered allocations of the default pool hold (hipMemPoolAttrUsedMemCurrent)."""
+    hip = knn.lib()                                                  # (the runtime that the library is linked to)
+    pool, used = ctypes.c_void_p(), ctypes.c_uint64()
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), torch.cuda.current_device()) == 0
+    assert hip.hipMemPoolGetAttribute(pool, 7, ctypes.byref(used)) == 0
+    return used.value
+
+
+def test_exact_scratch_is_taken_before_the_wait_and_given_back():
+    """With row numbers the call waits for the stream.  The scratch is taken in front of that wait, where the last call's is still to be had, and given
+    back whether the rows are good or not."""
+    n, d, nq = 40000, 64, 1000
+    X = torch.randn((n, d), device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    rows = torch.arange(nq, device="cuda")
+    want = knn.exact_knn(X, 8, "l2", rows)
+    torch.cuda.synchronize()
+    before = _pool_bytes_in_use()
+    side = torch.cuda.Stream()
+    got = []
+
+    def call():
+        with torch.cuda.stream(side):
+            got.append(knn.exact_knn(X, 8, "l2", rows))
+
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(400_000_000)                               # the call waits for this one
+    worker = threading.Thread(target=call)
+    worker.start()
+    held = 0
+    while not side.query() and held == 0:
+        held = _pool_bytes_in_use() - before
+    worker.join()
+    torch.cuda.synchronize()
+    assert held > n * d * 2                                          # (at least the fp16 copy of X)
+    assert all(torch.equal(a, b) for a, b in zip(got[0], want))
+    rows[nq - 1] = n
+    for _ in range(3):
+        with pytest.raises(knn.TagoreError, match="row %d out of range" % n):
+            knn.exact_knn(X, 8, "l2", rows)
+    torch.cuda.synchronize()
+    assert _pool_bytes_in_use() == before
