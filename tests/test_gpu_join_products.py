@@ -68,13 +68,15 @@ def test_products_are_those_of_fp32(d, kind, metric):
 
 
 @pytest.mark.parametrize("metric", ["l2", "ip", "cosine"])
-@pytest.mark.parametrize("d", [5, 50, 96, 128])
-def test_a_pair_has_one_distance(d, metric):
+@pytest.mark.parametrize("f16", [0, 1])
+@pytest.mark.parametrize("d", [5, 50, 64, 84, 96, 116, 128, 132, 200])
+def test_a_pair_has_one_distance(d, f16, metric):
     """The same two real-valued rows get the same bits in a block of at most 64 members (a wave, registers) and in a larger one (a workgroup,
-    LDS), whichever of them comes first: lists and thresholds must not depend on where a pair met."""
+    LDS), whichever of them comes first, from fp32 rows and from those rounded to fp16: lists and thresholds must not depend on where a pair
+    met, and the update of short lists finds the repeats of a candidate by their equal keys."""
     rng = np.random.default_rng(d)
     X = rng.standard_normal((300, d)).astype(np.float32)
-    b = knn.Builder(torch.from_numpy(X).cuda(), knn.default_params(8, 4, metric=metric))
+    b = knn.Builder(torch.from_numpy(X).cuda(), knn.default_params(8, 4, metric=metric, join_f16=f16))
     order = rng.permutation(300)[:128].astype(np.int32)
     seen = {}
     for members, sizes in ((order, (64, 64)), (order[::-1].copy(), (64, 64)), (order[:64], (64, 0)), (order[:64][::-1].copy(), (64, 0)),

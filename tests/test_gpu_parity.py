@@ -370,6 +370,29 @@ def test_whole_build_identical_to_oracle_at_mid_size():
     assert (dist.cpu().numpy().astype(np.float64) == od).all()
 
 
+# One part of more than 40 000 anchors: three launches of the join instead of one.  Rows of whole steps (64, 96, 128) and of others, in every metric;
+# whole numbers of a small range, for the cosine -1, 0 and 1 with 16 or 64 that are not 0, so that norms are 4 or 8 and every distance is exact.
+@pytest.mark.parametrize("metric,d", [("l2", 64), ("l2", 100), ("ip", 50), ("ip", 96), ("ip", 128), ("cosine", 50), ("cosine", 64), ("cosine", 96), ("cosine", 116)])
+def test_long_parts_identical_to_oracle(metric, d):
+    n, k = 40_101, 12
+    rng = np.random.default_rng(d)
+    if metric == "cosine":
+        some = 16 if d < 64 else 64
+        X = np.zeros((n, d), dtype=np.float32)
+        at = np.argsort(rng.random((n, d), dtype=np.float32), axis=1)[:, :some]
+        np.put_along_axis(X, at, rng.choice(np.array([-1, 1], dtype=np.float32), size=(n, some)), axis=1)
+    else:
+        X = rng.integers(-5, 6, size=(40, d))[rng.integers(0, 40, n)] + rng.integers(-2, 3, size=(n, d))
+        X = X.astype(np.float32)
+    prm = knn.default_params(k, 0, metric=metric, seed=5, it1=2, it2=0, delta=0.0, parts=1)
+    ids, dist, _ = knn.knn_build_ex(torch.from_numpy(X).cuda(), prm)
+    o = oracle.NNDescent(X, k, knn.METRICS[metric], **oracle.device_model(prm))
+    o.run(prm.it1, prm.it2)
+    oi, od, _ = o.graph()
+    assert (ids.cpu().numpy() == oi).all()
+    assert (dist.cpu().numpy().astype(np.float64) == od).all()
+
+
 def test_phase1_lists_keep_their_invariants_without_finalize():
     X = inputs.make("C1", n=4000)
     prm = knn.default_params(16, 8, seed=3)
