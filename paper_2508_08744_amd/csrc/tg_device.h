@@ -141,10 +141,11 @@ __device__ inline u32 tg_dpp32(u32 x)
 template <int XOR>
 __device__ inline u32 tg_partner32(u32 x)
 {
+    static_assert(XOR == 1 || XOR == 2 || XOR == 7 || XOR == 15, "one DPP move");
     if (XOR == 1) return tg_dpp32<0xB1>(x);
     if (XOR == 2) return tg_dpp32<0x4E>(x);
     if (XOR == 7) return tg_dpp32<0x141>(x);
-    return tg_dpp32<0x140>(x);          // 15
+    return tg_dpp32<0x140>(x);
 }
 __device__ inline u32 tg_median32(u32 a, u32 b, u32 c) { return max(min(a, b), min(max(a, b), c)); }
 // all ones where bit J of the lane is set

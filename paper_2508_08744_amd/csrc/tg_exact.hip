@@ -2,7 +2,7 @@
 // rows with the smallest (distance, id), distances computed directly from the vectors in fp32.
 //
 // Measuring every pair that way is bound by the vector units (245 ms for 10 000 queries against 1M x 128, k = 32:
-// 10.5 TFLOP/s; this search takes 4.2 ms).  Here the matrix cores bound every pair from both sides first, and only pairs that may be
+// 10.5 TFLOP/s; this search takes 3.9 ms).  Here the matrix cores bound every pair from both sides first, and only pairs that may be
 // among the k nearest are measured directly:
 //   w(q, r) = |r|^2 / 2 - <q, r>  (squared L2; -<q, r> for the inner product, the same on unit vectors for the
 //   cosine) orders the rows for query q.  A tile of w is formed on the matrix cores, either from the rows

@@ -1320,9 +1320,11 @@ static void launch_wave_dump(const TgGraph& g, const int32_t* blk, const int32_t
 
 static bool wave_path(const TgGraph& g) { return tg_join_wave_ok(g.ld); }
 
-// One launch for the three lists of a part where they are short: the two of small blocks and the mostly empty one of large blocks took 23 + 9 + 8 us
-// one after another in a build of 10 000 x 32.  Whole builds of eight rounds, three launches / one, us: 10 000 x 32, k = 16: 728 / 645; 3000 x 24,
+// One launch for the three lists of a part where they are short: the two of small blocks and that of large blocks (mostly empty up to k = 32) took
+// 23 + 9 + 8 us one after another in a build of 10 000 x 32, k = 16.  Whole builds of eight rounds, three launches / one, us: 10 000 x 32, k = 16: 728 / 645; 3000 x 24,
 // k = 32: 575 / 489; 20 000 x 128 bytes: 1609 / 1518; 37 511 x 50, k = 20: 2186 / 2115; 80 000 x 64, k = 24: 3593 / 3548; 60 000 x 20, k = 10: 1993 / 1994.
+// Where large blocks are many: 3000 x 24, k = 64: 755 / 668; 10 000 x 128, k = 64: 1587 / 1454; 40 000 x 128 bytes, k = 64 (six rounds): 3864 / 3656;
+// 80 000 x 100, k = 64: 8347 / 8046; 80 000 x 64 under the inner product, k = 64: 6024 / 5929; 80 000 x 128, k = 40: 6004 / 5998.
 #define JOIN_ALL_MOST 40000      // anchors of a part
 #define JOIN_ALL_LARGE 512       // workgroups for the blocks of more than 64 members
 template <int METRIC, int KS>

@@ -699,8 +699,8 @@ __device__ inline u64 update_once(u64 x)
     const u64 repeats = __ballot(x == tg_lane_before<false>(x) && x != TG_EMPTY_KEY);
     return repeats ? update_close_up(x, repeats) : x;
 }
-// The same, and the first k entries' ids are different whatever their keys: each lane writes its number to the place its id is hashed to,
-// and a lane that does not find itself there (1 list in 2 has one, by chance) looks for its id among the others.
+// The same, and the first k entries' ids are different whatever their keys, as they may be where a caller imported the lists: each lane writes its number
+// to the place its id is hashed to, and a lane that does not find itself there (1 list in 2 has one, by chance) looks for its id among the others.
 __device__ inline u64 update_settle(u64 x, int k, volatile unsigned char* place)
 {
     const int lane = tg_lane();

@@ -47,16 +47,15 @@ __device__ inline void prune_fill_table(PruneLaneTable& T, int p0, int k, int kp
 
 // A look-up goes on beyond its home bucket only where an id went past that when the map was built, which the bucket's second entry says: a full
 // bucket alone, which every other pass meets, used to start a loop of the whole wave.  1M lists of 32: 868 -> 670 us, 100 000 of 64: 594 -> 470,
-// 200 000 of 48: 659 -> 497, 300 000 of 16: 139 -> 120, 10 000 of 32: 20.1 -> 17.9.  (The figures below are from before.)
+// 200 000 of 48: 659 -> 497, 300 000 of 16: 139 -> 120, 10 000 of 32: 20.1 -> 17.9.
 // ONE (all pairs in one round of eight passes: k <= 32, the lane table never changes): the neighbours' entries are asked for before
 // the map is built, the next node's row before this one is looked up.  What bounds the kernel is instructions and the latency of the
-// entries: 1M lists of 32: 982 -> 931 us, of 16: 458 -> 436 us; without ONE 300 000 of 64: 1860 -> 1720 us (fewer table registers).  Asking
-// for the entries a whole node ahead took 1023 us (five waves per SIMD instead of six).
+// entries; without and with ONE, kernels under the profiler: 1M lists of 32: 871 / 760 us, of 16: 521 / 399, 300 000 of 24: 228 / 191.
 // NEAR: the lists are less than 4 GiB, so an entry's byte offset has 32 bits (half the address registers).
 // LONE (with ONE and NEAR): every wave serves one node.  No next row to ask for, the entries are asked for behind the map, which takes
 // 44 registers instead of 76 and leaves eight waves per SIMD to cover them; passes without a pair are left out, and idle lanes read one row that
-// is there already instead of the first neighbour's.  30 000 lists of 16: 24.6 -> 21.3 us, 14 448: 13.3 -> 11.8, 30 000 of 32: 42.5 -> 40.7,
-// 5000 of 32: 13.0 -> 12.1.
+// is there already instead of the first neighbour's.  Without and with it: 30 000 lists of 16: 24.2 / 21.0 us, 14 448: 13.4 / 12.1,
+// 30 000 of 32: 34.4 / 34.4, 5000 of 32: 11.4 / 11.5.
 template <bool ONE, bool NEAR, bool LONE>
 __global__ __launch_bounds__(256) void prune_rank_kernel(const int32_t* __restrict__ ids, int64_t n, int k, int kp, int d_out,
                                                          int32_t* __restrict__ out_ids, int32_t* __restrict__ counts)
